@@ -57,8 +57,9 @@ typedef enum {
 typedef enum { SBN_F32 = 0, SBN_BF16 = 1 } sbn_dtype;
 
 typedef enum {
-    SBN_PATH_AUTO = 0,       /* d_in % 128 == 0: GEMV for tokens <= 16, sparse MFMA GEMM for more.  Any other case: dense
-                                MFMA if d_in % 64 == 0, generic else */
+    SBN_PATH_AUTO = 0,       /* the kernels of GEMV for tokens <= 16, of SMFMAC for more, whatever d_in is: where it is no
+                                multiple of 128 the int8 rows lie in the workspace as rows of whole chunks (the packed
+                                form is padded to them with zero codes already) */
     SBN_PATH_GEMV = 1,       /* decode kernel: streams the packed weights once; tokens <= 16, d_in % 128 == 0.  2:4 runs
                                 on the sparse instruction and N = M (dense 2-bit codes) on the dense one as stored; 1:4
                                 is read as stored too (one bit per weight: the kernel builds the sparse instruction's
@@ -153,7 +154,7 @@ sbn_status sbn_act_quant(const void *X, int64_t tokens, int64_t d_in, int8_t *xq
  *   xq[t,k]  = clip(round_half_even(X[t,k] * s_x[t]), -128, 127)     (int8)
  *   acc[t,o] = sum_k W_eff[o,k] * xq[t,k]                            (int32, exact)
  *   Y[t,o]   = acc[t,o] * gamma / s_x[t] (+ bias[o])                 (fp32)
- *   X        device, bf16 [tokens, d_in], 16-byte aligned, d_in % 8 == 0 (d_in % 128 == 0 for the MFMA paths);
+ *   X        device, bf16 [tokens, d_in], 16-byte aligned, d_in % 8 == 0 (d_in % 128 == 0 where GEMV or SMFMAC is asked for);
  *            or NULL: then xq_out and sx_out are INPUTS holding activations already quantized by
  *            sbn_act_quant, and the quantizer is skipped
  *   packed   device, from sbn_quantize_mask_pack with the same d_out, d_in, N, M
@@ -182,7 +183,8 @@ sbn_status sbn_sparse_ternary_linear(const void *X, int64_t tokens, int64_t d_in
  *   limits      align256(tokens * d_in) + align256(4 * tokens) <= SBN_STATIC_SCRATCH_MIB MiB, else SBN_ESIZE
  *               (sbn_last_error() then says how much was needed); only paths that read the weights as stored:
  *               2:4 and N = M on SBN_PATH_GEMV / SBN_PATH_SMFMAC, 1:4 on SBN_PATH_GEMV, any pattern on SBN_PATH_GENERIC
- *               (SBN_PATH_AUTO when it resolves to one of these); every other case SBN_EUNSUPPORTED
+ *               (SBN_PATH_AUTO when it resolves to one of these; where d_in % 128 != 0 and the weights would need a
+ *               rewrite, or the wider rows do not fit, it takes the plain integer kernel); every other case SBN_EUNSUPPORTED
  *   sharing     all calls on a GPU use that GPU's one buffer, which keeps the last call's contents (nothing in it has
  *               to start at zero: flags left behind carry the number of the launch that raised them).  Calls that
  *               overlap on one GPU (two streams, two threads) race on it: serialise them, or use the call above.

@@ -40,18 +40,16 @@ static sbn_status check_shape(int64_t d_out, int64_t d_in, int N, int M, Pattern
     return SBN_OK;
 }
 
-static sbn_path resolve_path(sbn_path path, int64_t tokens, int64_t d_in, const Pattern &pat)
+static sbn_path resolve_path(sbn_path path, int64_t tokens)
 {
-    if (path != SBN_PATH_AUTO) return path;
-    const bool is24 = pat.N == 2 && pat.M == 4;
     // 2:4 and its instances (1:4, 2:8, ...: rewritten into the 2:4 operand form first) take the sparse instruction as
     // it is meant.  Every other pattern (the paper's 6:8 among them) has no sparse matrix instruction of its own on
     // this part: its weights run as dense 2-bit codes (N = M is stored that way, the rest is converted first), in
     // decode through the streaming kernel and beyond decode sizes through the same sparse instruction, issued twice
     // per group of four weights (positions 0, 1 and positions 2, 3 - the matrix-core time of a dense int8 product, at
-    // a quarter of its weight bytes)
-    if (d_in % CHUNK == 0) return tokens <= 16 ? SBN_PATH_GEMV : SBN_PATH_SMFMAC;
-    return d_in % 64 == 0 ? SBN_PATH_DENSE_MFMA : SBN_PATH_GENERIC;
+    // a quarter of its weight bytes).  An input dimension that is no multiple of 128 takes the same kernels on rows of
+    // whole chunks (50 tokens, 1000 -> 1500: 414 us on the plain integer kernel that served it before, 12 us here).
+    return path != SBN_PATH_AUTO ? path : tokens <= 16 ? SBN_PATH_GEMV : SBN_PATH_SMFMAC;
 }
 
 }  // namespace sbn
@@ -188,26 +186,29 @@ static sbn_status linear_one(const LinearItem &it_in, const Pattern &pat, sbn_pa
 {
     LinearItem it = it_in;
     const bool is24 = pat.N == 2 && pat.M == 4;
-    path = resolve_path(path, it.tokens, it.d_in, pat);
+    const bool chosen_here = path == SBN_PATH_AUTO;
+    path = resolve_path(path, it.tokens);
     const bool sparse_form = is24 || embeds_in_2of4(pat);   // runs on the sparse instruction (after a rewrite unless 2:4)
     const bool one4_decode = pat.N == 1 && pat.M == 4 && path == SBN_PATH_GEMV;   // the decode kernels read 1:4 as stored
     if (path == SBN_PATH_GEMV && it.tokens > 16) return SBN_EUNSUPPORTED;
-    if ((path == SBN_PATH_GEMV || path == SBN_PATH_SMFMAC) && it.d_in % CHUNK != 0) return SBN_EUNSUPPORTED;
+    if ((path == SBN_PATH_GEMV || path == SBN_PATH_SMFMAC) && it.d_in % CHUNK != 0 && !chosen_here) return SBN_EUNSUPPORTED;
     if (path == SBN_PATH_DENSE_MFMA && it.d_in % 64 != 0) return SBN_EUNSUPPORTED;
-    const size_t xq_bytes = align_up((size_t)it.tokens * it.d_in, 256);
     const size_t sx_bytes = align_up((size_t)it.tokens * sizeof(float), 256);
-    if (activations_only) {
-        const bool weights_as_stored = path == SBN_PATH_GENERIC ||
-                                       ((path == SBN_PATH_SMFMAC || path == SBN_PATH_GEMV) && (is24 || pat.N == pat.M)) ||
-                                       one4_decode;
-        if (!weights_as_stored) return SBN_EUNSUPPORTED;
-        if (ws_bytes < xq_bytes + sx_bytes) return SBN_ESIZE;
-    } else if (ws_bytes < linear_workspace_bytes(it.tokens, it.d_out, it.d_in)) {
-        return SBN_ESIZE;
-    }
-    // workspace: [xq int8 tokens*d_in][sx fp32 tokens][dense int8 W for the comparison path]
+    const bool weights_as_stored = path == SBN_PATH_GENERIC ||
+                                   ((path == SBN_PATH_SMFMAC || path == SBN_PATH_GEMV) && (is24 || pat.N == pat.M)) || one4_decode;
+    const int64_t kp = ceil_div(it.d_in, CHUNK) * CHUNK;
+    if (activations_only && chosen_here && it.d_in != kp && (!weights_as_stored || ws_bytes < align_up((size_t)it.tokens * kp, 256) + sx_bytes))
+        path = SBN_PATH_GENERIC;   // neither a rewrite of the weights nor, here, the wider rows fit the library's own scratch
+    else if (activations_only && !weights_as_stored) return SBN_EUNSUPPORTED;
+    // the matrix kernels walk whole chunks of 128: a shorter last chunk has zero codes behind the matrix's own, so whatever
+    // lies behind a row's int8 values does not count and the row only has to be there
+    const bool spread = it.d_in != kp && (path == SBN_PATH_GEMV || path == SBN_PATH_SMFMAC);
+    const size_t xq_bytes = align_up((size_t)it.tokens * (spread ? kp : it.d_in), 256);
+    if (ws_bytes < (activations_only ? xq_bytes + sx_bytes : linear_workspace_bytes(it.tokens, it.d_out, it.d_in))) return SBN_ESIZE;
+    // workspace: [xq int8 tokens * d_in, or rows of whole chunks][sx fp32 tokens][the weights in another form]
     uint8_t *ws = static_cast<uint8_t *>(workspace);
-    if (!it.xq) it.xq = reinterpret_cast<int8_t *>(ws);
+    int8_t *const ws_xq = reinterpret_cast<int8_t *>(ws);
+    if (!it.xq) it.xq = ws_xq;
     if (!it.sx) it.sx = reinterpret_cast<float *>(ws + xq_bytes);
     int8_t *w_dense = reinterpret_cast<int8_t *>(ws + xq_bytes + sx_bytes);
 
@@ -216,8 +217,18 @@ static sbn_status linear_one(const LinearItem &it_in, const Pattern &pat, sbn_pa
     // caller wants them back in its own buffers
     const bool defer = path == SBN_PATH_GEMV && it.X && !it_in.xq && !it_in.sx;
     it.quantized = !defer;
-    if (it.X && !defer) st = launch_act_quant(it.X, it.tokens, it.d_in, it.xq, it.sx, stream);
+    if (it.X && !defer) {
+        if (spread && !it_in.xq) st = launch_act_quant(it.X, it.tokens, it.d_in, ws_xq, it.sx, stream, kp);
+        else st = launch_act_quant(it.X, it.tokens, it.d_in, it.xq, it.sx, stream, it.d_in, spread ? ws_xq : nullptr, kp);
+    } else if (!it.X && spread) {
+        st = launch_spread_rows(it.xq, it.tokens, it.d_in, ws_xq, kp, stream);
+    }
     if (st != SBN_OK) return st;
+    if (spread) {
+        it.xq = ws_xq;
+        it.d_x = it.d_in;
+        it.d_in = kp;
+    }
     if ((path == SBN_PATH_GEMV || path == SBN_PATH_SMFMAC) && !is24 && sparse_form && !one4_decode) {
         // an instance of 2:4: the dense-weight region of the workspace takes its 2:4 operand form (a quarter of the size)
         st = launch_repack_2of4(it.packed, it.d_out, it.d_in, pat, reinterpret_cast<uint8_t *>(w_dense), stream);
@@ -347,10 +358,10 @@ sbn_status sbn_sparse_ternary_linear_grouped(int count, const void *const *X, co
         need += linear_workspace_bytes(tokens[i], d_out[i], d_in[i]);
         const bool is24 = pat.N == 2 && pat.M == 4;
         const bool one4 = pat.N == 1 && pat.M == 4;
-        if (resolve_path(path, tokens[i], d_in[i], pat) != SBN_PATH_GEMV || !(is24 || one4 || pat.N == pat.M) || tokens[i] > 16 ||
+        if (resolve_path(path, tokens[i]) != SBN_PATH_GEMV || !(is24 || one4 || pat.N == pat.M) || tokens[i] > 16 ||
             d_in[i] % CHUNK != 0)
             all_gemv = false;   // one launch streams 2:4, 1:4 or dense-code (N = M) weights as stored; other patterns need a rewrite each
-        if (resolve_path(path, tokens[i], d_in[i], pat) != SBN_PATH_SMFMAC || !(is24 || pat.N == pat.M) || d_in[i] % CHUNK != 0 ||
+        if (resolve_path(path, tokens[i]) != SBN_PATH_SMFMAC || !(is24 || pat.N == pat.M) || d_in[i] % CHUNK != 0 ||
             tokens[i] * d_out[i] >= (int64_t)1 << 40)
             all_smfmac = false;
     }

@@ -84,10 +84,17 @@ struct LinearItem {
     int32_t *acc_out;     // may be null
     int64_t tokens, d_in, d_out;
     bool quantized = true;   // xq / sx already hold the quantized activations (false: launch_gemv derives them from X)
+    // An input dimension that is no multiple of 128 runs as one of whole chunks: d_in is then rounded up (the packed form
+    // is padded with zero codes anyway), the rows of xq lie d_in bytes apart with anything behind their values, and d_x
+    // says how many values a row of X has.  0: d_in values.
+    int64_t d_x = 0;
+    int64_t row_values() const { return d_x ? d_x : d_in; }
 };
 size_t linear_workspace_bytes(int64_t tokens, int64_t d_out, int64_t d_in);
+// rows of xq ldq bytes apart (0: d_in); xq2, unless null, takes them as well, ld2 bytes apart
 sbn_status launch_act_quant(const void *X, int64_t tokens, int64_t d_in, int8_t *xq, float *sx,
-                            hipStream_t stream);
+                            hipStream_t stream, int64_t ldq = 0, int8_t *xq2 = nullptr, int64_t ld2 = 0);
+sbn_status launch_spread_rows(const int8_t *src, int64_t tokens, int64_t d_in, int8_t *dst, int64_t ldq, hipStream_t stream);
 sbn_status launch_rmsnorm_act_quant(const void *X, const float *gain, float eps, int64_t tokens, int64_t d_in, int8_t *xq,
                                     float *sx, void *xn, hipStream_t stream);
 // how the decode kernels read the packed weights: the 2:4 operand form, dense 2-bit codes (N = M), or the 1:4

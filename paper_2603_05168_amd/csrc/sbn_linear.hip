@@ -71,9 +71,12 @@ __device__ __forceinline__ uint2 quantize_bf16x8(const uint4 &d, float s)
 // in registers, so X is read once; the maximum magnitude is taken on the bf16 bit patterns (exact).
 // s_x = 127 / max(amax, 1e-5) is one IEEE fp32 division, x * s_x one fp32 multiply, rounding is
 // half-to-even.  Rows longer than VMAX * TPT vectors take the two-pass kernel below.
+// The int8 rows lie ldq bytes apart.  xq2 (or null) takes the same rows ld2 bytes apart: an input dimension that is no
+// multiple of 128 gives the caller its dense rows and the matrix kernels rows of whole chunks in one pass.
 template <int TPT, int VMAX>
 __global__ void __launch_bounds__(TPT < 256 ? 256 : TPT) act_quant_kernel(const uint4 *__restrict__ X, int64_t tokens, int nvec,
-                                                                         int8_t *__restrict__ xq, float *__restrict__ sx)
+                                                                         int8_t *__restrict__ xq, int64_t ldq, float *__restrict__ sx,
+                                                                         int8_t *__restrict__ xq2, int64_t ld2)
 {
     constexpr int BLOCK = TPT < 256 ? 256 : TPT;
     constexpr int TOK_PER_BLOCK = BLOCK / TPT;
@@ -107,18 +110,22 @@ __global__ void __launch_bounds__(TPT < 256 ? 256 : TPT) act_quant_kernel(const 
     const float s = scale_from_absmax_bits(m);
     if (!live) return;
     if (sub == 0) sx[t] = s;
-    uint2 *out = reinterpret_cast<uint2 *>(xq + t * (int64_t)nvec * 8);
+    uint2 *out = reinterpret_cast<uint2 *>(xq + t * ldq);
+    uint2 *out2 = reinterpret_cast<uint2 *>(xq2 + t * ld2);
 #pragma unroll
     for (int i = 0; i < VMAX; ++i) {
         const int idx = sub + i * TPT;
         if (idx >= nvec) break;
-        out[idx] = quantize_bf16x8(v[i], s);
+        const uint2 q = quantize_bf16x8(v[i], s);
+        out[idx] = q;
+        if (xq2) out2[idx] = q;
     }
 }
 
 // any row length: one wavefront per token, the row is read twice (the second read is cache resident)
 __global__ void __launch_bounds__(256) act_quant_two_pass_kernel(const uint4 *__restrict__ X, int64_t tokens, int nvec,
-                                                                int8_t *__restrict__ xq, float *__restrict__ sx)
+                                                                int8_t *__restrict__ xq, int64_t ldq, float *__restrict__ sx,
+                                                                int8_t *__restrict__ xq2, int64_t ld2)
 {
     const int lane = threadIdx.x & 63;
     const int64_t t = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -135,8 +142,20 @@ __global__ void __launch_bounds__(256) act_quant_two_pass_kernel(const uint4 *__
     }
     const float s = scale_from_absmax_bits(m);
     if (lane == 0) sx[t] = s;
-    uint2 *out = reinterpret_cast<uint2 *>(xq + t * (int64_t)nvec * 8);
-    for (int v = lane; v < nvec; v += 64) out[v] = quantize_bf16x8(row[v], s);
+    uint2 *out = reinterpret_cast<uint2 *>(xq + t * ldq);
+    uint2 *out2 = reinterpret_cast<uint2 *>(xq2 + t * ld2);
+    for (int v = lane; v < nvec; v += 64) {
+        const uint2 q = quantize_bf16x8(row[v], s);
+        out[v] = q;
+        if (xq2) out2[v] = q;
+    }
+}
+
+// int8 rows of d_in values (a multiple of 8) -> the same rows ldq bytes apart; what lies between is left as it is
+__global__ void __launch_bounds__(256) spread_rows_kernel(const uint2 *__restrict__ src, int64_t tokens, int nvec, int8_t *__restrict__ dst, int64_t ldq)
+{
+    const int64_t t = blockIdx.x;
+    for (int v = threadIdx.x; v < nvec; v += 256) reinterpret_cast<uint2 *>(dst + t * ldq)[v] = src[t * nvec + v];
 }
 
 // ---- RMS normalisation fused in front of the quantizer (Algorithm 1: x~ <- Q_a(Norm(x))) ---------
@@ -254,7 +273,8 @@ struct GemvItem {
     float *Y;
     int32_t *acc_out;
     const uint4 *X;   // bf16 activations when the block quantizes them itself (then xq and sx are unused), else null
-    int d_in, d_out, tokens, pad;
+    int d_in, d_out, tokens;
+    int d_x;          // values in a row of X (d_in rounded down to what X holds: d_in counts whole chunks)
 };
 constexpr int GEMV_MAX_ITEMS = 40;
 constexpr int GEMV_ROW_VEC = 14;   // 16-byte vectors of a token row per lane when a wavefront of the single-call kernel quantizes it
@@ -308,7 +328,7 @@ __global__ void __launch_bounds__(1024) gemv_smfmac_kernel(GemvTable tab)
     if (self_quant) {
         // every block quantizes the few token rows itself (the quantizer's arithmetic), saving the quantizer's
         // launch in front of a latency-bound call
-        const int nvec = K / 8, nthreads = (int)blockDim.x;
+        const int nvec = it.d_x / 8, nthreads = (int)blockDim.x;   // past d_x the LDS row keeps what it held: zero codes meet it
         if (nvec <= 64 * GEMV_ROW_VEC) {
             // a wavefront per token row, the row in registers (two short rows at a time): the rows of a block cost one
             // or two trips to memory in all, the maximum needs no barrier, the int8 row goes straight into LDS
@@ -939,27 +959,38 @@ __global__ void __launch_bounds__(128) linear_generic_kernel(const int8_t *__res
 
 size_t linear_workspace_bytes(int64_t tokens, int64_t d_out, int64_t d_in)
 {
-    // int8 activations + per-token scales + dense int8 weights of the comparison path
-    return align_up((size_t)tokens * d_in, 256) + align_up((size_t)tokens * sizeof(float), 256) +
-           align_up((size_t)d_out * d_in, 256);
+    // int8 activations in rows of whole chunks + per-token scales + the weights in another form: dense int8 for the
+    // comparison path, or at most two bits per weight of whole chunks
+    const int64_t kp = ceil_div(d_in, CHUNK) * CHUNK;
+    return align_up((size_t)tokens * kp, 256) + align_up((size_t)tokens * sizeof(float), 256) +
+           align_up((size_t)d_out * (d_in > kp / 4 ? d_in : kp / 4), 256);
 }
 
-sbn_status launch_act_quant(const void *X, int64_t tokens, int64_t d_in, int8_t *xq, float *sx, hipStream_t stream)
+sbn_status launch_act_quant(const void *X, int64_t tokens, int64_t d_in, int8_t *xq, float *sx, hipStream_t stream, int64_t ldq,
+                            int8_t *xq2, int64_t ld2)
 {
     const uint4 *x = static_cast<const uint4 *>(X);
     const int nvec = (int)(d_in / 8);
+    if (ldq == 0) ldq = d_in;
     if (tokens <= 64 && nvec <= 2 * 1024) {
-        hipLaunchKernelGGL((act_quant_kernel<1024, 2>), dim3((unsigned)tokens), dim3(1024), 0, stream, x, tokens, nvec, xq, sx);
+        hipLaunchKernelGGL((act_quant_kernel<1024, 2>), dim3((unsigned)tokens), dim3(1024), 0, stream, x, tokens, nvec, xq, ldq, sx, xq2, ld2);
     } else if (nvec <= 2 * 256) {
         // a block of four wavefronts per token (measured against one or two wavefronts per token with longer loops: same
         // kernel time, but the step that follows starts 1-2 % earlier)
-        hipLaunchKernelGGL((act_quant_kernel<256, 2>), dim3((unsigned)tokens), dim3(256), 0, stream, x, tokens, nvec, xq, sx);
+        hipLaunchKernelGGL((act_quant_kernel<256, 2>), dim3((unsigned)tokens), dim3(256), 0, stream, x, tokens, nvec, xq, ldq, sx, xq2, ld2);
     } else if (nvec <= 4 * 256) {
-        hipLaunchKernelGGL((act_quant_kernel<256, 4>), dim3((unsigned)tokens), dim3(256), 0, stream, x, tokens, nvec, xq, sx);
+        hipLaunchKernelGGL((act_quant_kernel<256, 4>), dim3((unsigned)tokens), dim3(256), 0, stream, x, tokens, nvec, xq, ldq, sx, xq2, ld2);
     } else {
-        hipLaunchKernelGGL(act_quant_two_pass_kernel, dim3((unsigned)ceil_div(tokens, 4)), dim3(256), 0, stream, x, tokens, nvec, xq, sx);
+        hipLaunchKernelGGL(act_quant_two_pass_kernel, dim3((unsigned)ceil_div(tokens, 4)), dim3(256), 0, stream, x, tokens, nvec, xq, ldq, sx, xq2, ld2);
     }
     return check_launch("act_quant_kernel");
+}
+
+sbn_status launch_spread_rows(const int8_t *src, int64_t tokens, int64_t d_in, int8_t *dst, int64_t ldq, hipStream_t stream)
+{
+    hipLaunchKernelGGL(spread_rows_kernel, dim3((unsigned)tokens), dim3(256), 0, stream, reinterpret_cast<const uint2 *>(src), tokens,
+                       (int)(d_in / 8), dst, ldq);
+    return check_launch("spread_rows_kernel");
 }
 
 sbn_status launch_rmsnorm_act_quant(const void *X, const float *gain, float eps, int64_t tokens, int64_t d_in, int8_t *xq,
@@ -987,7 +1018,7 @@ static void fill_gemv_item(GemvItem &g, const LinearItem &li)
 {
     g.xq = li.xq; g.sx = li.sx; g.packed = static_cast<const uint8_t *>(li.packed);
     g.gamma = li.gamma; g.bias = li.bias; g.Y = li.Y; g.acc_out = li.acc_out;
-    g.d_in = (int)li.d_in; g.d_out = (int)li.d_out; g.tokens = (int)li.tokens; g.pad = 0;
+    g.d_in = (int)li.d_in; g.d_out = (int)li.d_out; g.tokens = (int)li.tokens; g.d_x = (int)li.row_values();
     g.X = nullptr;
 }
 
@@ -1044,7 +1075,7 @@ static sbn_status launch_gemv_as(int count, const LinearItem *items, hipStream_t
         for (int i = 0; i < n; ++i) {
             const LinearItem &li = items[first + i];
             if (li.quantized || std::find(written.begin(), written.end(), li.xq) != written.end()) continue;
-            sbn_status st = launch_act_quant(li.X, li.tokens, li.d_in, li.xq, li.sx, stream);
+            sbn_status st = launch_act_quant(li.X, li.tokens, li.row_values(), li.xq, li.sx, stream, li.d_in);
             if (st != SBN_OK) return st;
             written.push_back(li.xq);
         }
@@ -1089,7 +1120,7 @@ static sbn_status launch_gemv_as(int count, const LinearItem *items, hipStream_t
             for (int i = 0; i < n && fuse; ++i) {
                 const LinearItem &li = items[first + i];
                 if (li.quantized || std::find(written.begin(), written.end(), li.xq) != written.end()) { one_input = false; continue; }
-                if (li.d_in > 8 * GEMV_QUANT_VEC * 64 * NW || li.tokens > 16) { fuse = false; break; }
+                if (li.d_in > 8 * GEMV_QUANT_VEC * 64 * NW || li.tokens > 16 || li.row_values() != li.d_in) { fuse = false; break; }
                 if (li.d_in > 8 * 64 * GEMV_OWN_VEC) one_input = false;
                 bool seen = false;
                 for (int j = 0; j < nin; ++j) seen = seen || in_xq[j] == li.xq;
