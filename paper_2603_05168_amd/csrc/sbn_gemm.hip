@@ -1059,12 +1059,42 @@ static int make_piece_table(const GemmGroup &grp, PieceTable &tab)
     return nb;
 }
 
+// Estimated time in us of a launch of the kernels below, next to which gemm_tile_estimate_us stands.  Measured:
+//   streaming kernel (<= 64 tokens)  one strip of 128 rows per block: 4 us + 5 us (up to 32 tokens) or 8.5 us per 2560 weights
+//       of the input dimension; strips of 256 rows: 12.5 or 17.5 us per round of the device
+//       (64 x (2560 -> 6912) at 32 / 64 tokens: 85 / 120 us; one layer alone 9.6 / 12.8, 6912 -> 2560 17.2 / 25.7)
+//   pieces of 512 rows x 32 .. 128 tokens  3.5 us + 9.5 us (14 with dense codes) per 2560 weights for the first unit of 32
+//       tokens a block has, 0.55 of that for each further one (2560 -> 2560 at 128 .. 1500 tokens 13.2 .. 13.9 us,
+//       6912 -> 2560 28 .. 30, 2560 -> 6912 at 777 / 1500 tokens, 2 / 3 units, 17.5 / 24)
+static float gemm_large_estimate_us(int count, const LinearItem *items, bool dense)
+{
+    bool stream = true;
+    int64_t strips = 0, units = 0, tokens = 0, depth = 0;
+    for (int i = 0; i < count; ++i) {
+        const LinearItem &li = items[i];
+        stream = stream && gemv_batch_takes(li);
+        strips += ceil_div(li.d_out, 256);
+        units += ceil_div(li.d_out, sp::ROWS) * ceil_div(li.tokens, 32);
+        tokens = li.tokens > tokens ? li.tokens : tokens;
+        depth = li.d_in > depth ? li.d_in : depth;
+    }
+    const float k = (float)depth / 2560.0f;
+    const int cus = device_cus();
+    if (stream) {
+        if (strips < cus) return 4.0f + k * (tokens <= 32 ? 5.0f : 8.5f);
+        return 4.0f + k * (tokens <= 32 ? 12.5f : 17.5f) * (float)strips / (float)cus;
+    }
+    return 3.5f + k * (dense ? 14.0f : 9.5f) * (1.0f + 0.55f * (float)(ceil_div(units, cus) - 1));
+}
+
 sbn_status launch_gemm_smfmac(int count, const LinearItem *items, bool dense_codes, hipStream_t stream)
 {
+    // small block tiles where they are faster: their time grows with rows x tokens from 4.5 us on, that of the large tiles
+    // starts two to five times higher and grows slower
+    if (gemm_tile_estimate_us(count, items, dense_codes) < gemm_large_estimate_us(count, items, dense_codes))
+        return launch_gemm_tile(count, items, dense_codes, stream);
     // problems of at most 16 token units (512 tokens: decode batches) are dealt by row tile, up to GEMM_GROUP_WIDE per launch
-    // (2: at most 64 tokens and nothing but Y asked for: the streaming kernel for decode batches.  Also for a single
-    // layer: with weights that come from HBM it measured 13.8 / 23.5 us at 32 tokens against 19.6 / 43.8 us on the
-    // pieces below, 6912 x 2560 / 2560 x 6912; a piece streams its 512 rows through one multiprocessor's shallow ring)
+    // (2: at most 64 tokens and nothing but Y asked for: the streaming kernel for decode batches)
     auto few_tokens = [&](int i) { return gemv_batch_takes(items[i]) ? 2 : items[i].tokens <= 16 * 32 ? 1 : 0; };
     for (int first = 0; first < count;) {
         const int few = few_tokens(first);

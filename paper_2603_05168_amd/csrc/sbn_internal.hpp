@@ -107,6 +107,9 @@ sbn_status launch_gemm_smfmac(int count, const LinearItem *items, bool dense_cod
 // once through a kernel of their own; launch_gemm_smfmac hands them over
 bool gemv_batch_takes(const LinearItem &it);
 sbn_status launch_gemv_batch(int count, const LinearItem *items, bool dense_codes, hipStream_t stream);
+// small block tiles (sbn_tile.hip): a few problems of few tokens; launch_gemm_smfmac hands over what this kernel is faster at
+float gemm_tile_estimate_us(int count, const LinearItem *items, bool dense_codes);
+sbn_status launch_gemm_tile(int count, const LinearItem *items, bool dense_codes, hipStream_t stream);
 sbn_status launch_gemm_dense(const LinearItem &it, const Pattern &pat, int8_t *w_dense, hipStream_t stream);
 sbn_status launch_gemm_dense_expanded(const LinearItem &it, const int8_t *w_dense, hipStream_t stream);
 sbn_status launch_linear_generic(const LinearItem &it, const Pattern &pat, hipStream_t stream);

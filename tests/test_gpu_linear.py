@@ -760,3 +760,27 @@ def test_streaming_decode_alternating_weight_forms_on_one_workspace():
         for r in range(R):
             y, *_ = oracle.sparse_ternary_linear(Xf, refs[nm][r][2], refs[nm][r][1])
             assert_rel(Ys[r].cpu().numpy(), y, Y_TOL, f"call {call} ({nm[0]}:{nm[1]}), copy {r}")
+
+
+@pytest.mark.parametrize("N,M", [(2, 4), (8, 8)])
+@pytest.mark.parametrize("tokens,shape", [(17, (33, 128)),       # 32 x 16 tiles: one row past a tile, a single odd chunk
+                                          (32, (2560, 384)),     # a full token tile pair, an odd number of chunks
+                                          (33, (100, 2304)),     # 32 x 32 tiles, nine stages on eight wavefronts
+                                          (65, (514, 640)),      # rows not a multiple of four: stores per element
+                                          (159, (2564, 896)),    # 64 x 32 tiles, 205 of them, last ones ragged both ways
+                                          (777, (1000, 1408))])  # many tiles per multiprocessor, an odd number of chunks
+@pytest.mark.parametrize("bias", [False, True])
+def test_small_block_tiles(N, M, tokens, shape, bias):
+    s = sbn()
+    W = sbn_synth.latent_weight(shape[0], shape[1], 5000 + shape[0])
+    X = sbn_synth.activations(tokens, shape[1], 5001 + tokens)
+    b = torch.randn(shape[0], generator=torch.Generator().manual_seed(7)) if bias else None
+    packed, gamma = hip_pack(W, N, M)
+    _, g, Weff, _ = oracle_pack(W, N, M)
+    y, *_ = oracle.sparse_ternary_linear(X.float().numpy(), Weff, g)
+    for want_acc in (False, True):
+        Y, *_ = hip_linear(X, packed, gamma, shape[0], N, M, s.SBN_PATH_AUTO, b, want_acc=want_acc)
+        # three roundings of the product (scale, accumulator to fp32, product), one more of the sum with the bias
+        bv = 0.0 if b is None else b.numpy().astype(np.float64)[None, :]
+        assert (np.abs(Y.astype(np.float64) - (y + bv)) <= 4 * 2.0 ** -24 * (np.abs(y) + np.abs(bv))).all()
+    check_forward(W, X, N, M, s.SBN_PATH_SMFMAC)
