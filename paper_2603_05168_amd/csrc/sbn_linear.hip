@@ -258,11 +258,11 @@ __global__ void __launch_bounds__(TPT < 256 ? 256 : TPT) rmsnorm_act_quant_kerne
 }
 
 // ---- decode GEMV on the sparse MFMA (tokens <= 16, 2:4) -----------------------------------------
-// A block owns 16 rows of W.  Its wavefronts split the input dimension in super-steps of 512
+// A block owns 16 RT rows of W.  Its wavefronts split the input dimension in super-steps of 512
 // weights: for such a super-step a lane (row r = lane % 16, quarter c = lane / 16) loads the whole
 // 32-byte chunk c of its row (one 16-byte index load, one 16-byte code load; a wavefront reads
 // 128 contiguous bytes per row), then issues four v_smfmac_i32_16x16x128_i8, the j-th using index
-// word j and code word j.  The tokens are the B operand (16 columns; columns >= tokens are zero).
+// word j and code word j.  The tokens are the B operand (16 columns; columns >= tokens are not stored).
 // Partial accumulators of the wavefronts are summed through LDS, rescaled and stored.
 struct GemvItem {
     const int8_t *xq;
@@ -272,192 +272,259 @@ struct GemvItem {
     const float *bias;
     float *Y;
     int32_t *acc_out;
-    const uint4 *X;   // bf16 activations when the block quantizes them itself (then xq and sx are unused), else null
+    const uint4 *X;   // bf16 activations of a block that quantizes them itself (then xq and sx are unused)
     int d_in, d_out, tokens;
     int d_x;          // values in a row of X (d_in rounded down to what X holds: d_in counts whole chunks)
 };
-constexpr int GEMV_MAX_ITEMS = 40;
-constexpr int GEMV_ROW_VEC = 14;   // 16-byte vectors of a token row per lane when a wavefront of the single-call kernel quantizes it
+template <int NI>
 struct GemvTable {
-    GemvItem it[GEMV_MAX_ITEMS];   // problem = blockIdx.y; row tile = blockIdx.x (surplus blocks exit at once)
+    GemvItem it[NI];  // problem = blockIdx.y; row tile = blockIdx.x (surplus blocks exit at once)
 };
-static_assert(sizeof(GemvTable) <= 4096, "the table travels as a kernel argument");
+// A launch of a few problems carries a short table: the 3 KB of the long one cost the host half a microsecond.
+constexpr int GEMV_FEW = 4, GEMV_MAX_ITEMS = 40;
+static_assert(sizeof(GemvTable<GEMV_MAX_ITEMS>) <= 4096, "the table travels as a kernel argument");
 
-// DENSE = true is the same kernel for weights stored as dense 2-bit codes (the packed form of
-// N = M, and what other patterns are rewritten to for decode): a chunk is eight code words, every
-// word is the A operand of one v_mfma_i32_16x16x64_i8 (lane quarter c holds k = 16c .. 16c+15 of
-// the instruction on both operands), so a super-step is eight dense instructions instead of four sparse.
-// FORM = GEMV_1OF4 reads the 1:4 packed form as stored (16-byte chunks, one load per lane and super-step) and builds
-// the sparse instruction's operands in registers (expand_1of4): half the weight bytes for three times the vector work.
-template <int FORM>
-__global__ void __launch_bounds__(1024) gemv_smfmac_kernel(GemvTable tab)
+// One super-step of one wavefront and row tile: idx4 / code4 = the lane's chunk, bfrag(j, x) = the lane's token operand.
+// FORM = GEMV_DENSE: weights stored as dense 2-bit codes (the packed form of N = M, and what other patterns are
+// rewritten to for decode): a chunk is eight code words, every word is the A operand of one v_mfma_i32_16x16x64_i8
+// (lane quarter c holds k = 16c .. 16c+15 of the instruction on both operands).  FORM = GEMV_1OF4 reads the 1:4 packed
+// form as stored (16-byte chunks, one load per lane and super-step) and builds the sparse instruction's operands in
+// registers (expand_1of4): half the weight bytes for three times the vector work.
+// x0 = the lane's token row at the super-step's first value; inside(k) = k, or an offset inside the row where k lies past
+// it (zero codes meet what is read there).  The operand loads stand in front, unconditional, so that all are in flight together.
+template <int FORM, int RT, class Inside>
+__device__ __forceinline__ void gemv_super_step(const uint4 (&idx4)[RT], const uint4 (&code4)[RT], const int8_t *x0, const int c4,
+                                                const uint32_t ones, Inside &&inside, v4i (&acc)[RT])
 {
-    constexpr bool DENSE = FORM == GEMV_DENSE, ONE4 = FORM == GEMV_1OF4;
-    constexpr int CB = ONE4 ? 16 : 32;   // bytes of a chunk
-    extern __shared__ __attribute__((aligned(16))) int8_t xs[];   // self-quantized activations [tokens][d_in + 16]
-    __shared__ v4i red[16][64];
-    __shared__ uint32_t amax_s[16][16];   // [token][wavefront]
-    __shared__ float sx_s[16];
+    uint4 x[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+        x[j] = *reinterpret_cast<const uint4 *>(x0 + inside(FORM == GEMV_DENSE ? 128 * c4 + 16 * j : 128 * (c4 >> 1) + 16 * (c4 & 1) + 32 * (j >> 1) + 256 * (j & 1)));
+    if constexpr (FORM == GEMV_DENSE) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const v4i b = __builtin_bit_cast(v4i, x[j]);
+#pragma unroll
+            for (int a = 0; a < RT; ++a) {
+                const uint4 &h = j < 4 ? idx4[a] : code4[a];
+                const uint32_t w = (j & 3) == 0 ? h.x : (j & 3) == 1 ? h.y : (j & 3) == 2 ? h.z : h.w;
+                acc[a] = __builtin_amdgcn_mfma_i32_16x16x64_i8(expand_codes(w, ones), b, acc[a], 0, 0, 0);
+            }
+        }
+    } else {
+        uint32_t iw1[RT][2][2];
+        v4i a1[RT][2][2];
+        if constexpr (FORM == GEMV_1OF4) {   // the chunk is two index words and two code words
+#pragma unroll
+            for (int a = 0; a < RT; ++a) {
+                expand_1of4(idx4[a].x, idx4[a].z, ones, iw1[a][0], a1[a][0]);
+                expand_1of4(idx4[a].y, idx4[a].w, ones, iw1[a][1], a1[a][1]);
+            }
+        }
+        // B operand: elements 0..15 pair with the A lanes of quarters 0/1, elements 16..31 with
+        // quarters 2/3 (measured operand layout of the instruction)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const uint4 &blo = x[2 * j], &bhi = x[2 * j + 1];
+            const v8i b = {(int)blo.x, (int)blo.y, (int)blo.z, (int)blo.w, (int)bhi.x, (int)bhi.y, (int)bhi.z, (int)bhi.w};
+#pragma unroll
+            for (int a = 0; a < RT; ++a) {
+                if constexpr (FORM == GEMV_1OF4) {
+                    acc[a] = __builtin_amdgcn_smfmac_i32_16x16x128_i8(a1[a][j >> 1][j & 1], b, acc[a], (int)iw1[a][j >> 1][j & 1], 0, 0);
+                } else {
+                    const uint32_t cw = j == 0 ? code4[a].x : j == 1 ? code4[a].y : j == 2 ? code4[a].z : code4[a].w;
+                    const uint32_t iw = j == 0 ? idx4[a].x : j == 1 ? idx4[a].y : j == 2 ? idx4[a].z : idx4[a].w;
+                    acc[a] = __builtin_amdgcn_smfmac_i32_16x16x128_i8(expand_codes(cw, ones), b, acc[a], (int)iw, 0, 0);
+                }
+            }
+        }
+    }
+}
+
+// the lane's chunk of super-step s of its row in each row tile; zero codes past the row
+template <int FORM, int RT>
+__device__ __forceinline__ void gemv_fetch(const uint8_t *const (&wrow)[RT], int s, int c4, int nchunks, uint4 (&idx4)[RT], uint4 (&code4)[RT])
+{
+    constexpr int CB = FORM == GEMV_1OF4 ? 16 : 32;   // bytes of a chunk
+    const int chunk = 4 * s + c4;
+#pragma unroll
+    for (int a = 0; a < RT; ++a) {
+        idx4[a] = code4[a] = make_uint4(0, 0, 0, 0);
+        if (chunk < nchunks) {
+            idx4[a] = *reinterpret_cast<const uint4 *>(wrow[a] + (int64_t)chunk * CB);
+            if constexpr (FORM != GEMV_1OF4) code4[a] = *reinterpret_cast<const uint4 *>(wrow[a] + (int64_t)chunk * CB + 16);
+        }
+    }
+}
+
+// Sums the wavefronts' partial accumulators (red: [wavefront][row tile][lane]), rescales and stores: wavefront a takes row
+// tile a.  Lane: token lane % 16 with the factor `scale`, rows 4 * (lane / 16) + i.
+template <int RT>
+__device__ __forceinline__ void gemv_finish(const GemvItem &it, const v4i (&acc)[RT], v4i *red, int row0, float scale, int wave, int nwaves, int lane)
+{
+#pragma unroll
+    for (int a = 0; a < RT; ++a) red[(wave * RT + a) * 64 + lane] = acc[a];
+    __syncthreads();
+    for (int a = wave; a < RT; a += nwaves) {
+        v4i sum = red[a * 64 + lane];
+        for (int w = 1; w < nwaves; ++w) sum += red[(w * RT + a) * 64 + lane];
+        const int tok = lane & 15, o = row0 + 16 * a + 4 * (lane >> 4);
+        if (tok >= it.tokens || o >= it.d_out) continue;
+        v4f y = {(float)sum[0] * scale, (float)sum[1] * scale, (float)sum[2] * scale, (float)sum[3] * scale};
+        float *dst = it.Y + (int64_t)tok * it.d_out + o;
+        if ((it.d_out & 3) == 0 && !it.bias && !it.acc_out) {
+            *reinterpret_cast<v4f *>(dst) = y;
+            continue;
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (o + i < it.d_out) {
+                dst[i] = it.bias ? y[i] + it.bias[o + i] : y[i];
+                if (it.acc_out) it.acc_out[(int64_t)tok * it.d_out + o + i] = sum[i];
+            }
+    }
+}
+
+// on activations that are quantized already
+template <int FORM, int RT, int NI>
+__global__ void __launch_bounds__(1024) gemv_smfmac_kernel(GemvTable<NI> tab)
+{
+    constexpr int CB = FORM == GEMV_1OF4 ? 16 : 32;
+    extern __shared__ __attribute__((aligned(16))) int8_t dyn[];
     const GemvItem &it = tab.it[blockIdx.y];
-    const int row0 = (int)blockIdx.x * 16;
+    const int row0 = (int)blockIdx.x * 16 * RT;
     if (row0 >= it.d_out) return;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwaves = blockDim.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nwaves = blockDim.x >> 6;
     const int r = lane & 15, c4 = lane >> 4;
     const uint32_t ones = vgpr_ones();
     const int K = it.d_in, nchunks = K / CHUNK, nsuper = (nchunks + 3) / 4;
-    int row = row0 + r;
-    row = row < it.d_out ? row : it.d_out - 1;   // rows past the end are computed and dropped
-    const uint8_t *wrow = it.packed + (int64_t)row * nchunks * CB;
-    const bool tok_ok = r < it.tokens;           // as B operand the lane holds token r
-    const bool self_quant = it.X != nullptr;
-    const int pitch = K + 16;
-    const int8_t *xrow = self_quant ? xs + (tok_ok ? r : 0) * pitch : it.xq + (int64_t)(tok_ok ? r : 0) * K;
-
-    // the wavefront's first weight words go out before anything else: they fly while the block quantizes
-    uint4 idx4 = make_uint4(0, 0, 0, 0), code4 = make_uint4(0, 0, 0, 0);
-    auto fetch = [&](int s) {
-        const int chunk = 4 * s + c4;
-        idx4 = make_uint4(0, 0, 0, 0);
-        code4 = make_uint4(0, 0, 0, 0);
-        if (s < nsuper && chunk < nchunks) {
-            idx4 = *reinterpret_cast<const uint4 *>(wrow + (int64_t)chunk * CB);
-            if constexpr (!ONE4) code4 = *reinterpret_cast<const uint4 *>(wrow + (int64_t)chunk * CB + 16);
-        }
-    };
-    fetch(wave);
-    if (self_quant) {
-        // every block quantizes the few token rows itself (the quantizer's arithmetic), saving the quantizer's
-        // launch in front of a latency-bound call
-        const int nvec = it.d_x / 8, nthreads = (int)blockDim.x;   // past d_x the LDS row keeps what it held: zero codes meet it
-        if (nvec <= 64 * GEMV_ROW_VEC) {
-            // a wavefront per token row, the row in registers (two short rows at a time): the rows of a block cost one
-            // or two trips to memory in all, the maximum needs no barrier, the int8 row goes straight into LDS
-            auto finish = [&](int t, uint32_t m, auto &xv, auto nv) {
+    const uint8_t *wrow[RT];
 #pragma unroll
-                for (int off = 32; off > 0; off >>= 1) {
-                    const uint32_t o = (uint32_t)__shfl_xor((int)m, off, 64);
-                    m = o > m ? o : m;
-                }
-                const float sc = scale_from_absmax_bits(m);
-                if (lane == 0) sx_s[t] = sc;
-#pragma unroll
-                for (int i = 0; i < nv(); ++i) {
-                    const int idx = lane + 64 * i;
-                    if (idx < nvec) *reinterpret_cast<uint2 *>(xs + t * pitch + idx * 8) = quantize_bf16x8(xv[i], sc);
-                }
-            };
-            auto request = [&](int t, auto &xv, auto nv) {
-                uint32_t m = 0;
-#pragma unroll
-                for (int i = 0; i < nv(); ++i) {
-                    const int idx = lane + 64 * i;
-                    xv[i] = it.X[(int64_t)t * nvec + (idx < nvec ? idx : nvec - 1)];   // past the end the last vector again
-                }
-#pragma unroll
-                for (int i = 0; i < nv(); ++i) m = absmax_bits_bf16x8(xv[i], m);
-                return m;
-            };
-            if (nvec <= 64 * (GEMV_ROW_VEC / 2)) {
-                std::integral_constant<int, GEMV_ROW_VEC / 2> nv;
-                for (int t = wave; t < it.tokens; t += 2 * nwaves) {
-                    uint4 xa[GEMV_ROW_VEC / 2], xb[GEMV_ROW_VEC / 2];
-                    const int t2 = t + nwaves < it.tokens ? t + nwaves : t;   // the last row alone: quantized twice, alike
-                    const uint32_t ma = request(t, xa, nv), mb = request(t2, xb, nv);
-                    finish(t, ma, xa, nv);
-                    finish(t2, mb, xb, nv);
-                }
-            } else {
-                std::integral_constant<int, GEMV_ROW_VEC> nv;
-                for (int t = wave; t < it.tokens; t += nwaves) {
-                    uint4 xa[GEMV_ROW_VEC];
-                    const uint32_t ma = request(t, xa, nv);
-                    finish(t, ma, xa, nv);
-                }
-            }
-        } else {
-            // long rows: pass 1 per-token maxima, pass 2 int8 rows into LDS
-            for (int t = 0; t < it.tokens; ++t) {
-                uint32_t m = 0;
-                for (int idx = threadIdx.x; idx < nvec; idx += nthreads) m = absmax_bits_bf16x8(it.X[(int64_t)t * nvec + idx], m);
-#pragma unroll
-                for (int off = 32; off > 0; off >>= 1) {
-                    const uint32_t o = (uint32_t)__shfl_xor((int)m, off, 64);
-                    m = o > m ? o : m;
-                }
-                if (lane == 0) amax_s[t][wave] = m;
-            }
-            __syncthreads();
-            for (int t = 0; t < it.tokens; ++t) {
-                uint32_t m = 0;
-                for (int w = 0; w < nwaves; ++w) m = amax_s[t][w] > m ? amax_s[t][w] : m;
-                const float sc = scale_from_absmax_bits(m);
-                if (threadIdx.x == 0) sx_s[t] = sc;
-                for (int idx = threadIdx.x; idx < nvec; idx += nthreads)
-                    *reinterpret_cast<uint2 *>(xs + t * pitch + idx * 8) = quantize_bf16x8(it.X[(int64_t)t * nvec + idx], sc);
-            }
-        }
-        __syncthreads();
+    for (int a = 0; a < RT; ++a) {
+        const int row = row0 + 16 * a + r;
+        wrow[a] = it.packed + (int64_t)(row < it.d_out ? row : it.d_out - 1) * nchunks * CB;   // rows past the end are computed and dropped
     }
-
-    v4i acc = {0, 0, 0, 0};
+    const int tok = r < it.tokens ? r : 0;   // as B operand the lane holds token r
+    const int8_t *xrow = it.xq + (int64_t)tok * K;
+    const float gamma = *it.gamma, sx = it.sx[tok];
+    uint4 idx4[RT], code4[RT];
+    gemv_fetch<FORM, RT>(wrow, wave, c4, nchunks, idx4, code4);
+    v4i acc[RT];
+#pragma unroll
+    for (int a = 0; a < RT; ++a) acc[a] = v4i{0, 0, 0, 0};
     for (int s = wave; s < nsuper; s += nwaves) {
-        const uint32_t idxw[4] = {idx4.x, idx4.y, idx4.z, idx4.w};
-        const uint32_t codew[4] = {code4.x, code4.y, code4.z, code4.w};
-        fetch(s + nwaves);   // the next super-step of this wavefront (zeros past the end)
-        // B operand: elements 0..15 pair with the A lanes of quarters 0/1, elements 16..31 with
-        // quarters 2/3 (measured operand layout of the instruction)
-        if constexpr (DENSE) {
-            const uint32_t w8[8] = {idxw[0], idxw[1], idxw[2], idxw[3], codew[0], codew[1], codew[2], codew[3]};
-            const int kd = s * 512 + 128 * c4;
+        uint4 ic[RT], cc[RT];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                uint4 bv = make_uint4(0, 0, 0, 0);
-                if (tok_ok && kd + 16 * j < K) bv = *reinterpret_cast<const uint4 *>(xrow + kd + 16 * j);
-                const v4i b = {(int)bv.x, (int)bv.y, (int)bv.z, (int)bv.w};
-                acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(expand_codes(w8[j], ones), b, acc, 0, 0, 0);
-            }
-            continue;
-        }
-        const int kb = s * 512 + 128 * (c4 >> 1) + 16 * (c4 & 1);
-        uint32_t iw1[2][2];
-        v4i a1[2][2];
-        if constexpr (ONE4) {   // the chunk is two index words and two code words
-            expand_1of4(idxw[0], idxw[2], ones, iw1[0], a1[0]);
-            expand_1of4(idxw[1], idxw[3], ones, iw1[1], a1[1]);
-        }
+        for (int a = 0; a < RT; ++a) { ic[a] = idx4[a]; cc[a] = code4[a]; }
+        gemv_fetch<FORM, RT>(wrow, s + nwaves, c4, nchunks, idx4, code4);   // the next super-step of this wavefront (zeros past the end)
+        gemv_super_step<FORM, RT>(ic, cc, xrow + s * 512, c4, ones, [&](int k) { return s * 512 + k < K ? k : K - 16 - s * 512; }, acc);
+    }
+    gemv_finish<RT>(it, acc, reinterpret_cast<v4i *>(dyn), row0, __fdiv_rn(gamma, sx), wave, nwaves, lane);
+}
+
+// The same with the quantizer inside, for rows of at most 16 super-steps: wavefront w owns super-step w of the weights AND of
+// the token rows.  Its 8 KB of weights and its 512 values of every token (one 16-byte load per lane and token) are asked
+// for together, the largest magnitude of each row meets in LDS behind one barrier, every wavefront quantizes its own
+// values (the quantizer's arithmetic) into its own part of LDS and reads the operand from there.  Two barriers in all, and
+// the quantizer's work is split over all wavefronts; a wavefront per token row left the other wavefronts waiting.
+// What bounds it: the chain of one load, two barriers and a store on top of the 1.9 us of any launch, from four tokens on
+// the vector work of the quantizer.  Measured, weights from memory, us at 1 / 4 / 8 / 16 tokens: 2560 -> 2560 3.6 / 4.4 / 5.1 / 6.6
+// (a wavefront per token row, one row tile per block: 5.6 / 6.0 / 6.3 / 8.4), 6912 -> 2560 4.5 / 5.9 / 7.3 / 10.2 (6.2 / 6.6 / 7.4 / 9.9),
+// 2560 -> 2 x 6912 in one call 5.4 / 6.4 / 7.8 / 10.6 (10.6 / 11.9 / 14.0 / 21.9).
+constexpr int GEMV_SELF_SUPER = 16;       // super-steps at most = wavefronts of a block
+constexpr int GEMV_SELF_PITCH = 512 + 16; // bytes between the token rows of a wavefront's part of LDS
+constexpr size_t gemv_self_lds(int64_t tokens, int nwaves, int rt) { return (size_t)nwaves * ((size_t)tokens * GEMV_SELF_PITCH + rt * 1024); }
+
+__device__ __forceinline__ uint32_t max_u16x2(uint32_t a, uint32_t b)
+{
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(ushort2_t, a), __builtin_bit_cast(ushort2_t, b)));
+}
+template <int CTRL> __device__ __forceinline__ uint32_t dpp_max_u16x2(uint32_t x)
+{
+    return max_u16x2(x, (uint32_t)__builtin_amdgcn_mov_dpp((int)x, CTRL, 0xf, 0xf, true));
+}
+// largest magnitude patterns of the even and of the odd ones of eight bf16 values
+__device__ __forceinline__ uint32_t absmax_pair_bf16x8(const uint4 &d)
+{
+    return max_u16x2(max_u16x2(d.x & 0x7fff7fffu, d.y & 0x7fff7fffu), max_u16x2(d.z & 0x7fff7fffu, d.w & 0x7fff7fffu));
+}
+
+template <int FORM, int RT, int NI, int TM>
+__global__ void __launch_bounds__(1024) gemv_self_kernel(GemvTable<NI> tab)
+{
+    constexpr int CB = FORM == GEMV_1OF4 ? 16 : 32;
+    extern __shared__ __attribute__((aligned(16))) int8_t dyn[];      // [wavefront][tokens][pitch], then the partial accumulators
+    __shared__ __attribute__((aligned(16))) uint32_t amax[TM][4 * GEMV_SELF_SUPER];   // [token][wavefront, row of 16 lanes]
+    const GemvItem &it = tab.it[blockIdx.y];
+    const int row0 = (int)blockIdx.x * 16 * RT;
+    if (row0 >= it.d_out) return;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nwaves = blockDim.x >> 6;
+    const int r = lane & 15, c4 = lane >> 4, T = it.tokens;
+    const uint32_t ones = vgpr_ones();
+    const int K = it.d_in, nchunks = K / CHUNK, nvec = it.d_x / 8;
+    const uint8_t *wrow[RT];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int k_lo = kb + 32 * j, k_hi = k_lo + 256;
-            uint4 blo = make_uint4(0, 0, 0, 0), bhi = make_uint4(0, 0, 0, 0);
-            if (tok_ok && k_lo < K) blo = *reinterpret_cast<const uint4 *>(xrow + k_lo);
-            if (tok_ok && k_hi < K) bhi = *reinterpret_cast<const uint4 *>(xrow + k_hi);
-            const v8i b = {(int)blo.x, (int)blo.y, (int)blo.z, (int)blo.w, (int)bhi.x, (int)bhi.y, (int)bhi.z, (int)bhi.w};
-            if constexpr (ONE4)
-                acc = __builtin_amdgcn_smfmac_i32_16x16x128_i8(a1[j >> 1][j & 1], b, acc, (int)iw1[j >> 1][j & 1], 0, 0);
-            else
-                acc = __builtin_amdgcn_smfmac_i32_16x16x128_i8(expand_codes(codew[j], ones), b, acc, (int)idxw[j], 0, 0);
+    for (int a = 0; a < RT; ++a) {
+        const int row = row0 + 16 * a + r;
+        wrow[a] = it.packed + (int64_t)(row < it.d_out ? row : it.d_out - 1) * nchunks * CB;
+    }
+    // the token values first: they are needed first
+    const int vec = 64 * wave + lane;
+    const uint4 *xp = it.X + (vec < nvec ? vec : nvec - 1);   // past the row its last vector again: the maximum is the same, the codes are zero
+    uint4 xv[TM];
+#pragma unroll
+    for (int t = 0; t < TM; ++t)
+        if (t < T) xv[t] = xp[(int64_t)t * nvec];
+    uint4 idx4[RT], code4[RT];
+    gemv_fetch<FORM, RT>(wrow, wave, c4, nchunks, idx4, code4);
+    const float gamma = *it.gamma;
+    // largest magnitudes, two tokens in a register; rows of 16 lanes are reduced here, the rest through LDS
+#pragma unroll
+    for (int t = 0; t < TM; t += 2) {
+        if (t >= T) break;
+        const uint32_t m0 = absmax_pair_bf16x8(xv[t]), m1 = t + 1 < T ? absmax_pair_bf16x8(xv[t + 1 < TM ? t + 1 : t]) : 0u;
+        uint32_t m = max_u16x2(__builtin_amdgcn_perm(m1, m0, 0x05040100u), __builtin_amdgcn_perm(m1, m0, 0x07060302u));   // low halves, high halves
+        m = dpp_max_u16x2<0xb1>(m);    // quad_perm 1 0 3 2
+        m = dpp_max_u16x2<0x4e>(m);    // quad_perm 2 3 0 1
+        m = dpp_max_u16x2<0x141>(m);   // row_half_mirror
+        m = dpp_max_u16x2<0x140>(m);   // row_mirror
+        if (r == 0) {
+            amax[t][4 * wave + c4] = m & 0xffffu;
+            if (t + 1 < TM) amax[t + 1][4 * wave + c4] = m >> 16;
         }
     }
-    red[wave][lane] = acc;
     __syncthreads();
-    if (wave == 0) {
-        for (int w = 1; w < nwaves; ++w) acc += red[w][lane];
-        // D layout: lane holds token (lane % 16), rows 4 * (lane / 16) + i
-        const int tok = lane & 15, rbase = row0 + 4 * (lane >> 4);
-        if (tok < it.tokens) {
-            const float scale = __fdiv_rn(*it.gamma, self_quant ? sx_s[tok] : it.sx[tok]);
+    // lane: the scale of token lane % 16
+    float s;
+    {
+        // quarter c4 reads what wavefronts c4, c4 + 4, ... found (past the last one that one again), then the quarters meet
+        const uint4 *col = reinterpret_cast<const uint4 *>(amax[r < T ? r : 0]);
+        uint32_t m = 0;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int o = rbase + i;
-                if (o < it.d_out) {
-                    float y = (float)acc[i] * scale;
-                    if (it.bias) y += it.bias[o];
-                    it.Y[(int64_t)tok * it.d_out + o] = y;
-                    if (it.acc_out) it.acc_out[(int64_t)tok * it.d_out + o] = acc[i];
-                }
-            }
+        for (int i = 0; i < GEMV_SELF_SUPER / 4; ++i) {
+            if (4 * i >= nwaves) break;
+            const uint4 v = col[4 * i + c4 < nwaves ? 4 * i + c4 : nwaves - 1];
+            const uint32_t a = v.x > v.y ? v.x : v.y, b = v.z > v.w ? v.z : v.w, c = a > b ? a : b;
+            m = c > m ? c : m;
         }
+        const auto x16 = __builtin_amdgcn_permlane16_swap(m, m, false, false);   // neighbouring quarters
+        m = x16[0] > x16[1] ? x16[0] : x16[1];
+        const auto x32 = __builtin_amdgcn_permlane32_swap(m, m, false, false);   // halves of the wavefront
+        m = x32[0] > x32[1] ? x32[0] : x32[1];
+        s = scale_from_absmax_bits(m);
     }
+    int8_t *const xs = dyn + wave * T * GEMV_SELF_PITCH;
+#pragma unroll
+    for (int t = 0; t < TM; ++t)
+        if (t < T)
+            *reinterpret_cast<uint2 *>(xs + t * GEMV_SELF_PITCH + 8 * lane) =
+                quantize_bf16x8(xv[t], __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(s), t)));
+    v4i acc[RT];
+#pragma unroll
+    for (int a = 0; a < RT; ++a) acc[a] = v4i{0, 0, 0, 0};
+    // what the wavefront wrote itself: its LDS operations complete in order
+    gemv_super_step<FORM, RT>(idx4, code4, xs + (r < T ? r : 0) * GEMV_SELF_PITCH, c4, ones, [](int k) { return k; }, acc);
+    gemv_finish<RT>(it, acc, reinterpret_cast<v4i *>(dyn + nwaves * T * GEMV_SELF_PITCH), row0, __fdiv_rn(gamma, s), wave, nwaves, lane);
 }
 
 // ---- streaming decode GEMV for grouped calls ---------------------------------------------------
@@ -1064,6 +1131,50 @@ static bool stream_is_capturing(hipStream_t stream)
     return status != hipStreamCaptureStatusNone;
 }
 
+constexpr size_t GEMV_SELF_LDS = 152 * 1024;   // next to 4 KB of maxima
+// Row tiles of 16 from which a block takes two of them: a multiprocessor then has more than one block either way, and the
+// quantizer's work is done half as often (480 tiles, eight tokens: 5.9 us against 6.4; 160 tiles, one token: 4.1 against 3.7).
+constexpr int64_t GEMV_PAIR_TILES = 400;
+// Every block quantizes all token rows, 0.04 to 0.06 us per 1000 values and block of a multiprocessor, where a launch of the
+// quantizer in front costs 2.2 us on the device and another launch on the host.  Measured at 16 tokens: 4096 -> 4096 7.3 us
+// against 8.0, 8192 -> 4096 12.4 against 12.3, 4096 -> 2 x 14336 (three blocks per multiprocessor) 29 against 20, at eight tokens 14.5
+// against 15.8.
+constexpr int64_t GEMV_SELF_VALUES = 16 * 8192;
+
+// one launch of the row-tile kernels; tm = 0: on quantized activations, else the token slots of the kernel that quantizes
+template <int FORM, int RT, int NI>
+static sbn_status launch_gemv_rows(int n, const LinearItem *items, int nwaves, int tm, hipStream_t stream)
+{
+    GemvTable<NI> tab;
+    int blocks = 0;
+    int64_t tokens = 1;
+    for (int i = 0; i < n; ++i) {
+        fill_gemv_item(tab.it[i], items[i]);
+        tab.it[i].X = static_cast<const uint4 *>(items[i].X);
+        const int nb = (int)ceil_div(items[i].d_out, 16 * RT);
+        blocks = nb > blocks ? nb : blocks;
+        tokens = items[i].tokens > tokens ? items[i].tokens : tokens;
+    }
+    for (int i = n; i < NI; ++i) tab.it[i] = tab.it[0];
+    const dim3 grid(blocks, n), block(64 * nwaves);
+    if (tm == 0) {
+        hipLaunchKernelGGL((gemv_smfmac_kernel<FORM, RT, NI>), grid, block, (size_t)nwaves * RT * 1024, stream, tab);
+        return check_launch("gemv_smfmac_kernel");
+    }
+    static thread_local bool raised = false;
+    if (!raised) {
+        for (const void *k : {reinterpret_cast<const void *>(&gemv_self_kernel<FORM, RT, NI, 2>), reinterpret_cast<const void *>(&gemv_self_kernel<FORM, RT, NI, 16>)}) {
+            hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)GEMV_SELF_LDS);
+            if (e != hipSuccess) { set_hip_error(e, "hipFuncSetAttribute"); return SBN_EHIP; }
+        }
+        raised = true;
+    }
+    const size_t lds = gemv_self_lds(tokens, nwaves, RT);
+    if (tm == 2) hipLaunchKernelGGL((gemv_self_kernel<FORM, RT, NI, 2>), grid, block, lds, stream, tab);
+    else hipLaunchKernelGGL((gemv_self_kernel<FORM, RT, NI, 16>), grid, block, lds, stream, tab);
+    return check_launch("gemv_self_kernel");
+}
+
 template <int FORM>
 static sbn_status launch_gemv_as(int count, const LinearItem *items, hipStream_t stream)
 {
@@ -1181,53 +1292,33 @@ static sbn_status launch_gemv_as(int count, const LinearItem *items, hipStream_t
             first += n;
             continue;
         }
-        // --- otherwise: one block per 16 rows, wavefronts split the input dimension (lowest latency)
+        // --- otherwise: blocks of 16 or 32 rows, wavefronts split the input dimension (lowest latency)
         n = count - first < GEMV_MAX_ITEMS ? count - first : GEMV_MAX_ITEMS;
-        // the blocks quantize the activations themselves (measured at 6912 x 2560 and 2560 x 6912: 9.3-9.7 us for
-        // 1-16 tokens against 12 us with the quantizer launched in front; a wavefront per token row with the row in
-        // registers - walking the tokens one after the other cost a trip to memory per token and pass: 13-16 us at 8)
-        constexpr int64_t GEMV_SELF_QUANT_LDS = 112 * 1024;
-        constexpr int64_t GEMV_SELF_QUANT_TOKENS = 16;
-        int64_t dyn_lds = 0;
+        int most_super = 1;
+        int64_t tiles = 0, most_tokens = 1;
         bool self_quant = true;
         for (int i = 0; i < n; ++i) {
             const LinearItem &li = items[first + i];
-            if (li.quantized) continue;
-            const int64_t b = li.tokens * (li.d_in + 16);
-            if (b > GEMV_SELF_QUANT_LDS || li.tokens > GEMV_SELF_QUANT_TOKENS ||
-                std::find(written.begin(), written.end(), li.xq) != written.end())
-                self_quant = false;
-            dyn_lds = b > dyn_lds ? b : dyn_lds;
+            const int nsuper = (int)ceil_div(li.d_in, 4 * CHUNK);
+            most_super = nsuper > most_super ? nsuper : most_super;
+            most_tokens = li.tokens > most_tokens ? li.tokens : most_tokens;
+            tiles += ceil_div(li.d_out, 16);
+            if (li.quantized || std::find(written.begin(), written.end(), li.xq) != written.end()) self_quant = false;
         }
+        // one wavefront per super-step up to 16, so that every wavefront has loads in flight at once
+        const int nwaves = most_super < GEMV_SELF_SUPER ? most_super : GEMV_SELF_SUPER;
+        const int rt = tiles >= GEMV_PAIR_TILES ? 2 : 1;
+        const int64_t per_cu = std::max<int64_t>(1, tiles / rt / device_cus());
+        if (most_super > GEMV_SELF_SUPER || most_tokens * most_super * 512 * per_cu > GEMV_SELF_VALUES ||
+            gemv_self_lds(most_tokens, nwaves, rt) > GEMV_SELF_LDS)
+            self_quant = false;
         if (!self_quant) {
             sbn_status st = quantize_run(first, n);
             if (st != SBN_OK) return st;
-            dyn_lds = 0;
         }
-        GemvTable tab;
-        int blocks = 0, max_super = 1;
-        for (int i = 0; i < n; ++i) {
-            const LinearItem &li = items[first + i];
-            fill_gemv_item(tab.it[i], li);
-            if (self_quant && !li.quantized) tab.it[i].X = static_cast<const uint4 *>(li.X);
-            const int nb = (int)ceil_div(li.d_out, 16);
-            blocks = nb > blocks ? nb : blocks;
-            const int nsuper = (int)ceil_div(li.d_in / CHUNK, 4);
-            max_super = nsuper > max_super ? nsuper : max_super;
-        }
-        // one wavefront per super-step up to 16, so that every wavefront has loads in flight at once
-        const int nwaves = max_super < 16 ? max_super : 16;
-        if (dyn_lds > 0) {
-            static thread_local bool raised_single = false;
-            if (!raised_single) {
-                hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&gemv_smfmac_kernel<FORM>),
-                                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)GEMV_SELF_QUANT_LDS);
-                if (e != hipSuccess) { set_hip_error(e, "hipFuncSetAttribute"); return SBN_EHIP; }
-                raised_single = true;
-            }
-        }
-        hipLaunchKernelGGL(gemv_smfmac_kernel<FORM>, dim3(blocks, n), dim3(64 * nwaves), (size_t)dyn_lds, stream, tab);
-        sbn_status st = check_launch("gemv_smfmac_kernel");
+        const int tm = !self_quant ? 0 : most_tokens <= 2 ? 2 : 16;
+        sbn_status st = n <= GEMV_FEW ? (rt == 2 ? launch_gemv_rows<FORM, 2, GEMV_FEW>(n, items + first, nwaves, tm, stream) : launch_gemv_rows<FORM, 1, GEMV_FEW>(n, items + first, nwaves, tm, stream))
+                                      : (rt == 2 ? launch_gemv_rows<FORM, 2, GEMV_MAX_ITEMS>(n, items + first, nwaves, tm, stream) : launch_gemv_rows<FORM, 1, GEMV_MAX_ITEMS>(n, items + first, nwaves, tm, stream));
         if (st != SBN_OK) return st;
         first += n;
     }
