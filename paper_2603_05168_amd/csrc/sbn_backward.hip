@@ -4,8 +4,8 @@
 //   dW[o,k] = sum_t (dY[t,o] / s_x[t]) * xq[t,k]          contraction over tokens; dense, unmasked
 // Both run on the dense bf16 matrix cores (v_mfma_f32_32x32x16_bf16, fp32 accumulation): the 2:4
 // structure lies along d_in, which is not the contracted dimension of either product, so the sparse
-// instruction does not apply.  One "NT" GEMM kernel serves both; small layout kernels put the
-// operands contraction-major first (ternary values and int8 activations are exact in bf16).
+// instruction does not apply.  One GEMM kernel serves both: dY is read as it lies (dW contracts its slow dimension: the
+// transposing LDS read), small layout kernels put W_eff^T (exact in bf16) and (x~ / s_x)^T contraction-major first.
 #include <algorithm>
 #include <vector>
 
@@ -43,29 +43,53 @@ __device__ __forceinline__ void write_tile_rows(const uint16_t *tile, int rows, 
     }
 }
 
-// packed 2:4 weights -> W_eff^T as bf16 [d_in, ld] (ld >= d_out): block = 64 rows of W x one chunk
+// One quarter (32 weights, quarter P of its chunk) of a packed row: put(k, code) for every slot, k = weight inside the quarter.
+template <int N, int M, int P, class Put>
+__device__ __forceinline__ void decode_quarter(const uint32_t *chunk, Put &&put)
+{
+    constexpr int B = N == M ? 0 : M == 2 ? 1 : M == 4 ? 2 : 3;
+    constexpr int SLOTS = 32 * N / M, FIRST = SLOTS * P;                 // slots of the quarter, its first one
+    constexpr int IDX_WORDS = 128 * N / M * B / 32;                      // words of the chunk's index field (a whole number here)
+    constexpr int I0 = FIRST * B / 32, I1 = B ? ((FIRST + SLOTS) * B - 1) / 32 : I0, C0 = FIRST / 16, C1 = (FIRST + SLOTS - 1) / 16;
+    uint32_t iw[I1 - I0 + 2], cw[C1 - C0 + 1];
+#pragma unroll
+    for (int i = 0; i <= I1 - I0; ++i) iw[i] = B ? chunk[I0 + i] : 0u;
+    iw[I1 - I0 + 1] = 0;
+#pragma unroll
+    for (int i = 0; i <= C1 - C0; ++i) cw[i] = chunk[IDX_WORDS + C0 + i];
+#pragma unroll
+    for (int i = 0; i < SLOTS; ++i) {
+        const int slot = FIRST + i, v = slot & 15, bit = slot * B - 32 * I0;
+        const uint32_t code = (cw[slot / 16 - C0] >> (8 * (v & 3) + 2 * (v >> 2))) & 3u;
+        uint32_t j = (uint32_t)(i % N);
+        if (B) j = ((bit & 31) + B <= 32 ? iw[bit >> 5] >> (bit & 31) : __funnelshift_r(iw[bit >> 5], iw[(bit >> 5) + 1], bit & 31)) & ((1u << B) - 1u);
+        put(i / N * M + (int)j, code);
+    }
+}
+
+// packed weights -> W_eff^T as bf16 [d_in, ld] (ld >= d_out; zeros for rows of W past d_out): block = 64 rows of W x one
+// chunk, a wavefront per quarter of the chunk.  Bound by the bytes it writes.
+template <int N, int M>
 __global__ void __launch_bounds__(256) unpack_transpose_kernel(const uint8_t *__restrict__ packed, int d_out, int d_in,
                                                               uint16_t *__restrict__ wt, int64_t ld)
 {
     __shared__ __attribute__((aligned(16))) uint16_t tile[128 * TP];
-    const int nchunks = d_in / CHUNK;
+    constexpr int B = N == M ? 0 : M == 2 ? 1 : M == 4 ? 2 : 3, CHUNK_WORDS = 128 * N / M * (2 + B) / 32;
+    const int nchunks = (d_in + CHUNK - 1) / CHUNK;
     const int chunk = blockIdx.x, o0 = blockIdx.y * 64;
-    const int ro = threadIdx.x & 63, word = threadIdx.x >> 6;
+    const int ro = threadIdx.x & 63, quarter = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int o = o0 + ro;
-    for (int k = 0; k < 32; ++k) tile[(32 * word + k) * TP + ro] = 0;
+    uint16_t *const col = tile + 32 * quarter * TP + ro;
+    for (int k = 0; k < 32; ++k) col[k * TP] = 0;
     if (o < d_out) {
-        const uint32_t *cw = reinterpret_cast<const uint32_t *>(packed + ((int64_t)o * nchunks + chunk) * 32);
-        const uint32_t idx = cw[word], codes = cw[4 + word];
-#pragma unroll
-        for (int t = 0; t < 8; ++t) {
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int v = 2 * t + h;
-                const uint32_t code = (codes >> (8 * (v & 3) + 2 * (v >> 2))) & 3u;
-                const uint32_t pos = (idx >> (4 * t + 2 * h)) & 3u;
-                if (code) tile[(32 * word + 4 * t + pos) * TP + ro] = code == 1u ? 0x3f80u : 0xbf80u;
-            }
-        }
+        const uint32_t *src = reinterpret_cast<const uint32_t *>(packed) + ((int64_t)o * nchunks + chunk) * CHUNK_WORDS;
+        auto put = [&](int k, uint32_t code) {
+            if (code) col[k * TP] = code == 1u ? 0x3f80u : 0xbf80u;
+        };
+        if (quarter == 0) decode_quarter<N, M, 0>(src, put);
+        else if (quarter == 1) decode_quarter<N, M, 1>(src, put);
+        else if (quarter == 2) decode_quarter<N, M, 2>(src, put);
+        else decode_quarter<N, M, 3>(src, put);
     }
     __syncthreads();
     write_tile_rows(tile, 128, wt, ld, (int64_t)chunk * CHUNK, o0, d_in, ld);
@@ -100,9 +124,10 @@ __device__ __forceinline__ void write_tile_transposed(const uint16_t *tile, uint
     }
 }
 
-// int8 [rows, cols] -> bf16 transposed: dst [cols, ld] with dst[c, r] = src[r, c], zeros for r in [rows, ld)
-__global__ void __launch_bounds__(256) transpose_i8_kernel(const int8_t *__restrict__ src, int64_t rows, int64_t cols,
-                                                          uint16_t *__restrict__ dst, int64_t ld)
+// int8 [rows, cols] -> bf16 transposed: dst [cols, ld] with dst[c, r] = src[r, c] (/ scale[r], unless null), zeros for r in
+// [rows, ld)
+__global__ void __launch_bounds__(256) transpose_i8_kernel(const int8_t *__restrict__ src, const float *__restrict__ scale, int64_t rows,
+                                                          int64_t cols, uint16_t *__restrict__ dst, int64_t ld)
 {
     __shared__ __attribute__((aligned(16))) uint16_t tile[64 * TQ];
     const int64_t r0 = (int64_t)blockIdx.y * 64, c0 = (int64_t)blockIdx.x * 64;
@@ -114,54 +139,29 @@ __global__ void __launch_bounds__(256) transpose_i8_kernel(const int8_t *__restr
     } else {
         for (int e = 0; e < 16; ++e) q[e] = (row_ok && c0 + cv + e < cols) ? src[(r0 + r) * cols + c0 + cv + e] : (int8_t)0;
     }
+    if (scale) {
+        // the fake-quantized activation x~ / s_x, rounded to bf16 once (the one rounding of an operand of dW)
+        const float s = row_ok ? scale[r0 + r] : 1.0f;
 #pragma unroll
-    for (int e = 0; e < 16; e += 2) {
-        const uint32_t lo = __float_as_uint((float)q[e]) >> 16, hi = __float_as_uint((float)q[e + 1]) & 0xffff0000u;
-        *reinterpret_cast<uint32_t *>(&tile[r * TQ + cv + e]) = lo | hi;   // |q| <= 128: exact in bf16
+        for (int e = 0; e < 16; e += 2)
+            *reinterpret_cast<uint32_t *>(&tile[r * TQ + cv + e]) =
+                f32_to_bf16(__fdiv_rn((float)q[e], s)) | (f32_to_bf16(__fdiv_rn((float)q[e + 1], s)) << 16);
+    } else {
+#pragma unroll
+        for (int e = 0; e < 16; e += 2) {
+            const uint32_t lo = __float_as_uint((float)q[e]) >> 16, hi = __float_as_uint((float)q[e + 1]) & 0xffff0000u;
+            *reinterpret_cast<uint32_t *>(&tile[r * TQ + cv + e]) = lo | hi;   // |q| <= 128: exact in bf16
+        }
     }
     __syncthreads();
     write_tile_transposed(tile, dst, ld, c0, r0, cols, ld);
 }
 
-// dY [tokens, d_out] bf16 -> (dY[t,:] / s_x[t])^T as bf16 [d_out, ld], zeros for t in [tokens, ld)
-__global__ void __launch_bounds__(256) transpose_scale_dy_kernel(const uint16_t *__restrict__ dY, const float *__restrict__ sx,
-                                                                int64_t tokens, int64_t d_out, uint16_t *__restrict__ dst,
-                                                                int64_t ld)
-{
-    __shared__ __attribute__((aligned(16))) uint16_t tile[64 * TQ];
-    const int64_t t0 = (int64_t)blockIdx.y * 64, o0 = (int64_t)blockIdx.x * 64;
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int v = threadIdx.x + 256 * h;
-        const int t = v >> 3, ov = (v & 7) * 8;
-        __attribute__((aligned(16))) uint16_t q[8];
-        const bool row_ok = t0 + t < tokens;
-        if (row_ok && o0 + ov + 8 <= d_out && (d_out & 7) == 0) {
-            *reinterpret_cast<uint4 *>(q) = *reinterpret_cast<const uint4 *>(dY + (t0 + t) * d_out + o0 + ov);
-        } else {
-            for (int e = 0; e < 8; ++e) q[e] = (row_ok && o0 + ov + e < d_out) ? dY[(t0 + t) * d_out + o0 + ov + e] : (uint16_t)0;
-        }
-        const float s = row_ok ? sx[t0 + t] : 1.0f;
-#pragma unroll
-        for (int e = 0; e < 8; e += 2) {
-            const uint32_t lo = f32_to_bf16(__fdiv_rn(__uint_as_float((uint32_t)q[e] << 16), s));
-            const uint32_t hi = f32_to_bf16(__fdiv_rn(__uint_as_float((uint32_t)q[e + 1] << 16), s));
-            *reinterpret_cast<uint32_t *>(&tile[t * TQ + ov + e]) = lo | (hi << 16);
-        }
-    }
-    __syncthreads();
-    write_tile_transposed(tile, dst, ld, o0, t0, d_out, ld);
-}
-
-// ---- bf16 "NT" GEMM ---------------------------------------------------------------------------------
-// C[m, n] (+)= alpha * sum_k Q[m, k] * P[n, k];  P is [N, ldp], Q is [M, ldq], both bf16 with k
-// contiguous; C is bf16 [M, ldc].  P supplies the rows of the MFMA result so that a lane ends up
-// with four consecutive n of one C row (one 8-byte store).
-// Block: 256 threads = 2 x 2 wavefronts, block tile 256 (n) x 128 (m), wave tile 128 (n) x 64 (m),
-// 64 k per iteration through a single LDS buffer with register prefetch of the next tile.
-constexpr int GB_N = 256, GB_M = 128, GB_K = 64;
-constexpr int GROW = GB_K * 2 + 16;   // LDS row pitch in bytes (128 data + 16 pad)
-
+// ---- bf16 GEMM -------------------------------------------------------------------------------------------
+// C[m, n] (+)= alpha * sum_k Q[m, k] * P[n, k], C bf16 [M, ldc].  P is [N, ldp] with k contiguous and K a multiple of 64
+// (the layout kernels pad it with zeros).  Q has k contiguous as well ([M, ldq], dX), or lies the other way round
+// ([k, ldq] with m contiguous, QT: dW reads dY as it is); it may end before K, where zeros of P meet what is read instead.
+// P supplies the rows of the MFMA result so that a lane ends up with four consecutive n of one C row (one 8-byte store).
 struct GemmBf16Args {
     const uint16_t *P;
     const uint16_t *Q;
@@ -169,6 +169,8 @@ struct GemmBf16Args {
     const float *alpha;   // device scalar or null (= 1)
     int64_t ldp, ldq, ldc;
     int N, M, K;
+    int kq;               // k that Q has (<= K)
+    int transposed;       // Q is [k, ldq]
     int accumulate;
     int tiles_n, tiles_m;
     const uint32_t *mask;   // null, or one bit per element of C (rows of mask_wpr words): zero bits block the new term
@@ -202,63 +204,63 @@ __device__ __forceinline__ bool bf16_tile_of_block(const GemmBf16Args &g, int bi
     return true;
 }
 
-// Result of a wavefront: 4 x 2 tiles of 32 x 32 at rows (of C) mw + 32 b + .., columns nw + 32 a + ..;
-// tile (a, b): lane holds m = column r, n = rows 8q + 4c + i: four consecutive n of one C row per store.
-template <int TBM>
-__device__ __forceinline__ void bf16_wave_epilogue(const GemmBf16Args &g, const v16f (&acc)[4][TBM], int nw, int mw, int lane)
+// Result of a wavefront: WP x WQ tiles of 32 x 32 at rows (of C) mw + 32 b + .., columns nw + 32 a + ..; tile (a, b): lane
+// holds m = column r, n = rows 8q + 4c + i.  Stored from there, an instruction would touch 32 rows with 16 bytes each
+// (16 us of a tile of 256 x 256, next to 60 us of matrix work at 2560 k).  So 32 rows at a time go through the wavefront's
+// 16 KB of the idle stages in fp32 (granules of 16 bytes XOR-swizzled with the row) and leave as whole rows of the
+// wavefront's tile, 16 bytes per lane.  N is a multiple of 8.
+template <int WP, int WQ>
+__device__ __forceinline__ void bf16_wave_epilogue(const GemmBf16Args &g, const v16f (&acc)[WP][WQ], uint8_t *stg, int nw, int mw, int lane)
 {
+    constexpr int ROW = WP * 128, LPR = ROW / 32;     // bytes of a staged row, lanes per row
     const int r = lane & 31, c = lane >> 5;
     const float alpha = g.alpha ? *g.alpha : 1.0f;
 #pragma unroll
-    for (int b = 0; b < TBM; ++b) {
-        const int m = mw + 32 * b + r;
-        if (m >= g.M) continue;
+    for (int b = 0; b < WQ; ++b) {
 #pragma unroll
-        for (int a = 0; a < 4; ++a) {
+        for (int a = 0; a < WP; ++a)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int n = nw + 32 * a + 8 * q + 4 * c;
-                uint16_t *dst = g.C + (int64_t)m * g.ldc + n;
-                float v[4];
+            for (int q = 0; q < 4; ++q)
+                *reinterpret_cast<v4f *>(stg + r * ROW + 16 * ((8 * a + 2 * q + c) ^ (r & 15))) =
+                    v4f{acc[a][b][4 * q], acc[a][b][4 * q + 1], acc[a][b][4 * q + 2], acc[a][b][4 * q + 3]};
+        // a wavefront's LDS operations complete in order: what it wrote itself is there
 #pragma unroll
-                for (int i = 0; i < 4; ++i) v[i] = acc[a][b][4 * q + i] * alpha;
-                if (g.mask && n < g.N) {   // n is a multiple of 4: its four mask bits sit in one word
-                    const uint32_t mb = g.mask[(int64_t)m * g.mask_wpr + (n >> 5)] >> (n & 31);
+        for (int j = 0; j < 32 * LPR / 64; ++j) {
+            const int row = (64 / LPR) * j + lane / LPR, h = lane % LPR;
+            const v4f lo = *reinterpret_cast<const v4f *>(stg + row * ROW + 16 * ((2 * h) ^ (row & 15)));
+            const v4f hi = *reinterpret_cast<const v4f *>(stg + row * ROW + 16 * ((2 * h + 1) ^ (row & 15)));
+            const int m = mw + 32 * b + row, n = nw + 8 * h;
+            if (m >= g.M || n >= g.N) continue;
+            float v[8];
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) v[i] = (mb >> i) & 1u ? v[i] : 0.0f;
-                }
-                if (n + 4 <= g.N && (g.ldc & 3) == 0) {
-                    if (g.accumulate) {
-                        const uint2 old = *reinterpret_cast<const uint2 *>(dst);
-                        v[0] += __uint_as_float(old.x << 16);
-                        v[1] += __uint_as_float(old.x & 0xffff0000u);
-                        v[2] += __uint_as_float(old.y << 16);
-                        v[3] += __uint_as_float(old.y & 0xffff0000u);
-                    }
-                    uint2 out;
-                    out.x = f32_to_bf16(v[0]) | (f32_to_bf16(v[1]) << 16);
-                    out.y = f32_to_bf16(v[2]) | (f32_to_bf16(v[3]) << 16);
-                    *reinterpret_cast<uint2 *>(dst) = out;
-                } else {
-                    for (int i = 0; i < 4; ++i) {
-                        if (n + i < g.N) {
-                            float x = v[i];
-                            if (g.accumulate) x += __uint_as_float((uint32_t)dst[i] << 16);
-                            dst[i] = (uint16_t)f32_to_bf16(x);
-                        }
-                    }
+            for (int i = 0; i < 4; ++i) { v[i] = lo[i] * alpha; v[4 + i] = hi[i] * alpha; }
+            if (g.mask) {   // n is a multiple of 8: its mask bits sit in one byte
+                const uint32_t mb = g.mask[(int64_t)m * g.mask_wpr + (n >> 5)] >> (n & 31);
+#pragma unroll
+                for (int i = 0; i < 8; ++i) v[i] = (mb >> i) & 1u ? v[i] : 0.0f;
+            }
+            uint4 *dst = reinterpret_cast<uint4 *>(g.C + (int64_t)m * g.ldc + n);
+            if (g.accumulate) {
+                const uint4 old = *dst;
+                const uint32_t w[4] = {old.x, old.y, old.z, old.w};
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    v[2 * i] += __uint_as_float(w[i] << 16);
+                    v[2 * i + 1] += __uint_as_float(w[i] & 0xffff0000u);
                 }
             }
+            uint32_t o[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) o[i] = f32_to_bf16(v[2 * i]) | (f32_to_bf16(v[2 * i + 1]) << 16);
+            *dst = make_uint4(o[0], o[1], o[2], o[3]);
         }
     }
 }
 
-// Up to two products share one launch (dW and dX of a layer): the block index space is the
-// concatenation of their tiles, the product with the longer contraction first, so that the short
-// tiles of the second fill the multiprocessors the first leaves idle in its last round (dW of a
-// 2560 x 2560 layer is 200 tiles for 512 block slots).  Each range starts at a multiple of 8 (the
-// blocks in between exit at once), which keeps block index mod 8 = XCD for the tile order below.
-// one launch covers the tiles of up to GB_GROUP_MAX products: product p owns the blocks [block0[p], block0[p + 1])
+// One launch covers the tiles of up to GB_GROUP_MAX products (dW and dX of the layers of a call): product p owns the blocks
+// [block0[p], block0[p + 1]), longest contraction first, so that the short tiles fill the multiprocessors the long ones
+// leave idle.  Each range starts at a multiple of 8 (the blocks in between exit at once), which keeps block index
+// mod 8 = XCD for the tile order above.
 constexpr int GB_GROUP_MAX = 8;
 struct GemmBf16Group {
     GemmBf16Args g[GB_GROUP_MAX];
@@ -273,310 +275,263 @@ __device__ __forceinline__ int bf16_product_of_block(const GemmBf16Group &grp)
     return prob;
 }
 
-__global__ void __launch_bounds__(256, 2) gemm_bf16_nt_kernel(GemmBf16Group grp)
+// Block tile 256 x 256 with eight wavefronts of 128 (n) x 64 (m), or 128 x 128 with four of 64 x 64 (two blocks per
+// multiprocessor), two LDS stages of 64 k filled by LDS-DMA.  A stage is consumed in quarters of 16 k; the fragments of the
+// next quarter are read under the matrix instructions of the current one, also across the barrier between two stages,
+// and the requests for the stage after next stand there as well, so a wavefront always has matrix instructions to issue:
+// 1.45 us per stage of the large tile (1.48 PFLOP/s) where one barrier, eight requests and a first read in front of every
+// stage's matrix instructions took 1.9 us.  What bounds it now: the matrix pipe at the clock the board holds (1.9 PFLOP/s on
+// operands from registers), and 10 us per tile for its first stages and its result, which nothing covers.
+// us per call, before and now: 2560 x 2560 at 16384 tokens, three layers 1283 -> 1090, one 495 -> 390; 6912 x 2560, two layers
+// 2251 -> 1900; 6912 x 2560 at 1024 tokens 168 -> 99 (a fifth of each gain: dY is no longer scaled and transposed in memory).
+constexpr int GD_K = 64;     // k per stage
+template <bool BIG> struct Bf16Tile {
+    static constexpr int N = BIG ? 256 : 128, M = BIG ? 256 : 128;
+    static constexpr int WAVES = BIG ? 8 : 4, WN = 2, WM = WAVES / WN;       // wavefronts along n and m
+    static constexpr int WP = N / WN / 32, WQ = M / WM / 32;                 // 32 x 32 tiles of a wavefront: 4 x 2 or 2 x 2
+    static constexpr int PBYTES = N * GD_K * 2, STAGE = (N + M) * GD_K * 2;
+    static constexpr int LDS = 2 * STAGE;
+};
+
+template <bool BIG, bool QT>
+__device__ __forceinline__ void bf16_tile_body(const GemmBf16Args &g, uint8_t *dlds, int n0, int m0)
 {
-    __shared__ __attribute__((aligned(16))) uint8_t ldsP[GB_N * GROW];
-    __shared__ __attribute__((aligned(16))) uint8_t ldsQ[GB_M * GROW];
-    const int prob = bf16_product_of_block(grp);
-    const GemmBf16Args &g = grp.g[prob];
-    int tn, tm;
-    if (!bf16_tile_of_block(g, (int)blockIdx.x - grp.block0[prob], tn, tm)) return;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    using S = Bf16Tile<BIG>;
+    constexpr int WP = S::WP, WQ = S::WQ;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wn = wave & 1, wm = wave >> 1;
     const int r = lane & 31, c = lane >> 5;
-    const int n0 = tn * GB_N, m0 = tm * GB_M;
+    const uint32_t lds0 = lds_address(dlds);
+    const int nk = g.K / GD_K;
 
-    // copy roles: 8 threads per row (16 bytes each), 32 rows per pass.  Addresses are a uniform tile base
-    // (scalar registers, advanced by 128 bytes per k step) plus a 32-bit byte offset per thread and pass,
-    // rows past the end clamped to the last one: the loads of the loop need no vector arithmetic.
-    const int cp_row = tid >> 3, cp_col = (tid & 7) * 8;   // column in elements
+    // DMA roles, four instructions per operand and wavefront.  k contiguous: one instruction fills 8 rows x 128 bytes (lane l:
+    // row l / 8, slot l % 8 holding global column slot ^ ((row >> 1) & 7)).  Transposed Q: a stage is 64 k rows of M values,
+    // one instruction fills 1024 bytes of them, slot s of row k holds the eight values of granule s ^ f(k),
+    // f = 4 (k & 3) | 2 ((k >> 2) & 1): the four k rows that a transposing read of 16 lanes takes lie in different banks.
+    // Past the matrix the last row or granule again (never stored, or met by zeros of P).
+    constexpr int QROW = S::M * 2;                        // bytes of a k row of the transposed stage
     const char *pbase = reinterpret_cast<const char *>(g.P + (int64_t)n0 * g.ldp);
-    const char *qbase = reinterpret_cast<const char *>(g.Q + (int64_t)m0 * g.ldq);
-    uint32_t poff[8], qoff[4];
+    const char *qbase = reinterpret_cast<const char *>(QT ? g.Q + m0 : g.Q + (int64_t)m0 * g.ldq);
+    const int64_t qstep = QT ? g.ldq * (GD_K * 2) : GD_K * 2;
+    const int kleft = g.kq - (nk - 1) * GD_K;             // k of the last stage that Q has
+    uint32_t poff[4], qoff[4], qlast[4];
 #pragma unroll
-    for (int p = 0; p < 8; ++p) {
-        int n = n0 + cp_row + 32 * p;
-        n = (n < g.N ? n : g.N - 1) - n0;
-        poff[p] = (uint32_t)(((int64_t)n * g.ldp + cp_col) * 2);
+    for (int i = 0; i < 4; ++i) {
+        const int row = 32 * wave + 8 * i + (lane >> 3);
+        const int col = (lane & 7) ^ ((row >> 1) & 7);
+        const int n = (n0 + row < g.N ? n0 + row : g.N - 1) - n0;
+        poff[i] = (uint32_t)(((int64_t)n * g.ldp + col * 8) * 2);
+        if constexpr (QT) {
+            constexpr int GPR = S::M / 8, RPI = 64 / GPR;      // granules of a k row, k rows per instruction
+            const int k = RPI * (4 * wave + i) + lane / GPR;
+            int gran = (lane % GPR) ^ (4 * (k & 3) | 2 * ((k >> 2) & 1));
+            gran = m0 + 8 * gran + 8 <= g.M ? gran : (g.M - m0) / 8 - 1;
+            qoff[i] = (uint32_t)(((int64_t)k * g.ldq + 8 * gran) * 2);
+            qlast[i] = (uint32_t)(((int64_t)(k < kleft ? k : kleft - 1) * g.ldq + 8 * gran) * 2);
+        } else {
+            const int m = (m0 + row < g.M ? m0 + row : g.M - 1) - m0;
+            qoff[i] = (uint32_t)(((int64_t)m * g.ldq + col * 8) * 2);
+            qlast[i] = (uint32_t)(((int64_t)m * g.ldq + (8 * col < kleft ? col : (kleft - 1) / 8) * 8) * 2);
+        }
     }
+    // the eight instructions of a wavefront and stage one by one, so that they can stand between matrix instructions; past the
+    // end the last stage is fetched again into a buffer nobody reads any more
+    auto dma_one = [&](int kt, const uint32_t stage, const int i) {
+        kt = kt < nk ? kt : nk - 1;
+        const uint32_t dst = lds0 + stage + wave * 4096;
+        if (i < 4) lds_dma16(pbase + (int64_t)kt * (GD_K * 2), poff[i], dst + i * 1024);
+        else lds_dma16(qbase + (int64_t)kt * qstep, kt == nk - 1 ? qlast[i - 4] : qoff[i - 4], dst + S::PBYTES + (i - 4) * 1024);
+    };
+    // LDS read addresses: k contiguous: row * 128 + 16 * ((2u + c) ^ ((row >> 1) & 7)); (row >> 1) & 7 = (r >> 1) & 7 for every
+    // tile of the wavefront, so one lane address per u, tiles are immediate offsets; the stage is one bit of the address.  Transposed: lane l of a
+    // group of 16 supplies the address of row k0 + (l >> 2), columns 4 (l & 3) .. + 3 and gets four k of column l; two
+    // reads (h = 0, 1) make the eight k of a fragment.
+    uint32_t pa[4], qa[4];
 #pragma unroll
-    for (int p = 0; p < 4; ++p) {
-        int m = m0 + cp_row + 32 * p;
-        m = (m < g.M ? m : g.M - 1) - m0;
-        qoff[p] = (uint32_t)(((int64_t)m * g.ldq + cp_col) * 2);
+    for (int u = 0; u < 4; ++u) {
+        const int slot = (2 * u + c) ^ ((r >> 1) & 7);
+        pa[u] = lds0 + (wn * 32 * WP + r) * 128 + 16 * slot;
+        if constexpr (!QT) qa[u] = lds0 + S::PBYTES + (wm * 32 * WQ + r) * 128 + 16 * slot;
     }
+    uint32_t qt[WQ][2];
+    if constexpr (QT) {
+        const int rr = (lane & 15) >> 2;
+#pragma unroll
+        for (int b = 0; b < WQ; ++b)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int gran = (wm * 32 * WQ + 32 * b) / 8 + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);
+                qt[b][h] = lds0 + S::PBYTES + (8 * c + 4 * h + rr) * QROW + 16 * (gran ^ (4 * rr | 2 * h)) + 8 * (lane & 1);
+            }
+    }
+    typedef __attribute__((address_space(3))) const v8bf *lds_v8bf;
+    typedef __bf16 v4bf __attribute__((ext_vector_type(4)));
+    typedef __attribute__((address_space(3))) v4bf *lds_v4bf;
 
-    v16f acc[4][2];
+    v16f acc[WP][WQ];
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
+    for (int a = 0; a < WP; ++a)
 #pragma unroll
-        for (int b = 0; b < 2; ++b)
+        for (int b = 0; b < WQ; ++b)
 #pragma unroll
             for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.0f;
 
-    // k steps that lie entirely inside K load unconditionally (straight-line loop body); a ragged last
-    // step (K % 8 == 0: a 16-byte vector is entirely inside or outside) masks its loads
-    const int nk_full = g.K / GB_K;
-    const int nk = (g.K + GB_K - 1) / GB_K;
-    uint4 preg[8], qreg[4];
-    auto load_full = [&](int kt) {
-        const char *pb = pbase + (int64_t)kt * (GB_K * 2), *qb = qbase + (int64_t)kt * (GB_K * 2);
-#pragma unroll
-        for (int p = 0; p < 8; ++p) preg[p] = *reinterpret_cast<const uint4 *>(pb + poff[p]);
-#pragma unroll
-        for (int p = 0; p < 4; ++p) qreg[p] = *reinterpret_cast<const uint4 *>(qb + qoff[p]);
-    };
-    auto load_ragged = [&](int kt) {
-        const char *pb = pbase + (int64_t)kt * (GB_K * 2), *qb = qbase + (int64_t)kt * (GB_K * 2);
-        const bool ok = kt * GB_K + cp_col + 8 <= g.K;
-#pragma unroll
-        for (int p = 0; p < 8; ++p) preg[p] = ok ? *reinterpret_cast<const uint4 *>(pb + poff[p]) : make_uint4(0, 0, 0, 0);
-#pragma unroll
-        for (int p = 0; p < 4; ++p) qreg[p] = ok ? *reinterpret_cast<const uint4 *>(qb + qoff[p]) : make_uint4(0, 0, 0, 0);
-    };
-    auto store_tile_lds = [&]() {
-#pragma unroll
-        for (int p = 0; p < 8; ++p) *reinterpret_cast<uint4 *>(&ldsP[(cp_row + 32 * p) * GROW + cp_col * 2]) = preg[p];
-#pragma unroll
-        for (int p = 0; p < 4; ++p) *reinterpret_cast<uint4 *>(&ldsQ[(cp_row + 32 * p) * GROW + cp_col * 2]) = qreg[p];
-    };
-    auto multiply_tile = [&]() {
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            // lane (r, c) supplies k = 16u + 8c + 0..7 of the tile for both operands
-            v8bf pf[4], qf[2];
-#pragma unroll
-            for (int a = 0; a < 4; ++a)
-                pf[a] = *reinterpret_cast<const v8bf *>(&ldsP[(wn * 128 + 32 * a + r) * GROW + 32 * u + 16 * c]);
-#pragma unroll
-            for (int b = 0; b < 2; ++b)
-                qf[b] = *reinterpret_cast<const v8bf *>(&ldsQ[(wm * 64 + 32 * b + r) * GROW + 32 * u + 16 * c]);
-#pragma unroll
-            for (int a = 0; a < 4; ++a)
-#pragma unroll
-                for (int b = 0; b < 2; ++b)
-                    acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pf[a], qf[b], acc[a][b], 0, 0, 0);
+    v8bf fp[2][WP], fq[2][WQ];
+    constexpr int READS = WP + (QT ? 2 : 1) * WQ;         // LDS reads of a quarter step
+    auto read_one = [&](const int u, const int i) {
+        const int set = u & 1;
+        if (i < WP) {
+            fp[set][i] = *(lds_v8bf)(uintptr_t)(pa[u] + i * 32 * 128);
+        } else if constexpr (QT) {
+            const int b = (i - WP) >> 1, h = (i - WP) & 1;
+            const v4bf v = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_v4bf)(uintptr_t)(qt[b][h] + 16 * u * QROW));
+            if (h == 0) fq[set][b].lo = v; else fq[set][b].hi = v;
+        } else {
+            fq[set][i - WP] = *(lds_v8bf)(uintptr_t)(qa[u] + (i - WP) * 32 * 128);
         }
     };
-
-    if (nk_full > 0) load_full(0); else load_ragged(0);
-    store_tile_lds();
+    static_assert((S::STAGE & (S::STAGE - 1)) == 0, "the other stage is the address with one bit flipped (dynamic LDS starts at 0)");
+    auto flip = [&]() {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            pa[u] ^= S::STAGE;
+            if constexpr (!QT) qa[u] ^= S::STAGE;
+        }
+        if constexpr (QT) {
+#pragma unroll
+            for (int b = 0; b < WQ; ++b) { qt[b][0] ^= S::STAGE; qt[b][1] ^= S::STAGE; }
+        }
+    };
+    // A quarter step: WP x WQ matrix instructions; side(s) is issued after instruction s.  The source order is the intended
+    // issue order, a scheduling barrier after every matrix instruction keeps it.
+    constexpr int SLOTS = WP * WQ;
+    auto quarter = [&](const int u, auto &&side) {
+#pragma unroll
+        for (int s = 0; s < SLOTS; ++s) {
+            const int a = s / WQ, b = s % WQ;
+            acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fp[u & 1][a], fq[u & 1][b], acc[a][b], 0, 0, 0);
+            side(s);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    // operations [0, n) spread over the slots of a quarter step
+    auto spread = [&](const int s, const int n, auto &&op) {
+#pragma unroll
+        for (int k = 0; k < n; ++k)
+            if (k * SLOTS / n == s) op(k);
+    };
+    // Step kt reads stage kt & 1.  Quarters 0 to 2 read the fragments of the next quarter under their matrix instructions; then
+    // stage kt + 1 must have landed and every wavefront holds the last fragments of stage kt, so behind the barrier the last
+    // quarter reads the first fragments of stage kt + 1 and asks for stage kt + 2 in the buffer just left.
+#pragma unroll
+    for (int i = 0; i < 8; ++i) dma_one(0, 0, i);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) dma_one(1, S::STAGE, i);
+    SBN_WAIT_VMCNT(8);
     __syncthreads();
-    int kt = 0;
-    for (; kt + 1 < nk_full; ++kt) {   // the next step is a full one
-        load_full(kt + 1);
-        multiply_tile();
+#pragma unroll
+    for (int i = 0; i < READS; ++i) read_one(0, i);
+    uint32_t stage = 0;
+    for (int kt = 0; kt < nk; ++kt) {
+#pragma unroll
+        for (int u = 0; u < 3; ++u)
+            quarter(u, [&](const int s) { spread(s, READS, [&](const int k) { read_one(u + 1, k); }); });
+        SBN_WAIT_VMCNT(0);
         __syncthreads();
-        store_tile_lds();
-        __syncthreads();
+        flip();
+        quarter(3, [&](const int s) {
+            spread(s, READS, [&](const int k) { read_one(0, k); });
+            spread(s, 8, [&](const int k) { dma_one(kt + 2, stage, k); });
+        });
+        stage ^= S::STAGE;
     }
-    if (kt + 1 < nk) {                 // one ragged step follows
-        load_ragged(kt + 1);
-        multiply_tile();
-        __syncthreads();
-        store_tile_lds();
-        __syncthreads();
-    }
-    multiply_tile();                   // last step: nothing left to fetch
-
-    bf16_wave_epilogue<2>(g, acc, n0 + wn * 128, m0 + wm * 64, lane);
+    SBN_WAIT_VMCNT(0);   // the surplus stages have landed
+    __syncthreads();
+    bf16_wave_epilogue<WP, WQ>(g, acc, dlds + wave * (S::LDS / S::WAVES), n0 + wn * 32 * WP, m0 + wm * 32 * WQ, lane);
 }
 
-// ---- the same product with the operands streamed into LDS by the DMA path --------------------------
-// Timing-only ablations of the kernel above (2 x 2 wavefronts, register prefetch, one LDS buffer): LDS
-// reads + matrix instructions alone run at 86 % of what the board sustains; the global-load ->
-// register -> LDS-store path costs the rest (the scheduler sinks the loads to the end of a k step to
-// save registers, and forcing them early costs the LDS read-ahead instead).  Here no operand touches a
-// register on its way in: block tile 256 (n) x 256 (m), 512 threads = 2 x 4 wavefronts of 128 x 64 (one
-// block per multiprocessor, two wavefronts per SIMD), two LDS stages of 64 k (128-byte rows, 64 KB per
-// stage), each wavefront issues eight LDS-DMA loads for the next stage before it multiplies the
-// current one; one barrier per k step.  The 16-byte column of a row is XOR-swizzled with (row >> 1) & 7 (on
-// the global side of the DMA, which deposits lane l at base + 16 l), so the 32 rows x 2 columns of an
-// operand read spread over all banks.  Needs K % 64 == 0 (no partial rows in a stage).
-// The matrix pipe still waits for the operands about a third of the time.  Measured on the backward of one 6912 x 2560
-// layer at 16384 tokens (1.05 ms in this kernel): without the DMA requests (LDS reads, matrix instructions and
-// barriers only) 0.75 ms, 80 % of what the board sustains; with every block fetching the same 512 operand rows (all
-// requests hit L2) 0.95 ms; the L2 miss rate of the real launch is 19.5 %, what 32 multiprocessors sharing a 4 x 8
-// rectangle of tiles must miss ((4 + 8) / 64).  So it is the deposit path into LDS, not L2 or HBM, that costs most: at
-// 64 bytes per clock the 64 KB of a stage take half of the stage's matrix time, and the fragment reads (192 KB at 256
-// bytes per clock) take most of the other half.  Tried and measured slower: a ring of four stages of 32 k with eight
-// wavefronts (5.96 against 5.43 ms for the backward of the block); one wavefront per SIMD with 128 x 128 wave tiles,
-// four stages of 32 k and counted waits (a third fewer LDS reads, no conflicts: 1.13 ms against 1.05); warming L2 two
-// steps ahead with one extra line-touching DMA load per wavefront and step (5.99 ms: it doubles the L2 requests).
-constexpr int GD_N = 256, GD_M = 256, GD_K = 64;
-constexpr int GD_STAGE = (GD_N + GD_M) * GD_K * 2;   // 64 KB
-constexpr int GD_LDS = 2 * GD_STAGE;
-
-__global__ void __launch_bounds__(512) gemm_bf16_dma_kernel(GemmBf16Group grp)
+template <bool BIG>
+__global__ void __launch_bounds__(64 * Bf16Tile<BIG>::WAVES) gemm_bf16_kernel(GemmBf16Group grp)
 {
     extern __shared__ __attribute__((aligned(1024))) uint8_t dlds[];
     const int prob = bf16_product_of_block(grp);
     const GemmBf16Args &g = grp.g[prob];
     int tn, tm;
     if (!bf16_tile_of_block(g, (int)blockIdx.x - grp.block0[prob], tn, tm)) return;
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wn = wave & 1, wm = wave >> 1;
-    const int r = lane & 31, c = lane >> 5;
-    const int n0 = tn * GD_N, m0 = tm * GD_M;
-    const uint32_t lds0 = lds_address(dlds);
-
-    // DMA roles: one instruction fills 8 rows x 128 bytes (lane l: row l / 8, slot l % 8 holding global
-    // column slot ^ ((row >> 1) & 7)); wavefront w fills rows 32 w .. 32 w + 31 of P and of Q: 4 + 4 instructions
-    const char *pbase = reinterpret_cast<const char *>(g.P + (int64_t)n0 * g.ldp);
-    const char *qbase = reinterpret_cast<const char *>(g.Q + (int64_t)m0 * g.ldq);
-    uint32_t poff[4], qoff[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int row = 32 * wave + 8 * i + (lane >> 3);
-        const int col = (lane & 7) ^ ((row >> 1) & 7);
-        int n = n0 + row;
-        n = (n < g.N ? n : g.N - 1) - n0;
-        poff[i] = (uint32_t)(((int64_t)n * g.ldp + col * 8) * 2);
-        int m = m0 + row;
-        m = (m < g.M ? m : g.M - 1) - m0;
-        qoff[i] = (uint32_t)(((int64_t)m * g.ldq + col * 8) * 2);
-    }
-    auto dma_stage = [&](int kt, int stage) {
-        const char *pb = pbase + (int64_t)kt * (GD_K * 2), *qb = qbase + (int64_t)kt * (GD_K * 2);
-        const uint32_t dp = lds0 + stage * GD_STAGE + wave * 4096, dq = dp + GD_N * GD_K * 2;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) lds_dma16(pb, poff[i], dp + i * 1024);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) lds_dma16(qb, qoff[i], dq + i * 1024);
-    };
-    // LDS read addresses: row * 128 + 16 * ((2u + c) ^ ((row >> 1) & 7)); (row >> 1) & 7 = (r >> 1) & 7 for every
-    // tile of the wavefront, so one lane address per u and operand, tiles and stages are immediate offsets.  (With
-    // row & 7 as the swizzle, rows r and r + 8 of a 16-lane group met in the same banks: four conflict cycles per read.)
-    uint32_t pa[4], qa[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const int slot = (2 * u + c) ^ ((r >> 1) & 7);
-        pa[u] = lds0 + (wn * 128 + r) * 128 + 16 * slot;
-        qa[u] = lds0 + GD_N * GD_K * 2 + (wm * 64 + r) * 128 + 16 * slot;
-    }
-    typedef __attribute__((address_space(3))) const v8bf *lds_v8bf;
-
-    v16f acc[4][2];
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.0f;
-
-    auto multiply_stage = [&](const int stage) {
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            v8bf pf[4], qf[2];
-#pragma unroll
-            for (int a = 0; a < 4; ++a) pf[a] = *(lds_v8bf)(uintptr_t)(pa[u] + stage * GD_STAGE + a * 32 * 128);
-#pragma unroll
-            for (int b = 0; b < 2; ++b) qf[b] = *(lds_v8bf)(uintptr_t)(qa[u] + stage * GD_STAGE + b * 32 * 128);
-#pragma unroll
-            for (int a = 0; a < 4; ++a)
-#pragma unroll
-                for (int b = 0; b < 2; ++b)
-                    acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pf[a], qf[b], acc[a][b], 0, 0, 0);
-        }
-    };
-    // step kt reads stage kt & 1 while the DMA fills the other one with step kt + 1 (past the end the last
-    // step is fetched again into a stage nobody reads any more); the barrier at the end of a step publishes
-    // the landed stage and frees the one just read.  Stage numbers are literals: two steps per loop trip.
-    const int nk = g.K / GD_K;
-    auto step = [&](const int kt, const int stage) {
-        dma_stage(kt + 1 < nk ? kt + 1 : nk - 1, stage ^ 1);
-        multiply_stage(stage);
-        SBN_WAIT_VMCNT(0);
-        __syncthreads();
-    };
-    dma_stage(0, 0);
-    SBN_WAIT_VMCNT(0);
-    __syncthreads();
-    int kt = 0;
-    for (; kt + 2 <= nk; kt += 2) {
-        step(kt, 0);
-        step(kt + 1, 1);
-    }
-    if (kt < nk) step(kt, 0);
-
-    bf16_wave_epilogue<2>(g, acc, n0 + wn * 128, m0 + wm * 64, lane);
+    const int n0 = tn * Bf16Tile<BIG>::N, m0 = tm * Bf16Tile<BIG>::M;
+    if (g.transposed) bf16_tile_body<BIG, true>(g, dlds, n0, m0);
+    else bf16_tile_body<BIG, false>(g, dlds, n0, m0);
 }
 
-GemmBf16Args make_bf16_args(const uint16_t *P, int64_t ldp, int N, const uint16_t *Q, int64_t ldq, int M, int K, uint16_t *C,
-                            int64_t ldc, const float *alpha, int accumulate)
+template <bool BIG>
+sbn_status launch_gemm_bf16_as(int count, const GemmBf16Args *args, hipStream_t stream)
 {
-    GemmBf16Args g;
-    g.P = P; g.Q = Q; g.C = C; g.alpha = alpha; g.ldp = ldp; g.ldq = ldq; g.ldc = ldc;
-    g.N = N; g.M = M; g.K = K; g.accumulate = accumulate;
-    g.tiles_n = (int)ceil_div(N, GB_N);   // for the register-prefetch kernel; the launcher recounts for the DMA kernel
-    g.tiles_m = (int)ceil_div(M, GB_M);
-    g.mask = nullptr;
-    g.mask_wpr = 0;
-    return g;
-}
-
-// one launch for one or two products; the one with the longer contraction goes first
-// Products of one launch, longest contraction first: the long tiles start at once and the short ones fill
-// the multiprocessors they leave idle.
-sbn_status launch_gemm_bf16(int count, const GemmBf16Args *args, hipStream_t stream)
-{
+    using S = Bf16Tile<BIG>;
     for (int first = 0; first < count; first += GB_GROUP_MAX) {
         GemmBf16Group grp;
         grp.count = count - first < GB_GROUP_MAX ? count - first : GB_GROUP_MAX;
         int order[GB_GROUP_MAX];
         for (int i = 0; i < grp.count; ++i) order[i] = first + i;
         std::stable_sort(order, order + grp.count, [&](int a, int b) { return args[a].K > args[b].K; });
-        // the DMA kernel takes whole 64-k stages and 16-byte aligned rows; anything else takes the register-prefetch kernel
-        bool dma = true;
-        for (int i = 0; i < grp.count; ++i) {
-            const GemmBf16Args &a = args[order[i]];
-            dma = dma && a.K % GD_K == 0 && a.ldp % 8 == 0 && a.ldq % 8 == 0 && aligned(a.P, 16) && aligned(a.Q, 16);
-        }
         int blocks = 0;
         for (int i = 0; i < grp.count; ++i) {
             grp.g[i] = args[order[i]];
-            if (dma) {
-                grp.g[i].tiles_n = (int)ceil_div(grp.g[i].N, GD_N);
-                grp.g[i].tiles_m = (int)ceil_div(grp.g[i].M, GD_M);
-            }
+            grp.g[i].tiles_n = (int)ceil_div(grp.g[i].N, S::N);
+            grp.g[i].tiles_m = (int)ceil_div(grp.g[i].M, S::M);
             grp.block0[i] = blocks;
             blocks += (grp.g[i].tiles_n * grp.g[i].tiles_m + 7) / 8 * 8;   // eight equal shares, one per XCD
         }
         for (int i = grp.count; i <= GB_GROUP_MAX; ++i) grp.block0[i] = blocks;
         for (int i = grp.count; i < GB_GROUP_MAX; ++i) grp.g[i] = grp.g[0];
-        if (dma) {
-            static thread_local bool raised = false;
-            if (!raised) {
-                hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_bf16_dma_kernel),
-                                                   hipFuncAttributeMaxDynamicSharedMemorySize, GD_LDS);
-                if (e != hipSuccess) { set_hip_error(e, "hipFuncSetAttribute"); return SBN_EHIP; }
-                raised = true;
-            }
-            hipLaunchKernelGGL(gemm_bf16_dma_kernel, dim3(blocks), dim3(512), GD_LDS, stream, grp);
-            sbn_status st = check_launch("gemm_bf16_dma_kernel");
-            if (st != SBN_OK) return st;
-        } else {
-            hipLaunchKernelGGL(gemm_bf16_nt_kernel, dim3(blocks), dim3(256), 0, stream, grp);
-            sbn_status st = check_launch("gemm_bf16_nt_kernel");
-            if (st != SBN_OK) return st;
+        static thread_local bool raised = false;
+        if (!raised) {
+            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_bf16_kernel<BIG>), hipFuncAttributeMaxDynamicSharedMemorySize, S::LDS);
+            if (e != hipSuccess) { set_hip_error(e, "hipFuncSetAttribute"); return SBN_EHIP; }
+            raised = true;
         }
+        hipLaunchKernelGGL(gemm_bf16_kernel<BIG>, dim3(blocks), dim3(64 * S::WAVES), S::LDS, stream, grp);
+        sbn_status st = check_launch("gemm_bf16_kernel");
+        if (st != SBN_OK) return st;
     }
     return SBN_OK;
 }
 
-inline int64_t pad8(int64_t x) { return (x + 7) / 8 * 8; }
+// Estimated time in us of the products of a call with the tiles of one size: every multiprocessor's share of all tiles, or the
+// longest tile.  Measured: 256 x 256 takes 1.45 us per stage of 64 k (1.2 while most multiprocessors idle) and 10 us for its
+// first stages and its result; of 128 x 128 a multiprocessor holds two, 1.05 us per stage (0.6) and 7 us.
+template <bool BIG>
+float gemm_bf16_estimate_us(int count, const GemmBf16Args *args)
+{
+    using S = Bf16Tile<BIG>;
+    const float step = BIG ? 1.45f : 1.05f, alone = BIG ? 1.2f : 0.6f, fixed = BIG ? 10.0f : 7.0f;
+    float total = 0, longest = 0;
+    for (int i = 0; i < count; ++i) {
+        const float tiles = (float)(ceil_div(args[i].N, S::N) * ceil_div(args[i].M, S::M)), stages = (float)(args[i].K / GD_K);
+        total += tiles * (stages * step + fixed);
+        longest = std::max(longest, stages * alone + fixed);
+    }
+    return std::max(longest, total / (float)((BIG ? 1 : 2) * device_cus()));
+}
+
+// Large tiles move half the operand bytes per product; small ones share the device better where there are few (us per call,
+// 6912 x 2560 at 1024 tokens 144 with large, 97 with small tiles; 1024 x 1024 at 512 tokens 35 / 18; 2560 x 2560 at 16384 tokens 390 / 450).
+sbn_status launch_gemm_bf16(int count, const GemmBf16Args *args, hipStream_t stream)
+{
+    return gemm_bf16_estimate_us<true>(count, args) <= gemm_bf16_estimate_us<false>(count, args) ? launch_gemm_bf16_as<true>(count, args, stream)
+                                                                                               : launch_gemm_bf16_as<false>(count, args, stream);
+}
+
+inline int64_t pad64(int64_t x) { return (x + 63) / 64 * 64; }
 
 }  // namespace
 
 size_t backward_workspace_bytes(int64_t tokens, int64_t d_out, int64_t d_in)
 {
-    // W_eff^T bf16 [d_in, pad8(d_out)] + int8 W_eff (generic patterns) + (dY/s_x)^T bf16 [d_out, pad8(tokens)]
-    // + xq^T bf16 [d_in, pad8(tokens)]
+    // W_eff^T bf16 [d_in, pad64(d_out)] + int8 W_eff (generic patterns) + (x~ / s_x)^T bf16 [d_in, pad64(tokens)]
     // + the mask bit plane of the gradient-masked variant
-    return align_up((size_t)d_in * pad8(d_out) * 2, 256) + align_up((size_t)d_out * d_in, 256) +
-           align_up((size_t)d_out * pad8(tokens) * 2, 256) + align_up((size_t)d_in * pad8(tokens) * 2, 256) +
-           align_up((size_t)d_out * ((d_in + 31) / 32) * 4, 256);
+    return align_up((size_t)d_in * pad64(d_out) * 2, 256) + align_up((size_t)d_out * d_in, 256) +
+           align_up((size_t)d_in * pad64(tokens) * 2, 256) + align_up((size_t)d_out * ((d_in + 31) / 32) * 4, 256);
 }
 
 // Backward products of `count` layers in one pass: the layout kernels of every layer, then ONE matrix-multiply
@@ -594,57 +549,61 @@ sbn_status launch_backward_grouped(int count, const BackwardItem *items, const P
         const int64_t tokens = it.tokens, d_in = it.d_in, d_out = it.d_out;
         uint8_t *ws = static_cast<uint8_t *>(it.workspace);
         uint16_t *wt = reinterpret_cast<uint16_t *>(ws);
-        ws += align_up((size_t)d_in * pad8(d_out) * 2, 256);
+        ws += align_up((size_t)d_in * pad64(d_out) * 2, 256);
         int8_t *w8 = reinterpret_cast<int8_t *>(ws);
         ws += align_up((size_t)d_out * d_in, 256);
-        uint16_t *dyt = reinterpret_cast<uint16_t *>(ws);
-        ws += align_up((size_t)d_out * pad8(tokens) * 2, 256);
         uint16_t *xt = reinterpret_cast<uint16_t *>(ws);
-        ws += align_up((size_t)d_in * pad8(tokens) * 2, 256);
+        ws += align_up((size_t)d_in * pad64(tokens) * 2, 256);
         uint32_t *mask_bits = reinterpret_cast<uint32_t *>(ws);
         const uint16_t *dy = static_cast<const uint16_t *>(it.dY);
 
         if (it.dX) {
-            const int64_t ldw = pad8(d_out);
-            if (pat.N == 2 && pat.M == 4 && d_in % CHUNK == 0) {
-                dim3 grid((unsigned)(d_in / CHUNK), (unsigned)ceil_div(d_out, 64));
-                hipLaunchKernelGGL(unpack_transpose_kernel, grid, dim3(256), 0, stream, static_cast<const uint8_t *>(it.packed),
-                                   (int)d_out, (int)d_in, wt, ldw);
-                st = check_launch("unpack_transpose_kernel");
-            } else {
+            const int64_t ldw = pad64(d_out);
+            const dim3 grid((unsigned)ceil_div(d_in, CHUNK), (unsigned)(ldw / 64));
+            auto unpack = [&](auto kernel) {
+                hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, static_cast<const uint8_t *>(it.packed), (int)d_out, (int)d_in, wt, ldw);
+                return check_launch("unpack_transpose_kernel");
+            };
+            if (pat.N == pat.M) st = unpack(unpack_transpose_kernel<8, 8>);   // dense codes look the same for every M
+            else if (pat.N == 2 && pat.M == 4) st = unpack(unpack_transpose_kernel<2, 4>);
+            else if (pat.N == 6 && pat.M == 8) st = unpack(unpack_transpose_kernel<6, 8>);
+            else if (pat.N == 1 && pat.M == 4) st = unpack(unpack_transpose_kernel<1, 4>);
+            else if (pat.N == 2 && pat.M == 8) st = unpack(unpack_transpose_kernel<2, 8>);
+            else {
                 st = launch_expand_groups(it.packed, d_out, d_in, pat, w8, stream);
                 if (st != SBN_OK) return st;
-                dim3 grid((unsigned)ceil_div(d_in, 64), (unsigned)ceil_div(d_out, 64));
-                hipLaunchKernelGGL(transpose_i8_kernel, grid, dim3(256), 0, stream, w8, d_out, d_in, wt, ldw);
+                hipLaunchKernelGGL(transpose_i8_kernel, dim3((unsigned)ceil_div(d_in, 64), (unsigned)(ldw / 64)), dim3(256), 0, stream, w8, nullptr,
+                                   d_out, d_in, wt, ldw);
                 st = check_launch("transpose_i8_kernel");
             }
             if (st != SBN_OK) return st;
             // dX[t, k] = gamma * sum_o dY[t, o] * W_eff^T[k, o]
-            products.push_back(make_bf16_args(wt, ldw, (int)d_in, dy, d_out, (int)tokens, (int)d_out, static_cast<uint16_t *>(it.dX),
-                                              d_in, it.gamma, 0));
+            GemmBf16Args a{};
+            a.P = wt; a.ldp = ldw; a.N = (int)d_in;
+            a.Q = dy; a.ldq = d_out; a.M = (int)tokens; a.kq = (int)d_out;
+            a.K = (int)ldw;
+            a.C = static_cast<uint16_t *>(it.dX); a.ldc = d_in; a.alpha = it.gamma;
+            products.push_back(a);
         }
         if (it.dW) {
-            const int64_t ldt = pad8(tokens);
-            {
-                dim3 grid((unsigned)ceil_div(d_out, 64), (unsigned)ceil_div(tokens, 64));
-                hipLaunchKernelGGL(transpose_scale_dy_kernel, grid, dim3(256), 0, stream, dy, it.sx, tokens, d_out, dyt, ldt);
-                st = check_launch("transpose_scale_dy_kernel");
-                if (st != SBN_OK) return st;
-            }
+            const int64_t ldt = pad64(tokens);
             const uint16_t *xts = nullptr;   // an earlier layer of the call already transposed the same activations
             for (int j = 0; j < i && !xts; ++j)
                 if (xt_of[j] && items[j].xq == it.xq && items[j].tokens == tokens && items[j].d_in == d_in) xts = xt_of[j];
             if (!xts) {
-                dim3 grid((unsigned)ceil_div(d_in, 64), (unsigned)ceil_div(tokens, 64));
-                hipLaunchKernelGGL(transpose_i8_kernel, grid, dim3(256), 0, stream, it.xq, tokens, d_in, xt, ldt);
+                dim3 grid((unsigned)ceil_div(d_in, 64), (unsigned)(ldt / 64));
+                hipLaunchKernelGGL(transpose_i8_kernel, grid, dim3(256), 0, stream, it.xq, it.sx, tokens, d_in, xt, ldt);
                 st = check_launch("transpose_i8_kernel");
                 if (st != SBN_OK) return st;
                 xts = xt;
             }
             xt_of[i] = xts;
-            // dW[o, k] = sum_t (dY/s_x)^T[o, t] * xq^T[k, t]; both operands are zero for t in [tokens, ldt)
-            GemmBf16Args a = make_bf16_args(xts, ldt, (int)d_in, dyt, ldt, (int)d_out, (int)ldt, static_cast<uint16_t *>(it.dW), d_in,
-                                            nullptr, accumulate);
+            // dW[o, k] = sum_t dY[t, o] * (x~ / s_x)[t, k]; x~^T is zero for t in [tokens, ldt)
+            GemmBf16Args a{};
+            a.P = xts; a.ldp = ldt; a.N = (int)d_in;
+            a.Q = dy; a.ldq = d_out; a.M = (int)d_out; a.kq = (int)tokens; a.transposed = 1;
+            a.K = (int)ldt;
+            a.C = static_cast<uint16_t *>(it.dW); a.ldc = d_in; a.accumulate = accumulate;
             if (flags & SBN_BWD_MASK_DW) {
                 // ablation variant: only the weights of the current mask receive the new gradient term
                 st = launch_mask_bitplane(it.packed, d_out, d_in, pat, mask_bits, stream);

@@ -270,3 +270,31 @@ def test_config5_training_step_as_timed():
         assert torch.equal(dWl[i].view(torch.int16), sW.view(torch.int16)), f"grouped dW of {name} differs from the single call"
         del sX, sW
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("N,M,tokens,d_out,d_in", [
+    (2, 4, 1, 8, 8), (2, 4, 63, 72, 136), (6, 8, 65, 120, 248), (4, 4, 129, 264, 128), (1, 4, 64, 64, 384), (2, 8, 200, 1000, 264),   # tiles of 128
+    (3, 8, 130, 136, 264),                                # a pattern without a decoder of its own
+    (2, 4, 4100, 2056, 2568), (6, 8, 4100, 2056, 2568)])  # tiles of 256: four tokens, eight rows and eight columns past whole stages and tiles
+@pytest.mark.parametrize("accumulate", [False, True])
+def test_backward_tile_edges(N, M, tokens, d_out, d_in, accumulate):
+    s = sbn()
+    W = sbn_synth.latent_weight(d_out, d_in, 7000 + d_out)
+    packed, gamma = hip_pack(W, N, M)
+    Weff = torch.empty(d_out, d_in, dtype=torch.int8, device=DEV)
+    s.sbn_unpack(packed, d_out, d_in, N, M, W_eff=Weff)
+    X, dY = sbn_synth.activations(tokens, d_in, 7001, device=DEV), sbn_synth.grad_output(tokens, d_out, 7002, device=DEV)
+    xq, sx = torch.empty(tokens, d_in, dtype=torch.int8, device=DEV), torch.empty(tokens, device=DEV)
+    s.sbn_act_quant(X, xq, sx)
+    old = sbn_synth.grad_output(d_out, d_in, 7003, device=DEV)
+    dX = torch.full((tokens, d_in), float("nan"), dtype=torch.bfloat16, device=DEV)
+    dW = old.clone() if accumulate else torch.full((d_out, d_in), float("nan"), dtype=torch.bfloat16, device=DEV)
+    ws = s.new_workspace(s.sbn_workspace_bytes(s.SBN_OP_BACKWARD, tokens, d_out, d_in, N, M))
+    ws.fill_(0xff)                                        # NaNs wherever a padded operand should have been cleared
+    s.sbn_sparse_ternary_linear_backward(dY, packed, gamma, xq, sx, N, M, ws, d_in, dX=dX, dW=dW, accumulate=accumulate)
+    ref_x = gamma.double() * (dY.double() @ Weff.double())
+    ref_w = (dY.double() / sx.double()[:, None]).t().contiguous() @ xq.double() + (old.double() if accumulate else 0.0)
+    for got, ref, what in ((dX, ref_x, "dX"), (dW, ref_w, "dW")):
+        # one rounding of an operand and one of the result to bf16, 2^-9 each, relative to the larger of value and rms
+        err = (got.double() - ref).abs() / torch.maximum(ref.abs(), ref.square().mean().sqrt())
+        assert err.max().item() <= 2e-2 and err.square().mean().sqrt().item() <= 2.0 ** -8, what
