@@ -1,9 +1,9 @@
 // quantize_mask_pack: absmean scale, N:M magnitude mask, ternary codes, packed layout.
 //
-// bf16 matrices of whole chunks at 2:4, 1:4 or 2:8 take the single-read form: one persistent kernel
-// (pack_stream_kernel, after a small clear of its counters) whose blocks keep units of 16384 weights
-// in registers between the |w| sum and the packing (ranked and compacted while they wait for the
-// threshold), so that W crosses HBM once.
+// Matrices of whole chunks at 2:4, 1:4, 2:8, 6:8 or N = M, bf16 or fp32, take the single-read form: one
+// persistent kernel (pack_stream_kernel, after a small clear of its counters) whose blocks keep units of
+// 16384 weights in registers between the |w| sum and the packing (ranked, and compacted where the pattern
+// drops enough, while they wait for the threshold), so that W crosses HBM once.
 // Everything else takes three enqueues per batch of up to PACK_MAX_ITEMS matrices:
 //   1. absmean_partial_kernel  one block per 16384 weights, |w| summed in fp64 (every term exact)
 //   2. absmean_finalize_kernel one block per matrix: fixed-order sum of the partials, gamma and
@@ -291,8 +291,8 @@ __global__ void __launch_bounds__(256) pack_kernel(PackTable tab, const float *t
     }
 }
 
-// ---- fast pack kernels: bf16, rows contiguous, d_in % 128 == 0, patterns 2:4, 1:4, 2:8 ----------------
-// A lane owns 8 consecutive weights (one 16-byte load).  Selection runs on integer keys
+// ---- fast pack kernels: rows contiguous, d_in % 128 == 0, patterns 2:4, 1:4, 2:8, 6:8, N = M ----------
+// A lane owns 8 consecutive weights (one 16-byte load, two for fp32).  On bf16 selection runs on integer keys
 //     magnitude << 17 | (M - 1 - position in the group) << 2 | 1 << 1 | sign
 // which are unique within a group, and the larger key is the larger magnitude or, among equals, the lower
 // position, so max/min networks give the top-N with the tie rule built in.  A key is one rotation of the
@@ -397,22 +397,34 @@ static_assert(sizeof(PackTable) + sizeof(PackSync) <= 4096, "both travel as kern
 
 constexpr int PACK_U = 8;   // 16-byte vectors per thread: a unit = 256 threads x 8 vectors = 128 chunks = 16384 weights
 
+// eight consecutive weights
+template <typename WT> struct Vec8 { uint4 q[sizeof(WT) / 2]; };
+template <typename WT> __device__ __forceinline__ Vec8<WT> load_vec8(const WT *p)
+{
+    Vec8<WT> v;
+#pragma unroll
+    for (int i = 0; i < (int)sizeof(WT) / 2; ++i) v.q[i] = reinterpret_cast<const uint4 *>(p)[i];
+    return v;
+}
+
 // the unit's weights into registers: thread (ql = tid / 16, l16 = tid % 16) takes vector l16 of chunk 16 u + ql
-__device__ __forceinline__ void load_unit(const PackItem &it, int64_t lb, uint4 (&v)[PACK_U])
+template <typename WT>
+__device__ __forceinline__ void load_unit(const PackItem &it, int64_t lb, Vec8<WT> (&v)[PACK_U])
 {
     const int64_t total_chunks = it.d_out * (it.d_in / CHUNK);
-    const uint16_t *W = static_cast<const uint16_t *>(it.W);
+    const WT *W = static_cast<const WT *>(it.W);
     const int ql = threadIdx.x >> 4, l16 = threadIdx.x & 15;
 #pragma unroll
     for (int u = 0; u < PACK_U; ++u) {
         const int64_t q = (lb * PACK_U + u) * 16 + ql;
-        v[u] = q < total_chunks ? *reinterpret_cast<const uint4 *>(W + q * CHUNK + l16 * 8) : make_uint4(0, 0, 0, 0);
+        v[u] = q < total_chunks ? load_vec8(W + q * CHUNK + l16 * 8) : Vec8<WT>{};
     }
 }
 
-// |w| of the eight bf16 values of a vector added to acc in element order (the order of the absmean pass)
-__device__ __forceinline__ double abs8(const uint4 &d, double acc)
+// |w| of the eight values of a vector added to acc in element order (the order of the absmean pass)
+__device__ __forceinline__ double abs8(const Vec8<uint16_t> &v, double acc)
 {
+    const uint4 &d = v.q[0];
     const uint32_t w[4] = {d.x, d.y, d.z, d.w};
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
@@ -422,53 +434,187 @@ __device__ __forceinline__ double abs8(const uint4 &d, double acc)
     }
     return acc;
 }
+__device__ __forceinline__ double abs8(const Vec8<float> &v, double acc)
+{
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        acc += (double)fabsf(__uint_as_float(v.q[i].x));
+        acc += (double)fabsf(__uint_as_float(v.q[i].y));
+        acc += (double)fabsf(__uint_as_float(v.q[i].z));
+        acc += (double)fabsf(__uint_as_float(v.q[i].w));
+    }
+    return acc;
+}
 
-// What is left of a unit once its groups have been ranked, which needs no threshold: the bf16 patterns of
-// the kept values, two per dword in position order, and one byte of index bits per vector (as they go into
-// the index field).  18, 10 and 10 registers per thread for 2:4, 1:4 and 2:8 against 32 for the weights.
-template <int N, int M> struct PackCompact {
-    static constexpr int SEL = (N == 2 && M == 4) ? 2 * PACK_U : PACK_U;
-    uint32_t sel[SEL];
+// What a unit is held as once its groups have been ranked, which needs no threshold.  2:4, 1:4 and 2:8: the
+// kept values in position order (bf16 two per dword) and one byte of index bits per vector as they go into the
+// index field: 18, 10 and 10 registers per thread against 32 for the bf16 weights, twice that in fp32.  6:8 and
+// N = M drop too little for that: the weights as loaded, and at 6:8 one byte of keep bits per vector.
+template <typename WT, int N, int M> struct PackCompact {
+    static constexpr bool WHOLE = N == M || N == 6;
+    static constexpr int PER = (WHOLE ? 8 : 8 * N / M) * (int)sizeof(WT) / 4;   // dwords held per vector
+    static constexpr bool BYTES = N != M;
+    uint32_t sel[PER * PACK_U];
     uint32_t idx[PACK_U / 4];
 };
 
+// bit set of the two smallest of eight unique keys, by position
+__device__ __forceinline__ uint32_t bottom2_of8(const uint32_t (&k)[8])
+{
+    uint32_t lo[2], hi[2];   // smallest and second smallest of each half
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const uint32_t l01 = umin(k[4 * h], k[4 * h + 1]), h01 = umax(k[4 * h], k[4 * h + 1]);
+        const uint32_t l23 = umin(k[4 * h + 2], k[4 * h + 3]), h23 = umax(k[4 * h + 2], k[4 * h + 3]);
+        lo[h] = umin(l01, l23);
+        hi[h] = umin(umax(l01, l23), umin(h01, h23));
+    }
+    const uint32_t first = umin(lo[0], lo[1]), second = umin(umax(lo[0], lo[1]), umin(hi[0], hi[1]));
+    return (0x80u >> ((first >> 2) & 7u)) | (0x80u >> ((second >> 2) & 7u));   // the position field holds 7 - position
+}
+
 template <int N, int M>
-__device__ __forceinline__ void select_unit(const uint4 (&v)[PACK_U], PackCompact<N, M> &c)
+__device__ __forceinline__ void select_unit(const Vec8<uint16_t> (&v)[PACK_U], PackCompact<uint16_t, N, M> &c)
 {
 #pragma unroll
     for (int w = 0; w < PACK_U / 4; ++w) c.idx[w] = 0;
 #pragma unroll
     for (int u = 0; u < PACK_U; ++u) {
-        uint32_t key[8];
-        make_keys<M>(v[u], key);
-        uint32_t idxb;
-        // position fields hold M - 1 - position: the index bits are inverted once they are assembled
-        if constexpr (N == 2 && M == 4) {
-            uint32_t klo[2], khi[2];
+        uint32_t idxb = 0;
+        if constexpr (PackCompact<uint16_t, N, M>::WHOLE) {
+            const uint4 &d = v[u].q[0];
+            c.sel[4 * u] = d.x; c.sel[4 * u + 1] = d.y; c.sel[4 * u + 2] = d.z; c.sel[4 * u + 3] = d.w;
+            if constexpr (N != M) {
+                uint32_t key[8];
+                make_keys<M>(d, key);
+                idxb = bottom2_of8(key) ^ 0xffu;
+            }
+        } else {
+            uint32_t key[8];
+            make_keys<M>(v[u].q[0], key);
+            // position fields hold M - 1 - position: the index bits are inverted once they are assembled
+            if constexpr (N == 2 && M == 4) {
+                uint32_t klo[2], khi[2];
+#pragma unroll
+                for (int g = 0; g < 2; ++g) {
+                    by_position<M>(top2_of4(key[4 * g], key[4 * g + 1], key[4 * g + 2], key[4 * g + 3]), klo[g], khi[g]);
+                    c.sel[2 * u + g] = pair_of_keys(klo[g], khi[g]);
+                }
+                const uint32_t n0 = ((klo[0] >> 2) & 3u) | (khi[0] & 0xcu), n1 = ((klo[1] >> 2) & 3u) | (khi[1] & 0xcu);
+                idxb = (n0 | (n1 << 4)) ^ 0xffu;
+            } else if constexpr (N == 1 && M == 4) {
+                const uint32_t t0 = umax(umax(key[0], key[1]), umax(key[2], key[3]));
+                const uint32_t t1 = umax(umax(key[4], key[5]), umax(key[6], key[7]));
+                c.sel[u] = pair_of_keys(t0, t1);
+                idxb = (((t0 >> 2) & 3u) | (t1 & 0xcu)) ^ 0xfu;
+            } else {   // 2:8
+                const Top2 ta = top2_of4(key[0], key[1], key[2], key[3]);
+                const Top2 tb = top2_of4(key[4], key[5], key[6], key[7]);
+                Top2 t;
+                t.first = umax(ta.first, tb.first);
+                t.second = umax(umin(ta.first, tb.first), umax(ta.second, tb.second));
+                uint32_t klo, khi;
+                by_position<M>(t, klo, khi);
+                c.sel[u] = pair_of_keys(klo, khi);
+                idxb = (((klo >> 2) & 7u) | ((khi & 0x1cu) << 1)) ^ 0x3fu;   // two 3-bit positions
+            }
+        }
+        if constexpr (PackCompact<uint16_t, N, M>::BYTES) c.idx[u / 4] |= idxb << (8 * (u % 4));
+    }
+}
+
+// fp32: magnitude and position do not fit one key.  Of eight: the second largest (smallest) magnitude by a max/min
+// network, then the elements beyond it, and as many equal to it, from the lowest (highest) position on, as make two;
+// 60 operations per vector where comparing every pair takes 120.  Bit set of the two elements, by position.
+template <bool LARGEST>
+__device__ __forceinline__ uint32_t extreme2_of8(const uint32_t (&m)[8])
+{
+    auto nearer = [](uint32_t a, uint32_t b) { return LARGEST ? umax(a, b) : umin(a, b); };
+    auto farther = [](uint32_t a, uint32_t b) { return LARGEST ? umin(a, b) : umax(a, b); };
+    uint32_t n[2], f[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const uint32_t *x = m + 4 * h;
+        const uint32_t n0 = nearer(x[0], x[1]), n1 = nearer(x[2], x[3]);
+        n[h] = nearer(n0, n1);
+        f[h] = nearer(farther(n0, n1), nearer(farther(x[0], x[1]), farther(x[2], x[3])));
+    }
+    const uint32_t second = nearer(farther(n[0], n[1]), nearer(f[0], f[1]));
+    // magnitudes are below 2^31: the sign of a difference tells their order
+    uint32_t less = 0, upto = 0;   // m < second, m <= second
+#pragma unroll
+    for (int j = 7; j >= 0; --j) {
+        less = __builtin_amdgcn_alignbit(less, m[j] - second, 31);
+        upto = __builtin_amdgcn_alignbit(upto, m[j] - second - 1u, 31);
+    }
+    const uint32_t beyond = LARGEST ? upto ^ 0xffu : less;   // none or one
+    uint32_t equal = less ^ upto;
+    const auto next = [&] { return LARGEST ? equal & (0u - equal) : 0x80000000u >> __builtin_clz(equal); };
+    uint32_t two = beyond | next();
+    equal ^= next();
+    if (beyond == 0) two |= next();
+    return two;
+}
+
+// Of four: pairs.  at_least2: two of three
+__device__ __forceinline__ bool at_least2(bool a, bool b, bool c) { return (a && b) || (c && (a || b)); }
+
+template <int N, int M>
+__device__ __forceinline__ void select_unit(const Vec8<float> (&v)[PACK_U], PackCompact<float, N, M> &c)
+{
+    typedef PackCompact<float, N, M> C;
+#pragma unroll
+    for (int w = 0; w < PACK_U / 4; ++w) c.idx[w] = 0;
+#pragma unroll
+    for (int u = 0; u < PACK_U; ++u) {
+        const uint4 a = v[u].q[0], b = v[u].q[1];
+        const uint32_t w[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+        uint32_t m[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) m[j] = w[j] & Raw<float>::MAG;
+        uint32_t idxb = 0;
+        if constexpr (C::WHOLE) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) c.sel[8 * u + j] = w[j];
+            if constexpr (N != M) idxb = extreme2_of8<false>(m) ^ 0xffu;
+        } else if constexpr (N == 2 && M == 4) {
 #pragma unroll
             for (int g = 0; g < 2; ++g) {
-                by_position<M>(top2_of4(key[4 * g], key[4 * g + 1], key[4 * g + 2], key[4 * g + 3]), klo[g], khi[g]);
-                c.sel[2 * u + g] = pair_of_keys(klo[g], khi[g]);
+                const uint32_t *x = m + 4 * g, *y = w + 4 * g;
+                // the later element beats the earlier one only if it is larger
+                const bool b01 = x[1] > x[0], b02 = x[2] > x[0], b03 = x[3] > x[0], b12 = x[2] > x[1], b13 = x[3] > x[1], b23 = x[3] > x[2];
+                const bool k0 = !at_least2(b01, b02, b03), k1 = !at_least2(!b01, b12, b13);
+                const bool k2 = !at_least2(!b02, !b12, b23), k3 = !at_least2(!b03, !b13, !b23);
+                c.sel[4 * u + 2 * g] = k0 ? y[0] : k1 ? y[1] : y[2];
+                c.sel[4 * u + 2 * g + 1] = k3 ? y[3] : k2 ? y[2] : y[1];
+                idxb |= ((k0 ? 0u : k1 ? 1u : 2u) | (k3 ? 12u : k2 ? 8u : 4u)) << (4 * g);
             }
-            const uint32_t n0 = ((klo[0] >> 2) & 3u) | (khi[0] & 0xcu), n1 = ((klo[1] >> 2) & 3u) | (khi[1] & 0xcu);
-            idxb = (n0 | (n1 << 4)) ^ 0xffu;
         } else if constexpr (N == 1 && M == 4) {
-            const uint32_t t0 = umax(umax(key[0], key[1]), umax(key[2], key[3]));
-            const uint32_t t1 = umax(umax(key[4], key[5]), umax(key[6], key[7]));
-            c.sel[u] = pair_of_keys(t0, t1);
-            idxb = (((t0 >> 2) & 3u) | (t1 & 0xcu)) ^ 0xfu;
+#pragma unroll
+            for (int g = 0; g < 2; ++g) {
+                uint32_t best = m[4 * g], val = w[4 * g], pos = 0;
+#pragma unroll
+                for (int j = 1; j < 4; ++j) {
+                    const bool up = m[4 * g + j] > best;
+                    best = up ? m[4 * g + j] : best;
+                    val = up ? w[4 * g + j] : val;
+                    pos = up ? (uint32_t)j : pos;
+                }
+                c.sel[2 * u + g] = val;
+                idxb |= pos << (2 * g);
+            }
         } else {   // 2:8
-            const Top2 ta = top2_of4(key[0], key[1], key[2], key[3]);
-            const Top2 tb = top2_of4(key[4], key[5], key[6], key[7]);
-            Top2 t;
-            t.first = umax(ta.first, tb.first);
-            t.second = umax(umin(ta.first, tb.first), umax(ta.second, tb.second));
-            uint32_t klo, khi;
-            by_position<M>(t, klo, khi);
-            c.sel[u] = pair_of_keys(klo, khi);
-            idxb = (((klo >> 2) & 7u) | ((khi & 0x1cu) << 1)) ^ 0x3fu;   // two 3-bit positions
+            const uint32_t keep = extreme2_of8<true>(m);
+            uint32_t first = w[6], second = w[1];
+#pragma unroll
+            for (int j = 5; j >= 0; --j) first = (keep >> j) & 1u ? w[j] : first;
+#pragma unroll
+            for (int j = 2; j < 8; ++j) second = (keep >> j) & 1u ? w[j] : second;
+            c.sel[2 * u] = first;
+            c.sel[2 * u + 1] = second;
+            idxb = (uint32_t)__builtin_ctz(keep) | ((31u - (uint32_t)__builtin_clz(keep)) << 3);
         }
-        c.idx[u / 4] |= idxb << (8 * (u % 4));
+        if constexpr (C::BYTES) c.idx[u / 4] |= idxb << (8 * (u % 4));
     }
 }
 
@@ -504,19 +650,61 @@ __device__ __forceinline__ uint32_t flips_2of8_half(uint64_t n, uint64_t o)
     return 32u - 2u * (uint32_t)(__popcll(same) + __popcll(cross));
 }
 
-// Codes of the compact unit with threshold th_val, fields assembled, and its 128 chunks (contiguous in the
-// packed buffer) stored.  lds: PACK_U * 16 * CBW words of staging; ends with the block's stores issued, LDS
+// ternary codes of the CNT held values of vector u, one per byte
+template <typename WT, int N, int M> struct HeldCodes {
+    static constexpr int CNT = PackCompact<WT, N, M>::WHOLE ? 8 : 8 * N / M;   // 2, 4 or 8
+    uint32_t lo, hi;
+    // th: the smallest magnitude pattern whose value is >= theta (at least 1: theta > 0); bf16: minus one, in both halves
+    __device__ __forceinline__ HeldCodes(const PackCompact<WT, N, M> &c, int u, uint32_t th)
+    {
+        lo = hi = 0;
+        const uint32_t *s = c.sel + PackCompact<WT, N, M>::PER * u;
+        if constexpr (sizeof(WT) == 2) {
+            // bytes 0 and 2 of each pair's codes
+            lo = __builtin_amdgcn_perm(CNT > 2 ? pair_codes(s[CNT > 2 ? 1 : 0], th) : 0u, pair_codes(s[0], th), 0x06040200u);
+            if constexpr (CNT == 8) hi = __builtin_amdgcn_perm(pair_codes(s[3], th), pair_codes(s[2], th), 0x06040200u);
+        } else {
+#pragma unroll
+            for (int j = 0; j < CNT; ++j) {
+                const uint32_t code = (s[j] & Raw<float>::MAG) >= th ? ((s[j] >> 30) & 2u) | 1u : 0u;
+                if (j < 4) lo |= code << (8 * j);
+                else hi |= code << (8 * (j - 4));
+            }
+        }
+    }
+};
+
+// dwords per chunk of the packed form: 32, 16, 20, 60 and 32 bytes
+template <int N, int M> constexpr int PACK_CBW = N == M ? 8 : N == 6 ? 15 : M == 8 ? 5 : N == 1 ? 4 : 8;
+// words of LDS that finish_unit stages a unit in; 6:8 needs room for its 96 slots per chunk, a byte each, besides
+template <int N, int M> constexpr int PACK_LDS_WORDS = PACK_U * 16 * (PACK_CBW<N, M> + (N == 6 ? 24 : 0));
+
+// 6:8: sixteen slots of a chunk, one per byte (code | position << 2), as their code word and 48 index bits
+__device__ __forceinline__ void fields_of_16_slots(const uint4 &s, uint32_t &codes, uint64_t &idx)
+{
+    constexpr uint32_t C = 0x03030303u;
+    codes = (s.x & C) | ((s.y & C) << 2) | ((s.z & C) << 4) | ((s.w & C) << 6);
+    auto twelve = [](uint32_t x) -> uint32_t {   // the four 3-bit positions of a dword, side by side
+        x = (x >> 2) & 0x07070707u;
+        x = (x | (x >> 5)) & 0x003f003fu;
+        return (x | (x >> 10)) & 0xfffu;
+    };
+    idx = (uint64_t)(twelve(s.x) | (twelve(s.y) << 12)) | ((uint64_t)(twelve(s.z) | (twelve(s.w) << 12)) << 24);
+}
+
+// Codes of the held unit with threshold th_val, fields assembled, and its 128 chunks (contiguous in the
+// packed buffer) stored.  lds: PACK_LDS_WORDS words of staging; ends with the block's stores issued, LDS
 // free after the next barrier.
 // FLIPS: the packed buffer still holds the matrix's previous packed form, which the unit replaces; the return value
 // is the number of mask positions that differ between the two in this thread's share of the unit (thread t: half
 // t % 2 of the index field of chunk t / 2).  The old index words are asked for first and have arrived before the
 // barrier behind which the block's stores begin: no thread overwrites a word another thread has yet to read.
-template <int N, int M, bool FLIPS>
-__device__ __forceinline__ uint32_t finish_unit(const PackItem &it, const int64_t lb, const PackCompact<N, M> &c, const float th_val,
+template <typename WT, int N, int M, bool FLIPS>
+__device__ __forceinline__ uint32_t finish_unit(const PackItem &it, const int64_t lb, const PackCompact<WT, N, M> &c, const float th_val,
                                                 uint32_t *lds)
 {
     constexpr int U = PACK_U;
-    constexpr int CBW = (M == 4 && N == 2) ? 8 : (M == 4 ? 4 : 5);   // dwords per chunk: 32, 16, 20 bytes
+    constexpr int CBW = PACK_CBW<N, M>;
     const int64_t total_chunks = it.d_out * (it.d_in / CHUNK);
     const int tid = threadIdx.x, ql = tid >> 4, l16 = tid & 15;
     // the block's chunks are contiguous in the packed buffer
@@ -535,15 +723,32 @@ __device__ __forceinline__ uint32_t finish_unit(const PackItem &it, const int64_
             if constexpr (!(M == 4 && N == 1)) old1 = po[1];
         }
     }
-    // smallest bf16 magnitude pattern whose value is >= theta (at least 1: theta > 0), minus one, in both halves
-    const uint32_t thm1x2 = (((__float_as_uint(th_val) + 0xffffu) >> 16) - 1u) * 0x10001u;
+    uint32_t th = Raw<WT>::threshold(th_val);
+    if constexpr (sizeof(WT) == 2) th = (th - 1u) * 0x10001u;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         uint32_t *out = lds + (u * 16 + ql) * CBW;
-        const uint32_t idxb = (c.idx[u / 4] >> (8 * (u % 4))) & 0xffu;
-        if constexpr (N == 2 && M == 4) {
-            // bytes 0 and 2 of each pair's codes -> the four code bytes of the vector
-            const uint32_t codeb = __builtin_amdgcn_perm(pair_codes(c.sel[2 * u + 1], thm1x2), pair_codes(c.sel[2 * u], thm1x2), 0x06040200u);
+        const HeldCodes<WT, N, M> codes(c, u, th);
+        const uint32_t idxb = PackCompact<WT, N, M>::BYTES ? (c.idx[u / 4] >> (8 * (u % 4))) & 0xffu : 0u;
+        if constexpr (N == M) {
+            // two lanes make a code word: slots 0-3 and 4-7 of the even lane in bits [0, 4) of its bytes, the odd lane's in [4, 8)
+            const uint32_t codew = dpp_or_t<0xB1>((codes.lo | (codes.hi << 2)) << (4 * (l16 & 1)));
+            if ((l16 & 1) == 0) out[l16 >> 1] = codew;
+        } else if constexpr (N == 6) {
+            // the two dropped positions a < b; slot k holds position k + (k >= a) + (k >= b - 1), which is also the byte
+            // selector that closes the gaps
+            const uint32_t drop = idxb ^ 0xffu;
+            const uint32_t a8 = 8u * (uint32_t)__builtin_ctz(drop), b8 = 8u * (30u - (uint32_t)__builtin_clz(drop));
+            const uint64_t ge = (0x010101010101ull << a8) + (0x010101010101ull << b8);
+            const uint32_t p0 = 0x03020100u + (uint32_t)ge, p1 = (0x0504u + (uint32_t)(ge >> 32)) & 0xffffu;
+            const uint32_t s0 = __builtin_amdgcn_perm(codes.hi, codes.lo, p0) | (p0 << 2);
+            const uint32_t s1 = __builtin_amdgcn_perm(codes.hi, codes.lo, p1) | (p1 << 2);
+            uint16_t *slots = reinterpret_cast<uint16_t *>(lds + U * 16 * CBW + (u * 16 + ql) * 24) + 3 * l16;
+            slots[0] = (uint16_t)s0;
+            slots[1] = (uint16_t)(s0 >> 16);
+            slots[2] = (uint16_t)s1;
+        } else if constexpr (N == 2 && M == 4) {
+            const uint32_t codeb = codes.lo;
             const int L = l16 & 3;
             const uint32_t idxw = group_or<4>(idxb << (8 * L));
             const uint32_t codew = group_or<4>(codeb << (2 * L));
@@ -552,7 +757,7 @@ __device__ __forceinline__ uint32_t finish_unit(const PackItem &it, const int64_
                 out[4 + (l16 >> 2)] = codew;
             }
         } else {
-            const uint32_t codeb = __builtin_amdgcn_perm(0u, pair_codes(c.sel[u], thm1x2), 0x0c0c0200u);
+            const uint32_t codeb = codes.lo;
             const int L8 = l16 & 7;
             const uint32_t codew = group_or<8>(codeb << (16 * (L8 & 1) + 2 * (L8 >> 1)));
             if constexpr (M == 4) {
@@ -572,6 +777,22 @@ __device__ __forceinline__ uint32_t finish_unit(const PackItem &it, const int64_
                 if (l16 == 0) { out[0] = i0; out[1] = i1; out[2] = i2; }
                 if (L8 == 0) out[3 + (l16 >> 3)] = codew;
             }
+        }
+    }
+    if constexpr (N == 6) {
+        __syncthreads();
+        const uint4 *slots = reinterpret_cast<const uint4 *>(lds + U * 16 * CBW);
+#pragma unroll
+        for (int i = 0; i < U * 16 * 6 / 256; ++i) {
+            const int t = i * 256 + tid, q = t / 6, w = t % 6;   // chunk, code word
+            uint32_t codew;
+            uint64_t idx;
+            fields_of_16_slots(slots[t], codew, idx);
+            lds[q * CBW + 9 + w] = codew;
+            uint16_t *field = reinterpret_cast<uint16_t *>(lds + q * CBW) + 3 * w;
+            field[0] = (uint16_t)idx;
+            field[1] = (uint16_t)(idx >> 16);
+            field[2] = (uint16_t)(idx >> 32);
         }
     }
     if constexpr (FLIPS) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the old words are in registers: see above
@@ -638,20 +859,19 @@ __global__ void __launch_bounds__(256) pack_flips_sum_kernel(PackTable tab, cons
 }
 
 // third kernel of the three-pass form: theta comes from the finalize kernel
-template <int N, int M, bool FLIPS>
+template <typename WT, int N, int M, bool FLIPS>
 __global__ void __launch_bounds__(256) pack_fast_kernel(PackTable tab, const float *theta, uint32_t *unit_flips)
 {
-    constexpr int CBW = (M == 4 && N == 2) ? 8 : (M == 4 ? 4 : 5);
-    __shared__ __attribute__((aligned(16))) uint32_t lds[PACK_U * 16 * CBW];
+    __shared__ __attribute__((aligned(16))) uint32_t lds[PACK_LDS_WORDS<N, M>];
     __shared__ uint32_t wave_flips[4];
     const int lo = find_item(tab.pack_block0, tab.count, blockIdx.x);
     const PackItem &it = tab.it[lo];
     const int64_t lb = (int)blockIdx.x - tab.pack_block0[lo];
-    uint4 v[PACK_U];
+    Vec8<WT> v[PACK_U];
     load_unit(it, lb, v);
-    PackCompact<N, M> c;
+    PackCompact<WT, N, M> c;
     select_unit<N, M>(v, c);
-    const uint32_t fl = finish_unit<N, M, FLIPS>(it, lb, c, theta[lo], lds);
+    const uint32_t fl = finish_unit<WT, N, M, FLIPS>(it, lb, c, theta[lo], lds);
     if constexpr (FLIPS) {
         flips_wave_sum(fl, wave_flips);
         __syncthreads();
@@ -672,19 +892,19 @@ __global__ void __launch_bounds__(256) pack_fast_kernel(PackTable tab, const flo
 // hand-over of a matrix (four device-scope hops of about 1.5 us) runs under the loads of the following
 // ones.  The smaller compact form also lets more blocks fit (2:4: six per SIMD instead of five).
 // W crosses HBM once.
-// Waits always end: a unit's matrix becomes ready once all its units are published; a block publishes
-// every unit it holds before it waits, and the units of a matrix (at most as many as there are
-// blocks: the host checks) all lie within one deal of the round-robin.  Take the block whose oldest unit
-// has the smallest number x: every unit of x's matrix lies below x + B, so the block it belongs to
-// already holds it, hence has published it; the same goes for the matrix's first unit, whose block finalizes.
+// Waits always end: a unit's matrix becomes ready once all its units are published; a block publishes the
+// unit QD deals behind its oldest before it waits, and the units of a matrix (at most QD + 1 per block: the
+// host checks) all lie within QD + 1 deals of the round-robin.  Take the block whose oldest unit has the
+// smallest number x: every unit of x's matrix lies below x + (QD + 1) B, so it is at most QD deals behind
+// the oldest unit (at least x) of the block it belongs to, hence published; the matrix's first unit is x
+// itself, and its block finalizes, or lies below x, and its block has finalized already.
 // The wait is bounded all the same (the grid might
 // not be fully resident when the device is shared): a block out of polls recomputes every partial of
 // the matrix from HBM itself - same arithmetic, same order, same theta - and goes on.
-template <int N, int M, int QD, int WAVES, bool FLIPS>
+template <typename WT, int N, int M, int QD, int WAVES, bool FLIPS>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES, WAVES))) pack_stream_kernel(PackTable tab, PackSync sync)
 {
-    constexpr int CBW = (M == 4 && N == 2) ? 8 : (M == 4 ? 4 : 5);
-    __shared__ __attribute__((aligned(16))) uint32_t lds[PACK_U * 16 * CBW];
+    __shared__ __attribute__((aligned(16))) uint32_t lds[PACK_LDS_WORDS<N, M>];
     __shared__ uint32_t wave_flips[4];
     __shared__ double red[256];
     __shared__ int role_s;      // 2: waited in vain
@@ -702,7 +922,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES,
         return un;
     };
     // the |w| sum of a loaded unit into its partial slot
-    auto publish = [&](const Unit &un, const uint4 (&v)[PACK_U]) {
+    auto publish = [&](const Unit &un, const Vec8<WT> (&v)[PACK_U]) {
         double acc = 0.0;
 #pragma unroll
         for (int u = 0; u < PACK_U; ++u) acc = abs8(v[u], acc);
@@ -774,7 +994,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES,
         if (alone) {
             // every partial sum of the matrix from HBM, added up in the finalize order: thread b % 256 takes partial b
             const int64_t total_chunks = it.d_out * (it.d_in / CHUNK);
-            const uint16_t *W = static_cast<const uint16_t *>(it.W);
+            const WT *W = static_cast<const WT *>(it.W);
             const int ql = tid >> 4, l16 = tid & 15;
             double a3 = 0.0;
             for (int b = 0; b < nblk; ++b) {
@@ -782,7 +1002,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES,
 #pragma unroll
                 for (int u = 0; u < PACK_U; ++u) {
                     const int64_t q = ((int64_t)b * PACK_U + u) * 16 + ql;
-                    if (q < total_chunks) pa = abs8(*reinterpret_cast<const uint4 *>(W + q * CHUNK + l16 * 8), pa);
+                    if (q < total_chunks) pa = abs8(load_vec8(W + q * CHUNK + l16 * 8), pa);
                 }
                 const double pb = block_sum(pa, red);
                 if ((b & 255) == tid) a3 += pb;
@@ -813,8 +1033,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES,
     };
     // A block has up to QD + 1 units in flight: the weights of the youngest in registers (loading), the QD
     // older ones ranked and compacted, waiting for their matrices' thresholds; q[0] is the oldest.
-    uint4 raw[PACK_U];
-    PackCompact<N, M> q[QD];
+    Vec8<WT> raw[PACK_U];
+    PackCompact<WT, N, M> q[QD];
     Unit uq[QD];
     int queued = 0;
     auto push = [&](const Unit &un) {   // rank the loaded unit and queue it
@@ -842,7 +1062,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES,
             publish(un, raw);
         }
         const float th = theta_of(uq[0]);
-        const uint32_t fl = finish_unit<N, M, FLIPS>(tab.it[uq[0].lo], uq[0].lb, q[0], th, lds);
+        const uint32_t fl = finish_unit<WT, N, M, FLIPS>(tab.it[uq[0].lo], uq[0].lb, q[0], th, lds);
         if constexpr (FLIPS) flips_wave_sum(fl, wave_flips);
         __syncthreads();   // the staging area is free for the next unit
         if constexpr (FLIPS) flips_commit(wave_flips, sync.unit_flips + tab.pack_block0[uq[0].lo] + uq[0].lb);
@@ -1111,43 +1331,76 @@ __global__ void __launch_bounds__(256) pack_sync_clear_kernel(unsigned *words, i
 }
 
 // blocks of the single-read pack kernel the device holds at once = its grid (per instantiation, cached per thread)
-// Compact units a block queues and wavefronts per SIMD of the single-read kernel, per pattern.  Measured
-// (sweep of 210 matrices): 2:4 with (queue, wavefronts) = (1, 6) 1.27 ms, (2, 5) 1.39, (1, 7) 1.50 (spills);
-// 1:4 / 2:8 with (2, 5) 1.11 / 1.27 ms, (3, 5) 1.12 / 1.31, (1, 7) 1.14 / 1.31, (2, 6) 1.17 / 1.36.
-template <int N, int M> struct PackStreamShape {
-    static constexpr int QD = (N == 2 && M == 4) ? 1 : 2;
-    static constexpr int WAVES = (N == 2 && M == 4) ? 6 : 5;
+// Compact units a block queues and wavefronts per SIMD of the single-read kernel, per type and pattern: as many as the
+// registers hold without more than a few spills.  Measured on bf16 (sweep of 210 matrices): 2:4 with (queue, wavefronts) =
+// (1, 6) 1.27 ms, (2, 5) 1.39, (1, 7) 1.50 (spills); 1:4 / 2:8 with (2, 5) 1.11 / 1.27 ms, (3, 5) 1.12 / 1.31,
+// (1, 7) 1.14 / 1.31, (2, 6) 1.17 / 1.36.  The seven matrices of a block (hidden 2560, FFN 6912), us in this form and in
+// three passes: bf16 6:8 67 / 141, N = M 48 / 77; fp32 2:4 88 / 137, 1:4 74 / 136, 2:8 86 / 159, 6:8 104 / 168, N = M
+// 82 / 115 (the weights alone at 5.5 TB/s: 29 bf16, 58 fp32).  Matrices of more units than the blocks have in flight
+// ((queue + 1) per block: 25 to 50 million weights) take three passes.
+template <typename WT, int N, int M> struct PackStreamShape {
+    static constexpr bool WHOLE = PackCompact<WT, N, M>::WHOLE, F32 = sizeof(WT) == 4;
+    static constexpr int QD = F32 || WHOLE || (N == 2 && M == 4) ? 1 : 2;
+    static constexpr int WAVES = F32 ? (WHOLE ? 3 : 4) : WHOLE ? 5 : N == 2 && M == 4 ? 6 : 5;
 };
 
-template <int N, int M>
-static void launch_pack_stream(int grid, hipStream_t stream, const PackTable &tab, const PackSync &sync)
+template <typename WT, int N, int M, bool FLIPS> static constexpr auto pack_stream_fn()
 {
-    if (sync.unit_flips)
-        hipLaunchKernelGGL((pack_stream_kernel<N, M, PackStreamShape<N, M>::QD, PackStreamShape<N, M>::WAVES, true>), dim3(grid), dim3(256), 0,
-                           stream, tab, sync);
-    else
-        hipLaunchKernelGGL((pack_stream_kernel<N, M, PackStreamShape<N, M>::QD, PackStreamShape<N, M>::WAVES, false>), dim3(grid), dim3(256), 0,
-                           stream, tab, sync);
+    return pack_stream_kernel<WT, N, M, PackStreamShape<WT, N, M>::QD, PackStreamShape<WT, N, M>::WAVES, FLIPS>;
 }
 
-template <int N, int M>
-static void launch_pack_fast(int grid, hipStream_t stream, const PackTable &tab, const float *theta, uint32_t *unit_flips)
-{
-    if (unit_flips) hipLaunchKernelGGL((pack_fast_kernel<N, M, true>), dim3(grid), dim3(256), 0, stream, tab, theta, unit_flips);
-    else hipLaunchKernelGGL((pack_fast_kernel<N, M, false>), dim3(grid), dim3(256), 0, stream, tab, theta, unit_flips);
-}
+// the fast kernels of one type and pattern
+struct PackFast {
+    int (*max_units)(int &grid);   // most units per matrix the single-read kernel takes, and its grid (0: not at all)
+    void (*stream)(int grid, hipStream_t stream, const PackTable &tab, const PackSync &sync);
+    void (*last_pass)(int grid, hipStream_t stream, const PackTable &tab, const float *theta, uint32_t *unit_flips);
+};
 
-template <int N, int M>
-static int fused_capacity()
-{
-    static thread_local int cap = 0;
-    if (cap == 0) {
-        int per_cu = 0;
-        // (the flip-counting instantiation has the same launch bounds, wavefronts per SIMD and LDS plus 16 bytes)
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, pack_stream_kernel<N, M, PackStreamShape<N, M>::QD, PackStreamShape<N, M>::WAVES, true>, 256, 0) != hipSuccess) per_cu = 0;
-        cap = per_cu > 0 ? per_cu * device_cus() : -1;
+template <typename WT, int N, int M> struct PackFastOf {
+    // flips are counted on bf16 at the patterns that keep two of four or fewer
+    static constexpr bool FLIPS = sizeof(WT) == 2 && !PackCompact<WT, N, M>::WHOLE;
+    static int max_units(int &grid)
+    {
+        static thread_local int cap = 0;
+        if (cap == 0) {
+            int per_cu = 0;
+            // (the flip-counting instantiation has the same launch bounds, wavefronts per SIMD and LDS plus 16 bytes)
+            if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, pack_stream_fn<WT, N, M, FLIPS>(), 256, 0) != hipSuccess) per_cu = 0;
+            cap = per_cu > 0 ? per_cu * device_cus() : -1;
+        }
+        grid = cap;
+        return cap > 0 ? cap * (PackStreamShape<WT, N, M>::QD + 1) : 0;
     }
-    return cap;
+    static void stream(int grid, hipStream_t stream, const PackTable &tab, const PackSync &sync)
+    {
+        if constexpr (FLIPS)
+            if (sync.unit_flips) {
+                hipLaunchKernelGGL((pack_stream_fn<WT, N, M, true>()), dim3(grid), dim3(256), 0, stream, tab, sync);
+                return;
+            }
+        hipLaunchKernelGGL((pack_stream_fn<WT, N, M, false>()), dim3(grid), dim3(256), 0, stream, tab, sync);
+    }
+    static void last_pass(int grid, hipStream_t stream, const PackTable &tab, const float *theta, uint32_t *unit_flips)
+    {
+        if constexpr (FLIPS)
+            if (unit_flips) {
+                hipLaunchKernelGGL((pack_fast_kernel<WT, N, M, true>), dim3(grid), dim3(256), 0, stream, tab, theta, unit_flips);
+                return;
+            }
+        hipLaunchKernelGGL((pack_fast_kernel<WT, N, M, false>), dim3(grid), dim3(256), 0, stream, tab, theta, unit_flips);
+    }
+    static constexpr PackFast table{max_units, stream, last_pass};
+};
+
+// null: no fast kernels for this pattern.  N = M is one form whatever M
+template <typename WT> static const PackFast *pack_fast_of(const Pattern &pat)
+{
+    if (pat.N == pat.M) return &PackFastOf<WT, 8, 8>::table;
+    if (pat.M == 4 && pat.N == 2) return &PackFastOf<WT, 2, 4>::table;
+    if (pat.M == 4 && pat.N == 1) return &PackFastOf<WT, 1, 4>::table;
+    if (pat.M == 8 && pat.N == 2) return &PackFastOf<WT, 2, 8>::table;
+    if (pat.M == 8 && pat.N == 6) return &PackFastOf<WT, 6, 8>::table;
+    return nullptr;
 }
 
 // flips: null, or one counter per matrix: the packed buffers then hold the previous packed forms, which are replaced, and
@@ -1200,15 +1453,15 @@ sbn_status launch_pack(int count, const PackItem *items, sbn_dtype wdt, const Pa
         tab.pack_block0[n] = pb;
         double *part = partials + sum_base;
         float *th = theta + first;
-        const bool fast_pattern = (pat.M == 4 && (pat.N == 1 || pat.N == 2)) || (pat.M == 8 && pat.N == 2);
-        const bool fast = wdt == SBN_BF16 && fast_pattern && flat_ok;
+        const PackFast *fast = !flat_ok ? nullptr : wdt == SBN_BF16 ? pack_fast_of<uint16_t>(pat) : pack_fast_of<float>(pat);
         sbn_status st = SBN_OK;
-        // single-read form: persistent grid of as many blocks as the device holds; no matrix may have more units than that
-        bool fused = fast;
+        // single-read form: persistent grid of as many blocks as the device holds; no matrix may have more units than
+        // these have in flight
+        bool fused = fast != nullptr;
         int cap = 0;
         if (fast) {
-            cap = pat.M == 4 && pat.N == 2 ? fused_capacity<2, 4>() : pat.M == 4 ? fused_capacity<1, 4>() : fused_capacity<2, 8>();
-            for (int i = 0; i < n; ++i) fused = fused && fb[i + 1] - fb[i] <= cap;
+            const int max_units = fast->max_units(cap);
+            for (int i = 0; i < n; ++i) fused = fused && fb[i + 1] - fb[i] <= max_units;
         }
         if (fused) {
             for (int i = 0; i < n; ++i) tab.pack_block0[i] = fb[i];
@@ -1221,9 +1474,7 @@ sbn_status launch_pack(int count, const PackItem *items, sbn_dtype wdt, const Pa
             if (st != SBN_OK) return st;
             PackSync sync{part, th, words, pack_spin_limit(), unit_flips};
             const int grid = fb[n] < cap ? fb[n] : cap;
-            if (pat.M == 4 && pat.N == 2) launch_pack_stream<2, 4>(grid, stream, tab, sync);
-            else if (pat.M == 4) launch_pack_stream<1, 4>(grid, stream, tab, sync);
-            else launch_pack_stream<2, 8>(grid, stream, tab, sync);
+            fast->stream(grid, stream, tab, sync);
             st = check_launch("pack_stream_kernel");
             if (st != SBN_OK) return st;
             if (flips) {
@@ -1246,9 +1497,7 @@ sbn_status launch_pack(int count, const PackItem *items, sbn_dtype wdt, const Pa
         if (fast) {
             for (int i = 0; i < n; ++i) tab.pack_block0[i] = fb[i];
             tab.pack_block0[n] = fb[n];
-            if (pat.M == 4 && pat.N == 2) launch_pack_fast<2, 4>(fb[n], stream, tab, th, unit_flips);
-            else if (pat.M == 4) launch_pack_fast<1, 4>(fb[n], stream, tab, th, unit_flips);
-            else launch_pack_fast<2, 8>(fb[n], stream, tab, th, unit_flips);
+            fast->last_pass(fb[n], stream, tab, th, unit_flips);
             st = check_launch("pack_fast_kernel");
             if (st == SBN_OK && flips) {
                 hipLaunchKernelGGL(pack_flips_sum_kernel, dim3(n), dim3(256), 0, stream, tab, unit_flips, flips + first);

@@ -328,3 +328,37 @@ def test_single_read_pack_when_blocks_do_not_wait(N, M, spin_limit, spin_limits)
         assert gammas[i].item() == g
         assert np.array_equal(packed[i].cpu().numpy(), ref)
         assert flips[i].item() == oracle_flips(W0, Wn, N, M)
+
+
+STREAM_FORMS = [(torch.bfloat16, 6, 8), (torch.bfloat16, 8, 8), (torch.float32, 2, 4), (torch.float32, 1, 4), (torch.float32, 2, 8),
+                (torch.float32, 6, 8), (torch.float32, 4, 4)]
+
+
+@pytest.mark.parametrize("dtype,N,M", STREAM_FORMS)
+@pytest.mark.parametrize("spin_limit", [-1, 3, None])
+def test_single_read_pack_types(dtype, N, M, spin_limit, spin_limits):
+    # the forms that hold fp32 weights, whole weights or six of eight between the sum and the packing: a last unit of
+    # 44 chunks, a single chunk, magnitudes that tie throughout; with the wait cut short and as usual
+    if spin_limit is not None:
+        spin_limits(pack_polls=spin_limit)
+    s = sbn()
+    Ws = [sbn_synth.latent_weight(100, 384, 1900, dtype=dtype), sbn_synth.latent_weight(1, 128, 1901, dtype=dtype),
+          sbn_synth.adversarial_weight(640, 1280, 1902, dtype=dtype), sbn_synth.latent_weight(1024, 2560, 1903, dtype=dtype)]
+    packed = [torch.zeros(s.sbn_packed_bytes(*W.shape, N, M), dtype=torch.uint8, device=DEV) for W in Ws]
+    gammas = torch.zeros(len(Ws), dtype=torch.float32, device=DEV)
+    ws = s.new_workspace(s.sbn_workspace_bytes(s.SBN_OP_QUANTIZE_MASK_PACK, len(Ws), 1024, 2560, N, M))
+    s.sbn_quantize_mask_pack_batched([W.to(DEV) for W in Ws], N, M, packed, [gammas[i:i + 1] for i in range(len(Ws))], ws)
+    torch.cuda.synchronize()
+    for i, W in enumerate(Ws):
+        ref, g, *_ = oracle_pack(W, N, M)
+        assert gammas[i].item() == g
+        assert np.array_equal(packed[i].cpu().numpy(), ref)
+
+
+@pytest.mark.parametrize("dtype,N,M,shape", [(torch.float32, 2, 4, (6912, 2560)),     # 1080 units over 1024 blocks
+                                             (torch.float32, 6, 8, (6912, 2560)),     # 1080 over 768
+                                             (torch.bfloat16, 6, 8, (8200, 2560)),    # 1282 over 1280, the last one partly filled
+                                             (torch.bfloat16, 2, 4, (9856, 2560)),    # 1540 over 1536
+                                             (torch.float32, 4, 4, (10240, 2560))])   # 1600 > 2 x 768: three passes
+def test_single_read_pack_matrix_of_more_units_than_blocks(dtype, N, M, shape):
+    check(sbn_synth.latent_weight(*shape, 1950, dtype=dtype), N, M)
