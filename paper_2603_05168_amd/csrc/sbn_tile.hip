@@ -252,8 +252,9 @@ sbn_status launch_tile_as(int count, const LinearItem *items, int max_nw, hipStr
     for (int i = count; i <= NI; ++i) tab.block0[i] = blocks;
     for (int i = count; i < NI; ++i) tab.it[i] = tab.it[0];
     tab.count = count;
-    // as few wavefronts as walk the stages in the same number of rounds
-    const int rounds = (int)ceil_div(most, max_nw), nw = (int)ceil_div(most, rounds);
+    // as few wavefronts as walk the stages in the same number of rounds, but a thread for every scale and bias of the tile (a
+    // wavefront without a stage adds zeros)
+    const int rounds = (int)ceil_div(most, max_nw), nw = std::max((int)ceil_div(most, rounds), (S::T + S::R + 63) / 64);
     const size_t lds = (size_t)nw * S::STAGE;
     static thread_local bool raised = false;
     if (!raised) {

@@ -768,7 +768,9 @@ def test_streaming_decode_alternating_weight_forms_on_one_workspace():
                                           (33, (100, 2304)),     # 32 x 32 tiles, nine stages on eight wavefronts
                                           (65, (514, 640)),      # rows not a multiple of four: stores per element
                                           (159, (2564, 896)),    # 64 x 32 tiles, 205 of them, last ones ragged both ways
-                                          (777, (1000, 1408))])  # many tiles per multiprocessor, an odd number of chunks
+                                          (777, (1000, 1408)),   # many tiles per multiprocessor, an odd number of chunks
+                                          (300, (1348, 128)),    # 64 x 32 tiles of a single stage: fewer wavefronts than rows and tokens need
+                                          (256, (2048, 256))])
 @pytest.mark.parametrize("bias", [False, True])
 def test_small_block_tiles(N, M, tokens, shape, bias):
     s = sbn()
