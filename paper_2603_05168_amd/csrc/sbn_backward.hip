@@ -587,9 +587,9 @@ sbn_status launch_backward_grouped(int count, const BackwardItem *items, const P
         }
         if (it.dW) {
             const int64_t ldt = pad64(tokens);
-            const uint16_t *xts = nullptr;   // an earlier layer of the call already transposed the same activations
+            const uint16_t *xts = nullptr;   // an earlier layer of the call already transposed the same activations with the same scales
             for (int j = 0; j < i && !xts; ++j)
-                if (xt_of[j] && items[j].xq == it.xq && items[j].tokens == tokens && items[j].d_in == d_in) xts = xt_of[j];
+                if (xt_of[j] && items[j].xq == it.xq && items[j].sx == it.sx && items[j].tokens == tokens && items[j].d_in == d_in) xts = xt_of[j];
             if (!xts) {
                 dim3 grid((unsigned)ceil_div(d_in, 64), (unsigned)(ldt / 64));
                 hipLaunchKernelGGL(transpose_i8_kernel, grid, dim3(256), 0, stream, it.xq, it.sx, tokens, d_in, xt, ldt);

@@ -298,3 +298,20 @@ def test_backward_tile_edges(N, M, tokens, d_out, d_in, accumulate):
         # one rounding of an operand and one of the result to bf16, 2^-9 each, relative to the larger of value and rms
         err = (got.double() - ref).abs() / torch.maximum(ref.abs(), ref.square().mean().sqrt())
         assert err.max().item() <= 2e-2 and err.square().mean().sqrt().item() <= 2.0 ** -8, what
+
+
+def test_backward_grouped_shared_rows_with_scales_of_their_own():
+    # two layers on the same int8 rows with different per-token scales: the operand that carries the scale is not shared
+    s = sbn()
+    tokens, d_in, d_out, N, M = 77, 136, 104, 2, 4
+    W = [sbn_synth.latent_weight(d_out, d_in, 1020 + i) for i in range(2)]
+    dY = [sbn_synth.grad_output(tokens, d_out, 1030 + i).to(DEV) for i in range(2)]
+    packed, gamma, xq, sx = _forward_state(W[0], sbn_synth.activations(tokens, d_in, 1040), N, M)
+    scales = [sx, (sx * 3).contiguous()]
+    dW = [torch.full((d_out, d_in), float("nan"), dtype=torch.bfloat16, device=DEV) for _ in range(2)]
+    ws = s.new_workspace(2 * s.sbn_workspace_bytes(s.SBN_OP_BACKWARD, tokens, d_out, d_in, N, M))
+    s.sbn_sparse_ternary_linear_backward_grouped(dY, [packed] * 2, [gamma] * 2, [xq] * 2, scales, N, M, ws, [d_in] * 2, [None] * 2, dW)
+    torch.cuda.synchronize()
+    for i in range(2):
+        ref = oracle.backward_dw(dY[i].float().cpu().numpy(), xq.cpu().numpy(), scales[i].cpu().numpy())
+        assert_rel_rms(dW[i].float().cpu().numpy(), ref, BWD_TOL, f"dW {i}")
