@@ -160,7 +160,7 @@ __global__ void __launch_bounds__(256) transpose_i8_kernel(const int8_t *__restr
 // ---- bf16 GEMM -------------------------------------------------------------------------------------------
 // C[m, n] (+)= alpha * sum_k Q[m, k] * P[n, k], C bf16 [M, ldc].  P is [N, ldp] with k contiguous and K a multiple of 64
 // (the layout kernels pad it with zeros).  Q has k contiguous as well ([M, ldq], dX), or lies the other way round
-// ([k, ldq] with m contiguous, QT: dW reads dY as it is); it may end before K, where zeros of P meet what is read instead.
+// ([k, ldq] with m contiguous, QT: dW reads dY as it is); it may end before K: the rest of its last stage is zeroed in LDS.
 // P supplies the rows of the MFMA result so that a lane ends up with four consecutive n of one C row (one 8-byte store).
 struct GemmBf16Args {
     const uint16_t *P;
@@ -309,7 +309,7 @@ __device__ __forceinline__ void bf16_tile_body(const GemmBf16Args &g, uint8_t *d
     // row l / 8, slot l % 8 holding global column slot ^ ((row >> 1) & 7)).  Transposed Q: a stage is 64 k rows of M values,
     // one instruction fills 1024 bytes of them, slot s of row k holds the eight values of granule s ^ f(k),
     // f = 4 (k & 3) | 2 ((k >> 2) & 1): the four k rows that a transposing read of 16 lanes takes lie in different banks.
-    // Past the matrix the last row or granule again (never stored, or met by zeros of P).
+    // Past the matrix the last row or granule again (never stored, or zeroed in LDS below).
     constexpr int QROW = S::M * 2;                        // bytes of a k row of the transposed stage
     const char *pbase = reinterpret_cast<const char *>(g.P + (int64_t)n0 * g.ldp);
     const char *qbase = reinterpret_cast<const char *>(QT ? g.Q + m0 : g.Q + (int64_t)m0 * g.ldq);
@@ -342,6 +342,17 @@ __device__ __forceinline__ void bf16_tile_body(const GemmBf16Args &g, uint8_t *d
         const uint32_t dst = lds0 + stage + wave * 4096;
         if (i < 4) lds_dma16(pbase + (int64_t)kt * (GD_K * 2), poff[i], dst + i * 1024);
         else lds_dma16(qbase + (int64_t)kt * qstep, kt == nk - 1 ? qlast[i - 4] : qoff[i - 4], dst + S::PBYTES + (i - 4) * 1024);
+    };
+    // k of the last stage past the end of Q: what was fetched in their place may be infinite, and zeros of P do not cancel that.
+    // A lane overwrites what it asked for itself, behind its own wait and in front of the barrier that publishes the stage.
+    auto zero_tail = [&](const uint32_t stage) {
+        typedef __attribute__((address_space(3))) v4i *lds_v4i;
+        asm volatile("" ::: "memory");   // not in front of the wait
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int k = QT ? (512 / S::M) * (4 * wave + i) + lane / (S::M / 8) : 8 * ((lane & 7) ^ (((32 * wave + 8 * i + (lane >> 3)) >> 1) & 7));
+            if (k >= kleft) *(lds_v4i)(uintptr_t)(lds0 + stage + wave * 4096 + S::PBYTES + i * 1024 + 16 * lane) = v4i{0, 0, 0, 0};
+        }
     };
     // LDS read addresses: k contiguous: row * 128 + 16 * ((2u + c) ^ ((row >> 1) & 7)); (row >> 1) & 7 = (r >> 1) & 7 for every
     // tile of the wavefront, so one lane address per u, tiles are immediate offsets; the stage is one bit of the address.  Transposed: lane l of a
@@ -429,6 +440,7 @@ __device__ __forceinline__ void bf16_tile_body(const GemmBf16Args &g, uint8_t *d
 #pragma unroll
     for (int i = 0; i < 8; ++i) dma_one(1, S::STAGE, i);
     SBN_WAIT_VMCNT(8);
+    if (nk == 1 && kleft < GD_K) zero_tail(0);
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < READS; ++i) read_one(0, i);
@@ -438,6 +450,7 @@ __device__ __forceinline__ void bf16_tile_body(const GemmBf16Args &g, uint8_t *d
         for (int u = 0; u < 3; ++u)
             quarter(u, [&](const int s) { spread(s, READS, [&](const int k) { read_one(u + 1, k); }); });
         SBN_WAIT_VMCNT(0);
+        if (kt == nk - 2 && kleft < GD_K) zero_tail(stage ^ S::STAGE);
         __syncthreads();
         flip();
         quarter(3, [&](const int s) {

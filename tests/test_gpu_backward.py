@@ -315,3 +315,25 @@ def test_backward_grouped_shared_rows_with_scales_of_their_own():
     for i in range(2):
         ref = oracle.backward_dw(dY[i].float().cpu().numpy(), xq.cpu().numpy(), scales[i].cpu().numpy())
         assert_rel_rms(dW[i].float().cpu().numpy(), ref, BWD_TOL, f"dW {i}")
+
+
+@pytest.mark.parametrize("tokens,shape", [(13, (40, 136)), (77, (104, 136)), (130, (520, 392)), (16390, (2568, 2560))])
+def test_backward_infinite_gradient_in_the_last_row_and_column(tokens, shape):
+    # sizes that end inside a stage of 64: nothing but the products of the infinite value may become infinite or NaN
+    s = sbn()
+    d_out, d_in = shape
+    packed, gamma, xq, sx = _forward_state(sbn_synth.latent_weight(d_out, d_in, 1050), sbn_synth.activations(tokens, d_in, 1051), 2, 4)
+    dY = sbn_synth.grad_output(tokens, d_out, 1052).to(DEV)
+    dY[-1, -1] = float("inf")
+    dX = torch.zeros(tokens, d_in, dtype=torch.bfloat16, device=DEV)
+    dW = torch.zeros(d_out, d_in, dtype=torch.bfloat16, device=DEV)
+    ws = s.new_workspace(s.sbn_workspace_bytes(s.SBN_OP_BACKWARD, tokens, d_out, d_in, 2, 4))
+    s.sbn_sparse_ternary_linear_backward(dY, packed, gamma, xq, sx, 2, 4, ws, d_in, dX=dX, dW=dW)
+    torch.cuda.synchronize()
+    assert torch.isfinite(dX[:-1]).all() and torch.isfinite(dW[:-1]).all()
+    x = xq[-1].float() * float("inf")
+    assert torch.equal(dW[-1].isnan(), x.isnan()) and torch.equal(dW[-1].float()[~x.isnan()], x[~x.isnan()])
+    Wt = oracle_pack(sbn_synth.latent_weight(d_out, d_in, 1050), 2, 4)[2]
+    w = torch.from_numpy(np.asarray(Wt[-1], dtype=np.float32)) * float("inf")
+    got = dX[-1].float().cpu()
+    assert torch.equal(got.isnan(), w.isnan()) and torch.equal(got[~w.isnan()], w[~w.isnan()])
