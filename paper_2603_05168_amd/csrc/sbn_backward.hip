@@ -4,8 +4,9 @@
 //   dW[o,k] = sum_t (dY[t,o] / s_x[t]) * xq[t,k]          contraction over tokens; dense, unmasked
 // Both run on the dense bf16 matrix cores (v_mfma_f32_32x32x16_bf16, fp32 accumulation): the 2:4
 // structure lies along d_in, which is not the contracted dimension of either product, so the sparse
-// instruction does not apply.  One GEMM kernel serves both: dY is read as it lies (dW contracts its slow dimension: the
-// transposing LDS read), small layout kernels put W_eff^T (exact in bf16) and (x~ / s_x)^T contraction-major first.
+// instruction does not apply.  One GEMM kernel serves both: dY, and dY / s_x in the same layout, are read as they lie (dW
+// contracts their slow dimension: the transposing LDS read), small kernels write dY / s_x and put W_eff^T and x~^T (both
+// exact in bf16) contraction-major first.
 #include <algorithm>
 #include <vector>
 
@@ -124,15 +125,9 @@ __device__ __forceinline__ void write_tile_transposed(const uint16_t *tile, uint
     }
 }
 
-// The int8 rows divided by their scales are rounded to bf16 once.  127 / s_x, the largest value of a row, lies near 4 for normal values, so the step
-// between its values is close to a power of two and their roundings fall in step: 1.72e-3 rms against 1.66e-3 for values that
-// lie anywhere.  With the operand 1 / 0.625 times as large (undone in the epilogue, in fp32) it is 1.63 to 1.65e-3.
-constexpr float X_SCALE = 0.625f;
-
-// int8 [rows, cols] -> bf16 transposed: dst [cols, ld] with dst[c, r] = src[r, c] (/ (X_SCALE scale[r]), unless null), zeros
-// for r in [rows, ld)
-__global__ void __launch_bounds__(256) transpose_i8_kernel(const int8_t *__restrict__ src, const float *__restrict__ scale, int64_t rows,
-                                                          int64_t cols, uint16_t *__restrict__ dst, int64_t ld)
+// int8 [rows, cols] -> bf16 transposed: dst [cols, ld] with dst[c, r] = src[r, c], zeros for r in [rows, ld)
+__global__ void __launch_bounds__(256) transpose_i8_kernel(const int8_t *__restrict__ src, int64_t rows, int64_t cols,
+                                                          uint16_t *__restrict__ dst, int64_t ld)
 {
     __shared__ __attribute__((aligned(16))) uint16_t tile[64 * TQ];
     const int64_t r0 = (int64_t)blockIdx.y * 64, c0 = (int64_t)blockIdx.x * 64;
@@ -144,35 +139,55 @@ __global__ void __launch_bounds__(256) transpose_i8_kernel(const int8_t *__restr
     } else {
         for (int e = 0; e < 16; ++e) q[e] = (row_ok && c0 + cv + e < cols) ? src[(r0 + r) * cols + c0 + cv + e] : (int8_t)0;
     }
-    if (scale) {
-        // the fake-quantized activation x~ / s_x over X_SCALE, rounded to bf16 once (the one rounding of an operand of dW)
-        const float s = row_ok ? scale[r0 + r] * X_SCALE : 1.0f;
 #pragma unroll
-        for (int e = 0; e < 16; e += 2)
-            *reinterpret_cast<uint32_t *>(&tile[r * TQ + cv + e]) =
-                f32_to_bf16(__fdiv_rn((float)q[e], s)) | (f32_to_bf16(__fdiv_rn((float)q[e + 1], s)) << 16);
-    } else {
-#pragma unroll
-        for (int e = 0; e < 16; e += 2) {
-            const uint32_t lo = __float_as_uint((float)q[e]) >> 16, hi = __float_as_uint((float)q[e + 1]) & 0xffff0000u;
-            *reinterpret_cast<uint32_t *>(&tile[r * TQ + cv + e]) = lo | hi;   // |q| <= 128: exact in bf16
-        }
+    for (int e = 0; e < 16; e += 2) {
+        const uint32_t lo = __float_as_uint((float)q[e]) >> 16, hi = __float_as_uint((float)q[e + 1]) & 0xffff0000u;
+        *reinterpret_cast<uint32_t *>(&tile[r * TQ + cv + e]) = lo | hi;   // |q| <= 128: exact in bf16
     }
     __syncthreads();
     write_tile_transposed(tile, dst, ld, c0, r0, cols, ld);
 }
 
+// dY [tokens, 8 nvec] bf16 -> dY[t, :] / s_x[t], rounded to bf16 (the one rounding of an operand of dW), same layout.  It is the
+// gradient that is rounded and not x~ / s_x, of which a row has 255 values at most: the error of a gradient is another one in
+// every token, that of a level would be the same wherever tokens share s_x (saturated or clipped activations) and add up over
+// them, and it would depend on where the levels lie between two powers of two, i.e. on the amplitude of the activations.
+// Block: up to 256 vectors of 8 values of four rows.  Bound by the bytes it moves.
+__global__ void __launch_bounds__(256) scale_rows_kernel(const uint4 *__restrict__ dY, const float *__restrict__ sx, int64_t tokens, int nvec,
+                                                        uint4 *__restrict__ dst)
+{
+    const int64_t t0 = 4 * (int64_t)blockIdx.x;
+    const int i = (int)(blockIdx.y * 256 + threadIdx.x);
+    if (i >= nvec) return;
+    uint4 v[4];
+    float s[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int64_t t = t0 + r < tokens ? t0 + r : tokens - 1;   // past the end the last row again (not stored)
+        v[r] = dY[t * nvec + i];
+        s[r] = sx[t];
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const uint32_t w[4] = {v[r].x, v[r].y, v[r].z, v[r].w};
+        uint32_t o[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            o[k] = f32_to_bf16(__fdiv_rn(__uint_as_float(w[k] << 16), s[r])) | (f32_to_bf16(__fdiv_rn(__uint_as_float(w[k] & 0xffff0000u), s[r])) << 16);
+        if (t0 + r < tokens) dst[(t0 + r) * nvec + i] = make_uint4(o[0], o[1], o[2], o[3]);
+    }
+}
+
 // ---- bf16 GEMM -------------------------------------------------------------------------------------------
 // C[m, n] (+)= alpha * sum_k Q[m, k] * P[n, k], C bf16 [M, ldc].  P is [N, ldp] with k contiguous and K a multiple of 64
 // (the layout kernels pad it with zeros).  Q has k contiguous as well ([M, ldq], dX), or lies the other way round
-// ([k, ldq] with m contiguous, QT: dW reads dY as it is); it may end before K: the rest of its last stage is zeroed in LDS.
+// ([k, ldq] with m contiguous, QT: dW reads dY / s_x as it lies); it may end before K: the rest of its last stage is zeroed in LDS.
 // P supplies the rows of the MFMA result so that a lane ends up with four consecutive n of one C row (one 8-byte store).
 struct GemmBf16Args {
     const uint16_t *P;
     const uint16_t *Q;
     uint16_t *C;
-    const float *alpha;   // device scalar or null (= factor)
-    float factor;
+    const float *alpha;   // device scalar or null (= 1)
     int64_t ldp, ldq, ldc;
     int N, M, K;
     int kq;               // k that Q has (<= K)
@@ -220,7 +235,7 @@ __device__ __forceinline__ void bf16_wave_epilogue(const GemmBf16Args &g, const 
 {
     constexpr int ROW = WP * 128, LPR = ROW / 32;     // bytes of a staged row, lanes per row
     const int r = lane & 31, c = lane >> 5;
-    const float alpha = g.alpha ? *g.alpha : g.factor;
+    const float alpha = g.alpha ? *g.alpha : 1.0f;
 #pragma unroll
     for (int b = 0; b < WQ; ++b) {
 #pragma unroll
@@ -288,8 +303,9 @@ __device__ __forceinline__ int bf16_product_of_block(const GemmBf16Group &grp)
 // 1.45 us per stage of the large tile (1.48 PFLOP/s) where one barrier, eight requests and a first read in front of every
 // stage's matrix instructions took 1.9 us.  What bounds it now: the matrix pipe at the clock the board holds (1.9 PFLOP/s on
 // operands from registers), and 10 us per tile for its first stages and its result, which nothing covers.
-// us per call, before and now: 2560 x 2560 at 16384 tokens, three layers 1283 -> 1090, one 495 -> 390; 6912 x 2560, two layers
-// 2251 -> 1900; 6912 x 2560 at 1024 tokens 168 -> 99 (a fifth of each gain: dY is no longer scaled and transposed in memory).
+// us per call, before and now: 2560 x 2560 at 16384 tokens, three layers 1305 -> 1200, one 523 -> 463; 6912 x 2560, two layers
+// 2274 -> 2090; 6912 x 2560 at 1024 tokens 170 -> 107.  dY / s_x in memory (scale_rows_kernel, 5.7 TB/s) is 90 of the 1200 and 8
+// of the 107 us.
 constexpr int GD_K = 64;     // k per stage
 template <bool BIG> struct Bf16Tile {
     static constexpr int N = BIG ? 256 : 128, M = BIG ? 256 : 128;
@@ -547,10 +563,11 @@ inline int64_t pad64(int64_t x) { return (x + 63) / 64 * 64; }
 
 size_t backward_workspace_bytes(int64_t tokens, int64_t d_out, int64_t d_in)
 {
-    // W_eff^T bf16 [d_in, pad64(d_out)] + int8 W_eff (generic patterns) + (x~ / s_x)^T bf16 [d_in, pad64(tokens)]
-    // + the mask bit plane of the gradient-masked variant
+    // W_eff^T bf16 [d_in, pad64(d_out)] + int8 W_eff (generic patterns) + x~^T bf16 [d_in, pad64(tokens)]
+    // + dY / s_x bf16 [tokens, d_out] + the mask bit plane of the gradient-masked variant
     return align_up((size_t)d_in * pad64(d_out) * 2, 256) + align_up((size_t)d_out * d_in, 256) +
-           align_up((size_t)d_in * pad64(tokens) * 2, 256) + align_up((size_t)d_out * ((d_in + 31) / 32) * 4, 256);
+           align_up((size_t)d_in * pad64(tokens) * 2, 256) + align_up((size_t)tokens * d_out * 2, 256) +
+           align_up((size_t)d_out * ((d_in + 31) / 32) * 4, 256);
 }
 
 // Backward products of `count` layers in one pass: the layout kernels of every layer, then ONE matrix-multiply
@@ -573,6 +590,8 @@ sbn_status launch_backward_grouped(int count, const BackwardItem *items, const P
         ws += align_up((size_t)d_out * d_in, 256);
         uint16_t *xt = reinterpret_cast<uint16_t *>(ws);
         ws += align_up((size_t)d_in * pad64(tokens) * 2, 256);
+        uint16_t *dys = reinterpret_cast<uint16_t *>(ws);
+        ws += align_up((size_t)tokens * d_out * 2, 256);
         uint32_t *mask_bits = reinterpret_cast<uint32_t *>(ws);
         const uint16_t *dy = static_cast<const uint16_t *>(it.dY);
 
@@ -591,8 +610,8 @@ sbn_status launch_backward_grouped(int count, const BackwardItem *items, const P
             else {
                 st = launch_expand_groups(it.packed, d_out, d_in, pat, w8, stream);
                 if (st != SBN_OK) return st;
-                hipLaunchKernelGGL(transpose_i8_kernel, dim3((unsigned)ceil_div(d_in, 64), (unsigned)(ldw / 64)), dim3(256), 0, stream, w8, nullptr,
-                                   d_out, d_in, wt, ldw);
+                hipLaunchKernelGGL(transpose_i8_kernel, dim3((unsigned)ceil_div(d_in, 64), (unsigned)(ldw / 64)), dim3(256), 0, stream, w8, d_out, d_in,
+                                   wt, ldw);
                 st = check_launch("transpose_i8_kernel");
             }
             if (st != SBN_OK) return st;
@@ -606,23 +625,27 @@ sbn_status launch_backward_grouped(int count, const BackwardItem *items, const P
         }
         if (it.dW) {
             const int64_t ldt = pad64(tokens);
-            const uint16_t *xts = nullptr;   // an earlier layer of the call already transposed the same activations with the same scales
+            const uint16_t *xts = nullptr;   // an earlier layer of the call already transposed the same activations
             for (int j = 0; j < i && !xts; ++j)
-                if (xt_of[j] && items[j].xq == it.xq && items[j].sx == it.sx && items[j].tokens == tokens && items[j].d_in == d_in) xts = xt_of[j];
+                if (xt_of[j] && items[j].xq == it.xq && items[j].tokens == tokens && items[j].d_in == d_in) xts = xt_of[j];
             if (!xts) {
                 dim3 grid((unsigned)ceil_div(d_in, 64), (unsigned)(ldt / 64));
-                hipLaunchKernelGGL(transpose_i8_kernel, grid, dim3(256), 0, stream, it.xq, it.sx, tokens, d_in, xt, ldt);
+                hipLaunchKernelGGL(transpose_i8_kernel, grid, dim3(256), 0, stream, it.xq, tokens, d_in, xt, ldt);
                 st = check_launch("transpose_i8_kernel");
                 if (st != SBN_OK) return st;
                 xts = xt;
             }
             xt_of[i] = xts;
-            // dW[o, k] = sum_t dY[t, o] * (x~ / s_x)[t, k]; x~^T is zero for t in [tokens, ldt)
+            hipLaunchKernelGGL(scale_rows_kernel, dim3((unsigned)ceil_div(tokens, 4), (unsigned)ceil_div(d_out / 8, 256)), dim3(256), 0, stream,
+                               reinterpret_cast<const uint4 *>(dy), it.sx, tokens, (int)(d_out / 8), reinterpret_cast<uint4 *>(dys));
+            st = check_launch("scale_rows_kernel");
+            if (st != SBN_OK) return st;
+            // dW[o, k] = sum_t (dY / s_x)[t, o] * x~[t, k]; x~^T is zero for t in [tokens, ldt)
             GemmBf16Args a{};
             a.P = xts; a.ldp = ldt; a.N = (int)d_in;
-            a.Q = dy; a.ldq = d_out; a.M = (int)d_out; a.kq = (int)tokens; a.transposed = 1;
+            a.Q = dys; a.ldq = d_out; a.M = (int)d_out; a.kq = (int)tokens; a.transposed = 1;
             a.K = (int)ldt;
-            a.C = static_cast<uint16_t *>(it.dW); a.ldc = d_in; a.accumulate = accumulate; a.factor = X_SCALE;
+            a.C = static_cast<uint16_t *>(it.dW); a.ldc = d_in; a.accumulate = accumulate;
             if (flags & SBN_BWD_MASK_DW) {
                 // ablation variant: only the weights of the current mask receive the new gradient term
                 st = launch_mask_bitplane(it.packed, d_out, d_in, pat, mask_bits, stream);

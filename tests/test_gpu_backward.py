@@ -337,3 +337,32 @@ def test_backward_infinite_gradient_in_the_last_row_and_column(tokens, shape):
     w = torch.from_numpy(np.asarray(Wt[-1], dtype=np.float32)) * float("inf")
     got = dX[-1].float().cpu()
     assert torch.equal(got.isnan(), w.isnan()) and torch.equal(got[~w.isnan()], w[~w.isnan()])
+
+
+@pytest.mark.parametrize("rows", ["sigma 0.6", "sigma 1", "sigma 1.6", "clipped", "clipped, mean"])
+def test_backward_dw_rounds_the_scaled_gradient_alone(rows):
+    # dW[o, k] = sum_t bf16(dY[t, o] / s_x[t]) x~[t, k]: the gradient over its scale is rounded, x~ enters as the whole number it is.
+    # So the rounding of an operand is another one in every token and does not depend on the amplitude of the activations, nor
+    # does it add up where tokens share s_x (clipped rows) and the gradients have a mean
+    s = sbn()
+    tokens, d_in, d_out = 1000, 520, 264
+    X = sbn_synth.activations(tokens, d_in, 1060).float()
+    dY = sbn_synth.grad_output(tokens, d_out, 1061).float()
+    if rows.startswith("sigma"):
+        X *= float(rows.split()[1])
+    elif rows == "clipped":
+        X = (2 * X).clamp(-1.5, 1.5)
+    else:
+        X, dY = (2 * X).clamp(0.0, 1.5), dY + 0.01
+    X, dY = X.to(torch.bfloat16).to(DEV), dY.to(torch.bfloat16).to(DEV)
+    xq, sx = torch.empty(tokens, d_in, dtype=torch.int8, device=DEV), torch.empty(tokens, device=DEV)
+    s.sbn_act_quant(X, xq, sx)
+    dW = torch.full((d_out, d_in), float("nan"), dtype=torch.bfloat16, device=DEV)
+    ws = s.new_workspace(s.sbn_workspace_bytes(s.SBN_OP_BACKWARD, tokens, d_out, d_in, 2, 4))
+    s.sbn_sparse_ternary_linear_backward(dY, None, None, xq, sx, 2, 4, ws, d_in, dW=dW)
+    g, x = (dY.cpu().float() / sx.cpu()[:, None]).to(torch.bfloat16).double(), xq.cpu().double()
+    ref, terms = g.t() @ x, g.abs().t() @ x.abs()
+    # the sum in fp32 (2^-24 of the terms per addition), then one rounding to bf16 (eight significant bits: 2^-8 of the value)
+    bound = 2.0 ** -8 * ref.abs() + tokens * 2.0 ** -24 * terms
+    err = (dW.cpu().double() - ref).abs()
+    assert (err <= bound).all(), f"{(err > bound).sum()} of {err.numel()} beyond the rounding of the result, worst {(err / bound).max():.2f}"
