@@ -72,6 +72,8 @@ def _load():
     lib.sbn_rmsnorm_act_quant.argtypes = [vp, i64, i64, vp, ctypes.c_float, vp, vp, vp, vp]
     lib.sbn_test_set_spin_limits.restype = None
     lib.sbn_test_set_spin_limits.argtypes = [cint, cint]
+    lib.sbn_test_linear_kernel.restype = cint
+    lib.sbn_test_linear_kernel.argtypes = [cint, cint, pp, pp, pi64, pi64, pi64, cint, cint, pp, pp, pp, pp, pp, vp]
     lib.sbn_mask_flips.restype = cint
     lib.sbn_mask_flips.argtypes = [vp, vp, i64, i64, cint, cint, vp, vp, sz, vp]
     return lib
@@ -337,6 +339,18 @@ SBN_SPIN_DEFAULT = -2 ** 31
 def sbn_test_set_spin_limits(gemv_polls: int = SBN_SPIN_DEFAULT, pack_polls: int = SBN_SPIN_DEFAULT):
     """Test hook: polls of the two bounded inter-block waits (negative: never wait; SBN_SPIN_DEFAULT restores)."""
     _lib.sbn_test_set_spin_limits(gemv_polls, pack_polls)
+
+
+SBN_KERNEL_TILES, SBN_KERNEL_STREAM, SBN_KERNEL_PIECES = 0, 1, 2
+
+
+def sbn_test_linear_kernel(kernel: int, xq_list, sx_list, packed_list, gamma_list, Y_list, N: int, M: int, bias_list=None, acc_list=None):
+    """Test hook: the products of quantized rows through one kernel of SBN_PATH_SMFMAC by name (SBN_KERNEL_...)."""
+    _check(_lib.sbn_test_linear_kernel(kernel, len(xq_list), _ptr_array(xq_list), _ptr_array(sx_list), _i64_array([x.shape[0] for x in xq_list]),
+                                       _i64_array([x.shape[1] for x in xq_list]), _i64_array([y.shape[1] for y in Y_list]), N, M,
+                                       _ptr_array(packed_list), _ptr_array(gamma_list), None if bias_list is None else _ptr_array(bias_list),
+                                       _ptr_array(Y_list), None if acc_list is None else _ptr_array(acc_list), _stream()),
+           "sbn_test_linear_kernel")
 
 
 def sbn_mask_flips(packed_a, packed_b, d_out: int, d_in: int, N: int, M: int, flips_out, workspace):

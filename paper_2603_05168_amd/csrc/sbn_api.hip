@@ -66,6 +66,33 @@ void sbn_test_set_spin_limits(int gemv_polls, int pack_polls)
     g_pack_spin.store(pack_polls == INT_MIN ? PACK_SPIN_DEFAULT : pack_polls, std::memory_order_relaxed);
 }
 
+sbn_status sbn_test_linear_kernel(int kernel, int count, const int8_t *const *xq, const float *const *sx, const int64_t *tokens,
+                                  const int64_t *d_in, const int64_t *d_out, int N, int M, const void *const *packed,
+                                  const float *const *gamma, const float *const *bias, float *const *Y, int32_t *const *acc_out,
+                                  void *stream)
+{
+    if (kernel < SBN_KERNEL_TILES || kernel > SBN_KERNEL_PIECES || count <= 0 || count > 4096) return SBN_EINVAL;
+    if (!xq || !sx || !tokens || !d_in || !d_out || !packed || !gamma || !Y) return SBN_EINVAL;
+    Pattern pat;
+    std::vector<LinearItem> items(count);
+    for (int i = 0; i < count; ++i) {
+        if (!xq[i] || !sx[i] || !packed[i] || !gamma[i] || !Y[i] || tokens[i] <= 0) return SBN_EINVAL;
+        sbn_status st = check_shape(d_out[i], d_in[i], N, M, pat);
+        if (st != SBN_OK) return st;
+        if (!aligned(xq[i], 16) || !aligned(packed[i], 16) || !aligned(Y[i], 16) || (acc_out && acc_out[i] && !aligned(acc_out[i], 16)))
+            return SBN_EALIGN;
+        items[i] = LinearItem{nullptr, packed[i], gamma[i], bias ? bias[i] : nullptr, Y[i], const_cast<int8_t *>(xq[i]), const_cast<float *>(sx[i]),
+                              acc_out ? acc_out[i] : nullptr, tokens[i], d_in[i], d_out[i]};
+        if (d_in[i] % CHUNK != 0 || tokens[i] * d_out[i] >= (int64_t)1 << 40 || (kernel == SBN_KERNEL_STREAM && !gemv_batch_takes(items[i])))
+            return SBN_EUNSUPPORTED;
+    }
+    if (!(N == 2 && M == 4) && N != M) return SBN_EUNSUPPORTED;
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    return kernel == SBN_KERNEL_TILES    ? launch_gemm_tile(count, items.data(), N == M, s)
+           : kernel == SBN_KERNEL_STREAM ? launch_gemv_batch(count, items.data(), N == M, s)
+                                         : launch_gemm_pieces(count, items.data(), N == M, s);
+}
+
 sbn_status sbn_packed_bytes(int64_t d_out, int64_t d_in, int N, int M, size_t *bytes)
 {
     Pattern pat;

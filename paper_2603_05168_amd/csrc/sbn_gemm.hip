@@ -1059,7 +1059,51 @@ static int make_piece_table(const GemmGroup &grp, PieceTable &tab)
     return nb;
 }
 
-// Estimated time in us of a launch of the kernels below, next to which gemm_tile_estimate_us stands.  Measured:
+sbn_status launch_gemm_pieces(int count, const LinearItem *items, bool dense_codes, hipStream_t stream)
+{
+    // problems of at most 16 token units (512 tokens: decode batches) are dealt by row tile, up to GEMM_GROUP_WIDE per launch
+    auto few_tokens = [&](int i) { return items[i].tokens <= 16 * 32; };
+    for (int first = 0; first < count;) {
+        const bool few = few_tokens(first);
+        const int most = few ? GEMM_GROUP_WIDE : GEMM_GROUP_MAX;
+        int n = 1;
+        while (first + n < count && n < most && few_tokens(first + n) == few) ++n;
+        if (few) {
+            GemmGroupWide grp;
+            grp.count = n;
+            for (int i = 0; i < n; ++i) grp.g[i] = make_args(items[first + i]);
+            // pieces of four token units feed the matrix pipe best; a launch with fewer pieces than multiprocessors (one
+            // layer of a decode step) is cut finer, down to single units, so that its latency is that of a small piece
+            int wmax = 4, pieces = 0;
+            for (;; wmax >>= 1) {
+                pieces = 0;
+                for (int i = 0; i < n; ++i)
+                    pieces += (int)ceil_div(items[first + i].d_out, sp::ROWS) * (int)ceil_div(ceil_div(items[first + i].tokens, 32), wmax);
+                if (wmax == 1 || pieces >= device_cus()) break;
+            }
+            PieceTableNone tab;
+            tab.per_block = -pieces;
+            tab.piece[0] = (uint32_t)wmax;
+            const int blocks = pieces < device_cus() ? pieces : device_cus();
+            if (dense_codes) hipLaunchKernelGGL((gemm_smfmac_kernel<true, GemmGroupWide, PieceTableNone>), dim3(blocks), dim3(64 * sp::NW), 0, stream, grp, tab);
+            else hipLaunchKernelGGL((gemm_smfmac_kernel<false, GemmGroupWide, PieceTableNone>), dim3(blocks), dim3(64 * sp::NW), 0, stream, grp, tab);
+        } else {
+            GemmGroup grp;
+            grp.count = n;
+            for (int i = 0; i < n; ++i) grp.g[i] = make_args(items[first + i]);
+            static thread_local PieceTable tab;
+            const int per_xcd = make_piece_table(grp, tab);
+            if (dense_codes) hipLaunchKernelGGL((gemm_smfmac_kernel<true, GemmGroup, PieceTable>), dim3(8 * per_xcd), dim3(64 * sp::NW), 0, stream, grp, tab);
+            else hipLaunchKernelGGL((gemm_smfmac_kernel<false, GemmGroup, PieceTable>), dim3(8 * per_xcd), dim3(64 * sp::NW), 0, stream, grp, tab);
+        }
+        sbn_status st = check_launch("gemm_smfmac_kernel");
+        if (st != SBN_OK) return st;
+        first += n;
+    }
+    return SBN_OK;
+}
+
+// Estimated time in us of a launch of the streaming kernel or of the pieces, next to which gemm_tile_estimate_us stands.  Measured:
 //   streaming kernel (<= 64 tokens)  one strip of 128 rows per block: 4 us + 5 us (up to 32 tokens) or 8.5 us per 2560 weights
 //       of the input dimension; strips of 256 rows: 12.5 or 17.5 us per round of the device
 //       (64 x (2560 -> 6912) at 32 / 64 tokens: 85 / 120 us; one layer alone 9.6 / 12.8, 6912 -> 2560 17.2 / 25.7)
@@ -1093,49 +1137,11 @@ sbn_status launch_gemm_smfmac(int count, const LinearItem *items, bool dense_cod
     // starts two to five times higher and grows slower
     if (gemm_tile_estimate_us(count, items, dense_codes) < gemm_large_estimate_us(count, items, dense_codes))
         return launch_gemm_tile(count, items, dense_codes, stream);
-    // problems of at most 16 token units (512 tokens: decode batches) are dealt by row tile, up to GEMM_GROUP_WIDE per launch
-    // (2: at most 64 tokens and nothing but Y asked for: the streaming kernel for decode batches)
-    auto few_tokens = [&](int i) { return gemv_batch_takes(items[i]) ? 2 : items[i].tokens <= 16 * 32 ? 1 : 0; };
     for (int first = 0; first < count;) {
-        const int few = few_tokens(first);
-        const int most = few == 2 ? count : few ? GEMM_GROUP_WIDE : GEMM_GROUP_MAX;
+        const bool streams = gemv_batch_takes(items[first]);
         int n = 1;
-        while (first + n < count && n < most && few_tokens(first + n) == few) ++n;
-        if (few == 2) {
-            sbn_status st = launch_gemv_batch(n, items + first, dense_codes, stream);
-            if (st != SBN_OK) return st;
-            first += n;
-            continue;
-        }
-        if (few) {
-            GemmGroupWide grp;
-            grp.count = n;
-            for (int i = 0; i < n; ++i) grp.g[i] = make_args(items[first + i]);
-            // pieces of four token units feed the matrix pipe best; a launch with fewer pieces than multiprocessors (one
-            // layer of a decode step) is cut finer, down to single units, so that its latency is that of a small piece
-            int wmax = 4, pieces = 0;
-            for (;; wmax >>= 1) {
-                pieces = 0;
-                for (int i = 0; i < n; ++i)
-                    pieces += (int)ceil_div(items[first + i].d_out, sp::ROWS) * (int)ceil_div(ceil_div(items[first + i].tokens, 32), wmax);
-                if (wmax == 1 || pieces >= device_cus()) break;
-            }
-            PieceTableNone tab;
-            tab.per_block = -pieces;
-            tab.piece[0] = (uint32_t)wmax;
-            const int blocks = pieces < device_cus() ? pieces : device_cus();
-            if (dense_codes) hipLaunchKernelGGL((gemm_smfmac_kernel<true, GemmGroupWide, PieceTableNone>), dim3(blocks), dim3(64 * sp::NW), 0, stream, grp, tab);
-            else hipLaunchKernelGGL((gemm_smfmac_kernel<false, GemmGroupWide, PieceTableNone>), dim3(blocks), dim3(64 * sp::NW), 0, stream, grp, tab);
-        } else {
-            GemmGroup grp;
-            grp.count = n;
-            for (int i = 0; i < n; ++i) grp.g[i] = make_args(items[first + i]);
-            static thread_local PieceTable tab;
-            const int per_xcd = make_piece_table(grp, tab);
-            if (dense_codes) hipLaunchKernelGGL((gemm_smfmac_kernel<true, GemmGroup, PieceTable>), dim3(8 * per_xcd), dim3(64 * sp::NW), 0, stream, grp, tab);
-            else hipLaunchKernelGGL((gemm_smfmac_kernel<false, GemmGroup, PieceTable>), dim3(8 * per_xcd), dim3(64 * sp::NW), 0, stream, grp, tab);
-        }
-        sbn_status st = check_launch("gemm_smfmac_kernel");
+        while (first + n < count && gemv_batch_takes(items[first + n]) == streams) ++n;
+        sbn_status st = streams ? launch_gemv_batch(n, items + first, dense_codes, stream) : launch_gemm_pieces(n, items + first, dense_codes, stream);
         if (st != SBN_OK) return st;
         first += n;
     }

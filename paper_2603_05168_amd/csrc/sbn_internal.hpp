@@ -101,13 +101,16 @@ sbn_status launch_rmsnorm_act_quant(const void *X, const float *gain, float eps,
 // packed form as stored (rewritten into sparse operands in registers)
 enum GemvForm : int { GEMV_2OF4 = 0, GEMV_DENSE = 1, GEMV_1OF4 = 2 };
 sbn_status launch_gemv(int count, const LinearItem *items, GemvForm form, hipStream_t stream);
-// dense_codes: the weights are dense 2-bit codes (packed form of N = M) instead of the 2:4 form
+// dense_codes: the weights are dense 2-bit codes (packed form of N = M) instead of the 2:4 form.  launch_gemm_smfmac chooses
+// between the three kernels named below it
 sbn_status launch_gemm_smfmac(int count, const LinearItem *items, bool dense_codes, hipStream_t stream);
+// pieces of 512 rows x 32 to 128 tokens (sbn_gemm.hip): any problem
+sbn_status launch_gemm_pieces(int count, const LinearItem *items, bool dense_codes, hipStream_t stream);
 // decode batches (sbn_batch.hip): problems of at most 64 tokens without bias or accumulator output stream their weights
-// once through a kernel of their own; launch_gemm_smfmac hands them over
+// once through a kernel of their own
 bool gemv_batch_takes(const LinearItem &it);
 sbn_status launch_gemv_batch(int count, const LinearItem *items, bool dense_codes, hipStream_t stream);
-// small block tiles (sbn_tile.hip): a few problems of few tokens; launch_gemm_smfmac hands over what this kernel is faster at
+// small block tiles (sbn_tile.hip): any problem, made for a few problems of few tokens
 float gemm_tile_estimate_us(int count, const LinearItem *items, bool dense_codes);
 sbn_status launch_gemm_tile(int count, const LinearItem *items, bool dense_codes, hipStream_t stream);
 sbn_status launch_gemm_dense(const LinearItem &it, const Pattern &pat, int8_t *w_dense, hipStream_t stream);

@@ -174,6 +174,19 @@ def test_argument_errors_come_before_any_launch(sbn):
     assert conv(to_N=1, to_M=4) == sbn.SBN_EUNSUPPORTED          # only 2:4 and N = M are decode forms
     assert conv(d_in=200) == sbn.SBN_EUNSUPPORTED                # whole 128-weight chunks only
     assert conv(to_N=9, to_M=8) == sbn.SBN_EINVAL
+    # kernels by name: no such kernel, null rows, misaligned outputs, and what a kernel does not take
+    lib.sbn_test_linear_kernel.restype = ctypes.c_int
+
+    def kernel(which=0, xq=A, Y=A, tokens=8, d_in=256, d_out=64, N=2, M=4, bias=0):
+        return lib.sbn_test_linear_kernel(ci(which), ci(1), one_p(xq), one_p(A), one_i(tokens), one_i(d_in), one_i(d_out), ci(N), ci(M),
+                                          one_p(A), one_p(A), one_p(bias), one_p(Y), None, vp(0))
+    assert kernel(which=3) == sbn.SBN_EINVAL
+    assert kernel(xq=0) == sbn.SBN_EINVAL
+    assert kernel(Y=A + 4) == sbn.SBN_EALIGN
+    assert kernel(d_in=200) == sbn.SBN_EUNSUPPORTED
+    assert kernel(N=6, M=8) == sbn.SBN_EUNSUPPORTED
+    for refused in ({"tokens": 65}, {"d_out": 66}, {"bias": A}):
+        assert kernel(which=1, **refused) == sbn.SBN_EUNSUPPORTED
     # ceiling probes (their own library): unknown kind, missing host output, buffer too small to stream
     from paper_2603_05168_amd import probe
     plib = ctypes.CDLL(probe.lib_path())

@@ -1,0 +1,94 @@
+"""GPU parity of the three forward kernels between which SBN_PATH_SMFMAC chooses by the sizes of a call (small block tiles, the
+streaming kernel for decode batches, the persistent kernel on pieces of 512 rows), each asked for by name, so that its edges
+are covered whatever that choice is: rows and tokens past a tile, rows that are no multiple of four, one and an odd number
+of chunks, both weight forms, bias, accumulator output, more problems than one launch holds."""
+import functools
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import sbn_synth
+from gpu_util import DEV, hip_pack, oracle_pack, sbn
+
+pytestmark = pytest.mark.gpu
+
+
+@functools.lru_cache(maxsize=None)
+def _weights(d_out, d_in, N, M, adversarial=False):
+    W = (sbn_synth.adversarial_weight if adversarial else sbn_synth.latent_weight)(d_out, d_in, 8000 + d_out + d_in)
+    _, gamma, Weff, _ = oracle_pack(W, N, M)
+    return (*hip_pack(W, N, M), gamma, Weff)
+
+
+@functools.lru_cache(maxsize=None)
+def _reference(tokens, d_out, d_in, N, M, adversarial=False):
+    X = (sbn_synth.adversarial_activations if adversarial else sbn_synth.activations)(tokens, d_in, 8100 + tokens + d_in)
+    _, _, gamma, Weff = _weights(d_out, d_in, N, M, adversarial)
+    y, acc, xq, sx = oracle.sparse_ternary_linear(X.float().numpy(), Weff, gamma)
+    return torch.from_numpy(xq).to(DEV), torch.from_numpy(sx).to(DEV), y, acc
+
+
+def _check(Y, y, bias, what):
+    # the accumulator is exact: three roundings of the product (scale, accumulator to fp32, product), one of the sum with the bias
+    b = 0.0 if bias is None else bias.cpu().numpy().astype(np.float64)[None, :]
+    err = np.abs(Y.cpu().numpy().astype(np.float64) - (y + b))
+    bound = 4 * 2.0 ** -24 * (np.abs(y) + np.abs(b))
+    assert (err <= bound).all(), f"{what}: {(~(err <= bound)).sum()} values beyond the bound"
+
+
+def _run(kernel, problems, N, M, bias=False, acc=False, adversarial=False):
+    """problems: (tokens, d_out, d_in) of one call."""
+    s = sbn()
+    refs = [_reference(*p, N, M, adversarial) for p in problems]
+    packs = [_weights(o, k, N, M, adversarial) for _, o, k in problems]
+    Ys = [torch.full((t, o), float("nan"), dtype=torch.float32, device=DEV) for t, o, _ in problems]
+    accs = [torch.full((t, o), -7, dtype=torch.int32, device=DEV) for t, o, _ in problems] if acc else None
+    biases = [torch.randn(o, generator=torch.Generator().manual_seed(o)).to(DEV) for _, o, _ in problems] if bias else None
+    s.sbn_test_linear_kernel(kernel, [r[0] for r in refs], [r[1] for r in refs], [p[0] for p in packs], [p[1] for p in packs], Ys, N, M,
+                             biases, accs)
+    torch.cuda.synchronize()
+    for i, (p, r) in enumerate(zip(problems, refs)):
+        _check(Ys[i], r[2], biases[i] if bias else None, f"problem {i} {p}")
+        if acc:
+            assert np.array_equal(accs[i].cpu().numpy(), r[3]), f"accumulators of problem {i} {p}"
+
+
+SHAPES = [(1, 16, 128), (16, 256, 256), (40, 130, 384), (97, 64, 2560), (129, 64, 128), (129, 1100, 128), (200, 300, 384), (200, 514, 640),
+          (300, 520, 1280), (512, 1030, 128),
+          # beyond 512 tokens the persistent kernel deals its pieces from a list
+          (513, 520, 640), (600, 1030, 384), (1100, 515, 640), (2100, 70, 128)]
+
+
+@pytest.mark.parametrize("N,M", [(2, 4), (8, 8)])
+@pytest.mark.parametrize("problem", SHAPES)
+@pytest.mark.parametrize("bias,acc", [(False, False), (True, False), (False, True), (True, True)])
+@pytest.mark.parametrize("kernel", ["TILES", "PIECES"])
+def test_kernel_edges(kernel, problem, N, M, bias, acc):
+    _run(getattr(sbn(), "SBN_KERNEL_" + kernel), [problem], N, M, bias, acc)
+
+
+@pytest.mark.parametrize("N,M", [(2, 4), (8, 8)])
+@pytest.mark.parametrize("problem", [(1, 4, 128), (16, 256, 256), (17, 132, 384), (32, 1100, 640), (33, 520, 128), (64, 2052, 1280), (48, 64, 2560),
+                                     (20, 65600, 128), (60, 65540, 256)])   # the last two: strips of 256 rows
+def test_streaming_kernel_edges(problem, N, M):
+    _run(sbn().SBN_KERNEL_STREAM, [problem], N, M)
+
+
+@pytest.mark.parametrize("N,M", [(2, 4), (8, 8)])
+@pytest.mark.parametrize("kernel", ["TILES", "STREAM", "PIECES"])
+def test_kernel_adversarial_inputs(kernel, N, M):
+    _run(getattr(sbn(), "SBN_KERNEL_" + kernel), [(64, 256, 512)], N, M, adversarial=True)
+
+
+@pytest.mark.parametrize("N,M", [(2, 4), (8, 8)])
+@pytest.mark.parametrize("kernel,count", [("TILES", 3), ("TILES", 91), ("PIECES", 3), ("PIECES", 71), ("STREAM", 10), ("STREAM", 131)])
+def test_kernel_groups(kernel, count, N, M):
+    # unequal problems in one call: token counts that are no multiple of a unit, ragged last rows, and, in the long calls, more
+    # problems than a launch holds (40 tiles, 32 or 8 of the pieces, 56 of the stream); the pieces: both ways of dealing in turn
+    base = [(1100, 256), (520, 384), (64, 128), (2052, 128)] if kernel == "STREAM" else [(1100, 256), (518, 384), (64, 128)]
+    toks = {"TILES": [17, 64, 100, 128, 200, 257, 600, 33], "PIECES": [17, 64, 100, 128, 200, 257, 512, 33] + [600] * 11 + [40],
+            "STREAM": [17, 64, 33, 20, 48, 32, 1, 16, 64, 64]}[kernel]
+    problems = [(toks[i % len(toks)], *base[i % len(base)]) for i in range(count)]
+    _run(getattr(sbn(), "SBN_KERNEL_" + kernel), problems, N, M, bias=kernel != "STREAM" and count == 3)

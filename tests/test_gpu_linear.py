@@ -107,8 +107,9 @@ def test_sparse_mfma_path_instances_of_2of4(N, M, tokens, shape):
 @pytest.mark.parametrize("tokens,shape", [(40, (130, 384)), (300, (520, 1280)), (129, (1100, 128)), (97, (64, 2560))])
 def test_sparse_mfma_path_dense_codes(N, M, tokens, shape):
     # patterns that keep more than two of an aligned four run beyond decode sizes as dense 2-bit codes (N = M as
-    # stored, the rest converted first) through two sparse instructions per group of four: ragged edges in rows and
-    # tokens, one chunk (128) and an odd number of chunks (384 = 3), bias; same integers as the oracle
+    # stored, the rest converted first) on the kernel that the sizes choose (test_gpu_kernels_by_name.py asks for each by
+    # name): ragged edges in rows and tokens, one chunk (128) and an odd number of chunks (384 = 3), bias; same integers as
+    # the oracle
     s = sbn()
     W = sbn_synth.latent_weight(shape[0], shape[1], 2440 + 10 * N + M)
     X = sbn_synth.activations(tokens, shape[1], 2450 + tokens)
@@ -166,7 +167,7 @@ def test_dense_comparison_kernel_alone(N, M):
 
 
 def test_grouped_prefill_dense_codes_matches_single():
-    # N = M problems of different shapes in one grouped launch of the GEMM kernel
+    # N = M problems of different shapes in one grouped call
     s = sbn()
     shapes = [(520, 384), (100, 128), (1030, 640)]
     tokens = [200, 40, 333]
@@ -561,8 +562,8 @@ def test_grouped_sparse_gemm_against_oracle():
 
 @pytest.mark.parametrize("N,M", [(2, 4), (8, 8)])
 def test_grouped_decode_batches_on_the_gemm_kernel(N, M):
-    # Decode batches of 17 .. 512 tokens (the batch sizes of the throughput table, Section 3.2): more problems than one
-    # launch of the row-tile work split holds (32), token counts that are no multiple of a token unit, one and several
+    # Decode batches of 17 .. 512 tokens (the batch sizes of the throughput table, Section 3.2) in one call, on the kernel that
+    # the sizes choose: more problems than one launch of the row-tile work split holds (32), token counts that are no multiple of a token unit, one and several
     # pieces per row tile, ragged last row tiles, one problem with enough tokens for the work-list split in between
     s = sbn()
     tokens_of = [17, 64, 100, 128, 200, 257, 512, 33, 40]
@@ -590,8 +591,9 @@ def test_grouped_decode_batches_on_the_gemm_kernel(N, M):
 
 @pytest.mark.parametrize("N,M", [(2, 4), (8, 8), (6, 8)])
 def test_grouped_decode_batches_streaming_kernel(N, M):
-    # Problems of at most 64 tokens with nothing but Y asked for take the streaming kernel for decode batches: 1 .. 64 tokens (two and four token tiles in separate launches), strips of 128 and of
-    # 256 rows (second call: enough rows for the wide strips), ragged last strips, an input dimension that is no
+    # Problems of at most 64 tokens with nothing but Y asked for take small block tiles in the first call and, by the rows
+    # there are, the streaming kernel for decode batches in the second (test_gpu_kernels_by_name.py asks for each by name):
+    # 1 .. 64 tokens (two and four token tiles in separate launches), ragged last strips, an input dimension that is no
     # multiple of a super-step (768 = 6 chunks), problems that share an input and problems that do not
     s = sbn()
     for reps in (1, 4):
@@ -663,7 +665,7 @@ def test_act_quant_entry_all_kernel_variants(tokens, d_in):
 
 @pytest.mark.parametrize("tokens,shape", [(200, (512, 384)), (4096, (2560, 2560)), (130, (768, 128))])
 def test_gemm_sparse_without_accumulator_output(tokens, shape):
-    # without acc_out the sparse GEMM takes its LDS-transposed full-row epilogue: same Y, bias included
+    # without acc_out the kernels store whole rows, which the large one transposes through LDS: same Y, bias included
     s = sbn()
     W = sbn_synth.latent_weight(shape[0], shape[1], 860 + shape[0])
     X = sbn_synth.activations(tokens, shape[1], 861 + tokens)
