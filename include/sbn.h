@@ -107,6 +107,8 @@ sbn_status sbn_workspace_bytes(sbn_op op, int64_t tokens, int64_t d_out, int64_t
  *   packed    device, sbn_packed_bytes() bytes, 16-byte aligned; written
  *   gamma     device, one float; written
  *   workspace device, >= sbn_workspace_bytes(SBN_OP_QUANTIZE_MASK_PACK, 1, ...) bytes
+ * Weights that are not finite: the call ends as ever; a mean that is infinite or NaN leaves such a gamma and a packed form
+ * that is valid (N positions per group) with codes that mean nothing.
  */
 sbn_status sbn_quantize_mask_pack(const void *W_latent, sbn_dtype wdt, int64_t d_out, int64_t d_in,
                                   int64_t ld_w, int N, int M, void *packed, float *gamma,

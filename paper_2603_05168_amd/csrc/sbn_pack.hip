@@ -135,14 +135,15 @@ __global__ void __launch_bounds__(256) absmean_partial_kernel(PackTable tab, dou
 // theta is the smallest fp32 magnitude a with fl32(a / gamma) > 0.5.  Because fl32(a / gamma) is
 // monotone in a, clip(round_half_even(w / gamma), -1, 1) != 0  <=>  |w| >= theta, so the pack
 // kernel needs one integer compare per weight instead of a division.
-// gamma and theta from the fp64 total of |w|
+// theta is the next fp32 value after gamma / 2, always: gamma / 2 is exact (gamma >= 1e-5 is normal) and its quotient is 0.5;
+// one ulp up is more than 2^-24 relative, so that quotient lies more than half an ulp of [0.5, 1) above 0.5 and rounds up.
+// (A search for it that steps until the quotient exceeds 0.5 never ends for a mean that is infinite or NaN.)
+// gamma and theta from the fp64 total of |w|; where that is not finite, gamma is neither and theta is a NaN pattern
 __device__ __forceinline__ float gamma_theta(double total, int64_t count, float &theta)
 {
     float g = (float)(total / (double)count);
     g = g < 1e-5f ? 1e-5f : g;
-    float a = 0.5f * g;
-    while (!(__fdiv_rn(a, g) > 0.5f)) a = __uint_as_float(__float_as_uint(a) + 1u);
-    theta = a;
+    theta = __uint_as_float(__float_as_uint(0.5f * g) + 1u);
     return g;
 }
 

@@ -362,3 +362,27 @@ def test_single_read_pack_types(dtype, N, M, spin_limit, spin_limits):
                                              (torch.float32, 4, 4, (10240, 2560))])   # 1600 > 2 x 768: three passes
 def test_single_read_pack_matrix_of_more_units_than_blocks(dtype, N, M, shape):
     check(sbn_synth.latent_weight(*shape, 1950, dtype=dtype), N, M)
+
+
+@pytest.mark.parametrize("value", [float("nan"), float("inf"), float("-inf"), 3e38])
+@pytest.mark.parametrize("dtype,N,M,d_in", [(torch.bfloat16, 2, 4, 384), (torch.float32, 6, 8, 384),       # single-read form
+                                            (torch.bfloat16, 2, 4, 200), (torch.float32, 3, 8, 384)])      # three passes
+def test_pack_of_weights_that_are_not_finite_ends(dtype, N, M, d_in, value):
+    # a diverged matrix must not keep the call from ending: its scale says so (3e38 alone leaves it finite), its neighbours in
+    # the batch are packed as ever, and every row is a valid packed form
+    s = sbn()
+    Ws = [sbn_synth.latent_weight(100, d_in, 1960 + i, dtype=dtype) for i in range(3)]
+    Ws[1][7, 13] = value
+    packed = [torch.zeros(s.sbn_packed_bytes(100, d_in, N, M), dtype=torch.uint8, device=DEV) for _ in Ws]
+    gammas = torch.zeros(3, dtype=torch.float32, device=DEV)
+    ws = s.new_workspace(s.sbn_workspace_bytes(s.SBN_OP_QUANTIZE_MASK_PACK, 3, 100, d_in, N, M))
+    s.sbn_quantize_mask_pack_batched([W.to(DEV) for W in Ws], N, M, packed, [gammas[i:i + 1] for i in range(3)], ws)
+    Weff, mask = (torch.empty(100, d_in, dtype=t, device=DEV) for t in (torch.int8, torch.uint8))
+    s.sbn_unpack(packed[1], 100, d_in, N, M, Weff, mask)
+    torch.cuda.synchronize()
+    assert bool(torch.isfinite(gammas[1])) == bool(np.isfinite(value))
+    assert (mask.view(100, -1, M).sum(-1) == N).all() and (Weff.abs() <= 1).all()
+    for i in (0, 2):
+        ref, g, *_ = oracle_pack(Ws[i], N, M)
+        assert gammas[i].item() == g
+        assert np.array_equal(packed[i].cpu().numpy(), ref)
