@@ -344,6 +344,11 @@ sbn_status sbn_test_linear_kernel(int kernel, int count, const int8_t *const *xq
                                   const float *const *gamma, const float *const *bias, float *const *Y,
                                   int32_t *const *acc_out, void *stream);
 
+/* Test hook, host only: the kernel (SBN_KERNEL_...) that SBN_PATH_SMFMAC chooses for each problem of a call that wants nothing
+ * but Y.  2:4 and N = M, d_in % 128 == 0; kernel: HOST array of length count. */
+sbn_status sbn_test_chosen_kernels(int count, const int64_t *tokens, const int64_t *d_in, const int64_t *d_out, int N, int M,
+                                   int *kernel);
+
 /* Text of the last HIP error seen by this thread ("" if none). */
 const char *sbn_last_error(void);
 

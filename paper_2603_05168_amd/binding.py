@@ -74,6 +74,8 @@ def _load():
     lib.sbn_test_set_spin_limits.argtypes = [cint, cint]
     lib.sbn_test_linear_kernel.restype = cint
     lib.sbn_test_linear_kernel.argtypes = [cint, cint, pp, pp, pi64, pi64, pi64, cint, cint, pp, pp, pp, pp, pp, vp]
+    lib.sbn_test_chosen_kernels.restype = cint
+    lib.sbn_test_chosen_kernels.argtypes = [cint, pi64, pi64, pi64, cint, cint, ctypes.POINTER(cint)]
     lib.sbn_mask_flips.restype = cint
     lib.sbn_mask_flips.argtypes = [vp, vp, i64, i64, cint, cint, vp, vp, sz, vp]
     return lib
@@ -351,6 +353,14 @@ def sbn_test_linear_kernel(kernel: int, xq_list, sx_list, packed_list, gamma_lis
                                        _ptr_array(packed_list), _ptr_array(gamma_list), None if bias_list is None else _ptr_array(bias_list),
                                        _ptr_array(Y_list), None if acc_list is None else _ptr_array(acc_list), _stream()),
            "sbn_test_linear_kernel")
+
+
+def sbn_test_chosen_kernels(problems, N: int, M: int):
+    """Test hook: the kernel (SBN_KERNEL_...) of each problem (tokens, d_in, d_out) of one call on SBN_PATH_SMFMAC."""
+    kernel = (ctypes.c_int * len(problems))()
+    _check(_lib.sbn_test_chosen_kernels(len(problems), *(_i64_array(column) for column in zip(*problems)), N, M, kernel),
+           "sbn_test_chosen_kernels")
+    return list(kernel)
 
 
 def sbn_mask_flips(packed_a, packed_b, d_out: int, d_in: int, N: int, M: int, flips_out, workspace):

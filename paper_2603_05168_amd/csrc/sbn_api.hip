@@ -93,6 +93,28 @@ sbn_status sbn_test_linear_kernel(int kernel, int count, const int8_t *const *xq
                                          : launch_gemm_pieces(count, items.data(), N == M, s);
 }
 
+sbn_status sbn_test_chosen_kernels(int count, const int64_t *tokens, const int64_t *d_in, const int64_t *d_out, int N, int M, int *kernel)
+{
+    if (count <= 0 || count > 4096 || !tokens || !d_in || !d_out || !kernel) return SBN_EINVAL;
+    if (!(N == 2 && M == 4) && N != M) return SBN_EUNSUPPORTED;
+    Pattern pat;
+    std::vector<LinearItem> items(count);
+    for (int i = 0; i < count; ++i) {
+        sbn_status st = check_shape(d_out[i], d_in[i], N, M, pat);
+        if (st != SBN_OK) return st;
+        if (tokens[i] <= 0) return SBN_EINVAL;
+        if (d_in[i] % CHUNK != 0) return SBN_EUNSUPPORTED;
+        items[i] = LinearItem{};
+        items[i].tokens = tokens[i];
+        items[i].d_in = d_in[i];
+        items[i].d_out = d_out[i];
+    }
+    const bool tiles = gemm_takes_tiles(count, items.data(), N == M);
+    for (int i = 0; i < count; ++i)
+        kernel[i] = tiles ? SBN_KERNEL_TILES : gemv_batch_takes(items[i]) ? SBN_KERNEL_STREAM : SBN_KERNEL_PIECES;
+    return SBN_OK;
+}
+
 sbn_status sbn_packed_bytes(int64_t d_out, int64_t d_in, int N, int M, size_t *bytes)
 {
     Pattern pat;

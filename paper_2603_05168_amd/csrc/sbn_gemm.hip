@@ -1103,22 +1103,26 @@ sbn_status launch_gemm_pieces(int count, const LinearItem *items, bool dense_cod
     return SBN_OK;
 }
 
-// Estimated time in us of a launch of the streaming kernel or of the pieces, next to which gemm_tile_estimate_us stands.  Measured:
+// Estimated time in us of a call on the streaming kernel or the pieces, next to which gemm_tile_estimate_us stands; every
+// problem counts with its own input dimension.  Measured, weights from memory, quantizer not included:
 //   streaming kernel (<= 64 tokens)  one strip of 128 rows per block: 4 us + 5 us (up to 32 tokens) or 8.5 us per 2560 weights
 //       of the input dimension; strips of 256 rows: 12.5 or 17.5 us per round of the device
-//       (64 x (2560 -> 6912) at 32 / 64 tokens: 85 / 120 us; one layer alone 9.6 / 12.8, 6912 -> 2560 17.2 / 25.7)
-//   pieces of 512 rows x 32 .. 128 tokens  3.5 us + 9.5 us (14 with dense codes) per 2560 weights for the first unit of 32
-//       tokens a block has, 0.55 of that for each further one (2560 -> 2560 at 128 .. 1500 tokens 13.2 .. 13.9 us,
-//       6912 -> 2560 28 .. 30, 2560 -> 6912 at 777 / 1500 tokens, 2 / 3 units, 17.5 / 24)
+//       (16 x (2560 -> 6912) at 32 / 64 tokens: 26 / 34 us; one layer alone 10 / 14, 6912 -> 2560 18 / 27)
+//   pieces of 512 rows x 32 .. 128 tokens  3.9 us, 10.7 us (dense codes 15.3) per 2560 weights of the deepest problem, 0.78 of
+//       that for each further unit of 32 tokens a multiprocessor has, 0.11 us per MB of outputs
+//       (2560 -> 2560 at 17 .. 1500 tokens 13.1 .. 13.9 us, 6912 -> 2560 37 .. 43, 2560 -> 6912 at 512 / 777 / 1500 / 3000
+//       tokens, up to 1 / 2 / 3 / 6 units, 17 / 19 / 24 / 47)
 static float gemm_large_estimate_us(int count, const LinearItem *items, bool dense)
 {
     bool stream = true;
-    int64_t strips = 0, units = 0, tokens = 0, depth = 0;
+    int64_t strips = 0, tokens = 0, depth = 0;
+    double units = 0, out_mb = 0;   // units weighted with their input dimension
     for (int i = 0; i < count; ++i) {
         const LinearItem &li = items[i];
         stream = stream && gemv_batch_takes(li);
         strips += ceil_div(li.d_out, 256);
-        units += ceil_div(li.d_out, sp::ROWS) * ceil_div(li.tokens, 32);
+        units += (double)(ceil_div(li.d_out, sp::ROWS) * ceil_div(li.tokens, 32)) * (double)li.d_in / 2560.0;
+        out_mb += 4e-6 * (double)li.tokens * (double)li.d_out;
         tokens = li.tokens > tokens ? li.tokens : tokens;
         depth = li.d_in > depth ? li.d_in : depth;
     }
@@ -1128,15 +1132,24 @@ static float gemm_large_estimate_us(int count, const LinearItem *items, bool den
         if (strips < cus) return 4.0f + k * (tokens <= 32 ? 5.0f : 8.5f);
         return 4.0f + k * (tokens <= 32 ? 12.5f : 17.5f) * (float)strips / (float)cus;
     }
-    return 3.5f + k * (dense ? 14.0f : 9.5f) * (1.0f + 0.55f * (float)(ceil_div(units, cus) - 1));
+    const float more = (float)units / (float)cus - k;
+    // (768 -> 6912 at 16384 tokens and 8192 -> 768 at 17 in one call: 278 us as small tiles, 158 this way, quantizers included)
+    return 3.9f + (dense ? 15.3f : 10.7f) * (k + 0.78f * (more > 0.0f ? more : 0.0f)) + 0.11f * (float)out_mb;
+}
+
+// Small block tiles where they are faster: their time grows with rows x tokens from 4.5 us on, that of the large kernels
+// starts two to five times higher and grows slower.  Over 279 calls of 17 to 16384 tokens, input dimensions 256 to 8192 and
+// one to sixteen problems, all kernels measured, the choice costs 0.7 % against the faster kernel of each (at worst 1.39, 384 tokens
+// 4096 -> 14336 with dense codes: 55 us against 40); 256 tokens, 2560 -> 6912: 12.4 us in tiles, 17.3 in pieces; 777 tokens,
+// 2560 -> 2560: 12.3 / 13.2; 1024 tokens: 14.5 / 13.2.
+bool gemm_takes_tiles(int count, const LinearItem *items, bool dense_codes)
+{
+    return gemm_tile_estimate_us(count, items, dense_codes) < gemm_large_estimate_us(count, items, dense_codes);
 }
 
 sbn_status launch_gemm_smfmac(int count, const LinearItem *items, bool dense_codes, hipStream_t stream)
 {
-    // small block tiles where they are faster: their time grows with rows x tokens from 4.5 us on, that of the large tiles
-    // starts two to five times higher and grows slower
-    if (gemm_tile_estimate_us(count, items, dense_codes) < gemm_large_estimate_us(count, items, dense_codes))
-        return launch_gemm_tile(count, items, dense_codes, stream);
+    if (gemm_takes_tiles(count, items, dense_codes)) return launch_gemm_tile(count, items, dense_codes, stream);
     for (int first = 0; first < count;) {
         const bool streams = gemv_batch_takes(items[first]);
         int n = 1;

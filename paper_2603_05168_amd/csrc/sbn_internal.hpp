@@ -112,6 +112,7 @@ bool gemv_batch_takes(const LinearItem &it);
 sbn_status launch_gemv_batch(int count, const LinearItem *items, bool dense_codes, hipStream_t stream);
 // small block tiles (sbn_tile.hip): any problem, made for a few problems of few tokens
 float gemm_tile_estimate_us(int count, const LinearItem *items, bool dense_codes);
+bool gemm_takes_tiles(int count, const LinearItem *items, bool dense_codes);   // whether launch_gemm_smfmac takes them
 sbn_status launch_gemm_tile(int count, const LinearItem *items, bool dense_codes, hipStream_t stream);
 sbn_status launch_gemm_dense(const LinearItem &it, const Pattern &pat, int8_t *w_dense, hipStream_t stream);
 sbn_status launch_gemm_dense_expanded(const LinearItem &it, const int8_t *w_dense, hipStream_t stream);

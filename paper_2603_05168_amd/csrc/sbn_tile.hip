@@ -12,11 +12,12 @@
 // (48 KB) per block, three blocks per multiprocessor, beat eight of them with one (40 against 23.5 us at 777 x 2560 ->
 // 6912).  Operands loaded straight into registers in the instruction's layout (consecutive lanes = rows) pass the vector
 // L1 at 16 bytes per clock and were up to twice as slow (57 us there).
-// Measured, us per launch, weights from memory, 2:4 (before: the kernels named in launch_gemm_smfmac):
-//   tokens               32           64          128          256          512          777
-//   2560 -> 2560   9.6 -> 4.5  12.8 -> 4.9  13.6 -> 5.9  13.9 -> 7.4   13.8 -> 9.2  13.2 -> 11.5
-//   2560 -> 6912   9.7 -> 5.2  13.0 -> 6.3  13.9 -> 7.8  14.9 -> 11.4  (15.2)       (17.5)
-//   6912 -> 2560  17.2 -> 5.7  25.7 -> 6.7  29.3 -> 8.3  30.2 -> 11.6  29.6 -> 15.7  28.2 -> 22.6
+// Measured, us per launch, weights from memory, 2:4 (the faster of the two kernels named in launch_gemm_smfmac -> this one;
+// in brackets where that one is chosen):
+//   tokens               32           64          128          256           512           777          1024
+//   2560 -> 2560   9.6 -> 4.5  12.8 -> 4.9  13.6 -> 5.9  13.9 -> 7.3   13.8 -> 9.5   13.2 -> 12.3  (13.2 -> 14.5)
+//   2560 -> 6912  10.4 -> 5.7  14.2 -> 7.1  17.1 -> 8.3  17.3 -> 12.4  (17.2 -> 18.4) (19.0 -> 25.0) (20.8 -> 30.3)
+//   6912 -> 2560  18.4 -> 6.8  27.1 -> 8.3  40.6 -> 9.5  40.7 -> 11.9  39.1 -> 17.7  37.1 -> 23.5  37.4 -> 27.2
 #include <algorithm>
 
 #include "sbn_internal.hpp"
@@ -286,22 +287,22 @@ int64_t wide_tiles(const LinearItem &li) { return ceil_div(li.d_out, 64) * ceil_
 
 }  // namespace
 
-// Estimated time of a launch of this kernel in us: the chain of one block (768 weights 2.9 us, from 2560 on 4.5); per tile of 64 x 32 over the whole device 2.2 ns
-// for its sums and outputs and 7 ns (dense codes 7.8) per 2560 weights for its deposits (1000 tiles: 13 us at 2560 weights,
-// 25.5 at 6912; 2240 tiles of 1024 weights 17.6); the weights once from memory at 5 TB/s.
+// Estimated time of a call on this kernel in us: the chain of one block (768 weights 3.6 us, from 1620 on 4.5); per tile of 64 x
+// 32 and multiprocessor 0.67 us for its sums and outputs and 1.54 us (dense codes 1.61) per 2560 weights for its deposits; the
+// weights once from memory at 6 TB/s.  (1728 tiles of 2560 weights 18.4 us, 6912 of 1024 31.4, 640 of 6912 17.7.)
 float gemm_tile_estimate_us(int count, const LinearItem *items, bool dense)
 {
     double us = 0, chain = 0;
     for (int i = 0; i < count; ++i) {
-        chain = std::max(chain, 2.5 + std::min(2.0, (double)items[i].d_in / 1280.0));
-        us += (double)wide_tiles(items[i]) * (0.0022 + (dense ? 0.0078 : 0.007) * (double)items[i].d_in / 2560.0) +
-              (double)items[i].d_out * (double)items[i].d_in / 4 / 5e6;
+        const double k = (double)items[i].d_in;
+        chain = std::max(chain, 2.7 + std::min(1.8, k / 900.0));
+        us += (double)wide_tiles(items[i]) / (double)device_cus() * (0.67 + (dense ? 1.61 : 1.54) * k / 2560.0) + (double)items[i].d_out * k / 4 / 6e6;
     }
     return (float)(us + chain);
 }
 
 // Tile shape: 64 x 32 moves the fewest bytes per product and takes over where it gives most multiprocessors a tile
-// (200 tiles; 128 tokens, 6912 -> 2560: 160 tiles, 8.3 us against 9.2 with 32 x 32, but 2560 -> 2560 6.1 against 5.5 with
+// (from 25 for 32 multiprocessors on, 200 on 256; 128 tokens, 6912 -> 2560: 160 tiles, 8.3 us against 9.2 with 32 x 32, but 2560 -> 2560 6.1 against 5.5 with
 // 32 x 16); below that smaller tiles, 32 x 16 up to 32 tokens (32 tokens, 6912 -> 2560: 5.7 us against 6.7 with 32 x 32), 32 x 32
 // beyond (64 tokens: 6.7 against 7.6 with 32 x 16).  Eight wavefronts walk the stages in fewer rounds and are faster while a
 // multiprocessor has one block (64 tokens, 6912 -> 2560: 6.7 us against 7.3 with four), four leave room for more blocks
@@ -314,7 +315,7 @@ sbn_status launch_gemm_tile(int count, const LinearItem *items, bool dense, hipS
         square += ceil_div(items[i].d_out, 32) * ceil_div(items[i].tokens, 32);
         tokens = items[i].tokens > tokens ? items[i].tokens : tokens;
     }
-    if (wide >= 200) return launch_tile_shape<4, 2>(count, items, dense, 4, stream);
+    if (32 * wide >= 25 * (int64_t)device_cus()) return launch_tile_shape<4, 2>(count, items, dense, 4, stream);
     if (tokens <= 32) return launch_tile_shape<2, 1>(count, items, dense, 8, stream);
     return launch_tile_shape<2, 2>(count, items, dense, square <= device_cus() ? 8 : 4, stream);
 }

@@ -56,6 +56,21 @@ def test_spin_limit_hook_is_callable_without_a_gpu(sbn):
     sbn.sbn_test_set_spin_limits()
 
 
+@pytest.mark.parametrize("N,M", [(2, 4), (8, 8)])
+def test_choice_between_the_forward_kernels(sbn, N, M):
+    # sizes at which the kernels measure far apart (on 256 multiprocessors, which the library assumes without a GPU)
+    tiles, stream, pieces = sbn.SBN_KERNEL_TILES, sbn.SBN_KERNEL_STREAM, sbn.SBN_KERNEL_PIECES
+    for problem in ((17, 2560, 2560), (64, 6912, 2560), (256, 2560, 6912), (384, 1024, 4096), (512, 2560, 2560), (1024, 6912, 2560)):
+        assert sbn.sbn_test_chosen_kernels([problem], N, M) == [tiles], problem
+    for problem in ((3000, 2560, 2560), (777, 2560, 6912), (2048, 1024, 4096), (1500, 768, 3072), (16384, 768, 6912)):
+        assert sbn.sbn_test_chosen_kernels([problem], N, M) == [pieces], problem
+    assert sbn.sbn_test_chosen_kernels([(32, 2560, 6912)] * 64, N, M) == [stream] * 64
+    # a long shallow layer beside a deep one of a few tokens: every problem counts with its own input dimension (278 us in tiles,
+    # 158 this way)
+    assert sbn.sbn_test_chosen_kernels([(16384, 768, 6912), (17, 8192, 768)], N, M) == [pieces, stream]
+    assert sbn.sbn_test_chosen_kernels([(200, 2560, 2560)] * 3, N, M) == [tiles] * 3
+
+
 def test_packed_bytes(sbn):
     assert sbn.sbn_packed_bytes(6912, 2560, 2, 4) == 6912 * 2560 // 4
     assert sbn.sbn_packed_bytes(6912, 2560, 1, 4) == 6912 * 2560 // 8
