@@ -291,18 +291,29 @@ static_assert(sizeof(GemvTable<GEMV_MAX_ITEMS>) <= 4096, "the table travels as a
 // form as stored (16-byte chunks, one load per lane and super-step) and builds the sparse instruction's operands in
 // registers (expand_1of4): half the weight bytes for three times the vector work.
 // x0 = the lane's token row at the super-step's first value; inside(k) = k, or an offset inside the row where k lies past
-// it (zero codes meet what is read there).  The operand loads stand in front, unconditional, so that all are in flight together.
-template <int FORM, int RT, class Inside>
+// it (zero codes meet what is read there).  The operand loads stand in front, unconditional, so that all are in flight together;
+// HALVES: in two batches, from LDS, where the registers of one are short.
+template <int FORM, int RT, bool HALVES = false, class Inside>
 __device__ __forceinline__ void gemv_super_step(const uint4 (&idx4)[RT], const uint4 (&code4)[RT], const int8_t *x0, const int c4,
                                                 const uint32_t ones, Inside &&inside, v4i (&acc)[RT])
 {
     uint4 x[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
+    const auto load = [&](int j) {
         x[j] = *reinterpret_cast<const uint4 *>(x0 + inside(FORM == GEMV_DENSE ? 128 * c4 + 16 * j : 128 * (c4 >> 1) + 16 * (c4 & 1) + 32 * (j >> 1) + 256 * (j & 1)));
+    };
+    const auto second_half = [&]() {
+        if constexpr (HALVES) {
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int j = 4; j < 8; ++j) load(j);
+        }
+    };
+#pragma unroll
+    for (int j = 0; j < (HALVES ? 4 : 8); ++j) load(j);
     if constexpr (FORM == GEMV_DENSE) {
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
+            if (j == 4) second_half();
             const v4i b = __builtin_bit_cast(v4i, x[j]);
 #pragma unroll
             for (int a = 0; a < RT; ++a) {
@@ -325,6 +336,7 @@ __device__ __forceinline__ void gemv_super_step(const uint4 (&idx4)[RT], const u
         // quarters 2/3 (measured operand layout of the instruction)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
+            if (j == 2) second_half();
             const uint4 &blo = x[2 * j], &bhi = x[2 * j + 1];
             const v8i b = {(int)blo.x, (int)blo.y, (int)blo.z, (int)blo.w, (int)bhi.x, (int)bhi.y, (int)bhi.z, (int)bhi.w};
 #pragma unroll
@@ -357,17 +369,46 @@ __device__ __forceinline__ void gemv_fetch(const uint8_t *const (&wrow)[RT], int
     }
 }
 
-// Sums the wavefronts' partial accumulators (red: [wavefront][row tile][lane]), rescales and stores: wavefront a takes row
-// tile a.  Lane: token lane % 16 with the factor `scale`, rows 4 * (lane / 16) + i.
+// A block's wavefronts in groups of four, their number as a compile-time value: what is read of all wavefronts is asked for at
+// once (a loop over a number known at run time waits for each of its reads: 0.05 us apiece)
+constexpr int GEMV_WAVE_GROUPS = 4;
+constexpr int gemv_groups(int nwaves) { return (nwaves + 3) / 4; }
+template <class F> __device__ __forceinline__ void with_wave_groups(int nwaves, F &&f)
+{
+    const int n = gemv_groups(nwaves);
+    if (n == 1) f(std::integral_constant<int, 1>());
+    else if (n == 2) f(std::integral_constant<int, 2>());
+    else if (n == 3) f(std::integral_constant<int, 3>());
+    else f(std::integral_constant<int, 4>());
+}
+constexpr size_t gemv_red_lds(int nwaves, int rt) { return (size_t)4 * gemv_groups(nwaves) * rt * 1024; }
+
+// Sums the wavefronts' partial accumulators (red: [wavefront, whole groups][row tile][lane]), rescales and stores: wavefront a
+// takes row tile a.  Lane: token lane % 16 with the factor `scale`, rows 4 * (lane / 16) + i.
 template <int RT>
 __device__ __forceinline__ void gemv_finish(const GemvItem &it, const v4i (&acc)[RT], v4i *red, int row0, float scale, int wave, int nwaves, int lane)
 {
 #pragma unroll
-    for (int a = 0; a < RT; ++a) red[(wave * RT + a) * 64 + lane] = acc[a];
+    for (int a = 0; a < RT; ++a) {
+        red[(wave * RT + a) * 64 + lane] = acc[a];
+        for (int w = nwaves + wave; w < 4 * gemv_groups(nwaves); w += nwaves) red[(w * RT + a) * 64 + lane] = v4i{0, 0, 0, 0};
+    }
     __syncthreads();
     for (int a = wave; a < RT; a += nwaves) {
-        v4i sum = red[a * 64 + lane];
-        for (int w = 1; w < nwaves; ++w) sum += red[(w * RT + a) * 64 + lane];
+        v4i sum = {0, 0, 0, 0};
+        with_wave_groups(nwaves, [&](auto groups) {
+            // half of them at a time from twelve on: with all in registers a multiprocessor would not hold two such blocks
+            constexpr int BATCH = groups() == 4 ? 8 : groups() == 3 ? 6 : 4 * groups();
+#pragma unroll
+            for (int w0 = 0; w0 < 4 * groups(); w0 += BATCH) {
+                v4i part[BATCH];
+#pragma unroll
+                for (int w = 0; w < BATCH; ++w) part[w] = red[((w0 + w) * RT + a) * 64 + lane];
+#pragma unroll
+                for (int w = 0; w < BATCH; ++w) sum += part[w];
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        });
         const int tok = lane & 15, o = row0 + 16 * a + 4 * (lane >> 4);
         if (tok >= it.tokens || o >= it.d_out) continue;
         v4f y = {(float)sum[0] * scale, (float)sum[1] * scale, (float)sum[2] * scale, (float)sum[3] * scale};
@@ -427,21 +468,29 @@ __global__ void __launch_bounds__(1024) gemv_smfmac_kernel(GemvTable<NI> tab)
 // for together, the largest magnitude of each row meets in LDS behind one barrier, every wavefront quantizes its own
 // values (the quantizer's arithmetic) into its own part of LDS and reads the operand from there.  Two barriers in all, and
 // the quantizer's work is split over all wavefronts; a wavefront per token row left the other wavefronts waiting.
-// What bounds it: the chain of one load, two barriers and a store on top of the 1.9 us of any launch, from four tokens on
-// the vector work of the quantizer.  Measured, weights from memory, us at 1 / 4 / 8 / 16 tokens: 2560 -> 2560 3.6 / 4.4 / 5.1 / 6.6
-// (a wavefront per token row, one row tile per block: 5.6 / 6.0 / 6.3 / 8.4), 6912 -> 2560 4.5 / 5.9 / 7.3 / 10.2 (6.2 / 6.6 / 7.4 / 9.9),
-// 2560 -> 2 x 6912 in one call 5.4 / 6.4 / 7.8 / 10.6 (10.6 / 11.9 / 14.0 / 21.9).
+// What bounds it: the chain of one load, two barriers and a store on top of the 1.9 us of any launch, and the vector work of
+// every wavefront (four of them share a SIMD), of the quantizer above all: 0.3 us per token at 14 wavefronts.  Measured, weights from
+// memory, us at 1 / 4 / 8 / 12 / 16 tokens: 2560 -> 2560 3.3 / 3.9 / 4.5 / 5.1 / 5.7 (a wavefront per token row: 5.4 / 5.9 / 6.1 / 7.6 / 8.3),
+// 6912 -> 2560 5.0 / 6.2 / 7.6 / 8.8 / 9.9 (6.7 / 7.0 / 7.7 / 8.6 / 10.0), 2560 -> 13824 5.7 / 6.5 / 7.5 / 8.7 / 9.7 (10.7 / 12.1 / 14.8 / 19.6 / 22.1).
 constexpr int GEMV_SELF_SUPER = 16;       // super-steps at most = wavefronts of a block
+static_assert(GEMV_SELF_SUPER <= 4 * GEMV_WAVE_GROUPS, "as many groups as with_wave_groups knows");
 constexpr int GEMV_SELF_PITCH = 512 + 16; // bytes between the token rows of a wavefront's part of LDS
-constexpr size_t gemv_self_lds(int64_t tokens, int nwaves, int rt) { return (size_t)nwaves * ((size_t)tokens * GEMV_SELF_PITCH + rt * 1024); }
+constexpr size_t gemv_self_lds(int64_t tokens, int nwaves, int ss, int rt) { return (size_t)nwaves * ss * (size_t)tokens * GEMV_SELF_PITCH + gemv_red_lds(nwaves, rt); }
 
 __device__ __forceinline__ uint32_t max_u16x2(uint32_t a, uint32_t b)
 {
     return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(ushort2_t, a), __builtin_bit_cast(ushort2_t, b)));
 }
-template <int CTRL> __device__ __forceinline__ uint32_t dpp_max_u16x2(uint32_t x)
+template <int CTRL> __device__ __forceinline__ uint32_t dpp_max_u16x2(uint32_t mine, uint32_t theirs)
 {
-    return max_u16x2(x, (uint32_t)__builtin_amdgcn_mov_dpp((int)x, CTRL, 0xf, 0xf, true));
+    return max_u16x2(mine, (uint32_t)__builtin_amdgcn_mov_dpp((int)theirs, CTRL, 0xf, 0xf, true));
+}
+// Exchange between two lanes of which one keeps the first half of the registers and the other (upper) the second: half as
+// many registers, each the maximum over both lanes.
+template <int CTRL, int H> __device__ __forceinline__ void halve_max_u16x2(uint32_t *m, bool upper)
+{
+#pragma unroll
+    for (int j = 0; j < H; ++j) m[j] = dpp_max_u16x2<CTRL>(upper ? m[j + H] : m[j], upper ? m[j] : m[j + H]);
 }
 // largest magnitude patterns of the even and of the odd ones of eight bf16 values
 __device__ __forceinline__ uint32_t absmax_pair_bf16x8(const uint4 &d)
@@ -449,12 +498,15 @@ __device__ __forceinline__ uint32_t absmax_pair_bf16x8(const uint4 &d)
     return max_u16x2(max_u16x2(d.x & 0x7fff7fffu, d.y & 0x7fff7fffu), max_u16x2(d.z & 0x7fff7fffu, d.w & 0x7fff7fffu));
 }
 
-template <int FORM, int RT, int NI, int TM>
-__global__ void __launch_bounds__(1024) gemv_self_kernel(GemvTable<NI> tab)
+// TM = token slots, SS = super-steps per wavefront: wavefront w owns the super-steps w, w + nwaves, ...  Up to four slots the
+// registers are held to what lets a multiprocessor run two blocks of 16 wavefronts (8192 -> 16384 at one token: 12.5 us without).
+template <int FORM, int RT, int NI, int TM, int SS>
+__global__ void __launch_bounds__(1024, TM * SS <= 4 ? 8 : 4) gemv_self_kernel(GemvTable<NI> tab)
 {
     constexpr int CB = FORM == GEMV_1OF4 ? 16 : 32;
-    extern __shared__ __attribute__((aligned(16))) int8_t dyn[];      // [wavefront][tokens][pitch], then the partial accumulators
-    __shared__ __attribute__((aligned(16))) uint32_t amax[TM][4 * GEMV_SELF_SUPER];   // [token][wavefront, row of 16 lanes]
+    extern __shared__ __attribute__((aligned(16))) int8_t dyn[];      // [wavefront][super-step][tokens][pitch], then the partial accumulators
+    constexpr int PAIRS = TM <= 2 ? 1 : TM <= 4 ? 2 : TM <= 8 ? 4 : 8;
+    __shared__ __attribute__((aligned(16))) uint32_t amax[PAIRS][4 * GEMV_SELF_SUPER + 4];   // [tokens 2 p, 2 p + 1][wavefront, row of 16 lanes]
     const GemvItem &it = tab.it[blockIdx.y];
     const int row0 = (int)blockIdx.x * 16 * RT;
     if (row0 >= it.d_out) return;
@@ -462,69 +514,109 @@ __global__ void __launch_bounds__(1024) gemv_self_kernel(GemvTable<NI> tab)
     const int r = lane & 15, c4 = lane >> 4, T = it.tokens;
     const uint32_t ones = vgpr_ones();
     const int K = it.d_in, nchunks = K / CHUNK, nvec = it.d_x / 8;
-    const uint8_t *wrow[RT];
+    // The token values first, they are needed first, then the weights, without a branch in between: behind a branch the wait
+    // for the first value would be one for everything.  Rows past the tokens lie past the end of the buffer, where a load
+    // returns zeros and fetches nothing.
+    const auto rows = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint4 *>(it.X), (short)0, T * nvec * 16, 0x00027000);
+    uint4 xv[SS][TM];
 #pragma unroll
-    for (int a = 0; a < RT; ++a) {
-        const int row = row0 + 16 * a + r;
-        wrow[a] = it.packed + (int64_t)(row < it.d_out ? row : it.d_out - 1) * nchunks * CB;
+    for (int ss = 0; ss < SS; ++ss) {
+        const int vec = 64 * (wave + ss * nwaves) + lane;
+        const uint32_t at = 16u * (uint32_t)(vec < nvec ? vec : nvec - 1);   // past the row its last vector again: the maximum is the same, the codes are zero
+#pragma unroll
+        for (int t = 0; t < TM; ++t)
+            xv[ss][t] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rows, at + 16u * (uint32_t)(t * nvec), 0, 0));
     }
-    // the token values first: they are needed first
-    const int vec = 64 * wave + lane;
-    const uint4 *xp = it.X + (vec < nvec ? vec : nvec - 1);   // past the row its last vector again: the maximum is the same, the codes are zero
-    uint4 xv[TM];
+    constexpr int WS = SS < 2 || (RT == 2 && TM * SS <= 4) ? 1 : 2;   // super-steps whose weights are asked for ahead
+    uint4 idx4[WS][RT], code4[WS][RT];
+    const uint8_t *const wbase = it.packed + (int64_t)row0 * nchunks * CB;
+    const auto chunk_of = [&](int ss) { return 4 * (wave + ss * nwaves) + c4; };
+    const auto fetch = [&](int ss) {
 #pragma unroll
-    for (int t = 0; t < TM; ++t)
-        if (t < T) xv[t] = xp[(int64_t)t * nvec];
-    uint4 idx4[RT], code4[RT];
-    gemv_fetch<FORM, RT>(wrow, wave, c4, nchunks, idx4, code4);
-    const float gamma = *it.gamma;
-    // largest magnitudes, two tokens in a register; rows of 16 lanes are reduced here, the rest through LDS
-#pragma unroll
-    for (int t = 0; t < TM; t += 2) {
-        if (t >= T) break;
-        const uint32_t m0 = absmax_pair_bf16x8(xv[t]), m1 = t + 1 < T ? absmax_pair_bf16x8(xv[t + 1 < TM ? t + 1 : t]) : 0u;
-        uint32_t m = max_u16x2(__builtin_amdgcn_perm(m1, m0, 0x05040100u), __builtin_amdgcn_perm(m1, m0, 0x07060302u));   // low halves, high halves
-        m = dpp_max_u16x2<0xb1>(m);    // quad_perm 1 0 3 2
-        m = dpp_max_u16x2<0x4e>(m);    // quad_perm 2 3 0 1
-        m = dpp_max_u16x2<0x141>(m);   // row_half_mirror
-        m = dpp_max_u16x2<0x140>(m);   // row_mirror
-        if (r == 0) {
-            amax[t][4 * wave + c4] = m & 0xffffu;
-            if (t + 1 < TM) amax[t + 1][4 * wave + c4] = m >> 16;
+        for (int a = 0; a < RT; ++a) {
+            // rows past the end are computed and dropped; the offsets within the block's rows (at most 256 chunks each) are small
+            const int row = 16 * a + r < it.d_out - row0 ? 16 * a + r : it.d_out - row0 - 1;
+            const uint8_t *src = wbase + (uint32_t)(row * nchunks + (chunk_of(ss) < nchunks ? chunk_of(ss) : nchunks - 1)) * (uint32_t)CB;
+            idx4[ss % WS][a] = *reinterpret_cast<const uint4 *>(src);
+            code4[ss % WS][a] = make_uint4(0, 0, 0, 0);
+            if constexpr (FORM != GEMV_1OF4) code4[ss % WS][a] = *reinterpret_cast<const uint4 *>(src + 16);
         }
+    };
+#pragma unroll
+    for (int ss = 0; ss < WS; ++ss) fetch(ss);
+    const float gamma = *it.gamma;
+    // largest magnitudes, two tokens in a register; rows of 16 lanes are reduced here, the rest through LDS.  Lanes that exchange
+    // keep half of the pairs each, so that a row ends with pair r % PAIRS in lane r: for 16 tokens 30 operations where
+    // reducing every pair over all lanes takes 64 (and eight stores).
+    uint32_t m[PAIRS];
+#pragma unroll
+    for (int p = 0; p < PAIRS; ++p) {
+        m[p] = 0;
+        if (2 * p >= TM || 2 * p >= T) continue;
+        uint32_t m0 = 0, m1 = 0;
+#pragma unroll
+        for (int ss = 0; ss < SS; ++ss) {
+            const uint32_t a0 = absmax_pair_bf16x8(xv[ss][2 * p < TM ? 2 * p : 0]), a1 = absmax_pair_bf16x8(xv[ss][2 * p < TM ? 2 * p + 1 : 1]);
+            m0 = ss ? max_u16x2(m0, a0) : a0;
+            m1 = ss ? max_u16x2(m1, a1) : a1;
+        }
+        m[p] = max_u16x2(__builtin_amdgcn_perm(m1, m0, 0x05040100u), __builtin_amdgcn_perm(m1, m0, 0x07060302u));   // low halves, high halves
     }
+    if constexpr (PAIRS >= 8) halve_max_u16x2<0x141, 4>(m, (r & 4) != 0);   // row_half_mirror
+    if constexpr (PAIRS >= 4) halve_max_u16x2<0x4e, 2>(m, (r & 2) != 0);    // quad_perm 2 3 0 1
+    if constexpr (PAIRS >= 2) halve_max_u16x2<0xb1, 1>(m, (r & 1) != 0);    // quad_perm 1 0 3 2
+    if constexpr (PAIRS < 2) m[0] = dpp_max_u16x2<0x121>(m[0], m[0]);       // row_ror 1, 2, 4, 8: lanes with the same pair
+    if constexpr (PAIRS < 4) m[0] = dpp_max_u16x2<0x122>(m[0], m[0]);
+    if constexpr (PAIRS < 8) m[0] = dpp_max_u16x2<0x124>(m[0], m[0]);
+    m[0] = dpp_max_u16x2<0x128>(m[0], m[0]);
+    if (r < PAIRS) amax[r][4 * wave + c4] = m[0];
     __syncthreads();
     // lane: the scale of token lane % 16
     float s;
     {
         // quarter c4 reads what wavefronts c4, c4 + 4, ... found (past the last one that one again), then the quarters meet
-        const uint4 *col = reinterpret_cast<const uint4 *>(amax[r < T ? r : 0]);
-        uint32_t m = 0;
+        const uint4 *col = reinterpret_cast<const uint4 *>(amax[(r >> 1) % PAIRS]);
+        uint32_t m2 = 0;
+        with_wave_groups(nwaves, [&](auto groups) {
+            uint4 v[groups()];
 #pragma unroll
-        for (int i = 0; i < GEMV_SELF_SUPER / 4; ++i) {
-            if (4 * i >= nwaves) break;
-            const uint4 v = col[4 * i + c4 < nwaves ? 4 * i + c4 : nwaves - 1];
-            const uint32_t a = v.x > v.y ? v.x : v.y, b = v.z > v.w ? v.z : v.w, c = a > b ? a : b;
-            m = c > m ? c : m;
-        }
+            for (int i = 0; i < groups(); ++i) v[i] = col[i + 1 < groups() || 4 * i + c4 < nwaves ? 4 * i + c4 : nwaves - 1];
+#pragma unroll
+            for (int i = 0; i < groups(); ++i) m2 = max_u16x2(m2, max_u16x2(max_u16x2(v[i].x, v[i].y), max_u16x2(v[i].z, v[i].w)));
+        });
+        uint32_t m = r & 1 ? m2 >> 16 : m2 & 0xffffu;
         const auto x16 = __builtin_amdgcn_permlane16_swap(m, m, false, false);   // neighbouring quarters
         m = x16[0] > x16[1] ? x16[0] : x16[1];
         const auto x32 = __builtin_amdgcn_permlane32_swap(m, m, false, false);   // halves of the wavefront
         m = x32[0] > x32[1] ? x32[0] : x32[1];
         s = scale_from_absmax_bits(m);
     }
-    int8_t *const xs = dyn + wave * T * GEMV_SELF_PITCH;
+    int8_t *const xs = dyn + wave * SS * T * GEMV_SELF_PITCH;
 #pragma unroll
-    for (int t = 0; t < TM; ++t)
-        if (t < T)
-            *reinterpret_cast<uint2 *>(xs + t * GEMV_SELF_PITCH + 8 * lane) =
-                quantize_bf16x8(xv[t], __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(s), t)));
+    for (int ss = 0; ss < SS; ++ss)
+#pragma unroll
+        for (int t = 0; t < TM; ++t)
+            if (t < T)
+                *reinterpret_cast<uint2 *>(xs + (ss * T + t) * GEMV_SELF_PITCH + 8 * lane) =
+                    quantize_bf16x8(xv[ss][t], __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(s), t)));
     v4i acc[RT];
 #pragma unroll
     for (int a = 0; a < RT; ++a) acc[a] = v4i{0, 0, 0, 0};
-    // what the wavefront wrote itself: its LDS operations complete in order
-    gemv_super_step<FORM, RT>(idx4, code4, xs + (r < T ? r : 0) * GEMV_SELF_PITCH, c4, ones, [](int k) { return k; }, acc);
-    gemv_finish<RT>(it, acc, reinterpret_cast<v4i *>(dyn + nwaves * T * GEMV_SELF_PITCH), row0, __fdiv_rn(gamma, s), wave, nwaves, lane);
+#pragma unroll
+    for (int ss = 0; ss < SS; ++ss) {
+#pragma unroll
+        for (int a = 0; a < RT; ++a) {   // past the row zero codes (the code words of 1:4 are the upper half of its one vector)
+            if (chunk_of(ss) < nchunks) continue;
+            if constexpr (FORM == GEMV_DENSE) idx4[ss % WS][a] = make_uint4(0, 0, 0, 0);
+            else if constexpr (FORM == GEMV_1OF4) idx4[ss % WS][a].z = idx4[ss % WS][a].w = 0;
+            code4[ss % WS][a] = make_uint4(0, 0, 0, 0);
+        }
+        // what the wavefront wrote itself: its LDS operations complete in order
+        gemv_super_step<FORM, RT, RT == 2 && TM * SS <= 4>(idx4[ss % WS], code4[ss % WS], xs + (ss * T + (r < T ? r : 0)) * GEMV_SELF_PITCH, c4, ones, [](int k) { return k; }, acc);
+        if constexpr (WS < SS) __builtin_amdgcn_sched_barrier(0);   // not in front of the step: no registers for it there
+        if (ss + WS < SS) fetch(ss + WS);
+    }
+    gemv_finish<RT>(it, acc, reinterpret_cast<v4i *>(dyn + nwaves * SS * T * GEMV_SELF_PITCH), row0, __fdiv_rn(gamma, s), wave, nwaves, lane);
 }
 
 // ---- streaming decode GEMV for grouped calls ---------------------------------------------------
@@ -1132,18 +1224,19 @@ static bool stream_is_capturing(hipStream_t stream)
 }
 
 constexpr size_t GEMV_SELF_LDS = 152 * 1024;   // next to 4 KB of maxima
-// Row tiles of 16 from which a block takes two of them: a multiprocessor then has more than one block either way, and the
-// quantizer's work is done half as often (480 tiles, eight tokens: 5.9 us against 6.4; 160 tiles, one token: 4.1 against 3.7).
-constexpr int64_t GEMV_PAIR_TILES = 400;
+// Row tiles of 16 from which a block takes two of them, in sixteenths of a multiprocessor: it then has more than one block either
+// way, and the quantizer's work is done half as often (480 tiles, eight tokens: 5.9 us against 6.4; 160 tiles, one token: 4.1
+// against 3.7).
+constexpr int64_t GEMV_PAIR_TILES = 25;
 // Every block quantizes all token rows, 0.04 to 0.06 us per 1000 values and block of a multiprocessor, where a launch of the
-// quantizer in front costs 2.2 us on the device and another launch on the host.  Measured at 16 tokens: 4096 -> 4096 7.3 us
-// against 8.0, 8192 -> 4096 12.4 against 12.3, 4096 -> 2 x 14336 (three blocks per multiprocessor) 29 against 20, at eight tokens 14.5
-// against 15.8.
+// quantizer in front costs 2.2 us on the device and another launch on the host.  Measured in this form and with the quantizer in
+// front: 8192 -> 8192 9.9 us against 11.2 at eight tokens, 13.3 against 13.4 at 16; 4096 -> 28672 (three blocks per multiprocessor)
+// 13.0 against 16.2 at eight, 25.5 against 20.6 at 16; 8192 -> 28672 33 against 29 at eight.
 constexpr int64_t GEMV_SELF_VALUES = 16 * 8192;
 
 // one launch of the row-tile kernels; tm = 0: on quantized activations, else the token slots of the kernel that quantizes
 template <int FORM, int RT, int NI>
-static sbn_status launch_gemv_rows(int n, const LinearItem *items, int nwaves, int tm, hipStream_t stream)
+static sbn_status launch_gemv_rows(int n, const LinearItem *items, int nwaves, int ss, int tm, hipStream_t stream)
 {
     GemvTable<NI> tab;
     int blocks = 0;
@@ -1158,21 +1251,30 @@ static sbn_status launch_gemv_rows(int n, const LinearItem *items, int nwaves, i
     for (int i = n; i < NI; ++i) tab.it[i] = tab.it[0];
     const dim3 grid(blocks, n), block(64 * nwaves);
     if (tm == 0) {
-        hipLaunchKernelGGL((gemv_smfmac_kernel<FORM, RT, NI>), grid, block, (size_t)nwaves * RT * 1024, stream, tab);
+        hipLaunchKernelGGL((gemv_smfmac_kernel<FORM, RT, NI>), grid, block, gemv_red_lds(nwaves, RT), stream, tab);
         return check_launch("gemv_smfmac_kernel");
     }
-    static thread_local bool raised = false;
-    if (!raised) {
-        for (const void *k : {reinterpret_cast<const void *>(&gemv_self_kernel<FORM, RT, NI, 2>), reinterpret_cast<const void *>(&gemv_self_kernel<FORM, RT, NI, 16>)}) {
-            hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)GEMV_SELF_LDS);
+    const size_t lds = gemv_self_lds(tokens, nwaves, ss, RT);
+    auto launch = [&](auto slots, auto steps) -> sbn_status {
+        constexpr auto kernel = &gemv_self_kernel<FORM, RT, NI, slots(), steps()>;
+        static thread_local bool raised = false;   // one for each kernel: the types of the arguments tell them apart
+        if (!raised) {
+            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)GEMV_SELF_LDS);
             if (e != hipSuccess) { set_hip_error(e, "hipFuncSetAttribute"); return SBN_EHIP; }
+            raised = true;
         }
-        raised = true;
-    }
-    const size_t lds = gemv_self_lds(tokens, nwaves, RT);
-    if (tm == 2) hipLaunchKernelGGL((gemv_self_kernel<FORM, RT, NI, 2>), grid, block, lds, stream, tab);
-    else hipLaunchKernelGGL((gemv_self_kernel<FORM, RT, NI, 16>), grid, block, lds, stream, tab);
-    return check_launch("gemv_self_kernel");
+        hipLaunchKernelGGL(kernel, grid, block, lds, stream, tab);
+        return check_launch("gemv_self_kernel");
+    };
+    const std::integral_constant<int, 1> one;
+    const std::integral_constant<int, 2> two;
+    const std::integral_constant<int, 4> four;
+    if (ss > 1) return tm == 2 ? (ss == 2 ? launch(two, two) : launch(two, four)) : ss == 2 ? launch(four, two) : launch(four, four);
+    return tm == 2   ? launch(two, one)
+           : tm == 4 ? launch(four, one)
+           : tm == 8 ? launch(std::integral_constant<int, 8>(), one)
+           : tm == 12 ? launch(std::integral_constant<int, 12>(), one)
+                      : launch(std::integral_constant<int, 16>(), one);
 }
 
 template <int FORM>
@@ -1307,18 +1409,23 @@ static sbn_status launch_gemv_as(int count, const LinearItem *items, hipStream_t
         }
         // one wavefront per super-step up to 16, so that every wavefront has loads in flight at once
         const int nwaves = most_super < GEMV_SELF_SUPER ? most_super : GEMV_SELF_SUPER;
-        const int rt = tiles >= GEMV_PAIR_TILES ? 2 : 1;
+        const int rt = 16 * tiles >= GEMV_PAIR_TILES * device_cus() ? 2 : 1;
         const int64_t per_cu = std::max<int64_t>(1, tiles / rt / device_cus());
-        if (most_super > GEMV_SELF_SUPER || most_tokens * most_super * 512 * per_cu > GEMV_SELF_VALUES ||
-            gemv_self_lds(most_tokens, nwaves, rt) > GEMV_SELF_LDS)
+        // Longer rows: two or four super-steps per wavefront while their values fit the registers, up to four tokens.  us in this
+        // form and with the separate quantizer: 14336 -> 4096 at 1 / 2 / 3 tokens 7.7 / 8.4 / 9.3 against 10.3 / 10.7 / 11.1, 28672 -> 8192
+        // 17 / 18 / 20 against 44 / 46 / 49 (the other form reads rows this long past the vector L1 again and again); but with two row tiles
+        // per block and two super-steps, at one token 9216 -> 16384 15.1 against 16.6, at three 21.2 against 17.4.
+        const int rounds = (int)ceil_div(most_super, GEMV_SELF_SUPER), ss = rounds <= 2 ? rounds : 4;
+        if (rounds > 4 || (rounds > 1 && most_tokens > (rounds == 2 && rt == 2 ? 2 : 4)) || most_tokens * most_super * 512 * per_cu > GEMV_SELF_VALUES ||
+            gemv_self_lds(most_tokens, nwaves, ss, rt) > GEMV_SELF_LDS)
             self_quant = false;
         if (!self_quant) {
             sbn_status st = quantize_run(first, n);
             if (st != SBN_OK) return st;
         }
-        const int tm = !self_quant ? 0 : most_tokens <= 2 ? 2 : 16;
-        sbn_status st = n <= GEMV_FEW ? (rt == 2 ? launch_gemv_rows<FORM, 2, GEMV_FEW>(n, items + first, nwaves, tm, stream) : launch_gemv_rows<FORM, 1, GEMV_FEW>(n, items + first, nwaves, tm, stream))
-                                      : (rt == 2 ? launch_gemv_rows<FORM, 2, GEMV_MAX_ITEMS>(n, items + first, nwaves, tm, stream) : launch_gemv_rows<FORM, 1, GEMV_MAX_ITEMS>(n, items + first, nwaves, tm, stream));
+        const int tm = !self_quant ? 0 : most_tokens <= 2 ? 2 : most_tokens <= 4 ? 4 : most_tokens <= 8 ? 8 : most_tokens <= 12 ? 12 : 16;
+        sbn_status st = n <= GEMV_FEW ? (rt == 2 ? launch_gemv_rows<FORM, 2, GEMV_FEW>(n, items + first, nwaves, ss, tm, stream) : launch_gemv_rows<FORM, 1, GEMV_FEW>(n, items + first, nwaves, ss, tm, stream))
+                                      : (rt == 2 ? launch_gemv_rows<FORM, 2, GEMV_MAX_ITEMS>(n, items + first, nwaves, ss, tm, stream) : launch_gemv_rows<FORM, 1, GEMV_MAX_ITEMS>(n, items + first, nwaves, ss, tm, stream));
         if (st != SBN_OK) return st;
         first += n;
     }
