@@ -59,7 +59,8 @@ typedef enum { SBN_F32 = 0, SBN_BF16 = 1 } sbn_dtype;
 typedef enum {
     SBN_PATH_AUTO = 0,       /* the kernels of GEMV for tokens <= 16, of SMFMAC for more, whatever d_in is: where it is no
                                 multiple of 128 the int8 rows lie in the workspace as rows of whole chunks (the packed
-                                form is padded to them with zero codes already) */
+                                form is padded to them with zero codes already).  DENSE_MFMA at 64, 192 and 320 with
+                                outputs by the tens of millions */
     SBN_PATH_GEMV = 1,       /* decode kernel: streams the packed weights once; tokens <= 16, d_in % 128 == 0.  2:4 runs
                                 on the sparse instruction and N = M (dense 2-bit codes) on the dense one as stored; 1:4
                                 is read as stored too (one bit per weight: the kernel builds the sparse instruction's

@@ -48,8 +48,21 @@ static sbn_path resolve_path(sbn_path path, int64_t tokens)
     // decode through the streaming kernel and beyond decode sizes through the same sparse instruction, issued twice
     // per group of four weights (positions 0, 1 and positions 2, 3 - the matrix-core time of a dense int8 product, at
     // a quarter of its weight bytes).  An input dimension that is no multiple of 128 takes the same kernels on rows of
-    // whole chunks (50 tokens, 1000 -> 1500: 414 us on the plain integer kernel that served it before, 12 us here).
+    // whole chunks (50 tokens, 1000 -> 1500: 414 us on the plain integer kernel that served it before, 8.9 us a call here).
     return path != SBN_PATH_AUTO ? path : tokens <= 16 ? SBN_PATH_GEMV : SBN_PATH_SMFMAC;
+}
+
+// An input dimension of 64, 192 or 320 with so many outputs that little but their stores is left: the dense path, which takes
+// halves of a chunk as they are and stores through the cache, is faster there.  us on the sparse path and on the dense one:
+// 32768 tokens -> 4096 at 64 / 192 / 320, 2:4 152 / 156 / 157 against 117 / 131 / 143; 12288 -> 8192 82 / 85 / 92 against 81 / 94 / 107;
+// 64 -> 8192 at 8192 tokens, N = M 59 against 57.  Weights that have to be rewritten for the sparse path: 2:8, 64 -> 2560 at 4096
+// tokens 19.6 against 18.4, at 1000 11.7 / 13.8; 6:8, 320 -> 8192 at 8192 tokens 77.4 / 75.7.
+static bool dense_path_is_faster(int64_t tokens, int64_t d_out, int64_t d_in, bool rewritten, bool sparse_form)
+{
+    if (d_in % 128 != 64 || d_in > 320) return false;
+    const int64_t outputs = tokens * d_out, mi = 1 << 20;
+    if (d_in == 64) return outputs >= (rewritten ? 8 * mi : 64 * mi);
+    return outputs >= (rewritten && !sparse_form ? 64 * mi : 112 * mi);
 }
 
 }  // namespace sbn
@@ -238,6 +251,8 @@ static sbn_status linear_one(const LinearItem &it_in, const Pattern &pat, sbn_pa
     const bool chosen_here = path == SBN_PATH_AUTO;
     path = resolve_path(path, it.tokens);
     const bool sparse_form = is24 || embeds_in_2of4(pat);   // runs on the sparse instruction (after a rewrite unless 2:4)
+    if (chosen_here && !activations_only && path == SBN_PATH_SMFMAC && dense_path_is_faster(it.tokens, it.d_out, it.d_in, !is24 && pat.N != pat.M, sparse_form))
+        path = SBN_PATH_DENSE_MFMA;
     const bool one4_decode = pat.N == 1 && pat.M == 4 && path == SBN_PATH_GEMV;   // the decode kernels read 1:4 as stored
     if (path == SBN_PATH_GEMV && it.tokens > 16) return SBN_EUNSUPPORTED;
     if ((path == SBN_PATH_GEMV || path == SBN_PATH_SMFMAC) && it.d_in % CHUNK != 0 && !chosen_here) return SBN_EUNSUPPORTED;

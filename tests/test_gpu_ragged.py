@@ -60,3 +60,21 @@ def test_ragged_input_dimension_static_scratch(N, M, tokens):
     torch.cuda.synchronize()
     y, *_ = oracle.sparse_ternary_linear(X.float().numpy(), Weff, g)
     assert_rel(Y.cpu().numpy(), y, Y_TOL, "Y")
+
+
+@pytest.mark.parametrize("N,M,tokens,d_out,d_in", [(2, 8, 4099, 2050, 64), (2, 8, 4080, 2050, 64),      # 8 Mi outputs: the dense path, and just below it
+                                                   (6, 8, 8209, 8190, 192), (6, 8, 8190, 8190, 192),    # 64 Mi
+                                                   (2, 4, 8209, 8190, 64), (2, 4, 14400, 8190, 320), (2, 4, 14300, 8190, 320)])   # 64 and 112 Mi
+def test_half_chunks_with_many_outputs(N, M, tokens, d_out, d_in):
+    s = sbn()
+    W = sbn_synth.latent_weight(d_out, d_in, 4200 + d_in)
+    X = sbn_synth.activations(tokens, d_in, 4201)
+    packed, gamma = hip_pack(W, N, M)
+    _, g, Weff, _ = oracle_pack(W, N, M)
+    Y = torch.full((tokens, d_out), float("nan"), dtype=torch.float32, device=DEV)
+    ws = s.new_workspace(s.sbn_workspace_bytes(s.SBN_OP_LINEAR, tokens, d_out, d_in, N, M))
+    s.sbn_sparse_ternary_linear(X.to(DEV), packed, gamma, Y, N, M, ws)
+    rows = np.unique(np.concatenate([np.arange(70), np.arange(tokens - 140, tokens), np.arange(0, tokens, 97)]))
+    y, *_ = oracle.sparse_ternary_linear(X[torch.from_numpy(rows)].float().numpy(), Weff, g)
+    assert torch.isfinite(Y).all()
+    assert_rel(Y[torch.from_numpy(rows).to(DEV)].cpu().numpy(), y, Y_TOL, "Y")
