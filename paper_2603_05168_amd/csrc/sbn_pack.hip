@@ -1354,8 +1354,14 @@ template <typename WT, int N, int M, bool FLIPS> static constexpr auto pack_stre
 struct PackFast {
     int (*max_units)(int &grid);   // most units per matrix the single-read kernel takes, and its grid (0: not at all)
     void (*stream)(int grid, hipStream_t stream, const PackTable &tab, const PackSync &sync);
-    void (*last_pass)(int grid, hipStream_t stream, const PackTable &tab, const float *theta, uint32_t *unit_flips);
+    void (*last_pass)(int grid, hipStream_t stream, const PackTable &tab, const float *theta, uint32_t *unit_flips);   // null: pack_kernel
+    int few_matrices;   // at most so many matrices of fewer than PACK_FEW_UNITS units in all take three passes with pack_kernel
 };
+// A launch of few units is the chain of one of them, which is the shorter the less of a unit a thread has to do; the blocks of
+// pack_kernel take an eighth of one.  us in the single-read form and in three passes: fp32 2:4 64 x 128 11.6 against 10.0, 1024 x 1024
+// 12.9 / 11.5, 1536 x 1536 (144 units) 13.1 / 12.7, 8 matrices of 128 x 128 12.5 / 11.8, 70 of them 12.9 / 13.2; 6:8 fp32 1024 x 1024 13.6 / 12.5,
+// 1536 x 1536 13.6 / 14.2; N = M 1024 x 1024 bf16 11.3 / 11.0, two of 128 x 128 9.8 / 10.3; the other forms are faster from one unit on.
+constexpr int PACK_FEW_UNITS = 128;
 
 template <typename WT, int N, int M> struct PackFastOf {
     // flips are counted on bf16 at the patterns that keep two of four or fewer
@@ -1390,7 +1396,11 @@ template <typename WT, int N, int M> struct PackFastOf {
             }
         hipLaunchKernelGGL((pack_fast_kernel<WT, N, M, false>), dim3(grid), dim3(256), 0, stream, tab, theta, unit_flips);
     }
-    static constexpr PackFast table{max_units, stream, last_pass};
+    static constexpr bool F32 = sizeof(WT) == 4;
+    static constexpr int FEW = F32 && (N == 6 || (N == 2 && M == 4)) ? 32 : PackCompact<WT, N, M>::WHOLE ? 1 : 0;
+    // (fp32 N = M: the last pass has nothing to rank, and pack_kernel reads the matrix a second time as fast: 16384 x 4096 90.7 us
+    // against 93.5, 24576 x 8192 305 against 321)
+    static constexpr PackFast table{max_units, stream, F32 && N == M ? nullptr : last_pass, FEW};
 };
 
 // null: no fast kernels for this pattern.  N = M is one form whatever M
@@ -1455,6 +1465,7 @@ sbn_status launch_pack(int count, const PackItem *items, sbn_dtype wdt, const Pa
         double *part = partials + sum_base;
         float *th = theta + first;
         const PackFast *fast = !flat_ok ? nullptr : wdt == SBN_BF16 ? pack_fast_of<uint16_t>(pat) : pack_fast_of<float>(pat);
+        if (fast && fb[n] < PACK_FEW_UNITS && n <= fast->few_matrices) fast = nullptr;
         sbn_status st = SBN_OK;
         // single-read form: persistent grid of as many blocks as the device holds; no matrix may have more units than
         // these have in flight
@@ -1495,7 +1506,7 @@ sbn_status launch_pack(int count, const PackItem *items, sbn_dtype wdt, const Pa
         hipLaunchKernelGGL(absmean_finalize_kernel, dim3(n), dim3(256), 0, stream, tab, part, th);
         st = check_launch("absmean_finalize_kernel");
         if (st != SBN_OK) return st;
-        if (fast) {
+        if (fast && fast->last_pass) {
             for (int i = 0; i < n; ++i) tab.pack_block0[i] = fb[i];
             tab.pack_block0[n] = fb[n];
             fast->last_pass(fb[n], stream, tab, th, unit_flips);

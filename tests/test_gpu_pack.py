@@ -364,9 +364,26 @@ def test_single_read_pack_matrix_of_more_units_than_blocks(dtype, N, M, shape):
     check(sbn_synth.latent_weight(*shape, 1950, dtype=dtype), N, M)
 
 
+@pytest.mark.parametrize("dtype,N,M", STREAM_FORMS)
+@pytest.mark.parametrize("shapes", [[(127, 16384)], [(128, 16384)], [(120, 384)] * 32, [(120, 384)] * 33, [(64, 128)] * 2])
+def test_pack_of_few_units(dtype, N, M, shapes):
+    # the line between three passes and the single-read form: 127 and 128 units, 32 and 33 matrices, one and two
+    s = sbn()
+    Ws = [sbn_synth.latent_weight(*sh, 1970 + i, dtype=dtype) for i, sh in enumerate(shapes)]
+    packed = [torch.zeros(s.sbn_packed_bytes(*sh, N, M), dtype=torch.uint8, device=DEV) for sh in shapes]
+    gammas = torch.zeros(len(Ws), dtype=torch.float32, device=DEV)
+    ws = s.new_workspace(s.sbn_workspace_bytes(s.SBN_OP_QUANTIZE_MASK_PACK, len(Ws), *shapes[0], N, M))
+    s.sbn_quantize_mask_pack_batched([W.to(DEV) for W in Ws], N, M, packed, [gammas[i:i + 1] for i in range(len(Ws))], ws)
+    torch.cuda.synchronize()
+    for i, W in enumerate(Ws):
+        ref, g, *_ = oracle_pack(W, N, M)
+        assert gammas[i].item() == g
+        assert np.array_equal(packed[i].cpu().numpy(), ref)
+
+
 @pytest.mark.parametrize("value", [float("nan"), float("inf"), float("-inf"), 3e38])
-@pytest.mark.parametrize("dtype,N,M,d_in", [(torch.bfloat16, 2, 4, 384), (torch.float32, 6, 8, 384),       # single-read form
-                                            (torch.bfloat16, 2, 4, 200), (torch.float32, 3, 8, 384)])      # three passes
+@pytest.mark.parametrize("dtype,N,M,d_in", [(torch.bfloat16, 2, 4, 384), (torch.float32, 1, 4, 384),       # single-read form
+                                            (torch.bfloat16, 2, 4, 200), (torch.float32, 6, 8, 384)])      # three passes
 def test_pack_of_weights_that_are_not_finite_ends(dtype, N, M, d_in, value):
     # a diverged matrix must not keep the call from ending: its scale says so (3e38 alone leaves it finite), its neighbours in
     # the batch are packed as ever, and every row is a valid packed form
