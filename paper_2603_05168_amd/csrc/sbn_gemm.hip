@@ -1104,14 +1104,14 @@ sbn_status launch_gemm_pieces(int count, const LinearItem *items, bool dense_cod
 }
 
 // Estimated time in us of a call on the streaming kernel or the pieces, next to which gemm_tile_estimate_us stands; every
-// problem counts with its own input dimension.  Measured, weights from memory, quantizer not included:
+// problem counts with its own input dimension.  Measured behind the quantizer, weights from memory, quantizer not included:
 //   streaming kernel (<= 64 tokens)  one strip of 128 rows per block: 4 us + 5 us (up to 32 tokens) or 8.5 us per 2560 weights
 //       of the input dimension; strips of 256 rows: 12.5 or 17.5 us per round of the device
 //       (16 x (2560 -> 6912) at 32 / 64 tokens: 26 / 34 us; one layer alone 10 / 14, 6912 -> 2560 18 / 27)
-//   pieces of 512 rows x 32 .. 128 tokens  3.9 us, 10.7 us (dense codes 15.3) per 2560 weights of the deepest problem, 0.78 of
+//   pieces of 512 rows x 32 .. 128 tokens  3.9 us, 10.5 us (dense codes 14.5) per 2560 weights of the deepest problem, 0.75 of
 //       that for each further unit of 32 tokens a multiprocessor has, 0.11 us per MB of outputs
-//       (2560 -> 2560 at 17 .. 1500 tokens 13.1 .. 13.9 us, 6912 -> 2560 37 .. 43, 2560 -> 6912 at 512 / 777 / 1500 / 3000
-//       tokens, up to 1 / 2 / 3 / 6 units, 17 / 19 / 24 / 47)
+//       (2560 -> 2560 at 17 .. 1500 tokens 13.2 .. 15.0 us, 6912 -> 2560 39 .. 43, 2560 -> 6912 at 512 / 777 / 1500 / 3000
+//       tokens, up to 1 / 2 / 3 / 6 units, 18 / 20 / 25 / 47)
 static float gemm_large_estimate_us(int count, const LinearItem *items, bool dense)
 {
     bool stream = true;
@@ -1134,14 +1134,14 @@ static float gemm_large_estimate_us(int count, const LinearItem *items, bool den
     }
     const float more = (float)units / (float)cus - k;
     // (768 -> 6912 at 16384 tokens and 8192 -> 768 at 17 in one call: 278 us as small tiles, 158 this way, quantizers included)
-    return 3.9f + (dense ? 15.3f : 10.7f) * (k + 0.78f * (more > 0.0f ? more : 0.0f)) + 0.11f * (float)out_mb;
+    return 3.9f + (dense ? 14.5f : 10.5f) * (k + 0.75f * (more > 0.0f ? more : 0.0f)) + 0.11f * (float)out_mb;
 }
 
 // Small block tiles where they are faster: their time grows with rows x tokens from 4.5 us on, that of the large kernels
 // starts two to five times higher and grows slower.  Over 279 calls of 17 to 16384 tokens, input dimensions 256 to 8192 and
-// one to sixteen problems, all kernels measured, the choice costs 0.7 % against the faster kernel of each (at worst 1.39, 384 tokens
-// 4096 -> 14336 with dense codes: 55 us against 40); 256 tokens, 2560 -> 6912: 12.4 us in tiles, 17.3 in pieces; 777 tokens,
-// 2560 -> 2560: 12.3 / 13.2; 1024 tokens: 14.5 / 13.2.
+// one to sixteen problems, all kernels measured, the choice costs 0.6 % against the faster kernel of each (at worst 1.40, 384 tokens
+// 4096 -> 14336 with dense codes: 56 us against 40); 256 tokens, 2560 -> 6912: 13.5 us in tiles, 17.8 in pieces; 512 tokens,
+// 2560 -> 2560: 11.1 / 14.0; 777 tokens: 14.9 / 13.8.
 bool gemm_takes_tiles(int count, const LinearItem *items, bool dense_codes)
 {
     return gemm_tile_estimate_us(count, items, dense_codes) < gemm_large_estimate_us(count, items, dense_codes);

@@ -12,12 +12,12 @@
 // (48 KB) per block, three blocks per multiprocessor, beat eight of them with one (40 against 23.5 us at 777 x 2560 ->
 // 6912).  Operands loaded straight into registers in the instruction's layout (consecutive lanes = rows) pass the vector
 // L1 at 16 bytes per clock and were up to twice as slow (57 us there).
-// Measured, us per launch, weights from memory, 2:4 (the faster of the two kernels named in launch_gemm_smfmac -> this one;
-// in brackets where that one is chosen):
-//   tokens               32           64          128          256           512           777          1024
-//   2560 -> 2560   9.6 -> 4.5  12.8 -> 4.9  13.6 -> 5.9  13.9 -> 7.3   13.8 -> 9.5   13.2 -> 12.3  (13.2 -> 14.5)
-//   2560 -> 6912  10.4 -> 5.7  14.2 -> 7.1  17.1 -> 8.3  17.3 -> 12.4  (17.2 -> 18.4) (19.0 -> 25.0) (20.8 -> 30.3)
-//   6912 -> 2560  18.4 -> 6.8  27.1 -> 8.3  40.6 -> 9.5  40.7 -> 11.9  39.1 -> 17.7  37.1 -> 23.5  37.4 -> 27.2
+// Measured, us per launch behind the quantizer, weights from memory, 2:4 (the faster of the two kernels named in
+// launch_gemm_smfmac -> this one; in brackets where that one is chosen):
+//   tokens               32           64          128          256            512            777           1024
+//   2560 -> 2560   9.7 -> 4.7  12.9 -> 5.2  13.7 -> 6.3  14.0 -> 8.3    14.0 -> 11.1  (13.8 -> 14.9) (14.1 -> 18.0)
+//   2560 -> 6912  10.4 -> 6.0  14.2 -> 7.3  17.4 -> 8.7  17.8 -> 13.5  (17.8 -> 20.5) (19.7 -> 27.2) (21.3 -> 33.4)
+//   6912 -> 2560  18.4 -> 7.0  27.1 -> 8.6  40.8 -> 10.5 41.5 -> 14.1   40.2 -> 21.1   38.8 -> 26.3   39.8 -> 29.8
 #include <algorithm>
 
 #include "sbn_internal.hpp"
@@ -42,7 +42,6 @@ template <int NI>
 struct TileTable {
     TileItem it[NI];
     int block0[NI + 1];   // first block of each problem; entries past the last problem hold the total
-    int count;
 };
 constexpr int TILE_FEW = 4, TILE_MANY = 40;
 static_assert(sizeof(TileTable<TILE_MANY>) <= 4096, "the table travels as a kernel argument");
@@ -52,16 +51,15 @@ template <int RT, int TT> struct TileShape {
     static constexpr int R = 16 * RT, T = 16 * TT;      // rows of W and tokens of a block
     static constexpr int ABYTES = R * 64, BBYTES = T * 256, STAGE = ABYTES + BBYTES;   // one stage of one wavefront: 256 weights deep
     static constexpr int PITCH = R + 4;                 // 32-bit words between the token rows of a partial tile in LDS
-    static constexpr int TP = TT < 2 ? TT : 2;          // token tiles reduced at a time
-    static_assert(16 * TP * PITCH * 4 <= STAGE, "a wavefront's partial sums fit where its operands were");
+    static_assert(T * PITCH * 4 <= STAGE, "a wavefront's partial sums fit where its operands were");
 };
 
 template <int RT, int TT, bool DENSE, int NI>
 __global__ void __launch_bounds__(64 * TILE_NW) gemm_tile_kernel(TileTable<NI> tab)
 {
     using S = TileShape<RT, TT>;
-    constexpr int R = S::R, PITCH = S::PITCH, TP = S::TP;
-    extern __shared__ __attribute__((aligned(1024))) int8_t lds[];   // [wavefront][stage], later [wavefront][16 TP tokens][PITCH] words
+    constexpr int R = S::R, PITCH = S::PITCH;
+    extern __shared__ __attribute__((aligned(1024))) int8_t lds[];   // [wavefront][stage], later [wavefront][token][PITCH] words
     __shared__ __attribute__((aligned(16))) float scale_s[S::T], bias_s[R];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = (int)blockDim.x >> 6;
     int p = 0;
@@ -193,41 +191,37 @@ __global__ void __launch_bounds__(64 * TILE_NW) gemm_tile_kernel(TileTable<NI> t
     }
     int *const red = reinterpret_cast<int *>(lds);
     constexpr int WRED = S::STAGE / 4;                 // words between two wavefronts' partial sums
-    constexpr int VPT = 16 * TP * R / 4;               // 16-byte vectors of a reduction pass
+    constexpr int VECS = S::T * R / 4;                 // 16-byte vectors of the tile's sums
 
-    // ---- the wavefronts' partial sums meet in LDS, TP token tiles at a time; whole token rows of the strip leave
+    // ---- the wavefronts' partial sums meet in LDS; whole token rows of the strip leave
     if (tid < S::T) scale_s[tid] = __fdiv_rn(gamma, pre);
     else if (tid - S::T < R) bias_s[tid - S::T] = pre;
     const bool vec = (g.d_out & 3) == 0;
 #pragma unroll
-    for (int b0 = 0; b0 < TT; b0 += TP) {
-        if (b0 > 0) __syncthreads();
+    for (int b = 0; b < TT; ++b)
 #pragma unroll
-        for (int b = 0; b < TP; ++b)
+        for (int a = 0; a < RT; ++a)   // lane: token r of its tile, rows 4 q .. + 3
+            *reinterpret_cast<v4i *>(&red[wave * WRED + (16 * b + r) * PITCH + 16 * a + 4 * q]) = acc[a][b];
+    __syncthreads();
+    for (int v = threadIdx.x; v < VECS; v += (int)blockDim.x) {
+        const int tl = v / (R / 4), o = row0 + 4 * (v % (R / 4)), t = t0 + tl;
+        if (t >= g.tokens || o >= g.d_out) continue;
+        v4i sum = *reinterpret_cast<const v4i *>(&red[tl * PITCH + 4 * (v % (R / 4))]);
+        for (int w = 1; w < nw; ++w) sum += *reinterpret_cast<const v4i *>(&red[w * WRED + tl * PITCH + 4 * (v % (R / 4))]);
+        const float scale = scale_s[tl];
+        v4f y = {(float)sum[0] * scale, (float)sum[1] * scale, (float)sum[2] * scale, (float)sum[3] * scale};
+        float *dst = g.Y + (int64_t)t * g.d_out + o;
+        if (vec) {
+            if (has_bias) y += *reinterpret_cast<const v4f *>(&bias_s[o - row0]);
+            *reinterpret_cast<v4f *>(dst) = y;
+            if (g.acc_out) *reinterpret_cast<v4i *>(g.acc_out + (int64_t)t * g.d_out + o) = sum;
+        } else {
 #pragma unroll
-            for (int a = 0; a < RT; ++a)   // lane: token r of its tile, rows 4 q .. + 3
-                *reinterpret_cast<v4i *>(&red[wave * WRED + (16 * b + r) * PITCH + 16 * a + 4 * q]) = acc[a][b0 + b];
-        __syncthreads();
-        for (int v = threadIdx.x; v < VPT; v += (int)blockDim.x) {
-            const int tl = v / (R / 4), o = row0 + 4 * (v % (R / 4)), t = t0 + 16 * b0 + tl;
-            if (t >= g.tokens || o >= g.d_out) continue;
-            v4i sum = *reinterpret_cast<const v4i *>(&red[tl * PITCH + 4 * (v % (R / 4))]);
-            for (int w = 1; w < nw; ++w) sum += *reinterpret_cast<const v4i *>(&red[w * WRED + tl * PITCH + 4 * (v % (R / 4))]);
-            const float scale = scale_s[16 * b0 + tl];
-            v4f y = {(float)sum[0] * scale, (float)sum[1] * scale, (float)sum[2] * scale, (float)sum[3] * scale};
-            float *dst = g.Y + (int64_t)t * g.d_out + o;
-            if (vec) {
-                if (has_bias) y += *reinterpret_cast<const v4f *>(&bias_s[o - row0]);
-                *reinterpret_cast<v4f *>(dst) = y;
-                if (g.acc_out) *reinterpret_cast<v4i *>(g.acc_out + (int64_t)t * g.d_out + o) = sum;
-            } else {
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    if (o + i < g.d_out) {
-                        dst[i] = has_bias ? y[i] + bias_s[o - row0 + i] : y[i];
-                        if (g.acc_out) g.acc_out[(int64_t)t * g.d_out + o + i] = sum[i];
-                    }
-            }
+            for (int i = 0; i < 4; ++i)
+                if (o + i < g.d_out) {
+                    dst[i] = has_bias ? y[i] + bias_s[o - row0 + i] : y[i];
+                    if (g.acc_out) g.acc_out[(int64_t)t * g.d_out + o + i] = sum[i];
+                }
         }
     }
 }
@@ -252,7 +246,6 @@ sbn_status launch_tile_as(int count, const LinearItem *items, int max_nw, hipStr
     }
     for (int i = count; i <= NI; ++i) tab.block0[i] = blocks;
     for (int i = count; i < NI; ++i) tab.it[i] = tab.it[0];
-    tab.count = count;
     // as few wavefronts as walk the stages in the same number of rounds, but a thread for every scale and bias of the tile (a
     // wavefront without a stage adds zeros)
     const int rounds = (int)ceil_div(most, max_nw), nw = std::max((int)ceil_div(most, rounds), (S::T + S::R + 63) / 64);
@@ -288,17 +281,20 @@ int64_t wide_tiles(const LinearItem &li) { return ceil_div(li.d_out, 64) * ceil_
 }  // namespace
 
 // Estimated time of a call on this kernel in us: the chain of one block (768 weights 3.6 us, from 1620 on 4.5); per tile of 64 x
-// 32 and multiprocessor 0.67 us for its sums and outputs and 1.54 us (dense codes 1.61) per 2560 weights for its deposits; the
-// weights once from memory at 6 TB/s.  (1728 tiles of 2560 weights 18.4 us, 6912 of 1024 31.4, 640 of 6912 17.7.)
+// 32 and multiprocessor 0.59 us for its sums and outputs and 1.46 us (dense codes 1.54) per 2560 weights for its deposits; the
+// weights once from memory at 6 TB/s; and the activations, which the quantizer or another kernel has just written and which every
+// XCD fetches from memory before its L2 has them, 1.3 us per MB up to 2.6 us, from where on the rounds of tiles cover it.  (Behind
+// a quantizer, its own time subtracted: 512 / 777 / 1024 tokens 2560 -> 2560 11.1 / 14.9 / 18.0 us; on rows that lie in the L2 9.5 / 12.3 / 14.5.)
 float gemm_tile_estimate_us(int count, const LinearItem *items, bool dense)
 {
-    double us = 0, chain = 0;
+    double us = 0, chain = 0, rows_mb = 0;
     for (int i = 0; i < count; ++i) {
         const double k = (double)items[i].d_in;
         chain = std::max(chain, 2.7 + std::min(1.8, k / 900.0));
-        us += (double)wide_tiles(items[i]) / (double)device_cus() * (0.67 + (dense ? 1.61 : 1.54) * k / 2560.0) + (double)items[i].d_out * k / 4 / 6e6;
+        rows_mb = std::max(rows_mb, 1e-6 * k * (double)items[i].tokens);
+        us += (double)wide_tiles(items[i]) / (double)device_cus() * (0.59 + (dense ? 1.54 : 1.46) * k / 2560.0) + (double)items[i].d_out * k / 4 / 6e6;
     }
-    return (float)(us + chain);
+    return (float)(us + chain + std::min(2.6, 1.3 * rows_mb));
 }
 
 // Tile shape: 64 x 32 moves the fewest bytes per product and takes over where it gives most multiprocessors a tile
