@@ -75,7 +75,9 @@ typedef enum {
                                 Decode batches (Section 3.2 measures decoding at batch 64 .. 512) take this path too:
                                 up to 64 tokens with neither bias nor acc_out a kernel that streams the weights once
                                 into registers (same instructions on 16 x 16 tiles), up to 512 tokens the GEMM kernel
-                                with its work dealt by row tile */
+                                with its work dealt by row tile; a layer or a few of up to some 700 tokens a kernel of
+                                small block tiles, where an estimate from the sizes has it faster (dense codes then on
+                                the dense int8 instruction) */
     SBN_PATH_DENSE_MFMA = 3, /* W_eff expanded to int8 with explicit zeros, dense int8 MFMA: the comparison path;
                                 d_in % 64 == 0 */
     SBN_PATH_GENERIC = 4     /* any supported pattern, plain integer kernel (reference speed only) */
