@@ -125,12 +125,10 @@ __device__ __forceinline__ void write_tile_transposed(const uint16_t *tile, uint
     }
 }
 
-// int8 [rows, cols] -> bf16 transposed: dst [cols, ld] with dst[c, r] = src[r, c], zeros for r in [rows, ld)
-__global__ void __launch_bounds__(256) transpose_i8_kernel(const int8_t *__restrict__ src, int64_t rows, int64_t cols,
-                                                          uint16_t *__restrict__ dst, int64_t ld)
+// int8 [rows, cols] -> bf16 transposed: dst [cols, ld] with dst[c, r] = src[r, c], zeros for r in [rows, ld); one tile of 64 x 64
+__device__ __forceinline__ void transpose_i8_tile(const int8_t *__restrict__ src, int64_t rows, int64_t cols, uint16_t *__restrict__ dst,
+                                                  int64_t ld, int64_t c0, int64_t r0, uint16_t (&tile)[64 * TQ])
 {
-    __shared__ __attribute__((aligned(16))) uint16_t tile[64 * TQ];
-    const int64_t r0 = (int64_t)blockIdx.y * 64, c0 = (int64_t)blockIdx.x * 64;
     const int r = threadIdx.x >> 2, cv = (threadIdx.x & 3) * 16;   // one 16-byte vector of a source row per thread
     __attribute__((aligned(16))) int8_t q[16];
     const bool row_ok = r0 + r < rows;
@@ -148,17 +146,21 @@ __global__ void __launch_bounds__(256) transpose_i8_kernel(const int8_t *__restr
     write_tile_transposed(tile, dst, ld, c0, r0, cols, ld);
 }
 
+__global__ void __launch_bounds__(256) transpose_i8_kernel(const int8_t *__restrict__ src, int64_t rows, int64_t cols,
+                                                          uint16_t *__restrict__ dst, int64_t ld)
+{
+    __shared__ __attribute__((aligned(16))) uint16_t tile[64 * TQ];
+    transpose_i8_tile(src, rows, cols, dst, ld, (int64_t)blockIdx.x * 64, (int64_t)blockIdx.y * 64, tile);
+}
+
 // dY [tokens, 8 nvec] bf16 -> dY[t, :] / s_x[t], rounded to bf16 (the one rounding of an operand of dW), same layout.  It is the
 // gradient that is rounded and not x~ / s_x, of which a row has 255 values at most: the error of a gradient is another one in
 // every token, that of a level would be the same wherever tokens share s_x (saturated or clipped activations) and add up over
 // them, and it would depend on where the levels lie between two powers of two, i.e. on the amplitude of the activations.
-// Block: up to 256 vectors of 8 values of four rows.  Bound by the bytes it moves.
-__global__ void __launch_bounds__(256) scale_rows_kernel(const uint4 *__restrict__ dY, const float *__restrict__ sx, int64_t tokens, int nvec,
-                                                        uint4 *__restrict__ dst)
+// Four rows from t0 on, vector i of 8 values.
+__device__ __forceinline__ void scale_four_rows(const uint4 *__restrict__ dY, const float *__restrict__ sx, int64_t tokens, int nvec,
+                                                uint4 *__restrict__ dst, int64_t t0, int i)
 {
-    const int64_t t0 = 4 * (int64_t)blockIdx.x;
-    const int i = (int)(blockIdx.y * 256 + threadIdx.x);
-    if (i >= nvec) return;
     uint4 v[4];
     float s[4];
 #pragma unroll
@@ -176,6 +178,24 @@ __global__ void __launch_bounds__(256) scale_rows_kernel(const uint4 *__restrict
             o[k] = f32_to_bf16(__fdiv_rn(__uint_as_float(w[k] << 16), s[r])) | (f32_to_bf16(__fdiv_rn(__uint_as_float(w[k] & 0xffff0000u), s[r])) << 16);
         if (t0 + r < tokens) dst[(t0 + r) * nvec + i] = make_uint4(o[0], o[1], o[2], o[3]);
     }
+}
+
+// Both operands of dW in one launch: the first `tiles` blocks transpose a tile of x~ each (tiles_c of them per 64 tokens; none where
+// another layer of the call has done it), the others scale 256 vectors of four rows of dY each (slices of them per row).
+// Bound by the bytes the two move; in two launches a call took 107 us at 1024 tokens (6912 x 2560) and 23.5 at 512
+// (1024 x 1024), in one 101.5 and 21.3.
+__global__ void __launch_bounds__(256) dw_operands_kernel(const int8_t *__restrict__ xq, int64_t tokens, int64_t d_in, uint16_t *__restrict__ xt,
+                                                         int64_t ldt, unsigned tiles_c, unsigned tiles, const uint4 *__restrict__ dY,
+                                                         const float *__restrict__ sx, int nvec, unsigned slices, uint4 *__restrict__ dys)
+{
+    __shared__ __attribute__((aligned(16))) uint16_t tile[64 * TQ];
+    if (blockIdx.x < tiles) {
+        transpose_i8_tile(xq, tokens, d_in, xt, ldt, (int64_t)(blockIdx.x % tiles_c) * 64, (int64_t)(blockIdx.x / tiles_c) * 64, tile);
+        return;
+    }
+    const unsigned b = blockIdx.x - tiles;
+    const int i = (int)(b % slices * 256 + threadIdx.x);
+    if (i < nvec) scale_four_rows(dY, sx, tokens, nvec, dys, 4 * (int64_t)(b / slices), i);
 }
 
 // ---- bf16 GEMM -------------------------------------------------------------------------------------------
@@ -304,8 +324,7 @@ __device__ __forceinline__ int bf16_product_of_block(const GemmBf16Group &grp)
 // stage's matrix instructions took 1.9 us.  What bounds it now: the matrix pipe at the clock the board holds (1.9 PFLOP/s on
 // operands from registers), and 10 us per tile for its first stages and its result, which nothing covers.
 // us per call, before and now: 2560 x 2560 at 16384 tokens, three layers 1305 -> 1200, one 523 -> 463; 6912 x 2560, two layers
-// 2274 -> 2090; 6912 x 2560 at 1024 tokens 170 -> 107.  dY / s_x in memory (scale_rows_kernel, 5.7 TB/s) is 90 of the 1200 and 8
-// of the 107 us.
+// 2274 -> 2100; 6912 x 2560 at 1024 tokens 170 -> 101.  dY / s_x in memory (5.7 TB/s) is 90 of the 1200 and 4 of the 101 us.
 constexpr int GD_K = 64;     // k per stage
 template <bool BIG> struct Bf16Tile {
     static constexpr int N = BIG ? 256 : 128, M = BIG ? 256 : 128;
@@ -628,17 +647,13 @@ sbn_status launch_backward_grouped(int count, const BackwardItem *items, const P
             const uint16_t *xts = nullptr;   // an earlier layer of the call already transposed the same activations
             for (int j = 0; j < i && !xts; ++j)
                 if (xt_of[j] && items[j].xq == it.xq && items[j].tokens == tokens && items[j].d_in == d_in) xts = xt_of[j];
-            if (!xts) {
-                dim3 grid((unsigned)ceil_div(d_in, 64), (unsigned)(ldt / 64));
-                hipLaunchKernelGGL(transpose_i8_kernel, grid, dim3(256), 0, stream, it.xq, tokens, d_in, xt, ldt);
-                st = check_launch("transpose_i8_kernel");
-                if (st != SBN_OK) return st;
-                xts = xt;
-            }
+            const unsigned tiles_c = (unsigned)ceil_div(d_in, 64), tiles = xts ? 0u : tiles_c * (unsigned)(ldt / 64);
+            const unsigned slices = (unsigned)ceil_div(d_out / 8, 256);
+            if (!xts) xts = xt;
             xt_of[i] = xts;
-            hipLaunchKernelGGL(scale_rows_kernel, dim3((unsigned)ceil_div(tokens, 4), (unsigned)ceil_div(d_out / 8, 256)), dim3(256), 0, stream,
-                               reinterpret_cast<const uint4 *>(dy), it.sx, tokens, (int)(d_out / 8), reinterpret_cast<uint4 *>(dys));
-            st = check_launch("scale_rows_kernel");
+            hipLaunchKernelGGL(dw_operands_kernel, dim3(tiles + slices * (unsigned)ceil_div(tokens, 4)), dim3(256), 0, stream, it.xq, tokens, d_in, xt, ldt,
+                               tiles_c, tiles, reinterpret_cast<const uint4 *>(dy), it.sx, (int)(d_out / 8), slices, reinterpret_cast<uint4 *>(dys));
+            st = check_launch("dw_operands_kernel");
             if (st != SBN_OK) return st;
             // dW[o, k] = sum_t (dY / s_x)[t, o] * x~[t, k]; x~^T is zero for t in [tokens, ldt)
             GemmBf16Args a{};
