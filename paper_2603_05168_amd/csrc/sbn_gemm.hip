@@ -1111,18 +1111,20 @@ sbn_status launch_gemm_pieces(int count, const LinearItem *items, bool dense_cod
 //   pieces of 512 rows x 32 .. 128 tokens  3.9 us, 10.5 us (dense codes 14.5) per 2560 weights of the deepest problem, 0.75 of
 //       that for each further unit of 32 tokens a multiprocessor has, 0.11 us per MB of outputs
 //       (2560 -> 2560 at 17 .. 1500 tokens 13.2 .. 15.0 us, 6912 -> 2560 39 .. 43, 2560 -> 6912 at 512 / 777 / 1500 / 3000
-//       tokens, up to 1 / 2 / 3 / 6 units, 18 / 20 / 25 / 47)
+//       tokens, up to 1 / 2 / 3 / 6 units, 18 / 20 / 25 / 47).  Output rows of no whole 16 bytes are stored in single words,
+//       another 3.2 us and 0.55 us per MB of them (512 -> 476 / 478 at 1000 tokens 6.5 / 10.2 us, 512 -> 6911 at 8000 179)
 static float gemm_large_estimate_us(int count, const LinearItem *items, bool dense)
 {
     bool stream = true;
     int64_t strips = 0, tokens = 0, depth = 0;
-    double units = 0, out_mb = 0;   // units weighted with their input dimension
+    double units = 0, out_mb = 0, word_mb = 0;   // units weighted with their input dimension; outputs, those stored in words
     for (int i = 0; i < count; ++i) {
         const LinearItem &li = items[i];
         stream = stream && gemv_batch_takes(li);
         strips += ceil_div(li.d_out, 256);
         units += (double)(ceil_div(li.d_out, sp::ROWS) * ceil_div(li.tokens, 32)) * (double)li.d_in / 2560.0;
         out_mb += 4e-6 * (double)li.tokens * (double)li.d_out;
+        if (li.d_out % 4 != 0) word_mb += 4e-6 * (double)li.tokens * (double)li.d_out;
         tokens = li.tokens > tokens ? li.tokens : tokens;
         depth = li.d_in > depth ? li.d_in : depth;
     }
@@ -1134,14 +1136,17 @@ static float gemm_large_estimate_us(int count, const LinearItem *items, bool den
     }
     const float more = (float)units / (float)cus - k;
     // (768 -> 6912 at 16384 tokens and 8192 -> 768 at 17 in one call: 278 us as small tiles, 158 this way, quantizers included)
-    return 3.9f + (dense ? 14.5f : 10.5f) * (k + 0.75f * (more > 0.0f ? more : 0.0f)) + 0.11f * (float)out_mb;
+    return 3.9f + (dense ? 14.5f : 10.5f) * (k + 0.75f * (more > 0.0f ? more : 0.0f)) + 0.11f * (float)out_mb +
+           (word_mb > 0.0 ? 3.2f + 0.55f * (float)word_mb : 0.0f);
 }
 
 // Small block tiles where they are faster: their time grows with rows x tokens from 4.5 us on, that of the large kernels
 // starts two to five times higher and grows slower.  Over 279 calls of 17 to 16384 tokens, input dimensions 256 to 8192 and
 // one to sixteen problems, all kernels measured, the choice costs 0.6 % against the faster kernel of each (at worst 1.40, 384 tokens
 // 4096 -> 14336 with dense codes: 56 us against 40); 256 tokens, 2560 -> 6912: 13.5 us in tiles, 17.8 in pieces; 512 tokens,
-// 2560 -> 2560: 11.1 / 14.0; 777 tokens: 14.9 / 13.8.
+// 2560 -> 2560: 11.1 / 14.0; 777 tokens: 14.9 / 13.8.  Over 365 calls more of 200 to 8000 tokens with 475 to 6912 outputs, most
+// of them no multiple of four: 0.2 %, at worst 1.09 (8000 tokens, 512 -> 1500: 23 / 25 us); 2181 tokens, 512 -> 475 7.6 in tiles,
+// 11.4 in pieces, 512 -> 512 6.9 either way.
 bool gemm_takes_tiles(int count, const LinearItem *items, bool dense_codes)
 {
     return gemm_tile_estimate_us(count, items, dense_codes) < gemm_large_estimate_us(count, items, dense_codes);

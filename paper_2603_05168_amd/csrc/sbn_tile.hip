@@ -285,15 +285,21 @@ int64_t wide_tiles(const LinearItem &li) { return ceil_div(li.d_out, 64) * ceil_
 // weights once from memory at 6 TB/s; and the activations, which the quantizer or another kernel has just written and which every
 // XCD fetches from memory before its L2 has them, 1.3 us per MB up to 2.6 us, from where on the rounds of tiles cover it.  (Behind
 // a quantizer, its own time subtracted: 512 / 777 / 1024 tokens 2560 -> 2560 11.1 / 14.9 / 18.0 us; on rows that lie in the L2 9.5 / 12.3 / 14.5.)
+// With up to eight row tiles in all, the rounds are too short to cover it: another 0.4 us per MB beyond 2 MB (4000 tokens, 2560 ->
+// 512: 20.6 us, 6912 -> 512 35.5; with 24 row tiles, 2560 -> 1500, nothing).  Outputs stored in single words: 0.1 us per MB.
 float gemm_tile_estimate_us(int count, const LinearItem *items, bool dense)
 {
     double us = 0, chain = 0, rows_mb = 0;
+    int64_t row_tiles = 0;
     for (int i = 0; i < count; ++i) {
         const double k = (double)items[i].d_in;
+        row_tiles += ceil_div(items[i].d_out, 64);
+        if (items[i].d_out % 4 != 0) us += 0.4e-6 * (double)items[i].tokens * (double)items[i].d_out;
         chain = std::max(chain, 2.7 + std::min(1.8, k / 900.0));
         rows_mb = std::max(rows_mb, 1e-6 * k * (double)items[i].tokens);
         us += (double)wide_tiles(items[i]) / (double)device_cus() * (0.59 + (dense ? 1.54 : 1.46) * k / 2560.0) + (double)items[i].d_out * k / 4 / 6e6;
     }
+    if (row_tiles <= 8) us += 0.4 * std::max(0.0, rows_mb - 2.0);
     return (float)(us + chain + std::min(2.6, 1.3 * rows_mb));
 }
 

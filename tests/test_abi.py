@@ -65,6 +65,13 @@ def test_choice_between_the_forward_kernels(sbn, N, M):
     for problem in ((3000, 2560, 2560), (777, 2560, 6912), (2048, 1024, 4096), (1500, 768, 3072), (16384, 768, 6912)):
         assert sbn.sbn_test_chosen_kernels([problem], N, M) == [pieces], problem
     assert sbn.sbn_test_chosen_kernels([(32, 2560, 6912)] * 64, N, M) == [stream] * 64
+    # output rows of no whole 16 bytes are stored in words, which costs the pieces more (2181 tokens, 512 -> 475: 11.4 us against
+    # 7.6; 512 -> 6911 at 8000: 179 against 111); few rows of outputs on many long rows of tokens cost the tiles more (8000
+    # tokens, 6912 -> 512: 64 us against 33)
+    for problem in ((2181, 512, 475), (4000, 512, 2559), (8000, 512, 6911), (1000, 2560, 2559), (500, 2560, 6911)):
+        assert sbn.sbn_test_chosen_kernels([problem], N, M) == [tiles], problem
+    for problem in ((8000, 6912, 512), (8000, 6912, 476), (8000, 2560, 512)):
+        assert sbn.sbn_test_chosen_kernels([problem], N, M) == [pieces], problem
     # a long shallow layer beside a deep one of a few tokens: every problem counts with its own input dimension (278 us in tiles,
     # 158 this way)
     assert sbn.sbn_test_chosen_kernels([(16384, 768, 6912), (17, 8192, 768)], N, M) == [pieces, stream]
