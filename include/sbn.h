@@ -347,8 +347,20 @@ sbn_status sbn_test_linear_kernel(int kernel, int count, const int8_t *const *xq
                                   const float *const *gamma, const float *const *bias, float *const *Y,
                                   int32_t *const *acc_out, void *stream);
 
-/* Test hook, host only: the kernel (SBN_KERNEL_...) that SBN_PATH_SMFMAC chooses for each problem of a call that wants nothing
- * but Y.  2:4 and N = M, d_in % 128 == 0; kernel: HOST array of length count. */
+/*
+ * Test hook: the forward products of up to eight problems, their activations quantized on the way, in one of the shapes of the
+ * kernel that small calls without quantized rows to give back run on, so that a test reaches the edges of each.  HOST arrays;
+ * X bf16; bias and acc_out may be NULL, and so may their entries.
+ *   form       0 .. 7 (SBN_EINVAL past the last)
+ *   supported  2:4 and N = M, d_in % 8 == 0, d_in <= 8192, tokens <= 4096, at most eight problems; anything else, and rows too
+ *              long for the shape, SBN_EUNSUPPORTED.  Other errors as sbn_sparse_ternary_linear.
+ */
+sbn_status sbn_test_self_kernel(int form, int count, const void *const *X, const int64_t *tokens, const int64_t *d_in,
+                                const int64_t *d_out, int N, int M, const void *const *packed, const float *const *gamma,
+                                const float *const *bias, float *const *Y, int32_t *const *acc_out, void *stream);
+
+/* Test hook, host only: the kernel (SBN_KERNEL_...) that SBN_PATH_SMFMAC chooses for each problem of a call on quantized rows that
+ * wants nothing but Y.  2:4 and N = M, d_in % 128 == 0; kernel: HOST array of length count. */
 sbn_status sbn_test_chosen_kernels(int count, const int64_t *tokens, const int64_t *d_in, const int64_t *d_out, int N, int M,
                                    int *kernel);
 

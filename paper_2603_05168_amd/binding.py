@@ -74,6 +74,8 @@ def _load():
     lib.sbn_test_set_spin_limits.argtypes = [cint, cint]
     lib.sbn_test_linear_kernel.restype = cint
     lib.sbn_test_linear_kernel.argtypes = [cint, cint, pp, pp, pi64, pi64, pi64, cint, cint, pp, pp, pp, pp, pp, vp]
+    lib.sbn_test_self_kernel.restype = cint
+    lib.sbn_test_self_kernel.argtypes = [cint, cint, pp, pi64, pi64, pi64, cint, cint, pp, pp, pp, pp, pp, vp]
     lib.sbn_test_chosen_kernels.restype = cint
     lib.sbn_test_chosen_kernels.argtypes = [cint, pi64, pi64, pi64, cint, cint, ctypes.POINTER(cint)]
     lib.sbn_mask_flips.restype = cint
@@ -353,6 +355,15 @@ def sbn_test_linear_kernel(kernel: int, xq_list, sx_list, packed_list, gamma_lis
                                        _ptr_array(packed_list), _ptr_array(gamma_list), None if bias_list is None else _ptr_array(bias_list),
                                        _ptr_array(Y_list), None if acc_list is None else _ptr_array(acc_list), _stream()),
            "sbn_test_linear_kernel")
+
+
+def sbn_test_self_kernel(form: int, X_list, packed_list, gamma_list, Y_list, N: int, M: int, bias_list=None, acc_list=None):
+    """Test hook: the products of bf16 rows in one shape of the kernel that quantizes them itself."""
+    _check(_lib.sbn_test_self_kernel(form, len(X_list), _ptr_array(X_list), _i64_array([x.shape[0] for x in X_list]),
+                                     _i64_array([x.shape[1] for x in X_list]), _i64_array([y.shape[1] for y in Y_list]), N, M,
+                                     _ptr_array(packed_list), _ptr_array(gamma_list), None if bias_list is None else _ptr_array(bias_list),
+                                     _ptr_array(Y_list), None if acc_list is None else _ptr_array(acc_list), _stream()),
+           "sbn_test_self_kernel")
 
 
 def sbn_test_chosen_kernels(problems, N: int, M: int):

@@ -106,6 +106,27 @@ sbn_status sbn_test_linear_kernel(int kernel, int count, const int8_t *const *xq
                                          : launch_gemm_pieces(count, items.data(), N == M, s);
 }
 
+sbn_status sbn_test_self_kernel(int form, int count, const void *const *X, const int64_t *tokens, const int64_t *d_in, const int64_t *d_out,
+                                int N, int M, const void *const *packed, const float *const *gamma, const float *const *bias,
+                                float *const *Y, int32_t *const *acc_out, void *stream)
+{
+    if (form < 0 || form >= self_form_count() || count <= 0 || !X || !tokens || !d_in || !d_out || !packed || !gamma || !Y) return SBN_EINVAL;
+    if (count > 8) return SBN_EUNSUPPORTED;
+    Pattern pat;
+    LinearItem items[8];
+    for (int i = 0; i < count; ++i) {
+        if (!X[i] || !packed[i] || !gamma[i] || !Y[i] || tokens[i] <= 0) return SBN_EINVAL;
+        sbn_status st = check_shape(d_out[i], d_in[i], N, M, pat);
+        if (st != SBN_OK) return st;
+        if (!aligned(X[i], 16) || !aligned(packed[i], 16) || !aligned(Y[i], 16) || (acc_out && acc_out[i] && !aligned(acc_out[i], 16))) return SBN_EALIGN;
+        if (d_in[i] % 8 != 0 || d_in[i] > 8192 || tokens[i] > 4096 || tokens[i] * d_out[i] >= (int64_t)1 << 40) return SBN_EUNSUPPORTED;
+        items[i] = LinearItem{X[i], packed[i], gamma[i], bias ? bias[i] : nullptr, Y[i], nullptr, nullptr, acc_out ? acc_out[i] : nullptr,
+                              tokens[i], ceil_div(d_in[i], CHUNK) * CHUNK, d_out[i], false, d_in[i]};
+    }
+    if (!(N == 2 && M == 4) && N != M) return SBN_EUNSUPPORTED;
+    return launch_gemm_self(count, items, N == M, static_cast<hipStream_t>(stream), form);
+}
+
 sbn_status sbn_test_chosen_kernels(int count, const int64_t *tokens, const int64_t *d_in, const int64_t *d_out, int N, int M, int *kernel)
 {
     if (count <= 0 || count > 4096 || !tokens || !d_in || !d_out || !kernel) return SBN_EINVAL;
@@ -278,8 +299,14 @@ static sbn_status linear_one(const LinearItem &it_in, const Pattern &pat, sbn_pa
 
     sbn_status st = SBN_OK;
     // the decode path derives the quantized activations itself (inside its kernel when it can) unless the
-    // caller wants them back in its own buffers
-    const bool defer = path == SBN_PATH_GEMV && it.X && !it_in.xq && !it_in.sx;
+    // caller wants them back in its own buffers, and so do small calls beyond it
+    bool defer = path == SBN_PATH_GEMV && it.X && !it_in.xq && !it_in.sx;
+    if (path == SBN_PATH_SMFMAC && it.X && !it_in.xq && !it_in.sx) {
+        LinearItem self = it;   // the same on whole chunks, with the row's own length beside it
+        self.d_x = it.d_in;
+        self.d_in = kp;
+        defer = gemm_takes_self(1, &self, !sparse_form);
+    }
     it.quantized = !defer;
     if (it.X && !defer) {
         if (spread && !it_in.xq) st = launch_act_quant(it.X, it.tokens, it.d_in, ws_xq, it.sx, stream, kp);
@@ -307,7 +334,7 @@ static sbn_status linear_one(const LinearItem &it_in, const Pattern &pat, sbn_pa
     }
     switch (path) {
     case SBN_PATH_GEMV: return launch_gemv(1, &it, one4_decode ? GEMV_1OF4 : sparse_form ? GEMV_2OF4 : GEMV_DENSE, stream);
-    case SBN_PATH_SMFMAC: return launch_gemm_smfmac(1, &it, !sparse_form, stream);
+    case SBN_PATH_SMFMAC: return defer ? launch_gemm_self(1, &it, !sparse_form, stream) : launch_gemm_smfmac(1, &it, !sparse_form, stream);
     case SBN_PATH_DENSE_MFMA: return launch_gemm_dense(it, pat, w_dense, stream);
     case SBN_PATH_GENERIC: return launch_linear_generic(it, pat, stream);
     default: return SBN_EINVAL;
@@ -459,14 +486,19 @@ sbn_status sbn_sparse_ternary_linear_grouped(int count, const void *const *X, co
                 it.sx = tl_items[j].sx;
                 shared = true;
             }
-        it.quantized = !all_gemv;   // the decode path derives the quantized activations itself
-        if (!shared && !all_gemv) {
-            sbn_status st = launch_act_quant(it.X, it.tokens, it.d_in, it.xq, it.sx, s);
-            if (st != SBN_OK) return st;
-        }
+        it.quantized = shared;   // who derives the rows: the decode path itself, and beyond it the launches below
     }
-    return all_gemv ? launch_gemv(count, tl_items.data(), pat.N == pat.M ? GEMV_DENSE : pat.M == 4 && pat.N == 1 ? GEMV_1OF4 : GEMV_2OF4, s)
-                    : launch_gemm_smfmac(count, tl_items.data(), pat.N == pat.M, s);
+    if (all_gemv) {
+        for (LinearItem &it : tl_items) it.quantized = false;
+        return launch_gemv(count, tl_items.data(), pat.N == pat.M ? GEMV_DENSE : pat.M == 4 && pat.N == 1 ? GEMV_1OF4 : GEMV_2OF4, s);
+    }
+    if (gemm_takes_self(count, tl_items.data(), pat.N == pat.M)) return launch_gemm_self(count, tl_items.data(), pat.N == pat.M, s);
+    for (const LinearItem &it : tl_items) {
+        if (it.quantized) continue;
+        sbn_status st = launch_act_quant(it.X, it.tokens, it.d_in, it.xq, it.sx, s);
+        if (st != SBN_OK) return st;
+    }
+    return launch_gemm_smfmac(count, tl_items.data(), pat.N == pat.M, s);
 }
 
 sbn_status sbn_sparse_ternary_linear_backward(const void *dY, int64_t tokens, int64_t d_in, int64_t d_out, int N,

@@ -1152,6 +1152,11 @@ bool gemm_takes_tiles(int count, const LinearItem *items, bool dense_codes)
     return gemm_tile_estimate_us(count, items, dense_codes) < gemm_large_estimate_us(count, items, dense_codes);
 }
 
+float gemm_estimate_us(int count, const LinearItem *items, bool dense_codes)
+{
+    return std::min(gemm_tile_estimate_us(count, items, dense_codes), gemm_large_estimate_us(count, items, dense_codes));
+}
+
 sbn_status launch_gemm_smfmac(int count, const LinearItem *items, bool dense_codes, hipStream_t stream)
 {
     if (gemm_takes_tiles(count, items, dense_codes)) return launch_gemm_tile(count, items, dense_codes, stream);

@@ -110,9 +110,16 @@ sbn_status launch_gemm_pieces(int count, const LinearItem *items, bool dense_cod
 // once through a kernel of their own
 bool gemv_batch_takes(const LinearItem &it);
 sbn_status launch_gemv_batch(int count, const LinearItem *items, bool dense_codes, hipStream_t stream);
+// the quantizer inside the product (sbn_self.hip): a few problems of few tokens whose quantized rows nobody wants back; one launch.
+// form: a shape by number below self_form_count(), -1: the one it estimates to be the fastest
+bool gemv_takes_self(int count, const LinearItem *items);                     // up to 16 tokens
+bool gemm_takes_self(int count, const LinearItem *items, bool dense_codes);   // beyond
+int self_form_count();
+sbn_status launch_gemm_self(int count, const LinearItem *items, bool dense_codes, hipStream_t stream, int form = -1);
 // small block tiles (sbn_tile.hip): any problem, made for a few problems of few tokens
 float gemm_tile_estimate_us(int count, const LinearItem *items, bool dense_codes);
 bool gemm_takes_tiles(int count, const LinearItem *items, bool dense_codes);   // whether launch_gemm_smfmac takes them
+float gemm_estimate_us(int count, const LinearItem *items, bool dense_codes);   // of the kernel launch_gemm_smfmac takes
 sbn_status launch_gemm_tile(int count, const LinearItem *items, bool dense_codes, hipStream_t stream);
 sbn_status launch_gemm_dense(const LinearItem &it, const Pattern &pat, int8_t *w_dense, hipStream_t stream);
 sbn_status launch_gemm_dense_expanded(const LinearItem &it, const int8_t *w_dense, hipStream_t stream);

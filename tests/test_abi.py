@@ -220,3 +220,21 @@ def test_argument_errors_come_before_any_launch(sbn):
     assert plib.sbn_ceiling_probe(ci(3), vp(A), sz(4096), ci(1), ctypes.byref(work), vp(0)) == -1
     assert plib.sbn_ceiling_probe(ci(3), vp(A + 16), sz(1 << 22), ci(1), ctypes.byref(work), vp(0)) == -4
     assert sbn.sbn_last_error() == ""
+
+
+def test_self_kernel_hook_refuses_on_the_host(sbn):
+    lib = ctypes.CDLL(sbn.lib_path())
+    lib.sbn_test_self_kernel.restype = ctypes.c_int
+    ci, A = ctypes.c_int, 0x10000
+
+    def one(v, t=ctypes.c_void_p):
+        return (t * 9)(*[v] * 9)
+
+    def call(form=0, count=1, X=A, Y=A, tokens=8, d_in=256, d_out=64, N=2, M=4):
+        return lib.sbn_test_self_kernel(ci(form), ci(count), one(X), one(tokens, ctypes.c_int64), one(d_in, ctypes.c_int64), one(d_out, ctypes.c_int64),
+                                        ci(N), ci(M), one(A), one(A), None, one(Y), None, ctypes.c_void_p(0))
+    assert call(form=8) == sbn.SBN_EINVAL and call(form=-1) == sbn.SBN_EINVAL
+    assert call(X=0) == sbn.SBN_EINVAL
+    assert call(X=A + 8) == sbn.SBN_EALIGN and call(Y=A + 4) == sbn.SBN_EALIGN
+    for refused in ({"count": 9}, {"d_in": 8200}, {"d_in": 12}, {"tokens": 4097}, {"N": 6, "M": 8}):
+        assert call(**refused) == sbn.SBN_EUNSUPPORTED, refused
