@@ -334,14 +334,15 @@ sbn_status sbn_dense_ternary_linear(const int8_t *xq, const float *sx, int64_t t
 void sbn_test_set_spin_limits(int gemv_polls, int pack_polls);
 
 /*
- * Test hook: the forward products of `count` problems through one of the three kernels between which SBN_PATH_SMFMAC
+ * Test hook: the forward products of `count` problems through one of the kernels between which SBN_PATH_SMFMAC
  * chooses by their sizes, so that a test reaches the edges of each whatever that choice is.  HOST arrays, one entry per
  * problem; xq, sx as written by sbn_act_quant; bias and acc_out may be NULL, and so may their entries.
  *   kernel     SBN_KERNEL_TILES: small block tiles; SBN_KERNEL_STREAM: streaming kernel for decode batches (at most 64
- *              tokens, d_out % 4 == 0, no bias and no acc_out); SBN_KERNEL_PIECES: persistent kernel on pieces of 512 rows
+ *              tokens, d_out % 4 == 0, no bias and no acc_out); SBN_KERNEL_PIECES: persistent kernel on pieces of 512 rows;
+ *              SBN_KERNEL_BLOCKS + 0, 1, 2: block tiles of 64 x 32, 128 x 32 and 128 x 64 rows x tokens
  *   supported  2:4 and N = M, d_in % 128 == 0; anything else SBN_EUNSUPPORTED.  Other errors as sbn_sparse_ternary_linear.
  */
-enum { SBN_KERNEL_TILES = 0, SBN_KERNEL_STREAM = 1, SBN_KERNEL_PIECES = 2 };
+enum { SBN_KERNEL_TILES = 0, SBN_KERNEL_STREAM = 1, SBN_KERNEL_PIECES = 2, SBN_KERNEL_BLOCKS = 16 };
 sbn_status sbn_test_linear_kernel(int kernel, int count, const int8_t *const *xq, const float *const *sx, const int64_t *tokens,
                                   const int64_t *d_in, const int64_t *d_out, int N, int M, const void *const *packed,
                                   const float *const *gamma, const float *const *bias, float *const *Y,
@@ -359,10 +360,13 @@ sbn_status sbn_test_self_kernel(int form, int count, const void *const *X, const
                                 const int64_t *d_out, int N, int M, const void *const *packed, const float *const *gamma,
                                 const float *const *bias, float *const *Y, int32_t *const *acc_out, void *stream);
 
-/* Test hook, host only: the kernel (SBN_KERNEL_...) that SBN_PATH_SMFMAC chooses for each problem of a call on quantized rows that
- * wants nothing but Y.  2:4 and N = M, d_in % 128 == 0; kernel: HOST array of length count. */
+/* Test hook, host only: which of SBN_KERNEL_TILES, _STREAM and _PIECES SBN_PATH_SMFMAC takes for each problem of a call on
+ * quantized rows that wants nothing but Y, where it does not take block tiles for the call (sbn_test_takes_blocks: *blocks 1 or
+ * 0).  2:4 and N = M, d_in % 128 == 0; kernel: HOST array of length count. */
 sbn_status sbn_test_chosen_kernels(int count, const int64_t *tokens, const int64_t *d_in, const int64_t *d_out, int N, int M,
                                    int *kernel);
+sbn_status sbn_test_takes_blocks(int count, const int64_t *tokens, const int64_t *d_in, const int64_t *d_out, int N, int M,
+                                 int *blocks);
 
 /* Text of the last HIP error seen by this thread ("" if none). */
 const char *sbn_last_error(void);

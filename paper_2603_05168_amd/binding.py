@@ -76,6 +76,8 @@ def _load():
     lib.sbn_test_linear_kernel.argtypes = [cint, cint, pp, pp, pi64, pi64, pi64, cint, cint, pp, pp, pp, pp, pp, vp]
     lib.sbn_test_self_kernel.restype = cint
     lib.sbn_test_self_kernel.argtypes = [cint, cint, pp, pi64, pi64, pi64, cint, cint, pp, pp, pp, pp, pp, vp]
+    lib.sbn_test_takes_blocks.restype = cint
+    lib.sbn_test_takes_blocks.argtypes = [cint, pi64, pi64, pi64, cint, cint, ctypes.POINTER(cint)]
     lib.sbn_test_chosen_kernels.restype = cint
     lib.sbn_test_chosen_kernels.argtypes = [cint, pi64, pi64, pi64, cint, cint, ctypes.POINTER(cint)]
     lib.sbn_mask_flips.restype = cint
@@ -345,7 +347,7 @@ def sbn_test_set_spin_limits(gemv_polls: int = SBN_SPIN_DEFAULT, pack_polls: int
     _lib.sbn_test_set_spin_limits(gemv_polls, pack_polls)
 
 
-SBN_KERNEL_TILES, SBN_KERNEL_STREAM, SBN_KERNEL_PIECES = 0, 1, 2
+SBN_KERNEL_TILES, SBN_KERNEL_STREAM, SBN_KERNEL_PIECES, SBN_KERNEL_BLOCKS = 0, 1, 2, 16
 
 
 def sbn_test_linear_kernel(kernel: int, xq_list, sx_list, packed_list, gamma_list, Y_list, N: int, M: int, bias_list=None, acc_list=None):
@@ -364,6 +366,14 @@ def sbn_test_self_kernel(form: int, X_list, packed_list, gamma_list, Y_list, N: 
                                      _ptr_array(packed_list), _ptr_array(gamma_list), None if bias_list is None else _ptr_array(bias_list),
                                      _ptr_array(Y_list), None if acc_list is None else _ptr_array(acc_list), _stream()),
            "sbn_test_self_kernel")
+
+
+def sbn_test_takes_blocks(problems, N: int, M: int) -> bool:
+    """Test hook: whether SBN_PATH_SMFMAC takes block tiles for a call of these problems (tokens, d_in, d_out)."""
+    blocks = ctypes.c_int(0)
+    _check(_lib.sbn_test_takes_blocks(len(problems), *(_i64_array(column) for column in zip(*problems)), N, M, ctypes.byref(blocks)),
+           "sbn_test_takes_blocks")
+    return bool(blocks.value)
 
 
 def sbn_test_chosen_kernels(problems, N: int, M: int):

@@ -84,7 +84,7 @@ sbn_status sbn_test_linear_kernel(int kernel, int count, const int8_t *const *xq
                                   const float *const *gamma, const float *const *bias, float *const *Y, int32_t *const *acc_out,
                                   void *stream)
 {
-    if (kernel < SBN_KERNEL_TILES || kernel > SBN_KERNEL_PIECES || count <= 0 || count > 4096) return SBN_EINVAL;
+    if (kernel < SBN_KERNEL_TILES || (kernel > SBN_KERNEL_PIECES && kernel < SBN_KERNEL_BLOCKS) || kernel >= SBN_KERNEL_BLOCKS + block_form_count() || count <= 0 || count > 4096) return SBN_EINVAL;
     if (!xq || !sx || !tokens || !d_in || !d_out || !packed || !gamma || !Y) return SBN_EINVAL;
     Pattern pat;
     std::vector<LinearItem> items(count);
@@ -101,6 +101,7 @@ sbn_status sbn_test_linear_kernel(int kernel, int count, const int8_t *const *xq
     }
     if (!(N == 2 && M == 4) && N != M) return SBN_EUNSUPPORTED;
     hipStream_t s = static_cast<hipStream_t>(stream);
+    if (kernel >= SBN_KERNEL_BLOCKS) return launch_gemm_block(count, items.data(), N == M, s, kernel - SBN_KERNEL_BLOCKS);
     return kernel == SBN_KERNEL_TILES    ? launch_gemm_tile(count, items.data(), N == M, s)
            : kernel == SBN_KERNEL_STREAM ? launch_gemv_batch(count, items.data(), N == M, s)
                                          : launch_gemm_pieces(count, items.data(), N == M, s);
@@ -127,7 +128,7 @@ sbn_status sbn_test_self_kernel(int form, int count, const void *const *X, const
     return launch_gemm_self(count, items, N == M, static_cast<hipStream_t>(stream), form);
 }
 
-sbn_status sbn_test_chosen_kernels(int count, const int64_t *tokens, const int64_t *d_in, const int64_t *d_out, int N, int M, int *kernel)
+static sbn_status chosen_kernels(int count, const int64_t *tokens, const int64_t *d_in, const int64_t *d_out, int N, int M, int *kernel, int *blocks)
 {
     if (count <= 0 || count > 4096 || !tokens || !d_in || !d_out || !kernel) return SBN_EINVAL;
     if (!(N == 2 && M == 4) && N != M) return SBN_EUNSUPPORTED;
@@ -143,10 +144,23 @@ sbn_status sbn_test_chosen_kernels(int count, const int64_t *tokens, const int64
         items[i].d_in = d_in[i];
         items[i].d_out = d_out[i];
     }
+    if (blocks) *blocks = gemm_takes_blocks(count, items.data(), N == M);
     const bool tiles = gemm_takes_tiles(count, items.data(), N == M);
     for (int i = 0; i < count; ++i)
         kernel[i] = tiles ? SBN_KERNEL_TILES : gemv_batch_takes(items[i]) ? SBN_KERNEL_STREAM : SBN_KERNEL_PIECES;
     return SBN_OK;
+}
+
+sbn_status sbn_test_chosen_kernels(int count, const int64_t *tokens, const int64_t *d_in, const int64_t *d_out, int N, int M, int *kernel)
+{
+    return chosen_kernels(count, tokens, d_in, d_out, N, M, kernel, nullptr);
+}
+
+sbn_status sbn_test_takes_blocks(int count, const int64_t *tokens, const int64_t *d_in, const int64_t *d_out, int N, int M, int *blocks)
+{
+    if (!blocks || count <= 0 || count > 4096) return SBN_EINVAL;
+    std::vector<int> kernel(count);
+    return chosen_kernels(count, tokens, d_in, d_out, N, M, kernel.data(), blocks);
 }
 
 sbn_status sbn_packed_bytes(int64_t d_out, int64_t d_in, int N, int M, size_t *bytes)

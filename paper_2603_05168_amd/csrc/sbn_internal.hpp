@@ -104,6 +104,12 @@ sbn_status launch_gemv(int count, const LinearItem *items, GemvForm form, hipStr
 // dense_codes: the weights are dense 2-bit codes (packed form of N = M) instead of the 2:4 form.  launch_gemm_smfmac chooses
 // between the three kernels named below it
 sbn_status launch_gemm_smfmac(int count, const LinearItem *items, bool dense_codes, hipStream_t stream);
+// block tiles of middle size (sbn_block.hip): any problem; chosen for up to eight of them that fill the device once or twice.  The
+// estimate of a call it is not made for is huge.  form: a shape by number below block_form_count(), -1: the one it estimates fastest
+float gemm_block_estimate_us(int count, const LinearItem *items, bool dense_codes);
+bool gemm_takes_blocks(int count, const LinearItem *items, bool dense_codes);   // whether launch_gemm_smfmac takes them
+int block_form_count();
+sbn_status launch_gemm_block(int count, const LinearItem *items, bool dense_codes, hipStream_t stream, int form = -1);
 // pieces of 512 rows x 32 to 128 tokens (sbn_gemm.hip): any problem
 sbn_status launch_gemm_pieces(int count, const LinearItem *items, bool dense_codes, hipStream_t stream);
 // decode batches (sbn_batch.hip): problems of at most 64 tokens without bias or accumulator output stream their weights
@@ -118,7 +124,7 @@ int self_form_count();
 sbn_status launch_gemm_self(int count, const LinearItem *items, bool dense_codes, hipStream_t stream, int form = -1);
 // small block tiles (sbn_tile.hip): any problem, made for a few problems of few tokens
 float gemm_tile_estimate_us(int count, const LinearItem *items, bool dense_codes);
-bool gemm_takes_tiles(int count, const LinearItem *items, bool dense_codes);   // whether launch_gemm_smfmac takes them
+bool gemm_takes_tiles(int count, const LinearItem *items, bool dense_codes);   // whether launch_gemm_smfmac takes them where no block tiles are taken
 float gemm_estimate_us(int count, const LinearItem *items, bool dense_codes);   // of the kernel launch_gemm_smfmac takes
 sbn_status launch_gemm_tile(int count, const LinearItem *items, bool dense_codes, hipStream_t stream);
 sbn_status launch_gemm_dense(const LinearItem &it, const Pattern &pat, int8_t *w_dense, hipStream_t stream);

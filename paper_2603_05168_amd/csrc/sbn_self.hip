@@ -192,26 +192,32 @@ __global__ void __launch_bounds__(64 * S::WAVES) gemm_self_kernel(SelfTable tab)
     for (int a = 0; a < RT; ++a)   // lane: token r, rows 4 c4 ..
         if (r < T) *reinterpret_cast<v4i *>(&red[(part * T + r) * PITCH + 16 * (RT * group + a) + 4 * c4]) = acc[a];
     __syncthreads();
-    const bool vec = (it.d_out & 3) == 0, has_bias = it.bias != nullptr;
-    for (int v = tid; v < T * R / 4; v += 64 * S::WAVES) {
-        const int tl = v / (R / 4), o = row0 + 4 * (v % (R / 4)), t = t0 + tl;
-        if (t >= it.tokens || o >= it.d_out) continue;
-        v4i sum = {0, 0, 0, 0};
+    const bool has_bias = it.bias != nullptr;
+    if ((it.d_out & 3) == 0) {
+        for (int v = tid; v < T * R / 4; v += 64 * S::WAVES) {
+            const int tl = v / (R / 4), o = row0 + 4 * (v % (R / 4)), t = t0 + tl;
+            if (t >= it.tokens || o >= it.d_out) continue;
+            v4i sum = {0, 0, 0, 0};
 #pragma unroll
-        for (int k = 0; k < KS; ++k) sum += *reinterpret_cast<const v4i *>(&red[(k * T + tl) * PITCH + 4 * (v % (R / 4))]);
-        const float scale = scale_s[tl];
-        v4f y = {(float)sum[0] * scale, (float)sum[1] * scale, (float)sum[2] * scale, (float)sum[3] * scale};
-        float *dst = it.Y + (int64_t)t * it.d_out + o;
-        if (vec && !has_bias) {
-            *reinterpret_cast<v4f *>(dst) = y;
+            for (int k = 0; k < KS; ++k) sum += *reinterpret_cast<const v4i *>(&red[(k * T + tl) * PITCH + 4 * (v % (R / 4))]);
+            const float scale = scale_s[tl];
+            v4f y = {(float)sum[0] * scale, (float)sum[1] * scale, (float)sum[2] * scale, (float)sum[3] * scale};
+            if (has_bias)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) y[i] += it.bias[o + i];
+            *reinterpret_cast<v4f *>(it.Y + (int64_t)t * it.d_out + o) = y;
             if (it.acc_out) *reinterpret_cast<v4i *>(it.acc_out + (int64_t)t * it.d_out + o) = sum;
-        } else {
+        }
+    } else {   // token rows of no whole 16 bytes leave word by word, neighbouring lanes side by side
+        for (int v = tid; v < T * R; v += 64 * S::WAVES) {
+            const int tl = v / R, o = row0 + v % R, t = t0 + tl;
+            if (t >= it.tokens || o >= it.d_out) continue;
+            int sum = 0;
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                if (o + i < it.d_out) {
-                    dst[i] = has_bias ? y[i] + it.bias[o + i] : y[i];
-                    if (it.acc_out) it.acc_out[(int64_t)t * it.d_out + o + i] = sum[i];
-                }
+            for (int k = 0; k < KS; ++k) sum += red[(k * T + tl) * PITCH + v % R];
+            const float y = (float)sum * scale_s[tl];
+            it.Y[(int64_t)t * it.d_out + o] = has_bias ? y + it.bias[o] : y;
+            if (it.acc_out) it.acc_out[(int64_t)t * it.d_out + o] = sum;
         }
     }
 }
@@ -282,25 +288,27 @@ constexpr SelfForm SELF_FORMS[] = {
 
 // Estimated time in us of a call in one shape: the chain; the rows of a block's tokens (of which the quantizer is a part) and its
 // weights, which take up to 1.6 times as long with the whole device reading; the steps of a wavefront; a further block of
-// a multiprocessor, 0.7 of the first where two are resident, 1.1 where not; the outputs.  Fitted to 315 calls of 1 to 384
+// a multiprocessor, 0.7 of the first where two are resident, 1.1 where not; the outputs, more where they are stored in
+// single words.  Fitted to 315 calls of 1 to 384
 // tokens, 512 to 8192 values and 512 to 28672 outputs, all shapes measured: 8 % off, and the shape it picks is 0.9 % from the fastest.
 float self_estimate_us(const SelfForm &f, int count, const LinearItem *items, bool dense)
 {
     const int R = 16 * f.RT * f.G, KS = f.WAVES / f.G;
     int64_t blocks = 0, longest = 0;
-    double out_mb = 0;
+    double out_mb = 0, word_mb = 0;
     for (int i = 0; i < count; ++i) {
+        if (items[i].d_out % 4 != 0) word_mb += 4e-6 * (double)items[i].tokens * (double)items[i].d_out;
         blocks += ceil_div(items[i].d_out, R) * ceil_div(items[i].tokens, f.T);
         longest = std::max(longest, items[i].d_in);
         out_mb += 4e-6 * (double)items[i].tokens * (double)items[i].d_out;
     }
     const size_t lds = (size_t)f.T * self_pitch(longest) + (size_t)f.WAVES * f.RT * 16 * 128;
-    if (lds > SELF_LDS) return 1e30f;
+    if (lds > SELF_LDS || blocks > 4 * (int64_t)device_cus()) return 1e30f;   // (the fit ends at four rounds)
     const double k = (double)longest / 2560.0, cus = device_cus(), load = std::min(1.0, (double)blocks / cus);
     const double steps = (double)(ceil_div(ceil_div(longest, 4 * CHUNK), KS) * f.RT);
     const double work = f.T / 8.0 * k + 0.326 * (R / 64.0) * k * (1.0 + 0.6 * load) + 0.168 * steps * (dense ? 1.735 : 1.0) + (f.WAVES == 16 ? 0.305 : 0.0);
     const double more = (double)(ceil_div(blocks, (int64_t)cus) - 1);
-    return (float)(2.955 + work + more * (0.104 + (lds <= SELF_LDS / 2 ? 0.706 : 1.085) * work) + 0.258 * out_mb);
+    return (float)(2.955 + work + more * (0.104 + (lds <= SELF_LDS / 2 ? 0.706 : 1.085) * work) + 0.258 * out_mb + 0.45 * word_mb);
 }
 
 int choose(int count, const LinearItem *items, bool dense, float &us)
@@ -318,8 +326,8 @@ bool self_accepts(int count, const LinearItem *items)
 {
     if (count > SELF_ITEMS) return false;
     for (int i = 0; i < count; ++i)
-        // the rows of X are addressed with 31 bits behind a buffer's base
-        if (!items[i].X || items[i].row_values() > SELF_MAX_ROW || items[i].tokens > 4096) return false;
+        // (the estimates are of calls of up to 384 tokens; the rows of X are addressed with 31 bits behind a buffer's base)
+        if (!items[i].X || items[i].row_values() > SELF_MAX_ROW || items[i].tokens > 512) return false;
     return true;
 }
 
@@ -354,9 +362,12 @@ bool gemm_takes_self(int count, const LinearItem *items, bool dense)
         for (int j = 0; j < i; ++j) seen = seen || (items[j].X == items[i].X && items[j].tokens == items[i].tokens && items[j].d_in == items[i].d_in);
         if (!seen) quantizer += 2.5 + 0.76e-6 * (double)items[i].tokens * (double)items[i].d_in;
     }
+    int64_t longest = 0;
+    for (int i = 0; i < count; ++i) longest = std::max(longest, items[i].d_in);
     float us;
     choose(count, items, dense, us);
-    return us < gemm_estimate_us(count, items, dense) + (float)quantizer + 0.6f;
+    // rows beyond 7168 values: the estimate is up to 1.5 us short (172 tokens, 8192 -> 1246: 13.8 us, 12.1 in two launches)
+    return us < gemm_estimate_us(count, items, dense) + (float)quantizer + (longest > 7168 ? -1.0f : 0.6f);
 }
 
 int self_form_count() { return (int)(sizeof(SELF_FORMS) / sizeof(SELF_FORMS[0])); }

@@ -238,3 +238,14 @@ def test_self_kernel_hook_refuses_on_the_host(sbn):
     assert call(X=A + 8) == sbn.SBN_EALIGN and call(Y=A + 4) == sbn.SBN_EALIGN
     for refused in ({"count": 9}, {"d_in": 8200}, {"d_in": 12}, {"tokens": 4097}, {"N": 6, "M": 8}):
         assert call(**refused) == sbn.SBN_EUNSUPPORTED, refused
+
+
+@pytest.mark.parametrize("N,M", [(2, 4), (8, 8)])
+def test_choice_of_block_tiles(sbn, N, M):
+    # sizes at which the kernels measure far apart (on 256 multiprocessors, which the library assumes without a GPU)
+    for problem in ((640, 2560, 2560), (256, 2560, 6912), (512, 4096, 4096)):
+        assert sbn.sbn_test_takes_blocks([problem], N, M), problem
+    # more than two rounds of the device, or few tokens through a long layer
+    for problem in ((2048, 2560, 6912), (777, 2560, 6912), (1400, 4096, 4096), (96, 8192, 2560), (16384, 768, 6912)):
+        assert not sbn.sbn_test_takes_blocks([problem], N, M), problem
+    assert not sbn.sbn_test_takes_blocks([(64, 2560, 256)] * 9, N, M)      # more problems than a launch holds
