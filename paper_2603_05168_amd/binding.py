@@ -7,7 +7,9 @@ non-zero status.  No step of the method runs here.
 from __future__ import annotations
 
 import ctypes
+import importlib.util
 import os
+import struct
 
 import torch
 
@@ -86,6 +88,27 @@ def _load():
 
 
 _lib = _load()
+
+
+def _load_fastcall():
+    """The marshalling of the two forward calls in C++ (csrc/sbn_fastcall.cpp), or None: the Python code here does the same."""
+    path = os.path.join(_HERE, "_fastcall.so")
+    if not os.path.exists(path):
+        return None
+    try:
+        spec = importlib.util.spec_from_file_location("_fastcall", path)
+        module = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(module)
+    except ImportError:   # built for another torch
+        return None
+    address = lambda f: ctypes.cast(f, ctypes.c_void_p).value   # noqa: E731
+    module.bind(address(_lib.sbn_sparse_ternary_linear), address(_lib.sbn_sparse_ternary_linear_grouped))
+    return module
+
+
+_fastcall = _load_fastcall()
+_fast_linear = _fastcall.linear if _fastcall else lambda *args: None
+_fast_grouped = _fastcall.grouped if _fastcall else lambda *args: None
 
 
 def lib_path() -> str:
@@ -212,6 +235,11 @@ def sbn_act_quant(X, xq, sx):
 def sbn_sparse_ternary_linear(X, packed, gamma, Y, N: int, M: int, workspace, bias=None, xq_out=None, sx_out=None,
                               acc_out=None, path: int = SBN_PATH_AUTO):
     """X = None runs on activations already quantized into xq_out / sx_out (then inputs)."""
+    status = _fast_linear(X, packed, gamma, Y, N, M, workspace, bias, xq_out, sx_out, acc_out, path)
+    if status is not None:
+        if status:
+            _check(status, "sbn_sparse_ternary_linear")
+        return
     tokens, d_in = X.shape if X is not None else xq_out.shape
     d_out = Y.shape[1]
     if (X is not None and X.dtype != torch.bfloat16) or Y.dtype != torch.float32:
@@ -252,9 +280,16 @@ class LinearGroup:
         self.Y = _ptr_array(Y_list)
         self.N, self.M, self.path, self.workspace = N, M, path, workspace
         self.keep = (X_list, packed_list, gamma_list, Y_list)
+        self.addresses = struct.pack("8q", self.count, *(ctypes.addressof(a) for a in (self.X, self.tokens, self.d_in, self.d_out, self.packed,
+                                                                                        self.gamma, self.Y)))
 
     def run(self):
         ws = self.workspace
+        status = _fast_grouped(self.addresses, self.N, self.M, self.path, ws)
+        if status is not None:
+            if status:
+                _check(status, "sbn_sparse_ternary_linear_grouped")
+            return
         _check(_lib.sbn_sparse_ternary_linear_grouped(self.count, self.X, self.tokens, self.d_in, self.d_out, self.N,
                                                       self.M, self.packed, self.gamma, self.Y, self.path, _ptr(ws),
                                                       ws.numel() * ws.element_size(), _stream()),

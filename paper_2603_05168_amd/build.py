@@ -1,5 +1,6 @@
 """Compile the HIP sources for gfx950: csrc/ into paper_2603_05168_amd/libsbn.so (the layer) and bench_csrc/ into
-paper_2603_05168_amd/libsbn_probe.so (ceiling probes of the benchmark, apart from the layer's library)."""
+paper_2603_05168_amd/libsbn_probe.so (ceiling probes of the benchmark, apart from the layer's library); and the marshalling of the
+forward calls, csrc/sbn_fastcall.cpp, against the installed torch into paper_2603_05168_amd/_fastcall.so."""
 import glob
 import os
 import subprocess
@@ -10,6 +11,8 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libsbn.so")
 PROBE_SRC = os.path.join(HERE, "bench_csrc")
 PROBE_LIB = os.path.join(HERE, "libsbn_probe.so")
+FASTCALL_SRC = os.path.join(CSRC, "sbn_fastcall.cpp")
+FASTCALL_LIB = os.path.join(HERE, "_fastcall.so")
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -23,11 +26,21 @@ def sources():
     return sorted(glob.glob(os.path.join(CSRC, "*.hip")))
 
 
+def fastcall_command():
+    import sysconfig
+    from torch.utils import cpp_extension
+    includes = cpp_extension.include_paths("cuda") + [sysconfig.get_paths()["include"]]
+    libs = cpp_extension.library_paths("cuda")
+    return (["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1"] + [f"-I{i}" for i in includes] +
+            ["-o", FASTCALL_LIB, FASTCALL_SRC] + [f"-L{l}" for l in libs] + ["-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"] +
+            [f"-Wl,-rpath,{libs[0]}"])
+
+
 def build(force: bool = True, verbose: bool = False) -> str:
     srcs = sources()
     probe_srcs = sorted(glob.glob(os.path.join(PROBE_SRC, "*.hip")))
-    deps = srcs + probe_srcs + glob.glob(os.path.join(CSRC, "*.hpp")) + glob.glob(os.path.join(HERE, "..", "include", "*.h"))
-    if not force and all(os.path.exists(l) and all(os.path.getmtime(l) >= os.path.getmtime(d) for d in deps) for l in (LIB, PROBE_LIB)):
+    deps = srcs + probe_srcs + [FASTCALL_SRC] + glob.glob(os.path.join(CSRC, "*.hpp")) + glob.glob(os.path.join(HERE, "..", "include", "*.h"))
+    if not force and all(os.path.exists(l) and all(os.path.getmtime(l) >= os.path.getmtime(d) for d in deps) for l in (LIB, PROBE_LIB, FASTCALL_LIB)):
         return LIB
     objs = []
     probe_objs = []
@@ -37,6 +50,7 @@ def build(force: bool = True, verbose: bool = False) -> str:
         (probe_objs if s in probe_srcs else objs).append(o)
         cmd = ["hipcc", "-c"] + [f for f in FLAGS if f != "-shared"] + ["-o", o, s]
         procs.append((s, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
+    procs.append((FASTCALL_SRC, subprocess.Popen(fastcall_command(), stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
     failed = False
     for s, p in procs:
         out, _ = p.communicate()
@@ -47,7 +61,7 @@ def build(force: bool = True, verbose: bool = False) -> str:
         elif verbose and out.strip():
             sys.stderr.write(f"--- {s}\n{out}\n")
     if failed:
-        raise RuntimeError("hipcc failed")
+        raise RuntimeError("compilation failed")
     subprocess.run(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs, check=True)
     subprocess.run(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", PROBE_LIB] + probe_objs, check=True)
     return LIB

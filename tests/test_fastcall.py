@@ -1,0 +1,70 @@
+"""The C++ marshalling of the forward calls against the Python one beside it: what it does not take goes to the Python code, with that code's
+errors; on the GPU the same statuses, stream and results."""
+import pytest
+import torch
+
+import paper_2603_05168_amd.binding as b
+
+
+def test_built_and_declines_what_it_does_not_know():
+    assert b._fastcall is not None
+    ws, Y, X = torch.zeros(256, dtype=torch.uint8), torch.zeros(2, 8), torch.zeros(2, 8, dtype=torch.bfloat16)
+    rest = (None, None, None, None, 0)
+    assert b._fast_linear(X, ws, ws, Y, 2, 4, ws, *rest) is None                # not on a GPU
+    assert b._fast_linear(X, 4096, ws, Y, 2, 4, ws, *rest) is None              # an address
+    assert b._fast_linear(X, ws, ws, torch.nn.Parameter(Y), 2, 4, ws, *rest) is None
+    assert b._fast_linear(X[0], ws, ws, Y, 2, 4, ws, *rest) is None             # one dimension
+    assert b._fast_linear(X, ws) is None
+    assert b._fast_grouped(b"short", 2, 4, 0, ws) is None
+    with pytest.raises(TypeError):
+        b.sbn_sparse_ternary_linear(X.float(), ws, ws, Y, 2, 4, ws)
+    with pytest.raises(ValueError):
+        b.sbn_sparse_ternary_linear(X[0], ws, ws, Y, 2, 4, ws)
+
+
+def _layer(tokens=5, d_in=512, d_out=96):
+    from gpu_util import hip_pack
+    import sbn_synth
+    packed, gamma = hip_pack(sbn_synth.latent_weight(d_out, d_in, 77), 2, 4)
+    X = sbn_synth.activations(tokens, d_in, 78).cuda()
+    ws = b.new_workspace(b.sbn_workspace_bytes(b.SBN_OP_LINEAR, tokens, d_out, d_in, 2, 4))
+    return X, packed, gamma, ws
+
+
+@pytest.mark.gpu
+def test_same_results_streams_and_errors(monkeypatch):
+    X, packed, gamma, ws = _layer()
+    out = {}
+    for name in ("fast", "python"):
+        if name == "python":
+            monkeypatch.setattr(b, "_fast_linear", lambda *args: None)
+            monkeypatch.setattr(b, "_fast_grouped", lambda *args: None)
+        side = torch.cuda.Stream()
+        side.wait_stream(torch.cuda.current_stream())
+        Y = [torch.full((5, 96), float("nan"), device="cuda") for _ in range(3)]
+        bias = torch.arange(96, dtype=torch.float32, device="cuda")
+        torch.cuda.synchronize()
+        with torch.cuda.stream(side):
+            assert b._fastcall.stream() == side.cuda_stream
+            b.sbn_sparse_ternary_linear(X, packed, gamma, Y[0], 2, 4, ws)
+            b.LinearGroup([X, X], [packed] * 2, [gamma] * 2, Y[1:], 2, 4, b.new_workspace(2 * ws.numel())).run()
+        assert b._fastcall.stream() == torch.cuda.current_stream().cuda_stream
+        torch.cuda.synchronize()
+        xq, sx = torch.zeros(5, 512, dtype=torch.int8, device="cuda"), torch.zeros(5, device="cuda")
+        Yb, Yq = torch.zeros(5, 96, device="cuda"), torch.zeros(5, 96, device="cuda")
+        b.sbn_sparse_ternary_linear(X, packed, gamma, Yb, 2, 4, ws, bias=bias, xq_out=xq, sx_out=sx)
+        b.sbn_sparse_ternary_linear(None, packed, gamma, Yq, 2, 4, ws, xq_out=xq, sx_out=sx)
+        b.sbn_sparse_ternary_linear(X, packed.data_ptr(), gamma, Yb[:, :], 2, 4, ws, bias=bias.data_ptr())
+        torch.cuda.synchronize()
+        assert torch.equal(Y[0], Y[1]) and torch.equal(Y[0], Y[2]) and torch.equal(Y[0], Yq)
+        errors = []
+        for call in (lambda: b.sbn_sparse_ternary_linear(X, packed, gamma, Yb, 9, 4, ws),
+                     lambda: b.sbn_sparse_ternary_linear(X, packed, gamma, Yb, 2, 4, ws[:256]),
+                     lambda: b.sbn_sparse_ternary_linear(X, packed[4:], gamma, Yb, 2, 4, ws),
+                     lambda: b.sbn_sparse_ternary_linear(X, None, gamma, Yb, 2, 4, ws),
+                     lambda: b.LinearGroup([X], [packed], [gamma], [Yb], 2, 4, ws[:256]).run()):
+            with pytest.raises(b.SbnError) as e:
+                call()
+            errors.append((e.value.status, str(e.value)))
+        out[name] = [y.cpu() for y in Y + [Yb, Yq]] + errors
+    assert all(torch.equal(a, c) if torch.is_tensor(a) else a == c for a, c in zip(out["fast"], out["python"]))
