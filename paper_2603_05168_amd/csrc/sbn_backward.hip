@@ -317,21 +317,24 @@ __device__ __forceinline__ int bf16_product_of_block(const GemmBf16Group &grp)
 }
 
 // Block tile 256 x 256 with eight wavefronts of 128 (n) x 64 (m), or 128 x 128 with four of 64 x 64 (two blocks per
-// multiprocessor), two LDS stages of 64 k filled by LDS-DMA.  A stage is consumed in quarters of 16 k; the fragments of the
-// next quarter are read under the matrix instructions of the current one, also across the barrier between two stages,
-// and the requests for the stage after next stand there as well, so a wavefront always has matrix instructions to issue:
-// 1.45 us per stage of the large tile (1.48 PFLOP/s) where one barrier, eight requests and a first read in front of every
-// stage's matrix instructions took 1.9 us.  What bounds it now: the matrix pipe at the clock the board holds (1.9 PFLOP/s on
-// operands from registers), and 10 us per tile for its first stages and its result, which nothing covers.
-// us per call, before and now: 2560 x 2560 at 16384 tokens, three layers 1305 -> 1200, one 523 -> 463; 6912 x 2560, two layers
-// 2274 -> 2100; 6912 x 2560 at 1024 tokens 170 -> 101.  dY / s_x in memory (5.7 TB/s) is 90 of the 1200 and 4 of the 101 us.
+// multiprocessor), stages of 64 k filled by LDS-DMA: a ring of five slots that the two operands take in turns, so that P lies in
+// LDS two stages ahead and Q one.  A stage is consumed in quarters of 16 k; the fragments of the next quarter are read under the
+// matrix instructions of the current one, also across the barrier between two stages, and the requests for later stages
+// stand there as well, so a wavefront always has matrix instructions to issue: 1.45 us per stage of the large tile where one
+// barrier, eight requests and a first read in front of every stage's matrix instructions took 1.9 us.  What bounds it now: the
+// matrix pipe at the clock the board holds (1.9 PFLOP/s on operands from registers), and 10 us per tile for its first stages and
+// its result, which nothing covers.
+// The fifth slot is what LDS has left beside two whole stages.  With two, all requests of a stage had three quarters of one to
+// arrive in: three layers of 2560 x 2560 at 16384 tokens 943 us then and 927 now (the products alone), two of 6912 x 2560 1844
+// and 1806, a training step of 6912 x 2560 in two parts of 1024 tokens (small tiles) 324 and 306.
 constexpr int GD_K = 64;     // k per stage
 template <bool BIG> struct Bf16Tile {
     static constexpr int N = BIG ? 256 : 128, M = BIG ? 256 : 128;
     static constexpr int WAVES = BIG ? 8 : 4, WN = 2, WM = WAVES / WN;       // wavefronts along n and m
     static constexpr int WP = N / WN / 32, WQ = M / WM / 32;                 // 32 x 32 tiles of a wavefront: 4 x 2 or 2 x 2
-    static constexpr int PBYTES = N * GD_K * 2, STAGE = (N + M) * GD_K * 2;
-    static constexpr int LDS = 2 * STAGE;
+    static constexpr int SLOT = N * GD_K * 2, SLOTS = 5;                     // one operand's share of a stage
+    static constexpr int LDS = SLOTS * SLOT, STAGING = 4 * SLOT / WAVES;     // the last: of a wavefront, for its result
+    static_assert(M == N, "the two operands take turns in the slots");
 };
 
 template <bool BIG, bool QT>
@@ -376,27 +379,29 @@ __device__ __forceinline__ void bf16_tile_body(const GemmBf16Args &g, uint8_t *d
             qlast[i] = (uint32_t)(((int64_t)m * g.ldq + (8 * col < kleft ? col : (kleft - 1) / 8) * 8) * 2);
         }
     }
-    // the eight instructions of a wavefront and stage one by one, so that they can stand between matrix instructions; past the
-    // end the last stage is fetched again into a buffer nobody reads any more
-    auto dma_one = [&](int kt, const uint32_t stage, const int i) {
+    // the four instructions of a wavefront and slot one by one, so that they can stand between matrix instructions; past the
+    // end the last stage is fetched again into a slot nobody reads any more
+    auto dma_p = [&](int kt, const uint32_t slot, const int i) {
         kt = kt < nk ? kt : nk - 1;
-        const uint32_t dst = lds0 + stage + wave * 4096;
-        if (i < 4) lds_dma16(pbase + (int64_t)kt * (GD_K * 2), poff[i], dst + i * 1024);
-        else lds_dma16(qbase + (int64_t)kt * qstep, kt == nk - 1 ? qlast[i - 4] : qoff[i - 4], dst + S::PBYTES + (i - 4) * 1024);
+        lds_dma16(pbase + (int64_t)kt * (GD_K * 2), poff[i], lds0 + slot + wave * 4096 + i * 1024);
+    };
+    auto dma_q = [&](int kt, const uint32_t slot, const int i) {
+        kt = kt < nk ? kt : nk - 1;
+        lds_dma16(qbase + (int64_t)kt * qstep, kt == nk - 1 ? qlast[i] : qoff[i], lds0 + slot + wave * 4096 + i * 1024);
     };
     // k of the last stage past the end of Q: what was fetched in their place may be infinite, and zeros of P do not cancel that.
     // A lane overwrites what it asked for itself, behind its own wait and in front of the barrier that publishes the stage.
-    auto zero_tail = [&](const uint32_t stage) {
+    auto zero_tail = [&](const uint32_t slot) {
         typedef __attribute__((address_space(3))) v4i *lds_v4i;
         asm volatile("" ::: "memory");   // not in front of the wait
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int k = QT ? (512 / S::M) * (4 * wave + i) + lane / (S::M / 8) : 8 * ((lane & 7) ^ (((32 * wave + 8 * i + (lane >> 3)) >> 1) & 7));
-            if (k >= kleft) *(lds_v4i)(uintptr_t)(lds0 + stage + wave * 4096 + S::PBYTES + i * 1024 + 16 * lane) = v4i{0, 0, 0, 0};
+            if (k >= kleft) *(lds_v4i)(uintptr_t)(lds0 + slot + wave * 4096 + i * 1024 + 16 * lane) = v4i{0, 0, 0, 0};
         }
     };
     // LDS read addresses: k contiguous: row * 128 + 16 * ((2u + c) ^ ((row >> 1) & 7)); (row >> 1) & 7 = (r >> 1) & 7 for every
-    // tile of the wavefront, so one lane address per u, tiles are immediate offsets; the stage is one bit of the address.  Transposed: lane l of a
+    // tile of the wavefront, so one lane address per u, tiles are immediate offsets; the addresses move on with the slot.  Transposed: lane l of a
     // group of 16 supplies the address of row k0 + (l >> 2), columns 4 (l & 3) .. + 3 and gets four k of column l; two
     // reads (h = 0, 1) make the eight k of a fragment.
     uint32_t pa[4], qa[4];
@@ -404,7 +409,7 @@ __device__ __forceinline__ void bf16_tile_body(const GemmBf16Args &g, uint8_t *d
     for (int u = 0; u < 4; ++u) {
         const int slot = (2 * u + c) ^ ((r >> 1) & 7);
         pa[u] = lds0 + (wn * 32 * WP + r) * 128 + 16 * slot;
-        if constexpr (!QT) qa[u] = lds0 + S::PBYTES + (wm * 32 * WQ + r) * 128 + 16 * slot;
+        if constexpr (!QT) qa[u] = lds0 + S::SLOT + (wm * 32 * WQ + r) * 128 + 16 * slot;
     }
     uint32_t qt[WQ][2];
     if constexpr (QT) {
@@ -414,7 +419,7 @@ __device__ __forceinline__ void bf16_tile_body(const GemmBf16Args &g, uint8_t *d
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 const int gran = (wm * 32 * WQ + 32 * b) / 8 + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);
-                qt[b][h] = lds0 + S::PBYTES + (8 * c + 4 * h + rr) * QROW + 16 * (gran ^ (4 * rr | 2 * h)) + 8 * (lane & 1);
+                qt[b][h] = lds0 + S::SLOT + (8 * c + 4 * h + rr) * QROW + 16 * (gran ^ (4 * rr | 2 * h)) + 8 * (lane & 1);
             }
     }
     typedef __attribute__((address_space(3))) const v8bf *lds_v8bf;
@@ -443,18 +448,8 @@ __device__ __forceinline__ void bf16_tile_body(const GemmBf16Args &g, uint8_t *d
             fq[set][i - WP] = *(lds_v8bf)(uintptr_t)(qa[u] + (i - WP) * 32 * 128);
         }
     };
-    static_assert((S::STAGE & (S::STAGE - 1)) == 0, "the other stage is the address with one bit flipped (dynamic LDS starts at 0)");
-    auto flip = [&]() {
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            pa[u] ^= S::STAGE;
-            if constexpr (!QT) qa[u] ^= S::STAGE;
-        }
-        if constexpr (QT) {
-#pragma unroll
-            for (int b = 0; b < WQ; ++b) { qt[b][0] ^= S::STAGE; qt[b][1] ^= S::STAGE; }
-        }
-    };
+    // byte offset of the slot two further on in the ring
+    auto advance = [](const uint32_t slot) { return slot < 3u * S::SLOT ? slot + 2u * S::SLOT : slot - 3u * S::SLOT; };
     // A quarter step: WP x WQ matrix instructions; side(s) is issued after instruction s.  The source order is the intended
     // issue order, a scheduling barrier after every matrix instruction keeps it.
     constexpr int SLOTS = WP * WQ;
@@ -473,36 +468,53 @@ __device__ __forceinline__ void bf16_tile_body(const GemmBf16Args &g, uint8_t *d
         for (int k = 0; k < n; ++k)
             if (k * SLOTS / n == s) op(k);
     };
-    // Step kt reads stage kt & 1.  Quarters 0 to 2 read the fragments of the next quarter under their matrix instructions; then
-    // stage kt + 1 must have landed and every wavefront holds the last fragments of stage kt, so behind the barrier the last
-    // quarter reads the first fragments of stage kt + 1 and asks for stage kt + 2 in the buffer just left.
+    // The slots are a ring in the order P(0), Q(0), P(1), Q(1), ...  Step kt: quarters 0 to 2 read the fragments of the next
+    // quarter under their matrix instructions; then stage kt + 1 must have landed and every wavefront holds the last fragments of
+    // stage kt, so behind the barrier the last quarter reads the first fragments of stage kt + 1 and asks for Q(kt + 2) and
+    // P(kt + 3) in the two slots just left.
 #pragma unroll
-    for (int i = 0; i < 8; ++i) dma_one(0, 0, i);
+    for (int j = 0; j < 5; ++j)
 #pragma unroll
-    for (int i = 0; i < 8; ++i) dma_one(1, S::STAGE, i);
-    SBN_WAIT_VMCNT(8);
-    if (nk == 1 && kleft < GD_K) zero_tail(0);
+        for (int i = 0; i < 4; ++i) {
+            if (j & 1) dma_q(j >> 1, j * S::SLOT, i);
+            else dma_p(j >> 1, j * S::SLOT, i);
+        }
+    SBN_WAIT_VMCNT(12);
+    if (nk == 1 && kleft < GD_K) zero_tail(S::SLOT);
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < READS; ++i) read_one(0, i);
-    uint32_t stage = 0;
+    uint32_t sp = 0, sq = S::SLOT;
     for (int kt = 0; kt < nk; ++kt) {
+        const uint32_t sp_next = advance(sp), sq_next = advance(sq);
 #pragma unroll
         for (int u = 0; u < 3; ++u)
             quarter(u, [&](const int s) { spread(s, READS, [&](const int k) { read_one(u + 1, k); }); });
-        SBN_WAIT_VMCNT(0);
-        if (kt == nk - 2 && kleft < GD_K) zero_tail(stage ^ S::STAGE);
+        SBN_WAIT_VMCNT(4);   // P(kt + 2) may fly
+        if (kt == nk - 2 && kleft < GD_K) zero_tail(sq_next);
         __syncthreads();
-        flip();
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            pa[u] += sp_next - sp;
+            if constexpr (!QT) qa[u] += sq_next - sq;
+        }
+        if constexpr (QT) {
+#pragma unroll
+            for (int b = 0; b < WQ; ++b) { qt[b][0] += sq_next - sq; qt[b][1] += sq_next - sq; }
+        }
         quarter(3, [&](const int s) {
             spread(s, READS, [&](const int k) { read_one(0, k); });
-            spread(s, 8, [&](const int k) { dma_one(kt + 2, stage, k); });
+            spread(s, 8, [&](const int k) {
+                if (k < 4) dma_q(kt + 2, sp, k);
+                else dma_p(kt + 3, sq, k - 4);
+            });
         });
-        stage ^= S::STAGE;
+        sp = sp_next;
+        sq = sq_next;
     }
     SBN_WAIT_VMCNT(0);   // the surplus stages have landed
     __syncthreads();
-    bf16_wave_epilogue<WP, WQ>(g, acc, dlds + wave * (S::LDS / S::WAVES), n0 + wn * 32 * WP, m0 + wm * 32 * WQ, lane);
+    bf16_wave_epilogue<WP, WQ>(g, acc, dlds + wave * S::STAGING, n0 + wn * 32 * WP, m0 + wm * 32 * WQ, lane);
 }
 
 template <bool BIG>
