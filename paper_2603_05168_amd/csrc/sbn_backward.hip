@@ -17,10 +17,12 @@ namespace sbn {
 
 namespace {
 
-__device__ __forceinline__ uint32_t f32_to_bf16(float f)
+// two values rounded to bf16 (to nearest, ties to even), lo in the low half: v_cvt_pk_bf16_f32
+__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
 {
-    const uint32_t u = __float_as_uint(f);
-    return (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;   // round to nearest even; inputs are finite
+    typedef float v2f __attribute__((ext_vector_type(2)));
+    typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v2f{lo, hi}, v2bf));
 }
 
 // ---- layout kernels -------------------------------------------------------------------------------
@@ -175,7 +177,7 @@ __device__ __forceinline__ void scale_four_rows(const uint4 *__restrict__ dY, co
         uint32_t o[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k)
-            o[k] = f32_to_bf16(__fdiv_rn(__uint_as_float(w[k] << 16), s[r])) | (f32_to_bf16(__fdiv_rn(__uint_as_float(w[k] & 0xffff0000u), s[r])) << 16);
+            o[k] = pack_bf16(__fdiv_rn(__uint_as_float(w[k] << 16), s[r]), __fdiv_rn(__uint_as_float(w[k] & 0xffff0000u), s[r]));
         if (t0 + r < tokens) dst[(t0 + r) * nvec + i] = make_uint4(o[0], o[1], o[2], o[3]);
     }
 }
@@ -292,7 +294,7 @@ __device__ __forceinline__ void bf16_wave_epilogue(const GemmBf16Args &g, const 
             }
             uint32_t o[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) o[i] = f32_to_bf16(v[2 * i]) | (f32_to_bf16(v[2 * i + 1]) << 16);
+            for (int i = 0; i < 4; ++i) o[i] = pack_bf16(v[2 * i], v[2 * i + 1]);
             *dst = make_uint4(o[0], o[1], o[2], o[3]);
         }
     }
