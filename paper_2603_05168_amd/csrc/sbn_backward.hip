@@ -70,16 +70,14 @@ __device__ __forceinline__ void decode_quarter(const uint32_t *chunk, Put &&put)
     }
 }
 
-// packed weights -> W_eff^T as bf16 [d_in, ld] (ld >= d_out; zeros for rows of W past d_out): block = 64 rows of W x one
-// chunk, a wavefront per quarter of the chunk.  Bound by the bytes it writes.
+// packed weights -> W_eff^T as bf16 [d_in, ld] (ld >= d_out; zeros for rows of W past d_out): 64 rows of W x one chunk, a
+// wavefront per quarter of the chunk
 template <int N, int M>
-__global__ void __launch_bounds__(256) unpack_transpose_kernel(const uint8_t *__restrict__ packed, int d_out, int d_in,
-                                                              uint16_t *__restrict__ wt, int64_t ld)
+__device__ __forceinline__ void unpack_transpose_tile(const uint8_t *__restrict__ packed, int d_out, int d_in, uint16_t *__restrict__ wt, int64_t ld,
+                                                      int chunk, int o0, uint16_t *tile)
 {
-    __shared__ __attribute__((aligned(16))) uint16_t tile[128 * TP];
     constexpr int B = N == M ? 0 : M == 2 ? 1 : M == 4 ? 2 : 3, CHUNK_WORDS = 128 * N / M * (2 + B) / 32;
     const int nchunks = (d_in + CHUNK - 1) / CHUNK;
-    const int chunk = blockIdx.x, o0 = blockIdx.y * 64;
     const int ro = threadIdx.x & 63, quarter = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int o = o0 + ro;
     uint16_t *const col = tile + 32 * quarter * TP + ro;
@@ -98,68 +96,58 @@ __global__ void __launch_bounds__(256) unpack_transpose_kernel(const uint8_t *__
     write_tile_rows(tile, 128, wt, ld, (int64_t)chunk * CHUNK, o0, d_in, ld);
 }
 
-// Transposition of a 64 x 64 bf16 tile through LDS: rows go in as they are read (vector loads along
-// the source's contiguous dimension), come out as eight values of one column per thread
-// (ds_read_u16 with a pitch of 33 words: the 64 lanes of a read hit 32 different banks, two lanes
-// per word), and leave as 16-byte stores, eight lanes per 128-byte line of the destination.
-constexpr int TQ = 66;   // LDS row pitch of these tiles in bf16 elements (33 words)
-
-// tile[a][b] (a = source row, b = source column) -> dst[(c0 + b) * ld + r0 + a]
-__device__ __forceinline__ void write_tile_transposed(const uint16_t *tile, uint16_t *dst, int64_t ld, int64_t c0, int64_t r0,
-                                                      int64_t cmax, int64_t rmax)
+// int8 [rows, cols] -> bf16 transposed: dst [cols, ld] with dst[c, r] = src[r, c], zeros for r in [rows, ld), ld a multiple of 64;
+// one tile of 64 rows x 128 columns, so that reads and writes are whole cache lines (rows of 64 bytes were asked for by two
+// XCDs each).  Rows go into LDS as they are read; a thread takes eight rows of a pair of columns back (a word each) and
+// sorts them into two vectors.  Pitch of 65 words: the 64 words of a read lie in different banks.
+constexpr int TQ = 128 + 2;
+__device__ __forceinline__ void transpose_i8_tile(const int8_t *__restrict__ src, int64_t rows, int64_t cols, uint16_t *__restrict__ dst,
+                                                  int64_t ld, int64_t c0, int64_t r0, uint16_t *tile)
 {
+    const int cv = (threadIdx.x & 7) * 16;   // one 16-byte vector of two source rows per thread
+    __attribute__((aligned(16))) int8_t q[2][16];
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-        const int v = threadIdx.x + 256 * h;
-        const int b = v >> 3, av = (v & 7) * 8;
-        if (c0 + b >= cmax) continue;
-        uint32_t w[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-            w[i] = (uint32_t)tile[(av + 2 * i) * TQ + b] | ((uint32_t)tile[(av + 2 * i + 1) * TQ + b] << 16);
-        uint16_t *d = dst + (c0 + b) * ld + r0 + av;
-        if (r0 + av + 8 <= rmax && (ld & 7) == 0) {
-            *reinterpret_cast<uint4 *>(d) = make_uint4(w[0], w[1], w[2], w[3]);
+        const int64_t row = r0 + 32 * h + (threadIdx.x >> 3);
+        const bool row_ok = row < rows;
+        if (row_ok && c0 + cv + 16 <= cols && (cols & 15) == 0) {
+            *reinterpret_cast<uint4 *>(q[h]) = *reinterpret_cast<const uint4 *>(src + row * cols + c0 + cv);
         } else {
-            for (int e = 0; e < 8; ++e)
-                if (r0 + av + e < rmax) d[e] = (uint16_t)(w[e >> 1] >> (16 * (e & 1)));
+            for (int e = 0; e < 16; ++e) q[h][e] = (row_ok && c0 + cv + e < cols) ? src[row * cols + c0 + cv + e] : (int8_t)0;
         }
     }
-}
-
-// int8 [rows, cols] -> bf16 transposed: dst [cols, ld] with dst[c, r] = src[r, c], zeros for r in [rows, ld); one tile of 64 x 64
-__device__ __forceinline__ void transpose_i8_tile(const int8_t *__restrict__ src, int64_t rows, int64_t cols, uint16_t *__restrict__ dst,
-                                                  int64_t ld, int64_t c0, int64_t r0, uint16_t (&tile)[64 * TQ])
-{
-    const int r = threadIdx.x >> 2, cv = (threadIdx.x & 3) * 16;   // one 16-byte vector of a source row per thread
-    __attribute__((aligned(16))) int8_t q[16];
-    const bool row_ok = r0 + r < rows;
-    if (row_ok && c0 + cv + 16 <= cols && (cols & 15) == 0) {
-        *reinterpret_cast<uint4 *>(q) = *reinterpret_cast<const uint4 *>(src + (r0 + r) * cols + c0 + cv);
-    } else {
-        for (int e = 0; e < 16; ++e) q[e] = (row_ok && c0 + cv + e < cols) ? src[(r0 + r) * cols + c0 + cv + e] : (int8_t)0;
-    }
 #pragma unroll
-    for (int e = 0; e < 16; e += 2) {
-        const uint32_t lo = __float_as_uint((float)q[e]) >> 16, hi = __float_as_uint((float)q[e + 1]) & 0xffff0000u;
-        *reinterpret_cast<uint32_t *>(&tile[r * TQ + cv + e]) = lo | hi;   // |q| <= 128: exact in bf16
-    }
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int e = 0; e < 16; e += 2)   // |q| <= 128: exact in bf16, the high half of the fp32 value
+            *reinterpret_cast<uint32_t *>(&tile[(32 * h + (threadIdx.x >> 3)) * TQ + cv + e]) =
+                __builtin_amdgcn_perm(__float_as_uint((float)q[h][e + 1]), __float_as_uint((float)q[h][e]), 0x07060302u);
     __syncthreads();
-    write_tile_transposed(tile, dst, ld, c0, r0, cols, ld);
-}
-
-__global__ void __launch_bounds__(256) transpose_i8_kernel(const int8_t *__restrict__ src, int64_t rows, int64_t cols,
-                                                          uint16_t *__restrict__ dst, int64_t ld)
-{
-    __shared__ __attribute__((aligned(16))) uint16_t tile[64 * TQ];
-    transpose_i8_tile(src, rows, cols, dst, ld, (int64_t)blockIdx.x * 64, (int64_t)blockIdx.y * 64, tile);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int v = threadIdx.x + 256 * h, b = (v >> 3) * 2, av = (v & 7) * 8;
+        if (c0 + b >= cols) continue;
+        uint32_t w[8], lo[4], hi[4];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) w[i] = *reinterpret_cast<const uint32_t *>(&tile[(av + i) * TQ + b]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            lo[i] = __builtin_amdgcn_perm(w[2 * i + 1], w[2 * i], 0x05040100u);
+            hi[i] = __builtin_amdgcn_perm(w[2 * i + 1], w[2 * i], 0x07060302u);
+        }
+        uint16_t *d = dst + (c0 + b) * ld + r0 + av;   // columns are a multiple of 8: both of a pair exist
+        *reinterpret_cast<uint4 *>(d) = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+        *reinterpret_cast<uint4 *>(d + ld) = make_uint4(hi[0], hi[1], hi[2], hi[3]);
+    }
 }
 
 // dY [tokens, 8 nvec] bf16 -> dY[t, :] / s_x[t], rounded to bf16 (the one rounding of an operand of dW), same layout.  It is the
 // gradient that is rounded and not x~ / s_x, of which a row has 255 values at most: the error of a gradient is another one in
 // every token, that of a level would be the same wherever tokens share s_x (saturated or clipped activations) and add up over
 // them, and it would depend on where the levels lie between two powers of two, i.e. on the amplitude of the activations.
-// Four rows from t0 on, vector i of 8 values.
+// Four rows from t0 on, vector i of 8 values.  The quotient is Markstein's: with r = 1 / s rounded once per row, a r and one
+// correction by the exact remainder give the IEEE quotient wherever the remainder does not underflow (|a| above 2^-100; below, an ulp
+// of fp32 in front of the rounding to bf16); v_div_fixup_f32 gives infinities, NaN and zeros what a division gives them.
 __device__ __forceinline__ void scale_four_rows(const uint4 *__restrict__ dY, const float *__restrict__ sx, int64_t tokens, int nvec,
                                                 uint4 *__restrict__ dst, int64_t t0, int i)
 {
@@ -174,30 +162,109 @@ __device__ __forceinline__ void scale_four_rows(const uint4 *__restrict__ dY, co
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const uint32_t w[4] = {v[r].x, v[r].y, v[r].z, v[r].w};
+        const float inv = __fdiv_rn(1.0f, s[r]);
+        auto over_s = [&](const uint32_t bits) {
+            const float a = __uint_as_float(bits), q = a * inv;
+            return __builtin_amdgcn_div_fixupf(__builtin_fmaf(__builtin_fmaf(-q, s[r], a), inv, q), s[r], a);
+        };
         uint32_t o[4];
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
-            o[k] = pack_bf16(__fdiv_rn(__uint_as_float(w[k] << 16), s[r]), __fdiv_rn(__uint_as_float(w[k] & 0xffff0000u), s[r]));
+        for (int k = 0; k < 4; ++k) o[k] = pack_bf16(over_s(w[k] << 16), over_s(w[k] & 0xffff0000u));
         if (t0 + r < tokens) dst[(t0 + r) * nvec + i] = make_uint4(o[0], o[1], o[2], o[3]);
     }
 }
 
-// Both operands of dW in one launch: the first `tiles` blocks transpose a tile of x~ each (tiles_c of them per 64 tokens; none where
-// another layer of the call has done it), the others scale 256 vectors of four rows of dY each (slices of them per row).
-// Bound by the bytes the two move; in two launches a call took 107 us at 1024 tokens (6912 x 2560) and 23.5 at 512
-// (1024 x 1024), in one 101.5 and 21.3.
-__global__ void __launch_bounds__(256) dw_operands_kernel(const int8_t *__restrict__ xq, int64_t tokens, int64_t d_in, uint16_t *__restrict__ xt,
-                                                         int64_t ldt, unsigned tiles_c, unsigned tiles, const uint4 *__restrict__ dY,
-                                                         const float *__restrict__ sx, int nvec, unsigned slices, uint4 *__restrict__ dys)
+// All operands of a call's products in one launch: W_eff^T (64 rows of W x one chunk per block), transposes of int8 matrices (x~,
+// or W_eff of a pattern that has no decoder here; 64 x 128 per block) and dY / s_x (256 x four rows of eight values per
+// block).  Bound by the bytes that they move; the decoders, which wait for their LDS, run beside the streams.
+// One launch per layer for W_eff^T and one for the other two left the device in a tail seven to fourteen times per training
+// step, and a block with 256 vectors of one row quad alone left a third of its lanes idle at 2560 outputs.  us per step of a block at
+// 16384 tokens, before and now: 617 -> 462 (5.6 to 5.8 TB/s); 6912 x 2560 at 1024 tokens (6:8) 23.0 -> 17.8.
+enum OperandKind { OPERAND_UNPACK, OPERAND_TRANSPOSE, OPERAND_SCALE };
+struct OperandJob {
+    const void *src;
+    const float *sx;
+    void *dst;
+    int64_t ld;        // row length of dst (unpack, transpose)
+    int rows, cols;    // of src; scale: tokens and vectors of eight values per token
+    int across;        // blocks along the columns of src (unpack: chunks)
+    int kind;
+};
+constexpr int OPERAND_JOBS_MAX = 24;
+struct OperandGroup {
+    OperandJob job[OPERAND_JOBS_MAX];
+    int block0[OPERAND_JOBS_MAX + 1];
+    int count;
+};
+
+template <int N, int M>   // 0, 0: no unpacking among the jobs
+__global__ void __launch_bounds__(256) operands_kernel(OperandGroup grp)
 {
-    __shared__ __attribute__((aligned(16))) uint16_t tile[64 * TQ];
-    if (blockIdx.x < tiles) {
-        transpose_i8_tile(xq, tokens, d_in, xt, ldt, (int64_t)(blockIdx.x % tiles_c) * 64, (int64_t)(blockIdx.x / tiles_c) * 64, tile);
+    static_assert(64 * TQ <= 128 * TP, "one LDS tile for both");
+    __shared__ __attribute__((aligned(16))) uint16_t tile[128 * TP];
+    int j = 0;
+    while (j + 1 < grp.count && (int)blockIdx.x >= grp.block0[j + 1]) ++j;
+    const OperandJob &job = grp.job[j];
+    const unsigned b = blockIdx.x - grp.block0[j];
+    if (job.kind == OPERAND_SCALE) {
+        // the vectors of a row quad one after another; a block starts at vector `first` of quad `quad`
+        const unsigned nvec = job.cols;
+        unsigned quad = b * 256 / nvec;   // vectors of a whole dY / 4: below 2^32 for any that fits the device
+        unsigned i = b * 256 - quad * nvec + threadIdx.x;
+        if (nvec >= 256) {
+            if (i >= nvec) { i -= nvec; ++quad; }
+        } else {
+            quad += i / nvec;
+            i %= nvec;
+        }
+        if (quad < (unsigned)(job.rows + 3) / 4)
+            scale_four_rows(static_cast<const uint4 *>(job.src), job.sx, job.rows, (int)nvec, static_cast<uint4 *>(job.dst), 4 * (int64_t)quad, (int)i);
         return;
     }
-    const unsigned b = blockIdx.x - tiles;
-    const int i = (int)(b % slices * 256 + threadIdx.x);
-    if (i < nvec) scale_four_rows(dY, sx, tokens, nvec, dys, 4 * (int64_t)(b / slices), i);
+    const int across = (int)(b % job.across), down = (int)(b / job.across);
+    if constexpr (N != 0) {
+        if (job.kind == OPERAND_UNPACK) {
+            unpack_transpose_tile<N, M>(static_cast<const uint8_t *>(job.src), job.rows, job.cols, static_cast<uint16_t *>(job.dst), job.ld, across, 64 * down,
+                                        tile);
+            return;
+        }
+    }
+    transpose_i8_tile(static_cast<const int8_t *>(job.src), job.rows, job.cols, static_cast<uint16_t *>(job.dst), job.ld, 128 * (int64_t)across,
+                      64 * (int64_t)down, tile);
+}
+
+// The jobs of a call, unpacking first (their blocks take longest), dealt out in launches of OPERAND_JOBS_MAX.
+sbn_status launch_operands(const std::vector<OperandJob> &jobs, const Pattern &pat, hipStream_t stream)
+{
+    for (size_t first = 0; first < jobs.size(); first += OPERAND_JOBS_MAX) {
+        OperandGroup grp;
+        grp.count = (int)std::min(jobs.size() - first, (size_t)OPERAND_JOBS_MAX);
+        std::copy_n(jobs.begin() + first, grp.count, grp.job);
+        std::stable_sort(grp.job, grp.job + grp.count, [](const OperandJob &a, const OperandJob &b) { return a.kind < b.kind; });
+        int64_t blocks = 0;
+        for (int i = 0; i < grp.count; ++i) {
+            const OperandJob &j = grp.job[i];
+            grp.block0[i] = (int)blocks;
+            blocks += j.kind == OPERAND_SCALE ? ceil_div(ceil_div(j.rows, 4) * (int64_t)j.cols, 256) : j.across * (j.ld / 64);
+        }
+        for (int i = grp.count; i <= OPERAND_JOBS_MAX; ++i) grp.block0[i] = (int)blocks;
+        auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(256), 0, stream, grp); };
+        if (grp.job[0].kind != OPERAND_UNPACK) launch(operands_kernel<0, 0>);
+        else if (pat.N == pat.M) launch(operands_kernel<8, 8>);   // dense codes look the same for every M
+        else if (pat.N == 2 && pat.M == 4) launch(operands_kernel<2, 4>);
+        else if (pat.N == 6) launch(operands_kernel<6, 8>);
+        else if (pat.N == 1) launch(operands_kernel<1, 4>);
+        else launch(operands_kernel<2, 8>);
+        const sbn_status st = check_launch("operands_kernel");
+        if (st != SBN_OK) return st;
+    }
+    return SBN_OK;
+}
+
+// patterns that operands_kernel decodes itself
+bool has_unpack(const Pattern &pat)
+{
+    return pat.N == pat.M || (pat.N == 2 && pat.M == 4) || (pat.N == 6 && pat.M == 8) || (pat.N == 1 && pat.M == 4) || (pat.N == 2 && pat.M == 8);
 }
 
 // ---- bf16 GEMM -------------------------------------------------------------------------------------------
@@ -603,7 +670,7 @@ size_t backward_workspace_bytes(int64_t tokens, int64_t d_out, int64_t d_in)
            align_up((size_t)d_out * ((d_in + 31) / 32) * 4, 256);
 }
 
-// Backward products of `count` layers in one pass: the layout kernels of every layer, then ONE matrix-multiply
+// Backward products of `count` layers in one pass: the operands of all layers in ONE launch, then ONE matrix-multiply
 // launch (per GB_GROUP_MAX products) over all dW and dX tiles.  Layers that share their quantized input (Q/K/V,
 // up/gate) share its transpose.
 sbn_status launch_backward_grouped(int count, const BackwardItem *items, const Pattern &pat, int flags, hipStream_t stream)
@@ -612,6 +679,8 @@ sbn_status launch_backward_grouped(int count, const BackwardItem *items, const P
     std::vector<GemmBf16Args> products;
     std::vector<const uint16_t *> xt_of(count, nullptr);
     products.reserve(2 * count);
+    std::vector<OperandJob> jobs;
+    jobs.reserve(3 * count);
     sbn_status st;
     for (int i = 0; i < count; ++i) {
         const BackwardItem &it = items[i];
@@ -630,24 +699,13 @@ sbn_status launch_backward_grouped(int count, const BackwardItem *items, const P
 
         if (it.dX) {
             const int64_t ldw = pad64(d_out);
-            const dim3 grid((unsigned)ceil_div(d_in, CHUNK), (unsigned)(ldw / 64));
-            auto unpack = [&](auto kernel) {
-                hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, static_cast<const uint8_t *>(it.packed), (int)d_out, (int)d_in, wt, ldw);
-                return check_launch("unpack_transpose_kernel");
-            };
-            if (pat.N == pat.M) st = unpack(unpack_transpose_kernel<8, 8>);   // dense codes look the same for every M
-            else if (pat.N == 2 && pat.M == 4) st = unpack(unpack_transpose_kernel<2, 4>);
-            else if (pat.N == 6 && pat.M == 8) st = unpack(unpack_transpose_kernel<6, 8>);
-            else if (pat.N == 1 && pat.M == 4) st = unpack(unpack_transpose_kernel<1, 4>);
-            else if (pat.N == 2 && pat.M == 8) st = unpack(unpack_transpose_kernel<2, 8>);
-            else {
+            if (has_unpack(pat)) {
+                jobs.push_back({it.packed, nullptr, wt, ldw, (int)d_out, (int)d_in, (int)ceil_div(d_in, CHUNK), OPERAND_UNPACK});
+            } else {
                 st = launch_expand_groups(it.packed, d_out, d_in, pat, w8, stream);
                 if (st != SBN_OK) return st;
-                hipLaunchKernelGGL(transpose_i8_kernel, dim3((unsigned)ceil_div(d_in, 64), (unsigned)(ldw / 64)), dim3(256), 0, stream, w8, d_out, d_in,
-                                   wt, ldw);
-                st = check_launch("transpose_i8_kernel");
+                jobs.push_back({w8, nullptr, wt, ldw, (int)d_out, (int)d_in, (int)ceil_div(d_in, 128), OPERAND_TRANSPOSE});
             }
-            if (st != SBN_OK) return st;
             // dX[t, k] = gamma * sum_o dY[t, o] * W_eff^T[k, o]
             GemmBf16Args a{};
             a.P = wt; a.ldp = ldw; a.N = (int)d_in;
@@ -661,14 +719,12 @@ sbn_status launch_backward_grouped(int count, const BackwardItem *items, const P
             const uint16_t *xts = nullptr;   // an earlier layer of the call already transposed the same activations
             for (int j = 0; j < i && !xts; ++j)
                 if (xt_of[j] && items[j].xq == it.xq && items[j].tokens == tokens && items[j].d_in == d_in) xts = xt_of[j];
-            const unsigned tiles_c = (unsigned)ceil_div(d_in, 64), tiles = xts ? 0u : tiles_c * (unsigned)(ldt / 64);
-            const unsigned slices = (unsigned)ceil_div(d_out / 8, 256);
-            if (!xts) xts = xt;
+            if (!xts) {
+                xts = xt;
+                jobs.push_back({it.xq, nullptr, xt, ldt, (int)tokens, (int)d_in, (int)ceil_div(d_in, 128), OPERAND_TRANSPOSE});
+            }
             xt_of[i] = xts;
-            hipLaunchKernelGGL(dw_operands_kernel, dim3(tiles + slices * (unsigned)ceil_div(tokens, 4)), dim3(256), 0, stream, it.xq, tokens, d_in, xt, ldt,
-                               tiles_c, tiles, reinterpret_cast<const uint4 *>(dy), it.sx, (int)(d_out / 8), slices, reinterpret_cast<uint4 *>(dys));
-            st = check_launch("dw_operands_kernel");
-            if (st != SBN_OK) return st;
+            jobs.push_back({dy, it.sx, dys, 0, (int)tokens, (int)(d_out / 8), 0, OPERAND_SCALE});
             // dW[o, k] = sum_t (dY / s_x)[t, o] * x~[t, k]; x~^T is zero for t in [tokens, ldt)
             GemmBf16Args a{};
             a.P = xts; a.ldp = ldt; a.N = (int)d_in;
@@ -685,7 +741,9 @@ sbn_status launch_backward_grouped(int count, const BackwardItem *items, const P
             products.push_back(a);
         }
     }
-    // all products are independent of each other (dX reads W_eff^T and dY, dW reads the two transposes)
+    st = launch_operands(jobs, pat, stream);
+    if (st != SBN_OK) return st;
+    // all products are independent of each other (dX reads W_eff^T and dY, dW reads x~^T and dY / s_x)
     return launch_gemm_bf16((int)products.size(), products.data(), stream);
 }
 

@@ -1,0 +1,57 @@
+"""The operands of the backward products value by value: where one factor of a product selects single elements, a sum has one
+term, the result is that operand itself (times gamma for dX) and has to be equal."""
+import pytest
+import torch
+
+import sbn_synth
+from gpu_util import DEV, hip_pack, oracle_pack, sbn
+
+pytestmark = pytest.mark.gpu
+
+
+def backward(dY, packed, gamma, xq, sx, N, M, dX=None, dW=None):
+    s = sbn()
+    tokens, d_out, d_in = dY.shape[0], dY.shape[1], xq.shape[1]
+    ws = s.new_workspace(s.sbn_workspace_bytes(s.SBN_OP_BACKWARD, tokens, d_out, d_in, N, M))
+    s.sbn_sparse_ternary_linear_backward(dY, packed, gamma, xq, sx, N, M, ws, d_in, dX=dX, dW=dW)
+    torch.cuda.synchronize()
+
+
+# d_out: one vector of eight, fewer than a block's 256 vectors, 256, 257 and two blocks less one; tokens off the row quads
+@pytest.mark.parametrize("tokens,d_out", [(1, 8), (3, 8), (66, 8), (5, 24), (133, 264), (4, 2048), (67, 2048), (129, 2056), (6, 4088)])
+def test_scaled_gradient(tokens, d_out):
+    d_in = (tokens + 7) // 8 * 8
+    g = torch.Generator().manual_seed(tokens + d_out)
+    dY = (torch.randn(tokens, d_out, generator=g) * torch.exp2(torch.randint(-40, 40, (tokens, d_out), generator=g).float())).to(torch.bfloat16)
+    dY[tokens - 1, d_out - 1] = 0
+    sx = torch.rand(tokens, generator=g) * 100 + 1e-3
+    xq = torch.zeros(tokens, d_in, dtype=torch.int8)
+    xq[torch.arange(tokens), torch.arange(tokens)] = 1                  # dW[o, t] = dY[t, o] / s_x[t]
+    dW = torch.full((d_out, d_in), float("nan"), dtype=torch.bfloat16, device=DEV)
+    backward(dY.to(DEV), None, None, xq.to(DEV), sx.to(DEV), 2, 4, dW=dW)
+    want = (dY.float() / sx[:, None]).to(torch.bfloat16)
+    assert torch.equal(dW[:, :tokens].T.float().cpu(), want.float())
+
+
+@pytest.mark.parametrize("tokens,d_in", [(1, 8), (63, 120), (64, 128), (65, 136), (130, 264), (200, 384)])
+def test_transposed_rows(tokens, d_in):
+    d_out = (tokens + 7) // 8 * 8
+    xq = torch.randint(-128, 128, (tokens, d_in), dtype=torch.int8, generator=torch.Generator().manual_seed(d_in))
+    sx = torch.full((tokens,), 2.0)
+    dY = torch.zeros(tokens, d_out, dtype=torch.bfloat16)
+    dY[torch.arange(tokens), torch.arange(tokens)] = 2                  # dW[t, k] = xq[t, k]
+    dW = torch.full((d_out, d_in), float("nan"), dtype=torch.bfloat16, device=DEV)
+    backward(dY.to(DEV), None, None, xq.to(DEV), sx.to(DEV), 2, 4, dW=dW)
+    assert torch.equal(dW[:tokens].float().cpu(), xq.float())
+
+
+@pytest.mark.parametrize("N,M", [(2, 4), (6, 8), (1, 4), (2, 8), (4, 4), (1, 2), (3, 4)])   # the last two through int8
+@pytest.mark.parametrize("d_out,d_in", [(8, 8), (72, 136), (128, 256)])
+def test_transposed_weights(N, M, d_out, d_in):
+    W = sbn_synth.latent_weight(d_out, d_in, 1200 + d_in)
+    packed, gamma = hip_pack(W, N, M)
+    _, _, Weff, _ = oracle_pack(W, N, M)
+    dY = torch.eye(d_out, dtype=torch.bfloat16, device=DEV)             # dX[o, k] = gamma W_eff[o, k]
+    dX = torch.full((d_out, d_in), float("nan"), dtype=torch.bfloat16, device=DEV)
+    backward(dY, packed, gamma, torch.zeros(d_out, d_in, dtype=torch.int8, device=DEV), torch.ones(d_out, device=DEV), N, M, dX=dX)
+    assert torch.equal(dX.float().cpu(), (torch.from_numpy(Weff).float() * gamma.cpu()).to(torch.bfloat16).float())
