@@ -9,7 +9,6 @@ from __future__ import annotations
 import ctypes
 import importlib.util
 import os
-import struct
 
 import torch
 
@@ -280,12 +279,11 @@ class LinearGroup:
         self.Y = _ptr_array(Y_list)
         self.N, self.M, self.path, self.workspace = N, M, path, workspace
         self.keep = (X_list, packed_list, gamma_list, Y_list)
-        self.addresses = struct.pack("8q", self.count, *(ctypes.addressof(a) for a in (self.X, self.tokens, self.d_in, self.d_out, self.packed,
-                                                                                        self.gamma, self.Y)))
 
     def run(self):
         ws = self.workspace
-        status = _fast_grouped(self.addresses, self.N, self.M, self.path, ws)
+        status = _fast_grouped(self.count, self.X, self.tokens, self.d_in, self.d_out, self.N, self.M, self.packed, self.gamma, self.Y,
+                               self.path, ws)
         if status is not None:
             if status:
                 _check(status, "sbn_sparse_ternary_linear_grouped")

@@ -77,31 +77,64 @@ PyObject *linear(PyObject *, PyObject *const *a, Py_ssize_t n)
     }
 }
 
-// (arrays, N, M, path, workspace): arrays = the count and the addresses of a LinearGroup's arrays, as its constructor packed them ->
-// status, or None
-struct Group { int64_t count, X, tokens, d_in, d_out, packed, gamma, Y; };
+// A ctypes array of at least `count` pointers or 64-bit integers, held while its address is in use; anything else is not held.
+struct Array {
+    Py_buffer view{};
+    bool held;
+    enum Kind { POINTERS, INTEGERS };
+    Array(PyObject *o, int count, Kind kind)
+    {
+        held = PyObject_GetBuffer(o, &view, PyBUF_ND | PyBUF_FORMAT) == 0;
+        if (!held) {
+            PyErr_Clear();
+            return;
+        }
+        // the formats of ctypes, which names the byte order; a ctypes pointer has no dimension
+        const auto is = [&](const char *format) { return !strcmp(view.format, format); };
+        if (view.ndim != 1 || view.itemsize != 8 || view.shape[0] < count || !(kind == POINTERS ? is("<P") : is("<q") || is("<l"))) release();
+    }
+    ~Array() { release(); }
+    Array(const Array &) = delete;
+    void release()
+    {
+        if (held) PyBuffer_Release(&view);
+        held = false;
+    }
+    template <class T> T as() const { return reinterpret_cast<T>(view.buf); }
+};
+
+// (count, X, tokens, d_in, d_out, N, M, packed, gamma, Y, path, workspace): the arrays as they are at this call -> status, or None
 PyObject *grouped(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
-    if (n != 5 || !g_grouped || !PyBytes_CheckExact(a[0]) || PyBytes_GET_SIZE(a[0]) != (Py_ssize_t)sizeof(Group)) Py_RETURN_NONE;
+    if (n != 12 || !g_grouped) Py_RETURN_NONE;
     try {
-        const at::Tensor *ws = plain(a[4]);
-        int N, M, path;
-        if (!ws || !ws->is_cuda() || !small_int(a[1], N) || !small_int(a[2], M) || !small_int(a[3], path)) Py_RETURN_NONE;
-        Group g;
-        memcpy(&g, PyBytes_AS_STRING(a[0]), sizeof g);
+        const at::Tensor *ws = plain(a[11]);
+        int count, N, M, path;
+        if (!ws || !ws->is_cuda() || !small_int(a[0], count) || count < 0 || !small_int(a[5], N) || !small_int(a[6], M) || !small_int(a[10], path))
+            Py_RETURN_NONE;
+        const Array X(a[1], count, Array::POINTERS), tokens(a[2], count, Array::INTEGERS), d_in(a[3], count, Array::INTEGERS),
+            d_out(a[4], count, Array::INTEGERS), packed(a[7], count, Array::POINTERS), gamma(a[8], count, Array::POINTERS), Y(a[9], count, Array::POINTERS);
+        if (!X.held || !tokens.held || !d_in.held || !d_out.held || !packed.held || !gamma.held || !Y.held) Py_RETURN_NONE;
         void *w = ws->data_ptr(), *stream = current_stream();
         const size_t bytes = ws->nbytes();
         int status;
         Py_BEGIN_ALLOW_THREADS
-        status = g_grouped((int)g.count, reinterpret_cast<const void *const *>(g.X), reinterpret_cast<const int64_t *>(g.tokens),
-                           reinterpret_cast<const int64_t *>(g.d_in), reinterpret_cast<const int64_t *>(g.d_out), N, M,
-                           reinterpret_cast<const void *const *>(g.packed), reinterpret_cast<const float *const *>(g.gamma),
-                           reinterpret_cast<float *const *>(g.Y), path, w, bytes, stream);
+        status = g_grouped(count, X.as<const void *const *>(), tokens.as<const int64_t *>(), d_in.as<const int64_t *>(), d_out.as<const int64_t *>(), N, M,
+                           packed.as<const void *const *>(), gamma.as<const float *const *>(), Y.as<float *const *>(), path, w, bytes, stream);
         Py_END_ALLOW_THREADS
         return PyLong_FromLong(status);
     } catch (...) {
         Py_RETURN_NONE;
     }
+}
+
+// (object, count): whether the grouped call takes the object as an array
+template <Array::Kind KIND> PyObject *takes_array(PyObject *, PyObject *args)
+{
+    PyObject *o;
+    int count;
+    if (!PyArg_ParseTuple(args, "Oi", &o, &count)) return nullptr;
+    return PyBool_FromLong(Array(o, count, KIND).held);
 }
 
 PyObject *stream(PyObject *, PyObject *) { return PyLong_FromVoidPtr(current_stream()); }
@@ -119,6 +152,8 @@ PyObject *bind(PyObject *, PyObject *args)
 PyMethodDef methods[] = {
     {"linear", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(linear)), METH_FASTCALL, nullptr},
     {"grouped", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(grouped)), METH_FASTCALL, nullptr},
+    {"array_of_pointers", takes_array<Array::POINTERS>, METH_VARARGS, nullptr},
+    {"array_of_integers", takes_array<Array::INTEGERS>, METH_VARARGS, nullptr},
     {"stream", stream, METH_NOARGS, nullptr},
     {"bind", bind, METH_VARARGS, nullptr},
     {nullptr, nullptr, 0, nullptr}};

@@ -1,5 +1,7 @@
 """The C++ marshalling of the forward calls against the Python one beside it: what it does not take goes to the Python code, with that code's
 errors; on the GPU the same statuses, stream and results."""
+import ctypes
+
 import pytest
 import torch
 
@@ -68,3 +70,43 @@ def test_same_results_streams_and_errors(monkeypatch):
             errors.append((e.value.status, str(e.value)))
         out[name] = [y.cpu() for y in Y + [Yb, Yq]] + errors
     assert all(torch.equal(a, c) if torch.is_tensor(a) else a == c for a, c in zip(out["fast"], out["python"]))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("fast", [True, False])
+def test_group_runs_on_the_arrays_it_has_now(monkeypatch, fast):
+    # attributes set after construction count, on both paths; the arrays that they replace are not looked at again
+    if not fast:
+        monkeypatch.setattr(b, "_fast_grouped", lambda *args: None)
+    X, packed, gamma, ws = _layer()
+    Y = [torch.full((5, 96), float("nan"), device="cuda") for _ in range(4)]
+    group = b.LinearGroup([X, X], [packed] * 2, [gamma] * 2, Y[:2], 2, 4, b.new_workspace(2 * ws.numel()))
+    group.run()
+    torch.cuda.synchronize()
+    want = Y[0].clone()
+    for y in Y:
+        y.fill_(float("nan"))
+    group.Y = b._ptr_array(Y[2:])
+    group.run()
+    torch.cuda.synchronize()
+    assert torch.equal(Y[2], want) and torch.equal(Y[3], want) and Y[0].isnan().all() and Y[1].isnan().all()
+    group.count, group.tokens = 1, b._i64_array([3, 3])
+    for y in Y:
+        y.fill_(float("nan"))
+    group.run()
+    torch.cuda.synchronize()
+    assert torch.equal(Y[2][:3], want[:3]) and Y[2][3:].isnan().all() and Y[3].isnan().all()
+    group.Y[0] = Y[0].data_ptr()          # an entry written in place
+    group.run()
+    torch.cuda.synchronize()
+    assert torch.equal(Y[0][:3], want[:3])
+
+
+def test_group_arrays_of_another_kind_are_left_to_python():
+    arrays = {"X": b._ptr_array([64]), "tokens": b._i64_array([1])}
+    assert b._fastcall.array_of_pointers(arrays["X"], 1) and b._fastcall.array_of_integers(arrays["tokens"], 1)
+    for other in (arrays["tokens"], b"12345678", [64], torch.zeros(1, dtype=torch.int64).numpy(), ctypes.pointer(ctypes.c_void_p(64)), None):
+        assert not b._fastcall.array_of_pointers(other, 1)
+    for other in (arrays["X"], (ctypes.c_int32 * 2)(), torch.zeros(1, dtype=torch.int64).numpy(), ctypes.pointer(ctypes.c_int64(1)), None):
+        assert not b._fastcall.array_of_integers(other, 1)
+    assert not b._fastcall.array_of_pointers(arrays["X"], 2)      # shorter than the count
