@@ -10,6 +10,8 @@
 
 #include <cstdint>
 #include <cstring>
+#include <exception>
+#include <new>
 
 namespace {
 
@@ -48,6 +50,31 @@ bool small_int(PyObject *o, int &v)
     return true;
 }
 
+// The call itself, without the interpreter's lock: -> status, or null with a Python error where it throws (the lock is held again by
+// then; the call has begun, so the Python code must not do it once more)
+template <class Call> PyObject *released(Call &&call)
+{
+    struct Unlocked {
+        PyThreadState *state = PyEval_SaveThread();
+        ~Unlocked() { PyEval_RestoreThread(state); }
+    };
+    try {
+        int status;
+        {
+            Unlocked unlocked;
+            status = call();
+        }
+        return PyLong_FromLong(status);
+    } catch (const std::bad_alloc &) {
+        return PyErr_NoMemory();
+    } catch (const std::exception &e) {
+        PyErr_SetString(PyExc_RuntimeError, e.what());
+    } catch (...) {
+        PyErr_SetString(PyExc_RuntimeError, "exception of an unknown kind");
+    }
+    return nullptr;
+}
+
 void *current_stream() { return c10::hip::getCurrentHIPStream().stream(); }
 
 // (X, packed, gamma, Y, N, M, workspace, bias, xq_out, sx_out, acc_out, path) -> status, or None
@@ -66,12 +93,10 @@ PyObject *linear(PyObject *, PyObject *const *a, Py_ssize_t n)
         const int64_t tokens = rows->size(0), d_in = rows->size(1), d_out = Y->size(1);
         void *y = Y->data_ptr(), *w = ws->data_ptr(), *stream = current_stream();
         const size_t bytes = ws->nbytes();
-        int status;
-        Py_BEGIN_ALLOW_THREADS
-        status = g_linear(x, tokens, d_in, d_out, N, M, packed, static_cast<const float *>(gamma), static_cast<const float *>(bias), static_cast<float *>(y),
-                          static_cast<int8_t *>(xq), static_cast<float *>(sx), static_cast<int32_t *>(acc), path, w, bytes, stream);
-        Py_END_ALLOW_THREADS
-        return PyLong_FromLong(status);
+        return released([&] {
+            return g_linear(x, tokens, d_in, d_out, N, M, packed, static_cast<const float *>(gamma), static_cast<const float *>(bias), static_cast<float *>(y),
+                            static_cast<int8_t *>(xq), static_cast<float *>(sx), static_cast<int32_t *>(acc), path, w, bytes, stream);
+        });
     } catch (...) {
         Py_RETURN_NONE;   // a tensor without storage, no device: the Python code raises its own error
     }
@@ -117,12 +142,10 @@ PyObject *grouped(PyObject *, PyObject *const *a, Py_ssize_t n)
         if (!X.held || !tokens.held || !d_in.held || !d_out.held || !packed.held || !gamma.held || !Y.held) Py_RETURN_NONE;
         void *w = ws->data_ptr(), *stream = current_stream();
         const size_t bytes = ws->nbytes();
-        int status;
-        Py_BEGIN_ALLOW_THREADS
-        status = g_grouped(count, X.as<const void *const *>(), tokens.as<const int64_t *>(), d_in.as<const int64_t *>(), d_out.as<const int64_t *>(), N, M,
-                           packed.as<const void *const *>(), gamma.as<const float *const *>(), Y.as<float *const *>(), path, w, bytes, stream);
-        Py_END_ALLOW_THREADS
-        return PyLong_FromLong(status);
+        return released([&] {
+            return g_grouped(count, X.as<const void *const *>(), tokens.as<const int64_t *>(), d_in.as<const int64_t *>(), d_out.as<const int64_t *>(), N, M,
+                             packed.as<const void *const *>(), gamma.as<const float *const *>(), Y.as<float *const *>(), path, w, bytes, stream);
+        });
     } catch (...) {
         Py_RETURN_NONE;
     }
@@ -139,6 +162,14 @@ template <Array::Kind KIND> PyObject *takes_array(PyObject *, PyObject *args)
 
 PyObject *stream(PyObject *, PyObject *) { return PyLong_FromVoidPtr(current_stream()); }
 
+// (address of a C function without arguments): called as the library's functions are
+PyObject *call(PyObject *, PyObject *args)
+{
+    unsigned long long f;
+    if (!PyArg_ParseTuple(args, "K", &f)) return nullptr;
+    return released(reinterpret_cast<int (*)()>(f));
+}
+
 // addresses of the C ABI's functions in the library that the binding has loaded
 PyObject *bind(PyObject *, PyObject *args)
 {
@@ -154,6 +185,7 @@ PyMethodDef methods[] = {
     {"grouped", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(grouped)), METH_FASTCALL, nullptr},
     {"array_of_pointers", takes_array<Array::POINTERS>, METH_VARARGS, nullptr},
     {"array_of_integers", takes_array<Array::INTEGERS>, METH_VARARGS, nullptr},
+    {"call", call, METH_VARARGS, nullptr},
     {"stream", stream, METH_NOARGS, nullptr},
     {"bind", bind, METH_VARARGS, nullptr},
     {nullptr, nullptr, 0, nullptr}};

@@ -1,6 +1,7 @@
 """The C++ marshalling of the forward calls against the Python one beside it: what it does not take goes to the Python code, with that code's
 errors; on the GPU the same statuses, stream and results."""
 import ctypes
+import subprocess
 
 import pytest
 import torch
@@ -110,3 +111,22 @@ def test_group_arrays_of_another_kind_are_left_to_python():
     for other in (arrays["X"], (ctypes.c_int32 * 2)(), torch.zeros(1, dtype=torch.int64).numpy(), ctypes.pointer(ctypes.c_int64(1)), None):
         assert not b._fastcall.array_of_integers(other, 1)
     assert not b._fastcall.array_of_pointers(arrays["X"], 2)      # shorter than the count
+
+
+def test_exceptions_of_a_call_reach_python_with_its_lock_held(tmp_path):
+    source = tmp_path / "throws.cpp"
+    source.write_text("""#include <new>
+#include <stdexcept>
+extern "C" int fine() { return -3; }
+extern "C" int no_memory() { throw std::bad_alloc(); }
+extern "C" int message() { throw std::runtime_error("as it says"); }
+extern "C" int anything() { throw 7; }
+""")
+    subprocess.run(["g++", "-shared", "-fPIC", "-o", tmp_path / "throws.so", source], check=True)
+    lib = ctypes.CDLL(str(tmp_path / "throws.so"))
+    address = lambda f: ctypes.cast(f, ctypes.c_void_p).value   # noqa: E731
+    assert b._fastcall.call(address(lib.fine)) == -3
+    for f, error, text in ((lib.no_memory, MemoryError, None), (lib.message, RuntimeError, "as it says"), (lib.anything, RuntimeError, "unknown")):
+        with pytest.raises(error, match=text):
+            b._fastcall.call(address(f))
+    assert b._fastcall.call(address(lib.fine)) == -3
