@@ -89,16 +89,18 @@ def _load():
 _lib = _load()
 
 
-def _load_fastcall():
-    """The marshalling of the two forward calls in C++ (csrc/sbn_fastcall.cpp), or None: the Python code here does the same."""
-    path = os.path.join(_HERE, "_fastcall.so")
+def _load_fastcall(path=os.path.join(_HERE, "_fastcall.so")):
+    """The marshalling of the two forward calls in C++ (csrc/sbn_fastcall.cpp), or None where it was not built, or was built for
+    another torch: the Python code here does the same."""
     if not os.path.exists(path):
         return None
     try:
         spec = importlib.util.spec_from_file_location("_fastcall", path)
         module = importlib.util.module_from_spec(spec)
         spec.loader.exec_module(module)
-    except ImportError:   # built for another torch
+    except ImportError:
+        return None
+    if module.torch_version != torch.__version__:
         return None
     address = lambda f: ctypes.cast(f, ctypes.c_void_p).value   # noqa: E731
     module.bind(address(_lib.sbn_sparse_ternary_linear), address(_lib.sbn_sparse_ternary_linear_grouped))

@@ -193,4 +193,13 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_fastcall", nullptr, -1, methods, 
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__fastcall() { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__fastcall()
+{
+    PyObject *m = PyModule_Create(&module);
+    // tensors are read by the layout of this version's headers, so the binding compares it with the torch that runs
+    if (m && PyModule_AddStringConstant(m, "torch_version", SBN_TORCH_VERSION) != 0) {
+        Py_DECREF(m);
+        return nullptr;
+    }
+    return m;
+}

@@ -1,6 +1,8 @@
 """The C++ marshalling of the forward calls against the Python one beside it: what it does not take goes to the Python code, with that code's
 errors; on the GPU the same statuses, stream and results."""
 import ctypes
+import importlib.util
+import os
 import subprocess
 
 import pytest
@@ -130,3 +132,29 @@ extern "C" int anything() { throw 7; }
         with pytest.raises(error, match=text):
             b._fastcall.call(address(f))
     assert b._fastcall.call(address(lib.fine)) == -3
+
+
+def _build_script():
+    spec = importlib.util.spec_from_file_location("sbn_build_script", os.path.join(os.path.dirname(b.__file__), "build.py"))
+    module = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(module)
+    return module
+
+
+def test_package_without_the_marshalling(tmp_path, monkeypatch, capsys):
+    # a compiler that is missing or fails is a warning, and no library of an earlier build is left in its place
+    script = _build_script()
+    monkeypatch.setattr(script, "FASTCALL_LIB", str(tmp_path / "_fastcall.so"))
+    for compiler in ("no-such-compiler", "false"):
+        (tmp_path / "_fastcall.so").write_bytes(b"old")
+        assert script.build_fastcall(compiler) is False
+        assert not (tmp_path / "_fastcall.so").exists() and "was not built" in capsys.readouterr().err
+    assert b._load_fastcall(str(tmp_path / "_fastcall.so")) is None
+    assert not script.fastcall_is_current()
+
+
+def test_marshalling_built_for_another_torch_is_not_used(monkeypatch):
+    script, path = _build_script(), b._fastcall.__file__
+    assert b._fastcall.torch_version == torch.__version__ and script.fastcall_is_current() and b._load_fastcall(path) is not None
+    monkeypatch.setattr(torch, "__version__", "0.0")
+    assert not script.fastcall_is_current() and b._load_fastcall(path) is None
