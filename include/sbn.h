@@ -360,6 +360,18 @@ sbn_status sbn_test_self_kernel(int form, int count, const void *const *X, const
                                 const int64_t *d_out, int N, int M, const void *const *packed, const float *const *gamma,
                                 const float *const *bias, float *const *Y, int32_t *const *acc_out, void *stream);
 
+/*
+ * Test hook, host only: the kernel that the forward call of `count` problems runs on (one: sbn_sparse_ternary_linear, more: the
+ * grouped call; SBN_PATH_GEMV up to 16 tokens, SBN_PATH_SMFMAC beyond), by the rules of the call itself.  HOST arrays.
+ *   X, Y       addresses, compared with each other and not read; X NULL: the rows are quantized already or wanted back
+ *   kernel     SBN_KERNEL_SELF + form (of sbn_test_self_kernel): quantizer and product in one launch; SBN_KERNEL_DECODE: the decode
+ *              kernels of up to 16 tokens; the others as above
+ *   supported  2:4 and N = M, d_in % 128 == 0, either at most 16 tokens in every problem or more in all of them
+ */
+enum { SBN_KERNEL_DECODE = 3, SBN_KERNEL_SELF = 32 };
+sbn_status sbn_test_forward_kernels(int count, const void *const *X, const int64_t *tokens, const int64_t *d_in, const int64_t *d_out,
+                                    int N, int M, void *const *Y, int *kernel);
+
 /* Test hook, host only: which of SBN_KERNEL_TILES, _STREAM and _PIECES SBN_PATH_SMFMAC takes for each problem of a call on
  * quantized rows that wants nothing but Y, where it does not take block tiles for the call (sbn_test_takes_blocks: *blocks 1 or
  * 0).  2:4 and N = M, d_in % 128 == 0; kernel: HOST array of length count. */

@@ -79,6 +79,8 @@ def _load():
     lib.sbn_test_self_kernel.argtypes = [cint, cint, pp, pi64, pi64, pi64, cint, cint, pp, pp, pp, pp, pp, vp]
     lib.sbn_test_takes_blocks.restype = cint
     lib.sbn_test_takes_blocks.argtypes = [cint, pi64, pi64, pi64, cint, cint, ctypes.POINTER(cint)]
+    lib.sbn_test_forward_kernels.restype = cint
+    lib.sbn_test_forward_kernels.argtypes = [cint, pp, pi64, pi64, pi64, cint, cint, pp, ctypes.POINTER(cint)]
     lib.sbn_test_chosen_kernels.restype = cint
     lib.sbn_test_chosen_kernels.argtypes = [cint, pi64, pi64, pi64, cint, cint, ctypes.POINTER(cint)]
     lib.sbn_mask_flips.restype = cint
@@ -382,7 +384,7 @@ def sbn_test_set_spin_limits(gemv_polls: int = SBN_SPIN_DEFAULT, pack_polls: int
     _lib.sbn_test_set_spin_limits(gemv_polls, pack_polls)
 
 
-SBN_KERNEL_TILES, SBN_KERNEL_STREAM, SBN_KERNEL_PIECES, SBN_KERNEL_BLOCKS = 0, 1, 2, 16
+SBN_KERNEL_TILES, SBN_KERNEL_STREAM, SBN_KERNEL_PIECES, SBN_KERNEL_DECODE, SBN_KERNEL_BLOCKS, SBN_KERNEL_SELF = 0, 1, 2, 3, 16, 32
 
 
 def sbn_test_linear_kernel(kernel: int, xq_list, sx_list, packed_list, gamma_list, Y_list, N: int, M: int, bias_list=None, acc_list=None):
@@ -409,6 +411,17 @@ def sbn_test_takes_blocks(problems, N: int, M: int) -> bool:
     _check(_lib.sbn_test_takes_blocks(len(problems), *(_i64_array(column) for column in zip(*problems)), N, M, ctypes.byref(blocks)),
            "sbn_test_takes_blocks")
     return bool(blocks.value)
+
+
+def sbn_test_forward_kernels(problems, N: int, M: int, X=None, Y=None, rows: bool = True):
+    """Test hook: the kernel (SBN_KERNEL_...) of each problem (tokens, d_in, d_out) of one forward call.  X, Y: addresses, by default
+    buffers that lie apart; rows False: quantized rows are handed in or wanted back."""
+    kernel = (ctypes.c_int * len(problems))()
+    X = X or [(i + 1) << 44 for i in range(len(problems))]
+    Y = Y or [(i + 1) << 44 | 1 << 43 for i in range(len(problems))]
+    _check(_lib.sbn_test_forward_kernels(len(problems), _ptr_array(X) if rows else None, *(_i64_array(column) for column in zip(*problems)), N, M,
+                                         _ptr_array(Y), kernel), "sbn_test_forward_kernels")
+    return list(kernel)
 
 
 def sbn_test_chosen_kernels(problems, N: int, M: int):

@@ -163,6 +163,37 @@ sbn_status sbn_test_takes_blocks(int count, const int64_t *tokens, const int64_t
     return chosen_kernels(count, tokens, d_in, d_out, N, M, kernel.data(), blocks);
 }
 
+sbn_status sbn_test_forward_kernels(int count, const void *const *X, const int64_t *tokens, const int64_t *d_in, const int64_t *d_out,
+                                    int N, int M, void *const *Y, int *kernel)
+{
+    if (count <= 0 || count > 4096 || !tokens || !d_in || !d_out || !Y || !kernel) return SBN_EINVAL;
+    if (!(N == 2 && M == 4) && N != M) return SBN_EUNSUPPORTED;
+    const bool dense = N == M;
+    Pattern pat;
+    std::vector<LinearItem> items(count);
+    int decode = 0;
+    for (int i = 0; i < count; ++i) {
+        sbn_status st = check_shape(d_out[i], d_in[i], N, M, pat);
+        if (st != SBN_OK) return st;
+        if (tokens[i] <= 0) return SBN_EINVAL;
+        if (d_in[i] % CHUNK != 0) return SBN_EUNSUPPORTED;
+        items[i] = LinearItem{X ? X[i] : nullptr, nullptr, nullptr, nullptr, static_cast<float *>(Y[i]), nullptr, nullptr, nullptr,
+                              tokens[i], d_in[i], d_out[i], X == nullptr};
+        decode += tokens[i] <= 16;
+    }
+    if (decode != 0 && decode != count) return SBN_EUNSUPPORTED;
+    const LinearItem *const it = items.data();
+    const bool self = X && (decode ? gemv_takes_self(count, it) : gemm_takes_self(count, it, dense));
+    const bool blocks = !self && !decode && gemm_takes_blocks(count, it, dense), tiles = !blocks && gemm_takes_tiles(count, it, dense);
+    for (int i = 0; i < count; ++i)
+        kernel[i] = self     ? SBN_KERNEL_SELF + self_form(count, it, dense)
+                    : decode ? SBN_KERNEL_DECODE
+                    : blocks ? SBN_KERNEL_BLOCKS + block_form(count, it, dense)
+                    : tiles  ? SBN_KERNEL_TILES
+                             : gemv_batch_takes(it[i]) ? SBN_KERNEL_STREAM : SBN_KERNEL_PIECES;
+    return SBN_OK;
+}
+
 sbn_status sbn_packed_bytes(int64_t d_out, int64_t d_in, int N, int M, size_t *bytes)
 {
     Pattern pat;

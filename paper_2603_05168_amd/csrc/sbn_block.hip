@@ -399,10 +399,15 @@ float gemm_block_estimate_us(int count, const LinearItem *items, bool dense)
 
 int block_form_count() { return 3; }
 
-sbn_status launch_gemm_block(int count, const LinearItem *items, bool dense, hipStream_t stream, int form)
+int block_form(int count, const LinearItem *items, bool dense)
 {
     float us;
-    if (form < 0) form = choose_block(count, items, dense, us);
+    return choose_block(count, items, dense, us);
+}
+
+sbn_status launch_gemm_block(int count, const LinearItem *items, bool dense, hipStream_t stream, int form)
+{
+    if (form < 0) form = block_form(count, items, dense);
     switch (form) {
     case 0: return launch_block_shape<BlockShape<2, 4, 1, 1, 3>>(count, items, dense, stream);
     case 1: return launch_block_shape<BlockShape<4, 2, 1, 1, 2>>(count, items, dense, stream);

@@ -102,13 +102,14 @@ sbn_status launch_rmsnorm_act_quant(const void *X, const float *gain, float eps,
 enum GemvForm : int { GEMV_2OF4 = 0, GEMV_DENSE = 1, GEMV_1OF4 = 2 };
 sbn_status launch_gemv(int count, const LinearItem *items, GemvForm form, hipStream_t stream);
 // dense_codes: the weights are dense 2-bit codes (packed form of N = M) instead of the 2:4 form.  launch_gemm_smfmac chooses
-// between the three kernels named below it
+// between the four kernels named below it
 sbn_status launch_gemm_smfmac(int count, const LinearItem *items, bool dense_codes, hipStream_t stream);
 // block tiles of middle size (sbn_block.hip): any problem; chosen for up to eight of them that fill the device once or twice.  The
 // estimate of a call it is not made for is huge.  form: a shape by number below block_form_count(), -1: the one it estimates fastest
 float gemm_block_estimate_us(int count, const LinearItem *items, bool dense_codes);
 bool gemm_takes_blocks(int count, const LinearItem *items, bool dense_codes);   // whether launch_gemm_smfmac takes them
 int block_form_count();
+int block_form(int count, const LinearItem *items, bool dense_codes);   // the shape estimated fastest
 sbn_status launch_gemm_block(int count, const LinearItem *items, bool dense_codes, hipStream_t stream, int form = -1);
 // pieces of 512 rows x 32 to 128 tokens (sbn_gemm.hip): any problem
 sbn_status launch_gemm_pieces(int count, const LinearItem *items, bool dense_codes, hipStream_t stream);
@@ -121,6 +122,7 @@ sbn_status launch_gemv_batch(int count, const LinearItem *items, bool dense_code
 bool gemv_takes_self(int count, const LinearItem *items);                     // up to 16 tokens
 bool gemm_takes_self(int count, const LinearItem *items, bool dense_codes);   // beyond
 int self_form_count();
+int self_form(int count, const LinearItem *items, bool dense_codes);   // the shape estimated fastest
 sbn_status launch_gemm_self(int count, const LinearItem *items, bool dense_codes, hipStream_t stream, int form = -1);
 // small block tiles (sbn_tile.hip): any problem, made for a few problems of few tokens
 float gemm_tile_estimate_us(int count, const LinearItem *items, bool dense_codes);

@@ -372,10 +372,15 @@ bool gemm_takes_self(int count, const LinearItem *items, bool dense)
 
 int self_form_count() { return (int)(sizeof(SELF_FORMS) / sizeof(SELF_FORMS[0])); }
 
-sbn_status launch_gemm_self(int count, const LinearItem *items, bool dense, hipStream_t stream, int form)
+int self_form(int count, const LinearItem *items, bool dense)
 {
     float us;
-    if (form < 0) form = choose(count, items, dense, us);
+    return choose(count, items, dense, us);
+}
+
+sbn_status launch_gemm_self(int count, const LinearItem *items, bool dense, hipStream_t stream, int form)
+{
+    if (form < 0) form = self_form(count, items, dense);
     switch (form) {
     case 0: return launch_self_shape<1, 1, 4, 4>(count, items, dense, stream);
     case 1: return launch_self_shape<2, 2, 4, 4>(count, items, dense, stream);

@@ -249,3 +249,34 @@ def test_choice_of_block_tiles(sbn, N, M):
     for problem in ((2048, 2560, 6912), (777, 2560, 6912), (1400, 4096, 4096), (96, 8192, 2560), (16384, 768, 6912)):
         assert not sbn.sbn_test_takes_blocks([problem], N, M), problem
     assert not sbn.sbn_test_takes_blocks([(64, 2560, 256)] * 9, N, M)      # more problems than a launch holds
+
+
+def test_kernels_of_forward_calls(sbn):
+    # what a call launches, quantizer included; sizes at which the kernels measure apart.  The first rows are those of
+    # test_public_call_equals_its_two_steps (1000 values run as 1024), whose two calls have to take two routes
+    self_, decode, blocks, tiles, pieces = sbn.SBN_KERNEL_SELF, sbn.SBN_KERNEL_DECODE, sbn.SBN_KERNEL_BLOCKS, sbn.SBN_KERNEL_TILES, sbn.SBN_KERNEL_PIECES
+
+    def kind(problems, N, M, **how):
+        kernels = set(sbn.sbn_test_forward_kernels(problems, N, M, **how))
+        assert len(kernels) == 1
+        k = kernels.pop()
+        return self_ if k >= self_ else blocks if k >= blocks else k
+
+    for N, M in ((2, 4), (8, 8)):
+        for problem in ((4, 512, 16388), (6, 1024, 300), (16, 2560, 130), (17, 2560, 130), (50, 1024, 1500), (128, 768, 257)):
+            assert kind([problem], N, M) == self_, problem
+            assert kind([problem], N, M, rows=False) != self_, problem
+        assert kind([(40, 2560, o) for o in (130, 514, 64)], N, M) == self_
+        assert kind([(64, 2560, 2560)] * 3, N, M) == self_ and kind([(64, 2560, 6912)] * 2, N, M) == self_
+        assert kind([(1, 2560, 2560)], N, M) == decode and kind([(4, 2560, 2560)] * 3, N, M) == decode and kind([(4, 6912, 2560)], N, M) == decode
+        assert kind([(8, 2560, 2560)] * 9, N, M) == decode            # more problems than a launch of the self kernel holds
+        for problem in ((640, 2560, 2560), (256, 2560, 6912), (512, 4096, 4096)):
+            assert kind([problem], N, M) == kind([problem], N, M, rows=False) == blocks, problem
+        assert kind([(777, 2560, 6912)], N, M) == kind([(3000, 2560, 2560)], N, M) == pieces
+        assert kind([(2181, 512, 475)], N, M) == kind([(4000, 512, 2559)], N, M) == tiles
+    assert kind([(64, 8192, 512)], 2, 4) == self_ and kind([(64, 8192, 512)], 8, 8) == tiles
+    # single-launch calls are refused where the rows are too long or too many
+    assert kind([(64, 8320, 512)], 2, 4) != self_ and kind([(513, 512, 512)], 2, 4) != self_
+    for refused in ([(4, 256, 64), (40, 256, 64)], [(4, 200, 64)]):
+        with pytest.raises(sbn.SbnError):
+            sbn.sbn_test_forward_kernels(refused, 2, 4)
