@@ -322,9 +322,21 @@ int choose(int count, const LinearItem *items, bool dense, float &us)
     return best;
 }
 
+// whether the outputs of one problem reach into the rows of another (or the same)
+bool writes_over_rows(const LinearItem &out, const LinearItem &in)
+{
+    const uintptr_t x = reinterpret_cast<uintptr_t>(in.X), x_end = x + 2 * (uintptr_t)(in.tokens * in.row_values());
+    const uintptr_t bytes = 4 * (uintptr_t)(out.tokens * out.d_out), y = reinterpret_cast<uintptr_t>(out.Y), acc = reinterpret_cast<uintptr_t>(out.acc_out);
+    return (y < x_end && x < y + bytes) || (acc && acc < x_end && x < acc + bytes);
+}
+
 bool self_accepts(int count, const LinearItem *items)
 {
     if (count > SELF_ITEMS) return false;
+    // blocks write their outputs while others still read the rows; behind a quantizer of its own a call may write over them
+    for (int i = 0; i < count; ++i)
+        for (int j = 0; j < count; ++j)
+            if (writes_over_rows(items[i], items[j])) return false;
     for (int i = 0; i < count; ++i)
         // (the estimates are of calls of up to 384 tokens; the rows of X are addressed with 31 bits behind a buffer's base)
         if (!items[i].X || items[i].row_values() > SELF_MAX_ROW || items[i].tokens > 512) return false;

@@ -280,3 +280,22 @@ def test_kernels_of_forward_calls(sbn):
     for refused in ([(4, 256, 64), (40, 256, 64)], [(4, 200, 64)]):
         with pytest.raises(sbn.SbnError):
             sbn.sbn_test_forward_kernels(refused, 2, 4)
+
+
+@pytest.mark.parametrize("N,M", [(2, 4), (8, 8)])
+@pytest.mark.parametrize("tokens,d_in,d_out", [(17, 2560, 1280), (64, 2560, 1280), (128, 512, 256), (8, 2560, 1280)])
+def test_outputs_over_the_rows_are_no_single_launch(sbn, tokens, d_in, d_out, N, M):
+    # its blocks write outputs while others still read the rows
+    X, rows, out = 1 << 44, 2 * tokens * d_in, 4 * tokens * d_out
+
+    def takes_self(problems, X, Y):
+        return sbn.sbn_test_forward_kernels(problems, N, M, X=X, Y=Y)[0] >= sbn.SBN_KERNEL_SELF
+
+    one = [(tokens, d_in, d_out)]
+    for Y in (X, X + 16, X + rows - 16, X - out + 16):
+        assert not takes_self(one, [X], [Y])
+    for Y in (X + rows, X - out):
+        assert takes_self(one, [X], [Y])
+    far = 1 << 45
+    assert takes_self(one * 2, [X, X], [far, far + out])
+    assert not takes_self(one * 2, [X, X], [far, X]) and not takes_self(one * 2, [X, X + rows], [X + rows, far])

@@ -124,3 +124,21 @@ def test_grouped_call_and_its_replay():
         torch.cuda.synchronize()
         assert all(torch.equal(a, b) for a, b in zip(got, Ys)) and not any(torch.isnan(a).any() for a in got)
         X.copy_(keep)
+
+
+@pytest.mark.parametrize("N,M", [(2, 4), (8, 8)])
+@pytest.mark.parametrize("tokens,d_in", [(17, 2560), (64, 2560), (200, 512)])
+def test_outputs_in_the_place_of_the_rows(tokens, d_in, N, M):
+    # beyond 16 tokens Y may lie over X, whole or in part: the rows are quantized before anything is written
+    s = sbn()
+    d_out = d_in // 2
+    X, packed, gamma, y, _ = _problem(tokens, d_out, d_in, N, M)
+    ws = s.new_workspace(2 * s.sbn_workspace_bytes(s.SBN_OP_LINEAR, tokens, d_out, d_in, N, M))
+    Y = X.clone().view(torch.float32)
+    s.sbn_sparse_ternary_linear(Y.view(torch.bfloat16), packed, gamma, Y, N, M, ws)
+    G = torch.cat([X, X]).view(torch.float32)
+    Ys = [torch.full((tokens, d_out), float("nan"), device=DEV), G[tokens // 2 : tokens // 2 + tokens]]
+    s.LinearGroup([G[:tokens].view(torch.bfloat16)] * 2, [packed] * 2, [gamma] * 2, Ys, N, M, ws).run()
+    torch.cuda.synchronize()
+    for got in (Y, *Ys):
+        _check(got, y, None, "over the rows")
