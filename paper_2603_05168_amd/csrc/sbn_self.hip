@@ -338,29 +338,51 @@ bool self_accepts(int count, const LinearItem *items)
         for (int j = 0; j < count; ++j)
             if (writes_over_rows(items[i], items[j])) return false;
     for (int i = 0; i < count; ++i)
-        // (the estimates are of calls of up to 384 tokens; the rows of X are addressed with 31 bits behind a buffer's base)
+        // (The rows of X are addressed with 31 bits behind a buffer's base.  The estimates are fitted to 384 tokens and hold to 512: of 50
+        // calls of 385 to 512 that are taken 46 are 1.002 to 1.97 times as fast as two launches, three 0.99, one 0.88 - 416 tokens,
+        // 768 -> 2 x 1336 with dense codes, 10.4 us against 9.2.)
         if (!items[i].X || items[i].row_values() > SELF_MAX_ROW || items[i].tokens > 512) return false;
     return true;
 }
 
 }  // namespace
 
-// Up to 16 tokens, against gemv_self_kernel and gemv_smfmac_kernel: from six tokens on (at eight between 0.98 and 1.35 times as fast,
-// 2560 -> 2 x 6912 5.4 us against 6.9; from twelve on always faster, 1.07 to 1.95 times), below that for wide layers of
-// short rows only (at four tokens 512 -> 8192 3.4 against 4.0, 2560 -> 2 x 6912 5.3 / 6.0, but 2560 -> 3 x 2560 4.7 / 4.8 and 6912 ->
-// 2560 6.7 / 5.5).  Calls large enough for the streaming kernel stay there.
+// Up to 16 tokens, against gemv_self_kernel and gemv_smfmac_kernel.  Those give a block one wavefront per 512 values: they are at
+// their best while every multiprocessor has one block (16 rows) and with as many wavefronts as SIMDs or multiples of it, at
+// their worst with five (2049 to 2560 values), in further rounds of blocks, and beyond eight tokens.  Measured both ways over 610
+// calls of 2 to 16 tokens, 256 to 8192 values, 256 to 63000 outputs in one to four problems, weights from memory (this kernel's time
+// against theirs):
+//   9 to 16 tokens  1.23 times as fast in the mean (0.91 to 2.3)
+//   6 to 8          1.00 to 1.78 with more than 16 outputs per multiprocessor or rows of 2049 to 2560 values (8 tokens, 2560 -> 3 x 2560
+//                   4.5 us / 5.4); with fewer outputs 0.89 to 0.95 at six and seven tokens beyond half as many (4096 -> 4096 5.3 / 4.9),
+//                   and 0.90 to 1.05 for several problems of short rows (6 tokens, 512 -> 2 x 492 3.5 / 3.2)
+//   3 to 5          outputs from 32 per multiprocessor on: rows of 2049 to 2560 values 1.03 to 1.36 (4 tokens, 2560 -> 2 x 6912 5.6 / 6.0); up to
+//                   512 values 1.01 to 1.10, less beyond 128 outputs; between them 0.86 to 0.98 (4 tokens, 1024 -> 8192 3.8 / 3.5) save
+//                   for five tokens from 1025 values on and where outputs are stored in words (3 tokens, 1536 -> 9883 4.3 / 4.9)
+// By this rule seven of the 610 are slower than there by more than 2 % (at worst 0.91), and of 400 others, 246 of them taken and 1.19 times as
+// fast, eleven (at worst 0.94).  In a stack, behind other calls, the two are closer: 4 tokens, eight blocks of 2560 and 6912 172.9 us
+// with 2560 -> 2 x 6912 on either.  Calls large enough for the streaming kernel stay there.
 bool gemv_takes_self(int count, const LinearItem *items)
 {
     if (!self_accepts(count, items)) return false;
-    int64_t tokens = 0, rows = 0, longest = 0;
+    const int64_t cus = device_cus();
+    int64_t tokens = 0, rows = 0, strips = 0, longest = 0;
+    bool words = false;
     for (int i = 0; i < count; ++i) {
         if (items[i].quantized) return false;
         tokens = std::max(tokens, items[i].tokens);
         rows += items[i].d_out;
+        strips += ceil_div(items[i].d_out, 128);
         longest = std::max(longest, items[i].d_in);
+        words = words || items[i].d_out % 4 != 0;
     }
-    if (rows >= 256 * (int64_t)device_cus()) return false;
-    return tokens >= 6 || (tokens >= 3 && longest <= 2560 && rows >= 32 * (int64_t)device_cus());
+    // (strips of 128 rows x 8 tokens fit with rows of any length: four rounds of them at most, for which the shapes are estimated)
+    if (rows >= 256 * cus || strips > 2 * cus) return false;
+    const bool five_waves = longest > 4 * 512 && longest <= 5 * 512;
+    if (tokens >= 9) return true;
+    if (tokens >= 6) return five_waves || rows > 16 * cus || ((count == 1 || longest > 1280) && (tokens == 8 || rows <= 8 * cus));
+    if (tokens < 3 || rows < 32 * cus || longest > 2560) return false;
+    return five_waves || (words || longest <= 512 ? rows < 128 * cus : tokens == 5 && longest > 1024);
 }
 
 // Beyond 16 tokens, against the quantizer (2.5 us and 0.38 us per MB of X) and the kernels of launch_gemm_smfmac, whose second launch
@@ -378,7 +400,8 @@ bool gemm_takes_self(int count, const LinearItem *items, bool dense)
     for (int i = 0; i < count; ++i) longest = std::max(longest, items[i].d_in);
     float us;
     choose(count, items, dense, us);
-    // rows beyond 7168 values: the estimate is up to 1.5 us short (172 tokens, 8192 -> 1246: 13.8 us, 12.1 in two launches)
+    // rows beyond 7168 values: the estimate is up to 1.5 us short (172 tokens, 8192 -> 1246: 13.8 us, 12.1 in two launches); of what is
+    // left, 30 calls of 17 to 300 tokens through 7296 to 8192 values, all are faster than two launches, 1.10 to 1.76 times
     return us < gemm_estimate_us(count, items, dense) + (float)quantizer + (longest > 7168 ? -1.0f : 0.6f);
 }
 

@@ -299,3 +299,20 @@ def test_outputs_over_the_rows_are_no_single_launch(sbn, tokens, d_in, d_out, N,
     far = 1 << 45
     assert takes_self(one * 2, [X, X], [far, far + out])
     assert not takes_self(one * 2, [X, X], [far, X]) and not takes_self(one * 2, [X, X + rows], [X + rows, far])
+
+
+@pytest.mark.parametrize("N,M", [(2, 4), (8, 8)])
+def test_kernels_of_decode_calls(sbn, N, M):
+    # tokens, d_in, d_out, problems, whether one launch with the quantizer inside was the faster one where both were measured
+    calls = [(3, 2560, 9000, 1, True), (4, 2560, 6912, 2, True), (4, 512, 8192, 1, True), (3, 1536, 9883, 1, True), (5, 2048, 5504, 2, True),
+             (3, 1024, 8192, 1, False), (4, 1024, 8192, 1, False), (4, 1024, 4096, 2, False), (3, 1280, 5840, 2, False), (3, 384, 15808, 4, False),
+             (5, 1024, 4096, 2, False), (3, 1152, 18754, 2, False), (2, 2560, 9000, 1, False), (4, 2560, 2560, 3, False), (3, 4096, 12208, 1, False),
+             (6, 4096, 4096, 1, False), (6, 2560, 2560, 1, True), (6, 512, 492, 2, False), (7, 512, 900, 4, False), (7, 512, 2360, 4, True),
+             (6, 1024, 1024, 1, True), (8, 768, 4376, 3, True), (8, 4096, 1000, 2, True), (8, 512, 300, 2, False), (9, 512, 300, 2, True), (16, 8192, 300, 1, True),
+             # strips of 128 rows that leave no shape with four rounds at most
+             (16, 8192, 8193, 7, True), (16, 8192, 8192, 8, False), (16, 8192, 8065, 8, True)]
+    for tokens, d_in, d_out, count, one in calls:
+        kernel = sbn.sbn_test_forward_kernels([(tokens, d_in, d_out)] * count, N, M, X=[1 << 44] * count)[0]
+        assert (kernel >= sbn.SBN_KERNEL_SELF) == one, (tokens, d_in, d_out, count)
+    many = [(16, 8192, 8193)] * 7 + [(16, 8192, 8184)]
+    assert set(sbn.sbn_test_forward_kernels(many, N, M)) == {sbn.SBN_KERNEL_DECODE}
