@@ -142,3 +142,29 @@ def test_outputs_in_the_place_of_the_rows(tokens, d_in, N, M):
     torch.cuda.synchronize()
     for got in (Y, *Ys):
         _check(got, y, None, "over the rows")
+
+
+@pytest.mark.parametrize("N,M", [(2, 4), (8, 8)])
+@pytest.mark.parametrize("form", FORMS)
+def test_rows_that_are_not_finite_stay_alone(form, N, M):
+    # what such a row gives is unspecified; here, as in the quantizer's own launch: an infinite or NaN scale's quotient, rows of zeros (the
+    # low byte of a quiet NaN and of 0 + 1.5 * 2^23), so NaN outputs and accumulators of zero.  The other rows do not notice
+    s = sbn()
+    tokens, d_out, d_in = 21, 130, 1000
+    X, packed, gamma, y, acc = _problem(tokens, d_out, d_in, N, M)
+    X = X.clone()
+    bad = {3: float("inf"), 7: float("-inf"), 8: float("nan"), 20: float("nan")}
+    for row, v in bad.items():
+        X[row, 17 * row] = v
+    X[8, 5] = float("inf")
+    Y = torch.full((tokens, d_out), 7.0, device=DEV)
+    got = torch.full((tokens, d_out), -7, dtype=torch.int32, device=DEV)
+    s.sbn_test_self_kernel(form, [X], [packed], [gamma], [Y], N, M, None, [got])
+    xq, sx = torch.full((tokens, d_in), 5, dtype=torch.int8, device=DEV), torch.full((tokens,), 5.0, device=DEV)
+    s.sbn_act_quant(X, xq, sx)
+    torch.cuda.synchronize()
+    rows, fine = list(bad), [t for t in range(tokens) if t not in bad]
+    assert Y[rows].isnan().all() and (got[rows] == 0).all() and (xq[rows] == 0).all()
+    assert (sx[[3, 7]] == 0).all() and sx[[8, 20]].isnan().all()
+    _check(Y[fine], y[fine], None, "finite rows")
+    assert np.array_equal(got[fine].cpu().numpy(), acc[fine])
