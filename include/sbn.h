@@ -61,7 +61,7 @@ typedef enum {
                                 multiple of 128 the int8 rows lie in the workspace as rows of whole chunks (the packed
                                 form is padded to them with zero codes already).  DENSE_MFMA at 64, 192 and 320 with
                                 outputs by the tens of millions */
-    SBN_PATH_GEMV = 1,       /* decode kernel: streams the packed weights once; tokens <= 16, d_in % 128 == 0.  2:4 runs
+    SBN_PATH_GEMV = 1,       /* decode kernels: stream the packed weights once; tokens <= 16, d_in % 128 == 0.  2:4 runs
                                 on the sparse instruction and N = M (dense 2-bit codes) on the dense one as stored; 1:4
                                 is read as stored too (one bit per weight: the kernel builds the sparse instruction's
                                 operands in registers); other patterns are rewritten per call into one of the two forms
@@ -75,9 +75,11 @@ typedef enum {
                                 Decode batches (Section 3.2 measures decoding at batch 64 .. 512) take this path too:
                                 up to 64 tokens with neither bias nor acc_out a kernel that streams the weights once
                                 into registers (same instructions on 16 x 16 tiles), up to 512 tokens the GEMM kernel
-                                with its work dealt by row tile; a layer or a few of up to some 700 tokens a kernel of
-                                small block tiles, where an estimate from the sizes has it faster (dense codes then on
-                                the dense int8 instruction) */
+                                with its work dealt by row tile; a layer or a few of up to some 1500 tokens kernels
+                                of block tiles in several sizes, where an estimate from the sizes has one faster.  Calls
+                                of up to 512 tokens that want no quantized rows back (neither xq_out nor sx_out) run in
+                                one launch with the quantizer inside, where that is estimated faster; outputs that lie
+                                over X are then left to two launches */
     SBN_PATH_DENSE_MFMA = 3, /* W_eff expanded to int8 with explicit zeros, dense int8 MFMA: the comparison path;
                                 d_in % 64 == 0 */
     SBN_PATH_GENERIC = 4     /* any supported pattern, plain integer kernel (reference speed only) */
