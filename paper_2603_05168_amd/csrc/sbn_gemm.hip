@@ -1160,7 +1160,9 @@ float gemm_estimate_us(int count, const LinearItem *items, bool dense_codes)
 
 // Block tiles of middle size where they are faster by more than the estimates are off: over 220 calls of 96 to 2048 tokens through
 // eleven layers, 2:4 and dense codes, all kernels measured, they are taken for 70 and are 1.14 times as fast there (at worst 0.93,
-// 256 tokens 2560 -> 1000: 6.2 us against 5.7; at best 1.35, 640 tokens 6912 -> 2560: 17.6 against 23.7).
+// 256 tokens 2560 -> 1000: 6.2 us against 5.7; at best 1.35, 640 tokens 6912 -> 2560: 17.6 against 23.7).  Of 420 others, whole calls of
+// 17 to 2500 tokens, 69 take them, in 0.84 of the time of tiles and pieces; two are slower by more than 2 % (55 tokens, 4608 -> 3 x 2984
+// 13.6 us against 12.3).
 bool gemm_takes_blocks(int count, const LinearItem *items, bool dense_codes)
 {
     return gemm_block_estimate_us(count, items, dense_codes) <

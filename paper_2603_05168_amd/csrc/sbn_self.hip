@@ -386,7 +386,9 @@ bool gemv_takes_self(int count, const LinearItem *items)
 }
 
 // Beyond 16 tokens, against the quantizer (2.5 us and 0.38 us per MB of X) and the kernels of launch_gemm_smfmac, whose second launch
-// costs a microsecond more than the sum of the two when they are not replayed from a graph.
+// costs a microsecond more than the sum of the two when they are not replayed from a graph.  Of 420 calls drawn from 17 to 2500 tokens, up to
+// 8192 values and outputs, one to three problems, whole and ragged chunks, 217 are taken, in 0.74 of the time of two launches; five are
+// slower by more than 2 % (152 tokens, 768 -> 3 x 3968 10.8 us against 9.0; 240 tokens, 1048 -> 4392 10.9 / 9.7).
 bool gemm_takes_self(int count, const LinearItem *items, bool dense)
 {
     if (!self_accepts(count, items)) return false;
