@@ -266,8 +266,9 @@ constexpr int issued_after(int NDT, int jlo, int jhi, bool want_pair, int id)
 constexpr int LEAD = NST > 2 * NWP - 1 ? NST : 2 * NWP - 1;          // prologue iterations -LEAD .. -1
 
 // What a wavefront needs to issue the DMA of one piece: uniform bases and 32-bit lane offsets (the per-iteration
-// advance is scalar arithmetic).  Token instruction i of wavefront w fills tile rows (NDT w + i) 8 .. + 7, weight
-// instruction i fills block rows (NDW w + i) 16 .. + 15.
+// advance is scalar arithmetic).  Token instruction i of wavefront w fills tile rows (NW i + w) 8 .. + 7, weight
+// instruction i fills block rows (NDW w + i) 16 .. + 15: a row of a slot is always filled by the same wavefront, whatever the
+// width of the piece, so a surplus request of one piece never lands behind another wavefront's request of the next.
 template <int NDT>
 struct PieceDma {
     const int8_t *xbase;
@@ -286,7 +287,7 @@ __device__ __forceinline__ void dma_setup(PieceDma<NDT> &d, const GemmArgs &g, i
     d.xbase = g.xq + (int64_t)t0 * K;
 #pragma unroll
     for (int i = 0; i < NDT; ++i) {
-        int row = (NDT * wave + i) * 8 + (lane >> 3);
+        int row = (NW * i + wave) * 8 + (lane >> 3);
         const int sw = (row >> 1) & 7;
         row = row < 32 * tb ? row : 32 * tb - 1;                      // rows past the piece: its last row again (never read)
         const int t = t0 + row < g.tokens ? row : g.tokens - 1 - t0;   // tokens past the matrix: its last token again
@@ -312,7 +313,7 @@ template <int NDT>
 __device__ __forceinline__ void dma_token(const PieceDma<NDT> &d, uint32_t lds0, int wave, int kc, int slot, int i)
 {
     kc = kc < d.nchunks ? kc : d.nchunks - 1;
-    lds_dma16(d.xbase + (int64_t)kc * KSTEP, d.xoff[i], lds0 + slot * TSTAGE + wave * (NDT * 1024) + i * 1024);
+    lds_dma16(d.xbase + (int64_t)kc * KSTEP, d.xoff[i], lds0 + slot * TSTAGE + (NW * i + wave) * 1024);
 }
 
 template <int NDT>
