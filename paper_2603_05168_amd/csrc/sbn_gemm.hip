@@ -389,7 +389,8 @@ __device__ __forceinline__ void piece_body(const Group &grp, const Piece &p, con
     constexpr int WAIT_TOP = cmin(issued_after(NDT, -LEAD, -1, false, 0), issued_after(NDT, -LEAD, -1, true, 0));
     // in the middle of iteration kc: token stage kc + 1 and, for odd kc, weight pair (kc + 1) / 2 must have landed
     constexpr int WAIT_EVEN = issued_after(NDT, -LEAD, 99, false, 101);
-    constexpr int WAIT_ODD = cmin(issued_after(NDT, -LEAD, 100, false, 102), issued_after(NDT, -LEAD, 100, true, 51));
+    // (in front of which an odd iteration has already asked for its weight pair)
+    constexpr int WAIT_ODD = cmin(issued_after(NDT, -LEAD, 100, false, 102), issued_after(NDT, -LEAD, 100, true, 51)) + NDW;
     static_assert(WAIT_TOP >= 0 && WAIT_EVEN >= 0 && WAIT_ODD >= 0 && WAIT_TOP < 64 && WAIT_EVEN < 64 && WAIT_ODD < 64,
                   "ring bookkeeping");
     const GemmArgs &g = grp.g[p.prob];
@@ -455,9 +456,9 @@ __device__ __forceinline__ void piece_body(const Group &grp, const Piece &p, con
             cv[a] = *(lds_u2)(uintptr_t)(a_code[h][a] + slot * WPAIR);
         }
     };
-    auto token_read = [&](const int slot, const int u, const int b, v8i &bf) {
-        bf.lo = *(lds_v4i)(uintptr_t)(b_lo[u] + slot * TSTAGE + 32 * b * KSTEP);
-        bf.hi = *(lds_v4i)(uintptr_t)(b_hi[u] + slot * TSTAGE + 32 * b * KSTEP);
+    auto token_read = [&](const int slot, const int u, const int b, v8i &bf) {   // the tile is an index, hence an immediate offset
+        bf.lo = ((lds_v4i)(uintptr_t)(b_lo[u] + slot * TSTAGE))[32 * b * KSTEP / 16];
+        bf.hi = ((lds_v4i)(uintptr_t)(b_hi[u] + slot * TSTAGE))[32 * b * KSTEP / 16];
     };
     // One sub-step: RA x TB matrix instructions; side(s) is issued after instruction s (s = 0 .. RA * TB - 1).  A
     // wavefront issues at most one instruction every few cycles, so what is placed between matrix instructions is free
@@ -524,23 +525,29 @@ __device__ __forceinline__ void piece_body(const Group &grp, const Piece &p, con
     auto iteration = [&](const int kc, const int ts, const int ps, const int h) {
         substep(0, bq[0], [&](const int s) {
             if constexpr (LIVE) { if (s < TB) token_read(ts, 1, s, bq[1][s]); }
+            // odd kc: the pair of this iteration is in this wavefront's registers (the instructions of the second row tile have
+            // waited for its last words), and its rows of the slot are read by no other
+            if (h == 1) {
+                constexpr int FIRST = NSLOT / RA;
+#pragma unroll
+                for (int k = 0; k < NDW; ++k)
+                    if (FIRST + k * (NSLOT - FIRST) / NDW == s) dma_weight(d, lds0, wave, kc / 2 + NWP, ps, k);
+            }
         });
         if (h == 0) SBN_WAIT_VMCNT(WAIT_EVEN); else SBN_WAIT_VMCNT(WAIT_ODD);
         __syncthreads();
         const int nts = ts + 1 == NST ? 0 : ts + 1;                         // slot of token stage kc + 1
         const int nps = h == 1 ? (ps + 1 == NWP ? 0 : ps + 1) : ps;         // slot of the pair of chunk kc + 1
         substep(1, bq[1], [&](const int s) {
-            // side operations in issue order: weight DMA (odd kc), token DMA, weight words, token fragments;
-            // operation k goes to slot k, the last slot takes what is left over
-            constexpr int NOPS = NDW + NDT + RA + TB;
+            // weight words, token fragments, token DMA: what the next iteration begins with is asked for first
+            constexpr int NOPS = RA + TB + NDT;
 #pragma unroll
             for (int k = 0; k < NOPS; ++k) {
                 if ((k < NSLOT ? k : NSLOT - 1) != s) continue;
-                if (k < NDW) { if (h == 1) dma_weight(d, lds0, wave, kc / 2 + NWP, ps, k); }
-                else if (k < NDW + NDT) dma_token(d, lds0, wave, kc + NST, ts, k - NDW);
+                if (k >= RA + TB) dma_token(d, lds0, wave, kc + NST, ts, k - RA - TB);
                 else if constexpr (LIVE) {
-                    if (k < NDW + NDT + RA) read_weights(nps, h ^ 1, k - NDW - NDT, inext, cnext);
-                    else token_read(nts, 0, k - NDW - NDT - RA, bq[0][k - NDW - NDT - RA]);
+                    if (k < RA) read_weights(nps, h ^ 1, k, inext, cnext);
+                    else token_read(nts, 0, k - RA, bq[0][k - RA]);
                 }
             }
         });
