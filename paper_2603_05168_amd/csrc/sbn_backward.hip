@@ -573,13 +573,13 @@ __device__ __forceinline__ void bf16_tile_body(const GemmBf16Args &g, uint8_t *d
     // stage kt, so behind the barrier the last quarter reads the first fragments of stage kt + 1 and asks for Q(kt + 2) and
     // P(kt + 3) in the two slots just left.
 #pragma unroll
-    for (int j = 0; j < 5; ++j)
+    for (int j = 0; j < 4; ++j)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             if (j & 1) dma_q(j >> 1, j * S::SLOT, i);
             else dma_p(j >> 1, j * S::SLOT, i);
         }
-    SBN_WAIT_VMCNT(12);
+    SBN_WAIT_VMCNT(8);
     if (nk == 1 && kleft < GD_K) zero_tail(S::SLOT);
     __syncthreads();
 #pragma unroll
@@ -587,9 +587,15 @@ __device__ __forceinline__ void bf16_tile_body(const GemmBf16Args &g, uint8_t *d
     uint32_t sp = 0, sq = S::SLOT;
     for (int kt = 0; kt < nk; ++kt) {
         const uint32_t sp_next = advance(sp), sq_next = advance(sq);
+        const uint32_t free = advance(sp_next);   // of Q(kt - 1)
+        constexpr int PQ[3] = {2, 2, 0};   // requests for P(kt + 2) in the quarters
 #pragma unroll
         for (int u = 0; u < 3; ++u)
-            quarter(u, [&](const int s) { spread(s, READS, [&](const int k) { read_one(u + 1, k); }); });
+            quarter(u, [&](const int s) {
+                spread(s, READS, [&](const int k) { read_one(u + 1, k); });
+                const int first = u == 0 ? 0 : u == 1 ? PQ[0] : PQ[0] + PQ[1];
+                if (PQ[u] > 0) spread(s, PQ[u], [&](const int k) { dma_p(kt + 2, free, first + k); });
+            });
         SBN_WAIT_VMCNT(4);   // P(kt + 2) may fly
         if (kt == nk - 2 && kleft < GD_K) zero_tail(sq_next);
         __syncthreads();
@@ -604,10 +610,7 @@ __device__ __forceinline__ void bf16_tile_body(const GemmBf16Args &g, uint8_t *d
         }
         quarter(3, [&](const int s) {
             spread(s, READS, [&](const int k) { read_one(0, k); });
-            spread(s, 8, [&](const int k) {
-                if (k < 4) dma_q(kt + 2, sp, k);
-                else dma_p(kt + 3, sq, k - 4);
-            });
+            spread(s, 4, [&](const int k) { dma_q(kt + 2, sp, k); });
         });
         sp = sp_next;
         sq = sq_next;
