@@ -6,6 +6,7 @@
 //   dense   v_mfma_i32_32x32x32_i8 on W_eff expanded to int8 with explicit zeros: the in-run
 //           comparison a dense ternary layer would run.
 #include <algorithm>
+#include <type_traits>
 #include <vector>
 
 #include "sbn_internal.hpp"
@@ -377,8 +378,9 @@ __device__ __forceinline__ void piece_prologue(const Group &grp, const Piece &p,
 
 // Main loop and epilogue of one piece whose prologue is already in flight: rows [512 to, +512) of W against tokens
 // [t0, t0 + 32 TB), the whole input dimension.  LIVE = false: a wavefront whose rows lie past the matrix (ragged last
-// row tile) only moves data and keeps the barriers.
-template <int TB, bool LIVE, bool DENSE, class Group>
+// row tile) only moves data and keeps the barriers.  UNIT = false: the codes are +-64 (expand_codes_x64), the accumulators 64 times
+// the sums.
+template <int TB, bool LIVE, bool DENSE, bool UNIT, class Group>
 __device__ __forceinline__ void piece_body(const Group &grp, const Piece &p, const Piece &next, int8_t *lds, const int wave,
                                            int lane)
 {
@@ -432,7 +434,7 @@ __device__ __forceinline__ void piece_body(const Group &grp, const Piece &p, con
     typedef __attribute__((address_space(3))) const v4i *lds_v4i;
     typedef unsigned v2u __attribute__((ext_vector_type(2)));
     typedef __attribute__((address_space(3))) const v2u *lds_u2;
-    const uint32_t ones = vgpr_ones();
+    const uint32_t ones = UNIT ? vgpr_ones() : 0;
 
     v16i acc[RA][TB];
 #pragma unroll
@@ -472,7 +474,8 @@ __device__ __forceinline__ void piece_body(const Group &grp, const Piece &p, con
         for (int a = 0; a < RA; ++a) {
             if constexpr (LIVE && DENSE) {
                 v4i a01, a23;   // sub-step u covers the lane's code words 2u, 2u + 1
-                expand_dense_codes(u ? ccur[a].x : icur[a].x, u ? ccur[a].y : icur[a].y, a01, a23);
+                if constexpr (UNIT) expand_dense_codes(u ? ccur[a].x : icur[a].x, u ? ccur[a].y : icur[a].y, a01, a23);
+                else expand_dense_codes_x64(u ? ccur[a].x : icur[a].x, u ? ccur[a].y : icur[a].y, a01, a23);
 #pragma unroll
                 for (int b = 0; b < TB; ++b) {
                     acc[a][b] = __builtin_amdgcn_smfmac_i32_32x32x64_i8(a01, bf[b], acc[a][b], 0x44444444, 0, 0);
@@ -487,7 +490,9 @@ __device__ __forceinline__ void piece_body(const Group &grp, const Piece &p, con
                 }
             } else if constexpr (LIVE) {
                 const int iv = (int)(u ? icur[a].y : icur[a].x);
-                const v4i av = expand_codes(u ? ccur[a].y : ccur[a].x, ones);
+                v4i av;
+                if constexpr (UNIT) av = expand_codes(u ? ccur[a].y : ccur[a].x, ones);
+                else av = expand_codes_x64(u ? ccur[a].y : ccur[a].x);
 #pragma unroll
                 for (int b = 0; b < TB; ++b) {
                     acc[a][b] = __builtin_amdgcn_smfmac_i32_32x32x64_i8(av, bf[b], acc[a][b], iv, 0, 0);
@@ -594,6 +599,12 @@ __device__ __forceinline__ void piece_body(const Group &grp, const Piece &p, con
         sxv[TB] = *g.gamma;
 #pragma unroll
         for (int b = 0; b < TB; ++b) sxv[b] = *reinterpret_cast<const float *>(lds + SCALES_OFF + 512 * p.parity + 4 * (32 * b + r));
+        auto shift_sums = [&](const int b) {
+#pragma unroll
+            for (int a = 0; a < RA; ++a)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) acc[a][b][i] >>= CODE_SHIFT;
+        };
         const int orow = o0 + wave * (32 * RA);
         const bool fast_store = (g.d_out & 3) == 0 && orow + 32 * RA <= g.d_out && !g.acc_out;
         if (fast_store) {
@@ -609,7 +620,11 @@ __device__ __forceinline__ void piece_body(const Group &grp, const Piece &p, con
             float *const ybase = g.Y + (int64_t)(t0 + lane / LPR) * d_out + orow + 4 * (lane % LPR);
 #pragma unroll
             for (int b = 0; b < TB; ++b) {
-                const float scale = __fdiv_rn(sxv[TB], sxv[b]);
+                float scale = __fdiv_rn(sxv[TB], sxv[b]);
+                if constexpr (!UNIT) {
+                    if (__builtin_expect(__any(!(fabsf(scale) >= 0x1p-100f)), 0)) shift_sums(b);   // scale / 64 might not be exact
+                    else scale *= 1.0f / (1 << CODE_SHIFT);
+                }
 #pragma unroll
                 for (int half = 0; half < 32 / STG_TOKENS; ++half) {
                     // the lanes that hold tokens 16 half .. + 15 of the tile stage their 32 values
@@ -644,6 +659,7 @@ __device__ __forceinline__ void piece_body(const Group &grp, const Piece &p, con
 #pragma unroll
             for (int b = 0; b < TB; ++b) {
                 const int t = t0 + 32 * b + r;
+                if constexpr (!UNIT) shift_sums(b);
 #pragma unroll
                 for (int a = 0; a < RA; ++a) store_tile(g, acc[a][b], orow + 32 * a + 4 * c, t, __fdiv_rn(sxv[TB], sxv[b]));
             }
@@ -651,21 +667,21 @@ __device__ __forceinline__ void piece_body(const Group &grp, const Piece &p, con
     }
 }
 
-template <int TB, bool DENSE, class Group>
+template <int TB, bool DENSE, bool UNIT, class Group>
 __device__ __forceinline__ void piece_live(const Group &grp, const Piece &p, const Piece &next, int8_t *lds, int wave, int lane)
 {
     const bool live = p.to * ROWS + wave * (32 * RA) < grp.g[p.prob].d_out;   // a ragged last row tile leaves whole wavefronts idle
-    if (live) piece_body<TB, true, DENSE>(grp, p, next, lds, wave, lane);
-    else piece_body<TB, false, DENSE>(grp, p, next, lds, wave, lane);
+    if (live) piece_body<TB, true, DENSE, UNIT>(grp, p, next, lds, wave, lane);
+    else piece_body<TB, false, DENSE, UNIT>(grp, p, next, lds, wave, lane);
 }
 
-template <bool DENSE, class Group>
+template <bool DENSE, bool UNIT, class Group>
 __device__ __forceinline__ void piece_run(const Group &grp, const Piece &p, const Piece &next, int8_t *lds, int wave, int lane)
 {
-    if (p.tb == 4) piece_live<4, DENSE>(grp, p, next, lds, wave, lane);
-    else if (p.tb == 3) piece_live<3, DENSE>(grp, p, next, lds, wave, lane);
-    else if (p.tb == 2) piece_live<2, DENSE>(grp, p, next, lds, wave, lane);
-    else piece_live<1, DENSE>(grp, p, next, lds, wave, lane);
+    if (p.tb == 4) piece_live<4, DENSE, UNIT>(grp, p, next, lds, wave, lane);
+    else if (p.tb == 3) piece_live<3, DENSE, UNIT>(grp, p, next, lds, wave, lane);
+    else if (p.tb == 2) piece_live<2, DENSE, UNIT>(grp, p, next, lds, wave, lane);
+    else piece_live<1, DENSE, UNIT>(grp, p, next, lds, wave, lane);
 }
 
 }  // namespace sp
@@ -678,7 +694,8 @@ __device__ __forceinline__ void piece_run(const Group &grp, const Piece &p, cons
 // the XCD's units in the order strip, unit (the same number of units each, +-1), cut into pieces of at most four units
 // that do not cross a strip.
 // DENSE = the weights are dense 2-bit codes (the stored form of N = M, or any pattern converted to it) instead of 2:4.
-template <bool DENSE, class Group, class Table>
+// UNIT = the rows are longer than CODE_SHIFT_MAX_K: codes +-1, whose sums fit an int32 whatever the length.
+template <bool DENSE, bool UNIT, class Group, class Table>
 __global__ void __launch_bounds__(64 * sp::NW) gemm_smfmac_kernel(Group grp, Table tab)
 {
     __shared__ __attribute__((aligned(1024))) int8_t lds[sp::LDS_BYTES];
@@ -718,28 +735,10 @@ __global__ void __launch_bounds__(64 * sp::NW) gemm_smfmac_kernel(Group grp, Tab
         sp::piece_prologue(grp, cur, lds, wave, lane);
         while (cur.tb > 0) {
             const sp::Piece next = piece_at(f);
-            sp::piece_run<DENSE>(grp, cur, next, lds, wave, lane);
+            sp::piece_run<DENSE, UNIT>(grp, cur, next, lds, wave, lane);
             cur = next;
         }
-        return;
     } else {
-    if (tab.per_block > 0) {
-        auto decode = [&](int i) {
-            if (i >= tab.per_block) return none;
-            const uint32_t pc = tab.piece[blockIdx.x * tab.per_block + i];
-            return sp::Piece{(int)(pc >> 25), (int)((pc >> 16) & 0x1ff), (int)((pc >> 3) & 0x1fff) * 32, (int)(pc & 7), i & 1};
-        };
-        // the pieces of a block are listed without gaps: the first empty entry ends the list
-        sp::Piece cur = decode(0);
-        if (cur.tb == 0) return;
-        sp::piece_prologue(grp, cur, lds, wave, lane);
-        for (int i = 1; cur.tb > 0; ++i) {
-            const sp::Piece next = decode(i);
-            sp::piece_run<DENSE>(grp, cur, next, lds, wave, lane);
-            cur = next;
-        }
-        return;
-    }
     const int x = blockIdx.x & 7, j = blockIdx.x >> 3, nb = gridDim.x >> 3;
     constexpr int GROUP_UNITS = 16;
     // units of problem p that XCD x owns: [x * upx, min((x + 1) * upx, units)), upx = ceil(units / 8)
@@ -749,8 +748,9 @@ __global__ void __launch_bounds__(64 * sp::NW) gemm_smfmac_kernel(Group grp, Tab
         const int n = units - first;
         return n < 0 ? 0 : n < upx ? n : upx;
     };
+    const bool listed = tab.per_block > 0;
     int total = 0;
-    for (int p = 0; p < grp.count; ++p) {
+    for (int p = 0; p < grp.count && !listed; ++p) {
         int first;
         total += (int)((grp.g[p].d_out + sp::ROWS - 1) / sp::ROWS) * own_units(p, first);
     }
@@ -758,8 +758,15 @@ __global__ void __launch_bounds__(64 * sp::NW) gemm_smfmac_kernel(Group grp, Tab
     int f = j * q + (j < rem ? j : rem);
     const int end = f + q + (j < rem ? 1 : 0);
     int prob = 0, group = 0, base = 0, parity = 0;
-    // the piece that starts at flat unit f (f only grows, so the search for its strip resumes where it stopped)
+    // The next piece of the block's list, whose pieces are listed without gaps (the first empty entry ends it); or the piece that
+    // starts at flat unit f (f only grows, so the search for its strip resumes where it stopped).
+    int entry = 0;
     auto piece_at = [&](int &f) {
+        if (listed) {
+            if (entry >= tab.per_block) return none;
+            const uint32_t pc = tab.piece[blockIdx.x * tab.per_block + entry++];
+            return sp::Piece{(int)(pc >> 25), (int)((pc >> 16) & 0x1ff), (int)((pc >> 3) & 0x1fff) * 32, (int)(pc & 7), entry & 1};
+        }
         if (f >= end) return none;
         int first, n, gsz, tiles_o;
         for (;;) {
@@ -786,7 +793,7 @@ __global__ void __launch_bounds__(64 * sp::NW) gemm_smfmac_kernel(Group grp, Tab
     sp::piece_prologue(grp, cur, lds, wave, lane);
     while (cur.tb > 0) {
         const sp::Piece next = piece_at(f);
-        sp::piece_run<DENSE>(grp, cur, next, lds, wave, lane);
+        sp::piece_run<DENSE, UNIT>(grp, cur, next, lds, wave, lane);
         cur = next;
     }
     }
@@ -1070,12 +1077,13 @@ static int make_piece_table(const GemmGroup &grp, PieceTable &tab)
 sbn_status launch_gemm_pieces(int count, const LinearItem *items, bool dense_codes, hipStream_t stream)
 {
     // problems of at most 16 token units (512 tokens: decode batches) are dealt by row tile, up to GEMM_GROUP_WIDE per launch
-    auto few_tokens = [&](int i) { return items[i].tokens <= 16 * 32; };
+    auto few_tokens = [&](int i) { return items[i].tokens <= 16 * 32 && items[i].d_in <= CODE_SHIFT_MAX_K; };
+    auto long_rows = [&](int i) { return items[i].d_in > CODE_SHIFT_MAX_K; };   // a kernel of their own
     for (int first = 0; first < count;) {
         const bool few = few_tokens(first);
         const int most = few ? GEMM_GROUP_WIDE : GEMM_GROUP_MAX;
         int n = 1;
-        while (first + n < count && n < most && few_tokens(first + n) == few) ++n;
+        while (first + n < count && n < most && few_tokens(first + n) == few && long_rows(first + n) == long_rows(first)) ++n;
         if (few) {
             GemmGroupWide grp;
             grp.count = n;
@@ -1093,16 +1101,24 @@ sbn_status launch_gemm_pieces(int count, const LinearItem *items, bool dense_cod
             tab.per_block = -pieces;
             tab.piece[0] = (uint32_t)wmax;
             const int blocks = pieces < device_cus() ? pieces : device_cus();
-            if (dense_codes) hipLaunchKernelGGL((gemm_smfmac_kernel<true, GemmGroupWide, PieceTableNone>), dim3(blocks), dim3(64 * sp::NW), 0, stream, grp, tab);
-            else hipLaunchKernelGGL((gemm_smfmac_kernel<false, GemmGroupWide, PieceTableNone>), dim3(blocks), dim3(64 * sp::NW), 0, stream, grp, tab);
+            if (dense_codes) hipLaunchKernelGGL((gemm_smfmac_kernel<true, false, GemmGroupWide, PieceTableNone>), dim3(blocks), dim3(64 * sp::NW), 0, stream, grp, tab);
+            else hipLaunchKernelGGL((gemm_smfmac_kernel<false, false, GemmGroupWide, PieceTableNone>), dim3(blocks), dim3(64 * sp::NW), 0, stream, grp, tab);
         } else {
             GemmGroup grp;
             grp.count = n;
             for (int i = 0; i < n; ++i) grp.g[i] = make_args(items[first + i]);
             static thread_local PieceTable tab;
             const int per_xcd = make_piece_table(grp, tab);
-            if (dense_codes) hipLaunchKernelGGL((gemm_smfmac_kernel<true, GemmGroup, PieceTable>), dim3(8 * per_xcd), dim3(64 * sp::NW), 0, stream, grp, tab);
-            else hipLaunchKernelGGL((gemm_smfmac_kernel<false, GemmGroup, PieceTable>), dim3(8 * per_xcd), dim3(64 * sp::NW), 0, stream, grp, tab);
+            auto launch = [&](auto dense, auto unit) {
+                hipLaunchKernelGGL((gemm_smfmac_kernel<dense(), unit(), GemmGroup, PieceTable>), dim3(8 * per_xcd), dim3(64 * sp::NW), 0, stream, grp, tab);
+            };
+            if (long_rows(first)) {
+                if (dense_codes) launch(std::true_type(), std::true_type());
+                else launch(std::false_type(), std::true_type());
+            } else {
+                if (dense_codes) launch(std::true_type(), std::false_type());
+                else launch(std::false_type(), std::false_type());
+            }
         }
         sbn_status st = check_launch("gemm_smfmac_kernel");
         if (st != SBN_OK) return st;

@@ -92,3 +92,44 @@ def test_kernel_groups(kernel, count, N, M):
             "STREAM": [17, 64, 33, 20, 48, 32, 1, 16, 64, 64]}[kernel]
     problems = [(toks[i % len(toks)], *base[i % len(base)]) for i in range(count)]
     _run(getattr(sbn(), "SBN_KERNEL_" + kernel), problems, N, M, bias=kernel != "STREAM" and count == 3)
+
+
+@pytest.mark.parametrize("N,M", [(2, 4), (8, 8)])
+@pytest.mark.parametrize("tokens", [33, 600])
+@pytest.mark.parametrize("d_in", [1 << 17, (1 << 17) + 128])
+def test_pieces_longest_sums(N, M, tokens, d_in):
+    # the pieces multiply by 64 times the codes up to rows of 2^17 values, beyond by the codes: the largest sums there are, on either side
+    s, d_out = sbn(), 70
+    W = torch.full((d_out, d_in), 0.02, dtype=torch.bfloat16)
+    W[1] = -W[1]
+    W[2, ::3] = 0.0
+    packed, gamma = hip_pack(W, N, M)
+    _, g, Weff, _ = oracle_pack(W, N, M)
+    xq = torch.from_numpy(np.random.default_rng(d_in).integers(-128, 128, (tokens, d_in), dtype=np.int8))
+    xq[0], xq[1], xq[2] = -128, 127, 0
+    sx = torch.full((tokens,), 30.0)
+    Y, acc = torch.full((tokens, d_out), float("nan"), device=DEV), torch.full((tokens, d_out), -7, dtype=torch.int32, device=DEV)
+    s.sbn_test_linear_kernel(s.SBN_KERNEL_PIECES, [xq.to(DEV)], [sx.to(DEV)], [packed], [gamma], [Y], N, M, None, [acc])
+    Y2 = torch.full_like(Y, float("nan"))   # whole rows leave on another path where no accumulators are wanted
+    s.sbn_test_linear_kernel(s.SBN_KERNEL_PIECES, [xq.to(DEV)], [sx.to(DEV)], [packed], [gamma], [Y2], N, M)
+    kept, which = np.unique(Weff, axis=0, return_inverse=True)   # few different rows
+    want = (xq.double() @ torch.from_numpy(kept).double().T).numpy().astype(np.int64)[:, which.reshape(-1)]   # exact: below 2^53
+    assert np.abs(want).max() == 128 * d_in * N // M
+    assert np.array_equal(acc.cpu().numpy(), want)
+    _check(Y, want * float(g) / 30.0, None, "Y")
+    assert torch.equal(Y, Y2)
+
+
+@pytest.mark.parametrize("N,M", [(2, 4), (8, 8)])
+def test_pieces_scales_below_the_normal_range(N, M):
+    # gamma / s_x near and below the smallest normal number: the same two roundings as in the plain formula
+    s, (tokens, d_out, d_in) = sbn(), (96, 128, 256)
+    packed, gamma, _, Weff = _weights(d_out, d_in, N, M)
+    xq, _, _, acc = _reference(tokens, d_out, d_in, N, M)
+    sx = torch.full((tokens,), 30.0)
+    sx[5:40] = torch.logspace(27, 38.4, 35)
+    Y = torch.full((tokens, d_out), float("nan"), device=DEV)
+    s.sbn_test_linear_kernel(s.SBN_KERNEL_PIECES, [xq], [sx.to(DEV)], [packed], [gamma], [Y], N, M)
+    scale = (gamma.cpu().numpy() / sx.numpy()).astype(np.float32)
+    assert (scale < 2.0 ** -126).any()
+    assert np.array_equal(Y.cpu().numpy(), acc.astype(np.float32) * scale[:, None])
