@@ -227,10 +227,8 @@ constexpr int NWP = 2;                         // weight pair slots (32 KB each)
 constexpr int TSTAGE = 128 * KSTEP;
 constexpr int WPAIR = ROWS * 64;
 constexpr int RING_BYTES = NST * TSTAGE + NWP * WPAIR;
-// epilogue staging, one area per wavefront: 16 tokens x (64 rows of fp32 + 16 bytes of padding)
-constexpr int STG_TOKENS = 16;
-constexpr int EROW = 128 * RA + 16;
-constexpr int STG_WAVE = STG_TOKENS * EROW;
+// epilogue staging, one area per wavefront: a tile of 32 tokens x 32 rows of fp32, its 16-byte granules swizzled with (token >> 1) & 7
+constexpr int STG_WAVE = 32 * 128;
 // per-token scales of a piece (128 floats), fetched by DMA with its first stages; two areas, used alternately, because
 // the scales of the next piece arrive while the epilogue of the current one still reads its own
 constexpr int SCALES_OFF = RING_BYTES + NW * STG_WAVE;
@@ -433,6 +431,7 @@ __device__ __forceinline__ void piece_body(const Group &grp, const Piece &p, con
     }
     typedef __attribute__((address_space(3))) const v4i *lds_v4i;
     typedef unsigned v2u __attribute__((ext_vector_type(2)));
+    typedef unsigned v4u __attribute__((ext_vector_type(4)));
     typedef __attribute__((address_space(3))) const v2u *lds_u2;
     const uint32_t ones = UNIT ? vgpr_ones() : 0;
 
@@ -449,7 +448,6 @@ __device__ __forceinline__ void piece_body(const Group &grp, const Piece &p, con
     v8i bq[2][TB];
     auto read_weights = [&](const int slot, const int h, const int a, v2u (&iv)[RA], v2u (&cv)[RA]) {
         if constexpr (DENSE) {
-            typedef unsigned v4u __attribute__((ext_vector_type(4)));
             const v4u w = *(__attribute__((address_space(3))) const v4u *)(uintptr_t)(a_idx[h][a] + slot * WPAIR);
             iv[a] = v2u{w.x, w.y};
             cv[a] = v2u{w.z, w.w};
@@ -588,10 +586,10 @@ __device__ __forceinline__ void piece_body(const Group &grp, const Piece &p, con
     // that the same wavefront's later requests overwrite in issue order; the staging area lies outside the ring.
     if (next.tb > 0) piece_prologue(grp, next, lds, wave, lane);
 
-    // ---- epilogue: rescale, transpose through the wavefront's staging area (16 tokens x 64 rows of fp32 per pass) and
-    // write whole rows of 256 bytes with streaming stores (Y is not read again here and must not push the operands out
+    // ---- epilogue: rescale, transpose through the wavefront's staging area (a tile of 32 tokens x 32 rows of fp32 at a time) and
+    // write whole lines with streaming stores (Y is not read again here and must not push the operands out
     // of L2; per-lane stores of 32 contiguous bytes measured 1.5x the write traffic); ragged edges and the int32
-    // accumulator output store per lane
+    // accumulator output store per lane.
     // The epilogue issues no vector loads: one would make the compiler wait for everything outstanding, the requests
     // for the next piece included.  gamma is a scalar load, the s_x of the piece came into LDS with its first stages.
     if constexpr (LIVE) {
@@ -606,55 +604,68 @@ __device__ __forceinline__ void piece_body(const Group &grp, const Piece &p, con
                 for (int i = 0; i < 16; ++i) acc[a][b][i] >>= CODE_SHIFT;
         };
         const int orow = o0 + wave * (32 * RA);
-        const bool fast_store = (g.d_out & 3) == 0 && orow + 32 * RA <= g.d_out && !g.acc_out;
+        float scale[TB];
+        bool exact = true;   // whether a 64th of the scales is
+#pragma unroll
+        for (int b = 0; b < TB; ++b) {
+            const float v = __fdiv_rn(sxv[TB], sxv[b]);
+            exact = exact && fabsf(v) >= 0x1p-100f;
+            scale[b] = UNIT ? v : v * (1.0f / (1 << CODE_SHIFT));
+        }
+        // (a piece's outputs are addressed with 31 bits behind its first)
+        const bool fast_store = (g.d_out & 3) == 0 && orow + 32 * RA <= g.d_out && !g.acc_out && g.d_out <= (1 << 22) && (UNIT || __all(exact));
         if (fast_store) {
-            constexpr int LPR = 8 * RA;              // lanes (16 bytes each) per token row
-            constexpr int RPI = 64 / LPR;            // token rows per store instruction
             int8_t *const est = lds + RING_BYTES + wave * STG_WAVE;
-            const int tokens = g.tokens;
-            const int64_t d_out = g.d_out;
-            const bool all_tokens = t0 + 32 * TB <= tokens;
             const bool has_bias = g.bias != nullptr;
-            v4f bias4 = {0.f, 0.f, 0.f, 0.f};
-            if (has_bias) bias4 = *reinterpret_cast<const v4f *>(g.bias + orow + 4 * (lane % LPR));
-            float *const ybase = g.Y + (int64_t)(t0 + lane / LPR) * d_out + orow + 4 * (lane % LPR);
+            v4f bias4[RA];
 #pragma unroll
-            for (int b = 0; b < TB; ++b) {
-                float scale = __fdiv_rn(sxv[TB], sxv[b]);
-                if constexpr (!UNIT) {
-                    if (__builtin_expect(__any(!(fabsf(scale) >= 0x1p-100f)), 0)) shift_sums(b);   // scale / 64 might not be exact
-                    else scale *= 1.0f / (1 << CODE_SHIFT);
+            for (int a = 0; a < RA; ++a)
+                bias4[a] = has_bias ? *reinterpret_cast<const v4f *>(g.bias + orow + 32 * a + 4 * (lane & 7)) : v4f{0.f, 0.f, 0.f, 0.f};
+            // tokens past the matrix lie past the end of the buffer, where stores are dropped
+            const int64_t first = (int64_t)t0 * g.d_out + orow;
+            const uint32_t pitch = 4u * (uint32_t)g.d_out;
+            const auto out = __builtin_amdgcn_make_buffer_rsrc(g.Y + first, (short)0, (int)((uint32_t)(g.tokens - t0 < 32 * TB ? g.tokens - t0 : 32 * TB) * pitch - 4u * (uint32_t)orow), 0x00027000);
+            const uint32_t voff = (uint32_t)(lane >> 3) * pitch + 16u * (lane & 7);
+            // A wavefront's LDS operations complete in order, so a tile can be written behind the reads of the one before without a
+            // wait, and what a tile's stores wait for is covered by the conversions of the next tile.
+            v4f yv[2][4];
+            auto stage = [&](const int n) {
+                const int a = n % RA, b = n / RA;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const v4f y = {(float)acc[a][b][4 * q + 0] * scale[b], (float)acc[a][b][4 * q + 1] * scale[b],
+                                   (float)acc[a][b][4 * q + 2] * scale[b], (float)acc[a][b][4 * q + 3] * scale[b]};
+                    *reinterpret_cast<v4f *>(est + r * 128 + 16 * ((2 * q + c) ^ ((r >> 1) & 7))) = y;
+                }
+                asm volatile("" ::: "memory");   // the reads are of what other lanes have written
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int t = 8 * i + (lane >> 3);
+                    yv[n & 1][i] = *reinterpret_cast<const v4f *>(est + t * 128 + 16 * ((lane & 7) ^ ((t >> 1) & 7)));
+                }
+                asm volatile("" ::: "memory");   // the next tile's writes stay behind them
+            };
+            auto leave = [&](const int n) {
+                const int a = n % RA, b = n / RA;
+                if (has_bias) {
+                    asm volatile("");   // a branch, not additions and selections
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) yv[n & 1][i] += bias4[a];
                 }
 #pragma unroll
-                for (int half = 0; half < 32 / STG_TOKENS; ++half) {
-                    // the lanes that hold tokens 16 half .. + 15 of the tile stage their 32 values
-                    if ((r >> 4) == half) {
+                for (int i = 0; i < 4; ++i)
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, yv[n & 1][i]), out, voff + (uint32_t)(32 * b + 8 * i) * pitch + 128u * a, 0, 2);   // 2: streaming
+            };
+            stage(0);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                        for (int a = 0; a < RA; ++a)
-#pragma unroll
-                            for (int q = 0; q < 4; ++q) {
-                                const v4f y = {(float)acc[a][b][4 * q + 0] * scale, (float)acc[a][b][4 * q + 1] * scale,
-                                               (float)acc[a][b][4 * q + 2] * scale, (float)acc[a][b][4 * q + 3] * scale};
-                                *reinterpret_cast<v4f *>(est + (r & 15) * EROW + (32 * a + 8 * q + 4 * c) * 4) = y;
-                            }
-                    }
-                    asm volatile("" ::: "memory");   // the reads below are of what the lanes above have just written
-                    // the wavefront reads back what it wrote itself (its LDS operations complete in order):
-                    // all reads of the pass first, then the stores, so that the LDS latency is paid once
-                    v4f yv[STG_TOKENS / RPI];
-#pragma unroll
-                    for (int j = 0; j < STG_TOKENS / RPI; ++j)
-                        yv[j] = *reinterpret_cast<const v4f *>(est + (RPI * j + lane / LPR) * EROW + (lane % LPR) * 16);
-#pragma unroll
-                    for (int j = 0; j < STG_TOKENS / RPI; ++j) {
-                        if (has_bias) yv[j] += bias4;
-                        const int trow = 32 * b + STG_TOKENS * half + RPI * j;
-                        if (all_tokens || t0 + trow + lane / LPR < tokens)
-                            __builtin_nontemporal_store(yv[j], reinterpret_cast<v4f *>(ybase + (int64_t)trow * d_out));
-                    }
-                    asm volatile("" ::: "memory");   // the next pass overwrites the staging area only after these reads
-                }
+            for (int n = 1; n < RA * TB; ++n) {
+                stage(n);
+                __builtin_amdgcn_sched_barrier(0);
+                leave(n - 1);
+                __builtin_amdgcn_sched_barrier(0);
             }
+            leave(RA * TB - 1);
         } else if (orow < g.d_out) {
 #pragma unroll
             for (int b = 0; b < TB; ++b) {
