@@ -264,122 +264,113 @@ constexpr int issued_after(int NDT, int jlo, int jhi, bool want_pair, int id)
 }
 constexpr int LEAD = NST > 2 * NWP - 1 ? NST : 2 * NWP - 1;          // prologue iterations -LEAD .. -1
 
-// What a wavefront needs to issue the DMA of one piece: uniform bases and 32-bit lane offsets (the per-iteration
-// advance is scalar arithmetic).  Token instruction i of wavefront w fills tile rows (NW i + w) 8 .. + 7, weight
-// instruction i fills block rows (NDW w + i) 16 .. + 15: a row of a slot is always filled by the same wavefront, whatever the
-// width of the piece, so a surplus request of one piece never lands behind another wavefront's request of the next.
-template <int NDT>
-struct PieceDma {
-    const int8_t *xbase;
-    const uint8_t *wbase;
-    uint32_t xoff[NDT], woff[NDW];
-    uint32_t wclip;            // bit i: instruction i fetches granules 2, 3 of its rows, which do not exist in an odd last pair
-    int nchunks, npairs;
-};
-
-template <int NDT>
-__device__ __forceinline__ void dma_setup(PieceDma<NDT> &d, const GemmArgs &g, int to, int t0, int tb, int wave, int lane)
-{
-    const int K = g.d_in;
-    d.nchunks = K / KSTEP;
-    d.npairs = (d.nchunks + 1) / 2;
-    d.xbase = g.xq + (int64_t)t0 * K;
-#pragma unroll
-    for (int i = 0; i < NDT; ++i) {
-        int row = (NW * i + wave) * 8 + (lane >> 3);
-        const int sw = (row >> 1) & 7;
-        row = row < 32 * tb ? row : 32 * tb - 1;                      // rows past the piece: its last row again (never read)
-        const int t = t0 + row < g.tokens ? row : g.tokens - 1 - t0;   // tokens past the matrix: its last token again
-        d.xoff[i] = (uint32_t)t * (uint32_t)K + 16u * ((lane & 7) ^ sw);
-    }
-    const int o0 = to * ROWS;
-    d.wbase = g.packed + (int64_t)o0 * d.nchunks * 32;
-    const bool odd_tail = (d.nchunks & 1) != 0;
-    d.wclip = 0;
-#pragma unroll
-    for (int i = 0; i < NDW; ++i) {
-        const int row = (NDW * wave + i) * 16 + (lane >> 2);
-        const int o = o0 + row < g.d_out ? row : g.d_out - 1 - o0;     // rows past the matrix: its last row again
-        const int gran = (lane & 3) ^ ((row >> 2) & 3);
-        d.woff[i] = (uint32_t)o * (uint32_t)(d.nchunks * 32) + 16u * gran;
-        if (odd_tail && gran >= 2) d.wclip |= 1u << i;
-    }
-}
-
-// stages and pairs past the end are fetched again from the last one (into a slot nobody reads): the DMA is
-// unconditional, so that the wait counts are the same in every iteration
-template <int NDT>
-__device__ __forceinline__ void dma_token(const PieceDma<NDT> &d, uint32_t lds0, int wave, int kc, int slot, int i)
-{
-    kc = kc < d.nchunks ? kc : d.nchunks - 1;
-    lds_dma16(d.xbase + (int64_t)kc * KSTEP, d.xoff[i], lds0 + slot * TSTAGE + (NW * i + wave) * 1024);
-}
-
-template <int NDT>
-__device__ __forceinline__ void dma_weight(const PieceDma<NDT> &d, uint32_t lds0, int wave, int pair, int slot, int i)
-{
-    pair = pair < d.npairs ? pair : d.npairs - 1;
-    // granules 2, 3 of a clipped pair lie past the row: fetch granule 0/1 again instead (never read)
-    const uint32_t off = (pair == d.npairs - 1 && ((d.wclip >> i) & 1u)) ? d.woff[i] - 32u : d.woff[i];
-    lds_dma16(d.wbase + (int64_t)pair * 64, off, lds0 + NST * TSTAGE + slot * WPAIR + wave * (NDW * 1024) + i * 1024);
-}
-
-// the items of iterations -LEAD .. -1, in the order the wait counts assume
-template <int NDT>
-__device__ __forceinline__ void dma_prologue(const PieceDma<NDT> &d, uint32_t lds0, int wave)
-{
-#pragma unroll
-    for (int j = -LEAD; j <= -1; ++j) {
-        if ((j & 1) && (j - 1) / 2 + NWP >= 0) {
-#pragma unroll
-            for (int i = 0; i < NDW; ++i) dma_weight(d, lds0, wave, (j - 1) / 2 + NWP, ((j - 1) / 2 + NWP) % NWP, i);
-        }
-        if (j + NST >= 0) {
-#pragma unroll
-            for (int i = 0; i < NDT; ++i) dma_token(d, lds0, wave, j + NST, (j + NST) % NST, i);
-        }
-    }
-}
-
 // A piece of the work list: (problem, row tile, first token, width in token tiles); width 0 = none.
 struct Piece {
     int prob, to, t0, tb;
     int parity;   // which of the two scale areas the piece uses
 };
 
-// requests the first stages of a piece (called with the ring idle: before the first piece and between the main loop
-// and the epilogue of the piece before)
-template <class Group>
-__device__ __forceinline__ void piece_prologue(const Group &grp, const Piece &p, int8_t *lds, int wave, int lane)
+// The stream of requests of a block, ahead of its products by NST token stages and NWP weight pairs and continuing from one
+// piece into the next.  Everything in it is uniform: the operands of the piece it is in as buffers (rows past the matrix or the
+// piece, and chunks past the last row, read as zeros and fetch nothing), and how far it has come.  Token instruction i of
+// wavefront w fills tile rows (NW i + w) 8 .. + 7, weight instruction i fills block rows (NDW w + i) 16 .. + 15: a row of a slot is
+// always filled by the same wavefront, whatever the width of the piece, so requests for it land in the order they were made.
+struct Stream {
+    v4i tokens, weights;
+    uint32_t token_at, weight_at;   // bytes into a row
+    int ts, ps;                     // ring slots of the next piece's first stage and pair
+    bool wide;                      // the piece has more than 64 tokens: two instructions per stage
+    bool landed;                    // everything asked for so far
+};
+
+__device__ __forceinline__ v4i token_buffer(const GemmArgs &g, const Piece &p)
 {
-    const uint32_t lds0 = lds_address(lds);
-    const GemmArgs &g = grp.g[p.prob];
-    // s_x of the piece's tokens, by the first wavefront and in front of everything else: the oldest request of the
-    // piece, so every wait for a stage covers it and no wait count changes
-    if (wave == 0) {
+    const int left = g.tokens - p.t0, rows = left < 32 * p.tb ? left : 32 * p.tb;
+    return buffer_of(g.xq + (int64_t)p.t0 * g.d_in, (uint32_t)rows * (uint32_t)g.d_in);
+}
+
+__device__ __forceinline__ v4i weight_buffer(const GemmArgs &g, const Piece &p)
+{
+    const int left = g.d_out - p.to * ROWS, rows = left < ROWS ? left : ROWS, pitch = g.d_in / KSTEP * 32;
+    return buffer_of(g.packed + (int64_t)p.to * ROWS * pitch, (uint32_t)rows * (uint32_t)pitch);
+}
+
+__device__ __forceinline__ v4i no_buffer() { return v4i{0, 0, 0, 0x00027000}; }
+
+// lane offsets; the further instructions of a wavefront are 64 token rows or 16 weight rows on
+__device__ __forceinline__ uint32_t token_offset(int d_in, int wave, int lane)
+{
+    const int row = 8 * wave + (lane >> 3);
+    return (uint32_t)row * (uint32_t)d_in + 16u * ((lane & 7) ^ ((row >> 1) & 7));
+}
+
+__device__ __forceinline__ uint32_t weight_offset(int d_in, int wave, int lane)
+{
+    const int row = 16 * NDW * wave + (lane >> 2);
+    return (uint32_t)row * (uint32_t)(d_in / KSTEP * 32) + 16u * ((lane & 3) ^ ((row >> 2) & 3));
+}
+
+// s_x of a piece's tokens, by the first wavefront
+__device__ __forceinline__ void request_scales(const GemmArgs &g, const Piece &p, uint32_t lds0, int wave, int lane)
+{
+    if (wave != 0) return;
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int t = p.t0 + 64 * i + lane;
-            lds_dma4(g.sx, 4u * (uint32_t)(t < g.tokens ? t : g.tokens - 1), lds0 + SCALES_OFF + 512 * p.parity + 256 * i);
-        }
-    }
-    if (token_dma(p.tb) == 2) {
-        PieceDma<2> d;
-        dma_setup(d, g, p.to, p.t0, p.tb, wave, lane);
-        dma_prologue(d, lds0, wave);
-    } else {
-        PieceDma<1> d;
-        dma_setup(d, g, p.to, p.t0, p.tb, wave, lane);
-        dma_prologue(d, lds0, wave);
+    for (int i = 0; i < 2; ++i) {
+        const int t = p.t0 + 64 * i + lane;
+        lds_dma4(g.sx, 4u * (uint32_t)(t < g.tokens ? t : g.tokens - 1), lds0 + SCALES_OFF + 512 * p.parity + 256 * i);
     }
 }
 
-// Main loop and epilogue of one piece whose prologue is already in flight: rows [512 to, +512) of W against tokens
+// Starts the stream at a piece: its first stages and pairs go to the slots (ts, ps) and on.
+__device__ __forceinline__ void start_stream(Stream &st, const GemmArgs &g, const Piece &p, uint32_t lds0, int wave, int lane)
+{
+    const uint32_t K = (uint32_t)g.d_in, pitch = K / KSTEP * 32;
+    st.tokens = token_buffer(g, p);
+    st.weights = weight_buffer(g, p);
+    st.wide = p.tb > 2;
+    const uint32_t xoff = token_offset(g.d_in, wave, lane), woff = weight_offset(g.d_in, wave, lane);
+    auto pair = [&](const int s) {
+        const uint32_t slot = (uint32_t)(st.ps + s) % NWP;
+        const v4i buffer = 64u * s < pitch ? st.weights : no_buffer();
+#pragma unroll
+        for (int i = 0; i < NDW; ++i)
+            lds_dma16_buffer(buffer, woff, 64u * s + 16u * i * pitch, lds0 + NST * TSTAGE + slot * WPAIR + (NDW * wave + i) * 1024);
+    };
+    auto stage = [&](const int s) {
+        const uint32_t slot = (uint32_t)(st.ts + s) % NST;
+        const v4i buffer = (uint32_t)KSTEP * s < K ? st.tokens : no_buffer();
+        lds_dma16_buffer(buffer, xoff, (uint32_t)KSTEP * s, lds0 + slot * TSTAGE + wave * 1024);
+        if (st.wide) lds_dma16_buffer(buffer, xoff, (uint32_t)KSTEP * s + 64u * K, lds0 + slot * TSTAGE + (NW + wave) * 1024);
+    };
+    // the order in which the iterations in front of the first would have asked
+#pragma unroll
+    for (int j = -LEAD; j < 0; ++j) {
+        if ((j & 1) && (j - 1) / 2 + NWP >= 0) pair((j - 1) / 2 + NWP);
+        if (j + NST >= 0) stage(j + NST);
+    }
+    st.token_at = NST * KSTEP;
+    st.weight_at = NWP * 64;
+}
+
+// the stream of a block at its first piece
+template <class Group>
+__device__ __forceinline__ Stream first_stream(const Group &grp, const Piece &p, int8_t *lds, int wave, int lane)
+{
+    const uint32_t lds0 = lds_address(lds);
+    Stream st;
+    st.ts = st.ps = 0;
+    request_scales(grp.g[p.prob], p, lds0, wave, lane);
+    start_stream(st, grp.g[p.prob], p, lds0, wave, lane);
+    st.landed = false;
+    return st;
+}
+
+// Main loop and epilogue of one piece whose first stages have landed or are in flight: rows [512 to, +512) of W against tokens
 // [t0, t0 + 32 TB), the whole input dimension.  LIVE = false: a wavefront whose rows lie past the matrix (ragged last
 // row tile) only moves data and keeps the barriers.  UNIT = false: the codes are +-64 (expand_codes_x64), the accumulators 64 times
 // the sums.
 template <int TB, bool LIVE, bool DENSE, bool UNIT, class Group>
-__device__ __forceinline__ void piece_body(const Group &grp, const Piece &p, const Piece &next, int8_t *lds, const int wave,
+__device__ __forceinline__ void piece_body(const Group &grp, const Piece &p, const Piece &next, Stream &st, int8_t *lds, const int wave,
                                            int lane)
 {
     // everything derived from the lane number is computed anew for every piece: hoisted out of the loop over pieces,
@@ -399,8 +390,34 @@ __device__ __forceinline__ void piece_body(const Group &grp, const Piece &p, con
     const int r = lane & 31, c = lane >> 5;
     const int nchunks = g.d_in / KSTEP;
     const int o0 = to * ROWS;
-    PieceDma<NDT> d;
-    dma_setup(d, g, to, t0, TB, wave, lane);
+
+    // ---- requests: at the end of the piece the stream goes on with the next one, where that has rows of the same length; otherwise
+    // it is started anew behind the main loop, and until then asks for nothing
+    const uint32_t K = (uint32_t)g.d_in, pitch = K / KSTEP * 32;
+    const uint32_t xoff = token_offset(g.d_in, wave, lane), woff = weight_offset(g.d_in, wave, lane);
+    const bool goes_on = next.tb > 0 && grp.g[next.prob].d_in == g.d_in && nchunks >= NST && nchunks > 2 * (NWP - 1);
+    const v4i next_tokens = goes_on ? token_buffer(grp.g[next.prob], next) : no_buffer();
+    const v4i next_weights = goes_on ? weight_buffer(grp.g[next.prob], next) : no_buffer();
+    auto request_tokens = [&](const int slot, const int i) {   // instruction i of NDT
+        if (i == 0) {   // selections: a branch would part the instructions around it
+            const bool turn = st.token_at >= K;
+            st.tokens = turn ? next_tokens : st.tokens;
+            st.wide = turn ? next.tb > 2 : st.wide;
+            st.token_at = turn ? 0 : st.token_at;
+        }
+        lds_dma16_buffer(st.tokens, xoff, st.token_at + 64u * i * K, lds0 + slot * TSTAGE + (NW * i + wave) * 1024);
+        if (NDT == 1 && st.wide) lds_dma16_buffer(st.tokens, xoff, st.token_at + 64u * K, lds0 + slot * TSTAGE + (NW + wave) * 1024);
+        if (i == NDT - 1) st.token_at += KSTEP;
+    };
+    auto request_weights = [&](const int slot, const int i) {   // instruction i of NDW
+        if (i == 0) {
+            const bool turn = st.weight_at >= pitch;
+            st.weights = turn ? next_weights : st.weights;
+            st.weight_at = turn ? 0 : st.weight_at;
+        }
+        lds_dma16_buffer(st.weights, woff, st.weight_at + 16u * i * pitch, lds0 + NST * TSTAGE + slot * WPAIR + (NDW * wave + i) * 1024);
+        if (i == NDW - 1) st.weight_at += 64;
+    };
 
     // ---- LDS read addresses (swizzles as in the DMA patterns above)
     uint32_t b_lo[2], b_hi[2];   // [sub-step]; the token tile is an immediate offset, the ring slot a scalar
@@ -504,87 +521,76 @@ __device__ __forceinline__ void piece_body(const Group &grp, const Piece &p, con
         }
     };
 
-    // Weight pair 0 and token stage 0 are in; what was requested after them may fly.  The count is of ALL outstanding
-    // vector-memory operations: loads complete in issue order among themselves, but stores (the epilogue of the piece
-    // before, issued after this piece's first requests) may be acknowledged before older loads, so they cannot be
-    // granted as outstanding - with at most WAIT_TOP operations of any kind in flight, at most WAIT_TOP loads are.
-    SBN_WAIT_VMCNT(WAIT_TOP);
+    int ts = st.ts, ps = st.ps;
+    if (!st.landed) SBN_WAIT_VMCNT(WAIT_TOP);   // pair 0 and stage 0; what was asked for after them may fly
     __syncthreads();
+    if (next.tb > 0) request_scales(grp.g[next.prob], next, lds0, wave, lane);   // its area was read by the epilogue before this piece
     if constexpr (LIVE) {
 #pragma unroll
-        for (int a = 0; a < RA; ++a) read_weights(0, 0, a, icur, ccur);
+        for (int a = 0; a < RA; ++a) read_weights(ps, 0, a, icur, ccur);
 #pragma unroll
-        for (int b = 0; b < TB; ++b) token_read(0, 0, b, bq[0][b]);
+        for (int b = 0; b < TB; ++b) token_read(ts, 0, b, bq[0][b]);
     }
-    // One iteration that has a successor; ts = kc % NST and ps = (kc / 2) % NWP are scalars, h = kc & 1 is a literal.
-    //   sub-step 0   compute (kc, first half); the token fragments of the second half are read under it
+    // One iteration; ts, ps are the slots of its token stage and weight pair, h = kc & 1 is a literal.
+    //   sub-step 0   compute (kc, first half); the token fragments of the second half are read under it.  Odd kc, and the last: the
+    //                words of this pair are in the wavefront's registers (the instructions of the second row tile have waited
+    //                for the last of them) and its rows of the slot are read by no other, so they take the pair NWP further on
     //   middle       wait for token stage kc + 1 (odd kc: and weight pair (kc + 1) / 2), barrier: every wavefront
-    //                now holds all of stage kc in registers, so its slot takes stage kc + NST, and for odd kc the
-    //                slot of pair kc / 2 takes pair kc / 2 + NWP
-    //   sub-step 1   compute (kc, second half); under it go the DMA instructions, the weight words of chunk kc + 1
-    //                and the token fragments of (kc + 1, first half), one per matrix instruction
-    // The wait counts hold the outstanding DMA of this wavefront only; stores of the epilogue before that are still in
-    // flight in the first iterations make a wait longer, never shorter.
-    auto iteration = [&](const int kc, const int ts, const int ps, const int h) {
+    //                now holds all of stage kc in registers, so its slot takes the stage NST further on
+    //   sub-step 1   compute (kc, second half); under it go the weight words of chunk kc + 1, the token fragments of (kc + 1,
+    //                first half) and the requests for tokens, one per matrix instruction: what the next iteration begins with
+    //                is asked for first
+    // The wait counts hold the outstanding requests of this wavefront only.  Everything that was asked for in front of a piece behind
+    // another has landed when it begins, so its first two iterations wait for nothing: there the stores of the epilogue before may
+    // still be in flight, and would be waited for.  Later they make a wait longer, never shorter.
+    const int settled = st.landed ? 2 : 0;
+    st.landed = true;
+    auto iteration = [&](const int kc, const int h, auto last) {
+        constexpr bool LAST = last();
         substep(0, bq[0], [&](const int s) {
             if constexpr (LIVE) { if (s < TB) token_read(ts, 1, s, bq[1][s]); }
-            // odd kc: the pair of this iteration is in this wavefront's registers (the instructions of the second row tile have
-            // waited for its last words), and its rows of the slot are read by no other
-            if (h == 1) {
+            if (h == 1 || LAST) {
                 constexpr int FIRST = NSLOT / RA;
 #pragma unroll
                 for (int k = 0; k < NDW; ++k)
-                    if (FIRST + k * (NSLOT - FIRST) / NDW == s) dma_weight(d, lds0, wave, kc / 2 + NWP, ps, k);
+                    if (FIRST + k * (NSLOT - FIRST) / NDW == s) request_weights(ps, k);
             }
         });
-        if (h == 0) SBN_WAIT_VMCNT(WAIT_EVEN); else SBN_WAIT_VMCNT(WAIT_ODD);
+        if (!LAST && kc >= settled) { if (h == 0) SBN_WAIT_VMCNT(WAIT_EVEN); else SBN_WAIT_VMCNT(WAIT_ODD); }
         __syncthreads();
-        const int nts = ts + 1 == NST ? 0 : ts + 1;                         // slot of token stage kc + 1
-        const int nps = h == 1 ? (ps + 1 == NWP ? 0 : ps + 1) : ps;         // slot of the pair of chunk kc + 1
+        const int nts = ts + 1 == NST ? 0 : ts + 1;                            // slot of token stage kc + 1
+        const int nps = h == 1 || LAST ? (ps + 1 == NWP ? 0 : ps + 1) : ps;    // slot of the pair of chunk kc + 1
         substep(1, bq[1], [&](const int s) {
-            // weight words, token fragments, token DMA: what the next iteration begins with is asked for first
-            constexpr int NOPS = RA + TB + NDT;
+            constexpr int READS = LAST ? 0 : RA + TB, NOPS = READS + NDT;
 #pragma unroll
             for (int k = 0; k < NOPS; ++k) {
                 if ((k < NSLOT ? k : NSLOT - 1) != s) continue;
-                if (k >= RA + TB) dma_token(d, lds0, wave, kc + NST, ts, k - RA - TB);
+                if (k >= READS) request_tokens(ts, k - READS);
                 else if constexpr (LIVE) {
                     if (k < RA) read_weights(nps, h ^ 1, k, inext, cnext);
                     else token_read(nts, 0, k - RA, bq[0][k - RA]);
                 }
             }
         });
-        if constexpr (LIVE) {
+        if constexpr (LIVE && !LAST) {
 #pragma unroll
             for (int a = 0; a < RA; ++a) { icur[a] = inext[a]; ccur[a] = cnext[a]; }
         }
+        ts = nts;
+        ps = nps;
     };
-    const int nsteady = nchunks - 1;   // iterations with a successor
-    int kc = 0, ts = 0, ps = 0;
-    for (; kc + 2 <= nsteady; kc += 2) {
-        iteration(kc, ts, ps, 0);
-        ts = ts + 1 == NST ? 0 : ts + 1;
-        iteration(kc + 1, ts, ps, 1);
-        ts = ts + 1 == NST ? 0 : ts + 1;
-        ps = ps + 1 == NWP ? 0 : ps + 1;
+    constexpr std::false_type more{};
+    constexpr std::true_type last{};
+    int kc = 0;
+    for (; kc + 2 < nchunks; kc += 2) {
+        iteration(kc, 0, more);
+        iteration(kc + 1, 1, more);
     }
-    if (kc < nsteady) {
-        iteration(kc, ts, ps, 0);
-        ts = ts + 1 == NST ? 0 : ts + 1;
-    }
-    // last chunk: nothing left to fetch
-    {
-        if constexpr (LIVE) {
-#pragma unroll
-            for (int b = 0; b < TB; ++b) token_read(ts, 1, b, bq[1][b]);
-        }
-        substep(0, bq[0], [&](const int) {});
-        substep(1, bq[1], [&](const int) {});
-    }
-    __syncthreads();     // every wavefront has read the last stage: the ring can take the next piece
-    // The surplus DMA of the last iterations is still in flight: it lands in ring slots that nobody reads any more and
-    // that the same wavefront's later requests overwrite in issue order; the staging area lies outside the ring.
-    if (next.tb > 0) piece_prologue(grp, next, lds, wave, lane);
+    if (kc + 1 < nchunks) iteration(kc, 0, more);
+    iteration(nchunks - 1, 0, last);
+    st.ts = ts;
+    st.ps = ps;
+    if (next.tb > 0 && !goes_on) start_stream(st, grp.g[next.prob], next, lds0, wave, lane);
 
     // ---- epilogue: rescale, transpose through the wavefront's staging area (a tile of 32 tokens x 32 rows of fp32 at a time) and
     // write whole lines with streaming stores (Y is not read again here and must not push the operands out
@@ -657,6 +663,7 @@ __device__ __forceinline__ void piece_body(const Group &grp, const Piece &p, con
                     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, yv[n & 1][i]), out, voff + (uint32_t)(32 * b + 8 * i) * pitch + 128u * a, 0, 2);   // 2: streaming
             };
             stage(0);
+            SBN_WAIT_VMCNT(0);   // what was asked for of the next piece (the youngest half a step ago), in front of the first store
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int n = 1; n < RA * TB; ++n) {
@@ -666,7 +673,8 @@ __device__ __forceinline__ void piece_body(const Group &grp, const Piece &p, con
                 __builtin_amdgcn_sched_barrier(0);
             }
             leave(RA * TB - 1);
-        } else if (orow < g.d_out) {
+        } else {
+            SBN_WAIT_VMCNT(0);
 #pragma unroll
             for (int b = 0; b < TB; ++b) {
                 const int t = t0 + 32 * b + r;
@@ -675,24 +683,26 @@ __device__ __forceinline__ void piece_body(const Group &grp, const Piece &p, con
                 for (int a = 0; a < RA; ++a) store_tile(g, acc[a][b], orow + 32 * a + 4 * c, t, __fdiv_rn(sxv[TB], sxv[b]));
             }
         }
+    } else {
+        SBN_WAIT_VMCNT(0);
     }
 }
 
 template <int TB, bool DENSE, bool UNIT, class Group>
-__device__ __forceinline__ void piece_live(const Group &grp, const Piece &p, const Piece &next, int8_t *lds, int wave, int lane)
+__device__ __forceinline__ void piece_live(const Group &grp, const Piece &p, const Piece &next, Stream &st, int8_t *lds, int wave, int lane)
 {
     const bool live = p.to * ROWS + wave * (32 * RA) < grp.g[p.prob].d_out;   // a ragged last row tile leaves whole wavefronts idle
-    if (live) piece_body<TB, true, DENSE, UNIT>(grp, p, next, lds, wave, lane);
-    else piece_body<TB, false, DENSE, UNIT>(grp, p, next, lds, wave, lane);
+    if (live) piece_body<TB, true, DENSE, UNIT>(grp, p, next, st, lds, wave, lane);
+    else piece_body<TB, false, DENSE, UNIT>(grp, p, next, st, lds, wave, lane);
 }
 
 template <bool DENSE, bool UNIT, class Group>
-__device__ __forceinline__ void piece_run(const Group &grp, const Piece &p, const Piece &next, int8_t *lds, int wave, int lane)
+__device__ __forceinline__ void piece_run(const Group &grp, const Piece &p, const Piece &next, Stream &st, int8_t *lds, int wave, int lane)
 {
-    if (p.tb == 4) piece_live<4, DENSE, UNIT>(grp, p, next, lds, wave, lane);
-    else if (p.tb == 3) piece_live<3, DENSE, UNIT>(grp, p, next, lds, wave, lane);
-    else if (p.tb == 2) piece_live<2, DENSE, UNIT>(grp, p, next, lds, wave, lane);
-    else piece_live<1, DENSE, UNIT>(grp, p, next, lds, wave, lane);
+    if (p.tb == 4) piece_live<4, DENSE, UNIT>(grp, p, next, st, lds, wave, lane);
+    else if (p.tb == 3) piece_live<3, DENSE, UNIT>(grp, p, next, st, lds, wave, lane);
+    else if (p.tb == 2) piece_live<2, DENSE, UNIT>(grp, p, next, st, lds, wave, lane);
+    else piece_live<1, DENSE, UNIT>(grp, p, next, st, lds, wave, lane);
 }
 
 }  // namespace sp
@@ -743,10 +753,10 @@ __global__ void __launch_bounds__(64 * sp::NW) gemm_smfmac_kernel(Group grp, Tab
         };
         sp::Piece cur = piece_at(f);
         if (cur.tb == 0) return;
-        sp::piece_prologue(grp, cur, lds, wave, lane);
+        sp::Stream st = sp::first_stream(grp, cur, lds, wave, lane);
         while (cur.tb > 0) {
             const sp::Piece next = piece_at(f);
-            sp::piece_run<DENSE, UNIT>(grp, cur, next, lds, wave, lane);
+            sp::piece_run<DENSE, UNIT>(grp, cur, next, st, lds, wave, lane);
             cur = next;
         }
     } else {
@@ -768,9 +778,25 @@ __global__ void __launch_bounds__(64 * sp::NW) gemm_smfmac_kernel(Group grp, Tab
     const int q = total / nb, rem = total % nb;
     int f = j * q + (j < rem ? j : rem);
     const int end = f + q + (j < rem ? 1 : 0);
-    int prob = 0, group = 0, base = 0, parity = 0;
-    // The next piece of the block's list, whose pieces are listed without gaps (the first empty entry ends it); or the piece that
-    // starts at flat unit f (f only grows, so the search for its strip resumes where it stopped).
+    // Where the next piece starts: token unit u of a strip of gsz units from unit0 on, row tile `to` of tiles_o, group `group` of
+    // problem `prob`, of which the XCD owns n units from `first` on.  Found once and then moved on without a division.
+    int prob = 0, group = 0, to = 0, u = 0, first = 0, n = 0, gsz = 0, tiles_o = 0, parity = 0;
+    auto enter_group = [&]() {   // the first group with units from (prob, group) on
+        for (; prob < grp.count; ++prob, group = 0) {
+            n = own_units(prob, first);
+            gsz = n - group * GROUP_UNITS;
+            gsz = gsz > GROUP_UNITS ? GROUP_UNITS : gsz;
+            tiles_o = (grp.g[prob].d_out + sp::ROWS - 1) / sp::ROWS;
+            if (gsz > 0) return;
+        }
+    };
+    if (!listed && f < end) {
+        int skip = f;   // units in front of the block's first
+        for (enter_group(); skip >= tiles_o * gsz; ++group, enter_group()) skip -= tiles_o * gsz;
+        to = skip / gsz;
+        u = skip % gsz;
+    }
+    // the next piece of the block's list, whose pieces are listed without gaps (the first empty entry ends it), or the next by formula
     int entry = 0;
     auto piece_at = [&](int &f) {
         if (listed) {
@@ -779,32 +805,29 @@ __global__ void __launch_bounds__(64 * sp::NW) gemm_smfmac_kernel(Group grp, Tab
             return sp::Piece{(int)(pc >> 25), (int)((pc >> 16) & 0x1ff), (int)((pc >> 3) & 0x1fff) * 32, (int)(pc & 7), entry & 1};
         }
         if (f >= end) return none;
-        int first, n, gsz, tiles_o;
-        for (;;) {
-            n = own_units(prob, first);
-            tiles_o = (grp.g[prob].d_out + sp::ROWS - 1) / sp::ROWS;
-            gsz = n - group * GROUP_UNITS;
-            gsz = gsz > GROUP_UNITS ? GROUP_UNITS : gsz;
-            const int cnt = gsz > 0 ? tiles_o * gsz : 0;
-            if (gsz > 0 && f < base + cnt) break;
-            base += cnt;
-            if (gsz <= 0 || (group + 1) * GROUP_UNITS >= n) { ++prob; group = 0; } else ++group;
-        }
-        const int local = f - base;
-        const int to = local / gsz, u = local % gsz;
         int w = gsz - u;
         w = w > 4 ? 4 : w;
         w = w > end - f ? end - f : w;
         f += w;
         parity ^= 1;
-        return sp::Piece{prob, to, (first + group * GROUP_UNITS + u) * 32, w, parity};
+        const sp::Piece piece{prob, to, (first + group * GROUP_UNITS + u) * 32, w, parity};
+        u += w;
+        if (u == gsz) {
+            u = 0;
+            if (++to == tiles_o) {
+                to = 0;
+                ++group;
+                enter_group();
+            }
+        }
+        return piece;
     };
     sp::Piece cur = piece_at(f);
     if (cur.tb == 0) return;
-    sp::piece_prologue(grp, cur, lds, wave, lane);
+    sp::Stream st = sp::first_stream(grp, cur, lds, wave, lane);
     while (cur.tb > 0) {
         const sp::Piece next = piece_at(f);
-        sp::piece_run<DENSE, UNIT>(grp, cur, next, lds, wave, lane);
+        sp::piece_run<DENSE, UNIT>(grp, cur, next, st, lds, wave, lane);
         cur = next;
     }
     }

@@ -165,6 +165,22 @@ __device__ __forceinline__ void lds_dma16(const void *base, uint32_t voff, uint3
                  : "memory", "m0");
 }
 
+// The same through a buffer resource: lane l fetches 16 bytes at its base + soff + voff.  From its number of bytes on (soff
+// included, measured) nothing is fetched and zeros are deposited.
+__device__ __forceinline__ void lds_dma16_buffer(const v4i rsrc, uint32_t voff, uint32_t soff, uint32_t lds_addr)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                 :
+                 : "s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff)
+                 : "memory", "m0");
+}
+
+__device__ __forceinline__ v4i buffer_of(const void *base, uint32_t bytes)
+{
+    const uint64_t a = reinterpret_cast<uint64_t>(base);
+    return v4i{(int)(uint32_t)a, (int)(uint32_t)(a >> 32), (int)bytes, 0x00027000};
+}
+
 // the same with one dword per lane: lane l deposits its 4 bytes at lds_addr + 4*l
 __device__ __forceinline__ void lds_dma4(const void *base, uint32_t voff, uint32_t lds_addr)
 {

@@ -133,3 +133,31 @@ def test_pieces_scales_below_the_normal_range(N, M):
     scale = (gamma.cpu().numpy() / sx.numpy()).astype(np.float32)
     assert (scale < 2.0 ** -126).any()
     assert np.array_equal(Y.cpu().numpy(), acc.astype(np.float32) * scale[:, None])
+
+
+@pytest.mark.parametrize("N,M", [(2, 4), (8, 8)])
+@pytest.mark.parametrize("problems", [
+    [(9000, 6000, 128)], [(9100, 5000, 256)], [(9000, 6000, 384)], [(8200, 6500, 640)],     # 1, 2, 3, 5 chunks: fewer than the ring, odd counts
+    [(4000, 3000, 640), (4000, 2600, 640), (5000, 3001, 640)],                              # rows of one length, others' outputs
+    [(3000, 4000, 384), (4100, 3000, 512), (2000, 2100, 128), (3333, 4444, 512)],           # the stream of requests is started anew in between
+    [(700, 1100, 384), (650, 900, 384), (97 * 8, 600, 896)],                                # from a list: pieces of all widths behind each other
+])
+def test_pieces_one_behind_the_other(N, M, problems):
+    s = sbn()
+    xqs, sxs, packs, Ys, refs = [], [], [], [], []
+    for i, (t, o, k) in enumerate(problems):
+        gen = torch.Generator(device=DEV).manual_seed(17 * i + t)
+        packed, gamma = hip_pack(sbn_synth.latent_weight(o, k, 8200 + i), N, M)
+        Weff = torch.zeros((o, k), dtype=torch.int8, device=DEV)
+        s.sbn_unpack(packed, o, k, N, M, Weff)
+        xq = torch.randint(-128, 128, (t, k), generator=gen, device=DEV, dtype=torch.int8)
+        sx = torch.rand(t, generator=gen, device=DEV) * 50 + 10
+        xqs.append(xq); sxs.append(sx); packs.append((packed, gamma))
+        Ys.append(torch.full((t, o), float("nan"), device=DEV))
+        # sums below 2^24 are exact in fp32 whatever their order; then the formula's two roundings
+        acc = xq.float() @ Weff.float().T
+        assert k * 128 < 1 << 24
+        refs.append(acc * (gamma / sx)[:, None])
+    s.sbn_test_linear_kernel(s.SBN_KERNEL_PIECES, xqs, sxs, [p[0] for p in packs], [p[1] for p in packs], Ys, N, M)
+    for Y, ref in zip(Ys, refs):
+        assert torch.equal(Y, ref)
