@@ -349,51 +349,77 @@ __device__ __forceinline__ bool bf16_tile_of_block(const GemmBf16Args &g, int bi
 // holds m = column r, n = rows 8q + 4c + i.  Stored from there, an instruction would touch 32 rows with 16 bytes each
 // (16 us of a tile of 256 x 256, next to 60 us of matrix work at 2560 k).  So 32 rows at a time go through the wavefront's
 // 16 KB of the idle stages in fp32 (granules of 16 bytes XOR-swizzled with the row) and leave as whole rows of the
-// wavefront's tile, 16 bytes per lane.  N is a multiple of 8.
+// wavefront's tile, 16 bytes per lane.  N is a multiple of 8.  A wavefront's LDS operations complete in order, so the next 32 rows
+// are written behind the reads of the last ones without a wait, and what is already in C is asked for in front of them.
 template <int WP, int WQ>
-__device__ __forceinline__ void bf16_wave_epilogue(const GemmBf16Args &g, const v16f (&acc)[WP][WQ], uint8_t *stg, int nw, int mw, int lane)
+__device__ __forceinline__ void bf16_wave_epilogue(const GemmBf16Args &g, const v16f (&acc)[WP][WQ], const float alpha, uint8_t *stg, int nw, int mw, int lane)
 {
-    constexpr int ROW = WP * 128, LPR = ROW / 32;     // bytes of a staged row, lanes per row
+    constexpr int ROW = WP * 128, LPR = ROW / 32, J = 32 * LPR / 64;     // bytes of a staged row, lanes per row, stores of 32 rows
     const int r = lane & 31, c = lane >> 5;
-    const float alpha = g.alpha ? *g.alpha : 1.0f;
-#pragma unroll
-    for (int b = 0; b < WQ; ++b) {
+    const int h = lane % LPR, n = nw + 8 * h;
+    uint16_t *const dst = g.C + (int64_t)(mw + lane / LPR) * g.ldc + n;
+    auto inside = [&](const int b, const int j) { return mw + 32 * b + (64 / LPR) * j + lane / LPR < g.M && n < g.N; };
+    auto at = [&](const int b, const int j) { return reinterpret_cast<uint4 *>(dst + (int64_t)(32 * b + (64 / LPR) * j) * g.ldc); };
+    v4f lo[J], hi[J];
+    auto stage = [&](const int b) {
 #pragma unroll
         for (int a = 0; a < WP; ++a)
 #pragma unroll
             for (int q = 0; q < 4; ++q)
                 *reinterpret_cast<v4f *>(stg + r * ROW + 16 * ((8 * a + 2 * q + c) ^ (r & 15))) =
                     v4f{acc[a][b][4 * q], acc[a][b][4 * q + 1], acc[a][b][4 * q + 2], acc[a][b][4 * q + 3]};
-        // a wavefront's LDS operations complete in order: what it wrote itself is there
+        asm volatile("" ::: "memory");   // the reads are of what other lanes have written
 #pragma unroll
-        for (int j = 0; j < 32 * LPR / 64; ++j) {
-            const int row = (64 / LPR) * j + lane / LPR, h = lane % LPR;
-            const v4f lo = *reinterpret_cast<const v4f *>(stg + row * ROW + 16 * ((2 * h) ^ (row & 15)));
-            const v4f hi = *reinterpret_cast<const v4f *>(stg + row * ROW + 16 * ((2 * h + 1) ^ (row & 15)));
-            const int m = mw + 32 * b + row, n = nw + 8 * h;
-            if (m >= g.M || n >= g.N) continue;
+        for (int j = 0; j < J; ++j) {
+            const int row = (64 / LPR) * j + lane / LPR;
+            lo[j] = *reinterpret_cast<const v4f *>(stg + row * ROW + 16 * ((2 * h) ^ (row & 15)));
+            hi[j] = *reinterpret_cast<const v4f *>(stg + row * ROW + 16 * ((2 * h + 1) ^ (row & 15)));
+        }
+        asm volatile("" ::: "memory");   // the next rows' writes stay behind them
+    };
+    if (!g.accumulate && !g.mask) {
+#pragma unroll
+        for (int b = 0; b < WQ; ++b) {
+            stage(b);
+#pragma unroll
+            for (int j = 0; j < J; ++j) {
+                const uint4 o = make_uint4(pack_bf16(lo[j][0] * alpha, lo[j][1] * alpha), pack_bf16(lo[j][2] * alpha, lo[j][3] * alpha),
+                                           pack_bf16(hi[j][0] * alpha, hi[j][1] * alpha), pack_bf16(hi[j][2] * alpha, hi[j][3] * alpha));
+                if (inside(b, j)) *at(b, j) = o;
+            }
+        }
+        return;
+    }
+#pragma unroll
+    for (int b = 0; b < WQ; ++b) {
+        uint4 old[J];
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            old[j] = make_uint4(0, 0, 0, 0);
+            if (g.accumulate && inside(b, j)) old[j] = *at(b, j);
+        }
+        stage(b);
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            if (!inside(b, j)) continue;
             float v[8];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) { v[i] = lo[i] * alpha; v[4 + i] = hi[i] * alpha; }
+            for (int i = 0; i < 4; ++i) { v[i] = lo[j][i] * alpha; v[4 + i] = hi[j][i] * alpha; }
             if (g.mask) {   // n is a multiple of 8: its mask bits sit in one byte
+                const int m = mw + 32 * b + (64 / LPR) * j + lane / LPR;
                 const uint32_t mb = g.mask[(int64_t)m * g.mask_wpr + (n >> 5)] >> (n & 31);
 #pragma unroll
                 for (int i = 0; i < 8; ++i) v[i] = (mb >> i) & 1u ? v[i] : 0.0f;
             }
-            uint4 *dst = reinterpret_cast<uint4 *>(g.C + (int64_t)m * g.ldc + n);
             if (g.accumulate) {
-                const uint4 old = *dst;
-                const uint32_t w[4] = {old.x, old.y, old.z, old.w};
+                const uint32_t w[4] = {old[j].x, old[j].y, old[j].z, old[j].w};
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     v[2 * i] += __uint_as_float(w[i] << 16);
                     v[2 * i + 1] += __uint_as_float(w[i] & 0xffff0000u);
                 }
             }
-            uint32_t o[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) o[i] = pack_bf16(v[2 * i], v[2 * i + 1]);
-            *dst = make_uint4(o[0], o[1], o[2], o[3]);
+            *at(b, j) = make_uint4(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]), pack_bf16(v[4], v[5]), pack_bf16(v[6], v[7]));
         }
     }
 }
@@ -448,55 +474,67 @@ __device__ __forceinline__ void bf16_tile_body(const GemmBf16Args &g, uint8_t *d
     const int r = lane & 31, c = lane >> 5;
     const uint32_t lds0 = lds_address(dlds);
     const int nk = g.K / GD_K;
+    const float alpha = g.alpha ? *g.alpha : 1.0f;   // here it is a scalar load: in front of everything that writes memory
 
     // DMA roles, four instructions per operand and wavefront.  k contiguous: one instruction fills 8 rows x 128 bytes (lane l:
     // row l / 8, slot l % 8 holding global column slot ^ ((row >> 1) & 7)).  Transposed Q: a stage is 64 k rows of M values,
     // one instruction fills 1024 bytes of them, slot s of row k holds the eight values of granule s ^ f(k),
     // f = 4 (k & 3) | 2 ((k >> 2) & 1): the four k rows that a transposing read of 16 lanes takes lie in different banks.
-    // Past the matrix the last row or granule again (never stored, or zeroed in LDS below).
+    // Operands are buffers: rows and k rows past the matrix, and stages past the last, read as zeros and fetch nothing.
     constexpr int QROW = S::M * 2;                        // bytes of a k row of the transposed stage
-    const char *pbase = reinterpret_cast<const char *>(g.P + (int64_t)n0 * g.ldp);
-    const char *qbase = reinterpret_cast<const char *>(QT ? g.Q + m0 : g.Q + (int64_t)m0 * g.ldq);
-    const int64_t qstep = QT ? g.ldq * (GD_K * 2) : GD_K * 2;
     const int kleft = g.kq - (nk - 1) * GD_K;             // k of the last stage that Q has
-    uint32_t poff[4], qoff[4], qlast[4];
+    const int prows = g.N - n0 < S::N ? g.N - n0 : S::N, qrows = g.M - m0 < S::M ? g.M - m0 : S::M;
+    const uint32_t ppitch = 2u * (uint32_t)g.ldp;
+    const uint32_t qpitch = 2u * (uint32_t)g.ldq, pbytes = (uint32_t)prows * ppitch;
+    const uint32_t qbytes = QT ? GD_K * qpitch - 2u * (uint32_t)m0 : (uint32_t)qrows * qpitch;        // of a transposed stage: up to the end of its rows
+    const uint32_t qbytes_last = QT ? (uint32_t)kleft * qpitch - 2u * (uint32_t)m0 : qbytes;
+    v4i pbuffer = buffer_of(g.P + (int64_t)n0 * g.ldp, pbytes);
+    v4i qbuffer = buffer_of(QT ? g.Q + m0 : g.Q + (int64_t)m0 * g.ldq, nk > 1 ? qbytes : qbytes_last);
+    uint32_t pat = 0, qat = 0;                            // k contiguous: bytes into a row
+    uint32_t poff[4], qoff[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int row = 32 * wave + 8 * i + (lane >> 3);
         const int col = (lane & 7) ^ ((row >> 1) & 7);
-        const int n = (n0 + row < g.N ? n0 + row : g.N - 1) - n0;
-        poff[i] = (uint32_t)(((int64_t)n * g.ldp + col * 8) * 2);
+        poff[i] = (uint32_t)row * ppitch + 16u * col;
         if constexpr (QT) {
             constexpr int GPR = S::M / 8, RPI = 64 / GPR;      // granules of a k row, k rows per instruction
             const int k = RPI * (4 * wave + i) + lane / GPR;
-            int gran = (lane % GPR) ^ (4 * (k & 3) | 2 * ((k >> 2) & 1));
-            gran = m0 + 8 * gran + 8 <= g.M ? gran : (g.M - m0) / 8 - 1;
-            qoff[i] = (uint32_t)(((int64_t)k * g.ldq + 8 * gran) * 2);
-            qlast[i] = (uint32_t)(((int64_t)(k < kleft ? k : kleft - 1) * g.ldq + 8 * gran) * 2);
+            const int gran = (lane % GPR) ^ (4 * (k & 3) | 2 * ((k >> 2) & 1));
+            qoff[i] = (uint32_t)k * qpitch + 16u * gran;
         } else {
-            const int m = (m0 + row < g.M ? m0 + row : g.M - 1) - m0;
-            qoff[i] = (uint32_t)(((int64_t)m * g.ldq + col * 8) * 2);
-            qlast[i] = (uint32_t)(((int64_t)m * g.ldq + (8 * col < kleft ? col : (kleft - 1) / 8) * 8) * 2);
+            qoff[i] = (uint32_t)row * qpitch + 16u * col;
         }
     }
-    // the four instructions of a wavefront and slot one by one, so that they can stand between matrix instructions; past the
-    // end the last stage is fetched again into a slot nobody reads any more
-    auto dma_p = [&](int kt, const uint32_t slot, const int i) {
-        kt = kt < nk ? kt : nk - 1;
-        lds_dma16(pbase + (int64_t)kt * (GD_K * 2), poff[i], lds0 + slot + wave * 4096 + i * 1024);
+    // the four instructions of a wavefront and slot one by one, so that they can stand between matrix instructions; the fourth moves
+    // the operand on to its next stage, kt + 1
+    auto dma_p = [&](const int kt, const uint32_t slot, const int i) {
+        lds_dma16_buffer(pbuffer, poff[i], pat, lds0 + slot + wave * 4096 + i * 1024);
+        if (i < 3) return;
+        pat += GD_K * 2;
+        pbuffer[2] = kt + 1 < nk ? (int)pbytes : 0;
     };
-    auto dma_q = [&](int kt, const uint32_t slot, const int i) {
-        kt = kt < nk ? kt : nk - 1;
-        lds_dma16(qbase + (int64_t)kt * qstep, kt == nk - 1 ? qlast[i] : qoff[i], lds0 + slot + wave * 4096 + i * 1024);
+    auto dma_q = [&](const int kt, const uint32_t slot, const int i) {
+        lds_dma16_buffer(qbuffer, qoff[i], QT ? 0 : qat, lds0 + slot + wave * 4096 + i * 1024);
+        if (i < 3) return;
+        if constexpr (QT) {
+            const uint64_t base = ((uint64_t)(uint32_t)qbuffer[1] << 32 | (uint32_t)qbuffer[0]) + (uint64_t)g.ldq * (GD_K * 2);
+            qbuffer[0] = (int)(uint32_t)base;
+            qbuffer[1] = (int)(uint32_t)(base >> 32);
+        } else {
+            qat += GD_K * 2;
+        }
+        qbuffer[2] = kt + 2 < nk ? (int)qbytes : kt + 2 == nk ? (int)qbytes_last : 0;
     };
-    // k of the last stage past the end of Q: what was fetched in their place may be infinite, and zeros of P do not cancel that.
+    // k of the last stage past the end of a row of Q: what was fetched in their place is the next row, which may be infinite, and zeros
+    // of P do not cancel that (k rows past the end of a transposed Q are zeros already).
     // A lane overwrites what it asked for itself, behind its own wait and in front of the barrier that publishes the stage.
     auto zero_tail = [&](const uint32_t slot) {
         typedef __attribute__((address_space(3))) v4i *lds_v4i;
         asm volatile("" ::: "memory");   // not in front of the wait
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const int k = QT ? (512 / S::M) * (4 * wave + i) + lane / (S::M / 8) : 8 * ((lane & 7) ^ (((32 * wave + 8 * i + (lane >> 3)) >> 1) & 7));
+            const int k = 8 * ((lane & 7) ^ (((32 * wave + 8 * i + (lane >> 3)) >> 1) & 7));
             if (k >= kleft) *(lds_v4i)(uintptr_t)(lds0 + slot + wave * 4096 + i * 1024 + 16 * lane) = v4i{0, 0, 0, 0};
         }
     };
@@ -580,7 +618,7 @@ __device__ __forceinline__ void bf16_tile_body(const GemmBf16Args &g, uint8_t *d
             else dma_p(j >> 1, j * S::SLOT, i);
         }
     SBN_WAIT_VMCNT(8);
-    if (nk == 1 && kleft < GD_K) zero_tail(S::SLOT);
+    if (!QT && nk == 1 && kleft < GD_K) zero_tail(S::SLOT);
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < READS; ++i) read_one(0, i);
@@ -597,7 +635,7 @@ __device__ __forceinline__ void bf16_tile_body(const GemmBf16Args &g, uint8_t *d
                 if (PQ[u] > 0) spread(s, PQ[u], [&](const int k) { dma_p(kt + 2, free, first + k); });
             });
         SBN_WAIT_VMCNT(4);   // P(kt + 2) may fly
-        if (kt == nk - 2 && kleft < GD_K) zero_tail(sq_next);
+        if (!QT && kt == nk - 2 && kleft < GD_K) zero_tail(sq_next);
         __syncthreads();
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
@@ -617,7 +655,7 @@ __device__ __forceinline__ void bf16_tile_body(const GemmBf16Args &g, uint8_t *d
     }
     SBN_WAIT_VMCNT(0);   // the surplus stages have landed
     __syncthreads();
-    bf16_wave_epilogue<WP, WQ>(g, acc, dlds + wave * S::STAGING, n0 + wn * 32 * WP, m0 + wm * 32 * WQ, lane);
+    bf16_wave_epilogue<WP, WQ>(g, acc, alpha, dlds + wave * S::STAGING, n0 + wn * 32 * WP, m0 + wm * 32 * WQ, lane);
 }
 
 template <bool BIG>
