@@ -357,10 +357,26 @@ __device__ __forceinline__ void bf16_wave_epilogue(const GemmBf16Args &g, const 
     constexpr int ROW = WP * 128, LPR = ROW / 32, J = 32 * LPR / 64;     // bytes of a staged row, lanes per row, stores of 32 rows
     const int r = lane & 31, c = lane >> 5;
     const int h = lane % LPR, n = nw + 8 * h;
-    uint16_t *const dst = g.C + (int64_t)(mw + lane / LPR) * g.ldc + n;
-    auto inside = [&](const int b, const int j) { return mw + 32 * b + (64 / LPR) * j + lane / LPR < g.M && n < g.N; };
-    auto at = [&](const int b, const int j) { return reinterpret_cast<uint4 *>(dst + (int64_t)(32 * b + (64 / LPR) * j) * g.ldc); };
+    const int m0 = mw + lane / LPR, rows = n < g.N ? g.M - m0 : 0;     // of C, from the lane's first on
+    const int64_t step = (int64_t)(64 / LPR) * g.ldc;
+    uint16_t *dst = g.C + (int64_t)m0 * g.ldc + n;
+    auto inside = [&](const int b, const int j) { return 32 * b + (64 / LPR) * j < rows; };
+    auto at = [&](uint16_t *&p) {   // address by address: all of them at once would not fit the registers
+        uint4 *const here = reinterpret_cast<uint4 *>(p);
+        p += step;
+        asm volatile("" : "+v"(p));
+        return here;
+    };
     v4f lo[J], hi[J];
+    auto read = [&](const int first, const int n) {   // staged rows of stores [first, first + n)
+#pragma unroll
+        for (int j = first; j < first + n; ++j) {
+            const int row = (64 / LPR) * j + lane / LPR;
+            lo[j] = *reinterpret_cast<const v4f *>(stg + row * ROW + 16 * ((2 * h) ^ (row & 15)));
+            hi[j] = *reinterpret_cast<const v4f *>(stg + row * ROW + 16 * ((2 * h + 1) ^ (row & 15)));
+        }
+        asm volatile("" ::: "memory");   // the next rows' writes stay behind them
+    };
     auto stage = [&](const int b) {
 #pragma unroll
         for (int a = 0; a < WP; ++a)
@@ -369,23 +385,18 @@ __device__ __forceinline__ void bf16_wave_epilogue(const GemmBf16Args &g, const 
                 *reinterpret_cast<v4f *>(stg + r * ROW + 16 * ((8 * a + 2 * q + c) ^ (r & 15))) =
                     v4f{acc[a][b][4 * q], acc[a][b][4 * q + 1], acc[a][b][4 * q + 2], acc[a][b][4 * q + 3]};
         asm volatile("" ::: "memory");   // the reads are of what other lanes have written
-#pragma unroll
-        for (int j = 0; j < J; ++j) {
-            const int row = (64 / LPR) * j + lane / LPR;
-            lo[j] = *reinterpret_cast<const v4f *>(stg + row * ROW + 16 * ((2 * h) ^ (row & 15)));
-            hi[j] = *reinterpret_cast<const v4f *>(stg + row * ROW + 16 * ((2 * h + 1) ^ (row & 15)));
-        }
-        asm volatile("" ::: "memory");   // the next rows' writes stay behind them
     };
     if (!g.accumulate && !g.mask) {
 #pragma unroll
         for (int b = 0; b < WQ; ++b) {
             stage(b);
+            read(0, J);
 #pragma unroll
             for (int j = 0; j < J; ++j) {
                 const uint4 o = make_uint4(pack_bf16(lo[j][0] * alpha, lo[j][1] * alpha), pack_bf16(lo[j][2] * alpha, lo[j][3] * alpha),
                                            pack_bf16(hi[j][0] * alpha, hi[j][1] * alpha), pack_bf16(hi[j][2] * alpha, hi[j][3] * alpha));
-                if (inside(b, j)) *at(b, j) = o;
+                uint4 *const out = at(dst);
+                if (inside(b, j)) *out = o;
             }
         }
         return;
@@ -393,20 +404,24 @@ __device__ __forceinline__ void bf16_wave_epilogue(const GemmBf16Args &g, const 
 #pragma unroll
     for (int b = 0; b < WQ; ++b) {
         uint4 old[J];
+        uint16_t *from = dst;
 #pragma unroll
         for (int j = 0; j < J; ++j) {
+            const uint4 *const in = at(from);
             old[j] = make_uint4(0, 0, 0, 0);
-            if (g.accumulate && inside(b, j)) old[j] = *at(b, j);
+            if (g.accumulate && inside(b, j)) old[j] = *in;
         }
         stage(b);
 #pragma unroll
         for (int j = 0; j < J; ++j) {
+            if (j % (J / 2) == 0) read(j, J / 2);   // in two parts, beside what is in C already
+            uint4 *const out = at(dst);
             if (!inside(b, j)) continue;
             float v[8];
 #pragma unroll
             for (int i = 0; i < 4; ++i) { v[i] = lo[j][i] * alpha; v[4 + i] = hi[j][i] * alpha; }
             if (g.mask) {   // n is a multiple of 8: its mask bits sit in one byte
-                const int m = mw + 32 * b + (64 / LPR) * j + lane / LPR;
+                const int m = m0 + 32 * b + (64 / LPR) * j;
                 const uint32_t mb = g.mask[(int64_t)m * g.mask_wpr + (n >> 5)] >> (n & 31);
 #pragma unroll
                 for (int i = 0; i < 8; ++i) v[i] = (mb >> i) & 1u ? v[i] : 0.0f;
@@ -419,7 +434,7 @@ __device__ __forceinline__ void bf16_wave_epilogue(const GemmBf16Args &g, const 
                     v[2 * i + 1] += __uint_as_float(w[i] & 0xffff0000u);
                 }
             }
-            *at(b, j) = make_uint4(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]), pack_bf16(v[4], v[5]), pack_bf16(v[6], v[7]));
+            *out = make_uint4(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]), pack_bf16(v[4], v[5]), pack_bf16(v[6], v[7]));
         }
     }
 }
