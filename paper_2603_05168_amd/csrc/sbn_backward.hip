@@ -5,8 +5,8 @@
 // Both run on the dense bf16 matrix cores (v_mfma_f32_32x32x16_bf16, fp32 accumulation): the 2:4
 // structure lies along d_in, which is not the contracted dimension of either product, so the sparse
 // instruction does not apply.  One GEMM kernel serves both: dY, and dY / s_x in the same layout, are read as they lie (dW
-// contracts their slow dimension: the transposing LDS read), small kernels write dY / s_x and put W_eff^T and x~^T (both
-// exact in bf16) contraction-major first.
+// contracts their slow dimension: the transposing LDS read), one kernel writes dY / s_x and puts W_eff^T (a byte per weight) and x~^T
+// (exact in bf16) contraction-major first.
 #include <algorithm>
 #include <vector>
 
@@ -26,26 +26,6 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
 }
 
 // ---- layout kernels -------------------------------------------------------------------------------
-constexpr int TP = 64 + 8;   // padded LDS row (bf16 elements) of the 64-wide transposition tiles
-
-// writes a [rows][64] bf16 LDS tile (row pitch TP) to dst[(r0 + row) * ld + c0 + 0..63], 16 bytes per thread
-__device__ __forceinline__ void write_tile_rows(const uint16_t *tile, int rows, uint16_t *dst, int64_t ld, int64_t r0,
-                                                int64_t c0, int64_t rmax, int64_t cmax)
-{
-    for (int v = threadIdx.x; v < rows * 8; v += 256) {
-        const int row = v >> 3, col = (v & 7) * 8;
-        if (r0 + row >= rmax) continue;
-        const uint16_t *s = tile + row * TP + col;
-        uint16_t *d = dst + (r0 + row) * ld + c0 + col;
-        if (c0 + col + 8 <= cmax) {
-            *reinterpret_cast<uint4 *>(d) = *reinterpret_cast<const uint4 *>(s);
-        } else {
-            for (int e = 0; e < 8; ++e)
-                if (c0 + col + e < cmax) d[e] = s[e];
-        }
-    }
-}
-
 // One quarter (32 weights, quarter P of its chunk) of a packed row: put(k, code) for every slot, k = weight inside the quarter.
 template <int N, int M, int P, class Put>
 __device__ __forceinline__ void decode_quarter(const uint32_t *chunk, Put &&put)
@@ -70,30 +50,57 @@ __device__ __forceinline__ void decode_quarter(const uint32_t *chunk, Put &&put)
     }
 }
 
-// packed weights -> W_eff^T as bf16 [d_in, ld] (ld >= d_out; zeros for rows of W past d_out): 64 rows of W x one chunk, a
-// wavefront per quarter of the chunk
+// W_eff^T for dX: a byte per weight, the high half of the bf16 value +-0.5 or 0 (the low half is zero).  [d_in, ld], ld >= d_out a
+// multiple of 128, zeros for rows of W past d_out.  One tile is 128 rows of W x 128 weights, so that whole cache lines leave.
+constexpr int TB = 128 + 16;   // pitch of a row of the tile
+constexpr uint32_t code_byte(uint32_t code) { return code == 0 ? 0u : code == 1 ? 0x3fu : 0xbfu; }
+
+__device__ __forceinline__ void write_code_tile(const uint8_t *tile, uint8_t *__restrict__ dst, int64_t ld, int64_t k0, int64_t o0, int64_t kmax)
+{
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int v = threadIdx.x + 256 * i, row = v >> 3, col = (v & 7) * 16;
+        if (k0 + row < kmax) *reinterpret_cast<uint4 *>(dst + (k0 + row) * ld + o0 + col) = *reinterpret_cast<const uint4 *>(tile + row * TB + col);
+    }
+}
+
+// from packed weights, a wavefront per quarter of the chunk
 template <int N, int M>
-__device__ __forceinline__ void unpack_transpose_tile(const uint8_t *__restrict__ packed, int d_out, int d_in, uint16_t *__restrict__ wt, int64_t ld,
-                                                      int chunk, int o0, uint16_t *tile)
+__device__ __forceinline__ void unpack_transpose_tile(const uint8_t *__restrict__ packed, int d_out, int d_in, uint8_t *__restrict__ wt, int64_t ld,
+                                                      int chunk, int o0, uint8_t *tile)
 {
     constexpr int B = N == M ? 0 : M == 2 ? 1 : M == 4 ? 2 : 3, CHUNK_WORDS = 128 * N / M * (2 + B) / 32;
     const int nchunks = (d_in + CHUNK - 1) / CHUNK;
-    const int ro = threadIdx.x & 63, quarter = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int o = o0 + ro;
-    uint16_t *const col = tile + 32 * quarter * TP + ro;
-    for (int k = 0; k < 32; ++k) col[k * TP] = 0;
-    if (o < d_out) {
+    const int quarter = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    for (int k = threadIdx.x & 63; k < 32 * 8; k += 64) *reinterpret_cast<uint4 *>(tile + (32 * quarter + (k >> 3)) * TB + 16 * (k & 7)) = make_uint4(0, 0, 0, 0);
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+        const int ro = 64 * half + (threadIdx.x & 63), o = o0 + ro;
+        uint8_t *const col = tile + 32 * quarter * TB + ro;
+        if (o >= d_out) continue;
         const uint32_t *src = reinterpret_cast<const uint32_t *>(packed) + ((int64_t)o * nchunks + chunk) * CHUNK_WORDS;
         auto put = [&](int k, uint32_t code) {
-            if (code) col[k * TP] = code == 1u ? 0x3f80u : 0xbf80u;
+            if (code) col[k * TB] = (uint8_t)(code == 1u ? code_byte(1) : code_byte(3));
         };
         if (quarter == 0) decode_quarter<N, M, 0>(src, put);
         else if (quarter == 1) decode_quarter<N, M, 1>(src, put);
         else if (quarter == 2) decode_quarter<N, M, 2>(src, put);
         else decode_quarter<N, M, 3>(src, put);
     }
-    __syncthreads();
-    write_tile_rows(tile, 128, wt, ld, (int64_t)chunk * CHUNK, o0, d_in, ld);
+    write_code_tile(tile, wt, ld, (int64_t)chunk * CHUNK, o0, d_in);
+}
+
+// from int8 W_eff [rows, cols] (patterns without a decoder here)
+__device__ __forceinline__ void transpose_codes_tile(const int8_t *__restrict__ src, int64_t rows, int64_t cols, uint8_t *__restrict__ wt, int64_t ld,
+                                                     int64_t k0, int64_t o0, uint8_t *tile)
+{
+    for (int v = threadIdx.x; v < 128 * 128; v += 256) {
+        const int64_t o = o0 + (v >> 7), k = k0 + (v & 127);
+        const int8_t w = o < rows && k < cols ? src[o * cols + k] : (int8_t)0;
+        tile[(v & 127) * TB + (v >> 7)] = (uint8_t)code_byte((uint32_t)w & 3u);
+    }
+    write_code_tile(tile, wt, ld, k0, o0, cols);
 }
 
 // int8 [rows, cols] -> bf16 transposed: dst [cols, ld] with dst[c, r] = src[r, c], zeros for r in [rows, ld), ld a multiple of 64;
@@ -205,20 +212,19 @@ __device__ __forceinline__ void scale_four_rows(const uint4 *__restrict__ dY, co
     }
 }
 
-// All operands of a call's products in one launch: W_eff^T (64 rows of W x one chunk per block), transposes of int8 matrices (x~,
-// or W_eff of a pattern that has no decoder here; 64 x 128 per block) and dY / s_x (256 x four rows of eight values per
-// block).  Bound by the bytes that they move; the decoders, which wait for their LDS, run beside the streams.
+// All operands of a call's products in one launch: W_eff^T (128 rows of W x one chunk per block), the transpose of x~ (64 x 128
+// per block) and dY / s_x (256 x four rows of eight values per block).  Bound by the bytes that they move; the decoders, which wait for their LDS, run beside the streams.
 // One launch per layer for W_eff^T and one for the other two left the device in a tail seven to fourteen times per training
 // step, and a block with 256 vectors of one row quad alone left a third of its lanes idle at 2560 outputs.  us per step of a block at
 // 16384 tokens, before and now: 617 -> 462 (5.6 to 5.8 TB/s); 6912 x 2560 at 1024 tokens (6:8) 23.0 -> 17.8.
-enum OperandKind { OPERAND_UNPACK, OPERAND_TRANSPOSE, OPERAND_SCALE };
+enum OperandKind { OPERAND_UNPACK, OPERAND_CODES, OPERAND_TRANSPOSE, OPERAND_SCALE };   // W_eff^T from packed weights, from int8; x~^T; dY / s_x
 struct OperandJob {
     const void *src;
     const float *sx;
     void *dst;
-    int64_t ld;        // row length of dst (unpack, transpose)
+    int64_t ld;        // row length of dst (all but scale)
     int rows, cols;    // of src; scale: tokens and vectors of eight values per token
-    int across;        // blocks along the columns of src (unpack: chunks)
+    int across;        // blocks along the columns of src, 128 each
     int kind;
 };
 constexpr int OPERAND_JOBS_MAX = 24;
@@ -231,8 +237,7 @@ struct OperandGroup {
 template <int N, int M>   // 0, 0: no unpacking among the jobs
 __global__ void __launch_bounds__(256) operands_kernel(OperandGroup grp)
 {
-    static_assert(64 * TQ <= 128 * TP, "one LDS tile for both");
-    __shared__ __attribute__((aligned(16))) uint16_t tile[128 * TP];
+    __shared__ __attribute__((aligned(16))) uint8_t tile[128 * TB > 128 * TQ ? 128 * TB : 128 * TQ];
     int j = 0;
     while (j + 1 < grp.count && (int)blockIdx.x >= grp.block0[j + 1]) ++j;
     const OperandJob &job = grp.job[j];
@@ -255,13 +260,18 @@ __global__ void __launch_bounds__(256) operands_kernel(OperandGroup grp)
     const int across = (int)(b % job.across), down = (int)(b / job.across);
     if constexpr (N != 0) {
         if (job.kind == OPERAND_UNPACK) {
-            unpack_transpose_tile<N, M>(static_cast<const uint8_t *>(job.src), job.rows, job.cols, static_cast<uint16_t *>(job.dst), job.ld, across, 64 * down,
+            unpack_transpose_tile<N, M>(static_cast<const uint8_t *>(job.src), job.rows, job.cols, static_cast<uint8_t *>(job.dst), job.ld, across, 128 * down,
                                         tile);
             return;
         }
     }
+    if (job.kind == OPERAND_CODES) {
+        transpose_codes_tile(static_cast<const int8_t *>(job.src), job.rows, job.cols, static_cast<uint8_t *>(job.dst), job.ld, 128 * (int64_t)across,
+                             128 * (int64_t)down, tile);
+        return;
+    }
     transpose_i8_tile(static_cast<const int8_t *>(job.src), job.rows, job.cols, static_cast<uint16_t *>(job.dst), job.ld, 128 * (int64_t)across,
-                      64 * (int64_t)down, tile);
+                      64 * (int64_t)down, reinterpret_cast<uint16_t *>(tile));
 }
 
 // The jobs of a call, unpacking first (their blocks take longest), dealt out in launches of OPERAND_JOBS_MAX.
@@ -276,7 +286,7 @@ sbn_status launch_operands(const std::vector<OperandJob> &jobs, const Pattern &p
         for (int i = 0; i < grp.count; ++i) {
             const OperandJob &j = grp.job[i];
             grp.block0[i] = (int)blocks;
-            blocks += j.kind == OPERAND_SCALE ? ceil_div(ceil_div(j.rows, 4) * (int64_t)j.cols, 256) : j.across * (j.ld / 64);
+            blocks += j.kind == OPERAND_SCALE ? ceil_div(ceil_div(j.rows, 4) * (int64_t)j.cols, 256) : j.across * (j.ld / (j.kind == OPERAND_TRANSPOSE ? 64 : 128));
         }
         for (int i = grp.count; i <= OPERAND_JOBS_MAX; ++i) grp.block0[i] = (int)blocks;
         auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(256), 0, stream, grp); };
@@ -301,10 +311,10 @@ bool has_unpack(const Pattern &pat)
 // ---- bf16 GEMM -------------------------------------------------------------------------------------------
 // C[m, n] (+)= alpha * sum_k Q[m, k] * P[n, k], C bf16 [M, ldc].  P is [N, ldp] with k contiguous and K a multiple of 64
 // (the layout kernels pad it with zeros).  Q has k contiguous as well ([M, ldq], dX), or lies the other way round
-// ([k, ldq] with m contiguous, QT: dW reads dY / s_x as it lies); it may end before K: the rest of its last stage is zeroed in LDS.
+// ([k, ldq] with m contiguous, transposed: dW reads dY / s_x as it lies); it may end before K.
 // P supplies the rows of the MFMA result so that a lane ends up with four consecutive n of one C row (one 8-byte store).
 struct GemmBf16Args {
-    const uint16_t *P;
+    const void *P;        // bf16, or (not transposed) a byte per value: see bf16_dx_body
     const uint16_t *Q;
     uint16_t *C;
     const float *alpha;   // device scalar or null (= 1)
@@ -478,8 +488,9 @@ template <bool BIG> struct Bf16Tile {
     static_assert(M == N, "the two operands take turns in the slots");
 };
 
-template <bool BIG, bool QT>
-__device__ __forceinline__ void bf16_tile_body(const GemmBf16Args &g, uint8_t *dlds, int n0, int m0)
+// dW: P bf16, Q transposed.
+template <bool BIG>
+__device__ __forceinline__ void bf16_dw_body(const GemmBf16Args &g, uint8_t *dlds, int n0, int m0)
 {
     using S = Bf16Tile<BIG>;
     constexpr int WP = S::WP, WQ = S::WQ;
@@ -491,35 +502,32 @@ __device__ __forceinline__ void bf16_tile_body(const GemmBf16Args &g, uint8_t *d
     const int nk = g.K / GD_K;
     const float alpha = g.alpha ? *g.alpha : 1.0f;   // here it is a scalar load: in front of everything that writes memory
 
-    // DMA roles, four instructions per operand and wavefront.  k contiguous: one instruction fills 8 rows x 128 bytes (lane l:
-    // row l / 8, slot l % 8 holding global column slot ^ ((row >> 1) & 7)).  Transposed Q: a stage is 64 k rows of M values,
+    // DMA roles, four instructions per operand and wavefront.  P: one instruction fills 8 rows x 128 bytes (lane l:
+    // row l / 8, slot l % 8 holding global column slot ^ ((row >> 1) & 7)).  Q: a stage is 64 k rows of M values,
     // one instruction fills 1024 bytes of them, slot s of row k holds the eight values of granule s ^ f(k),
     // f = 4 (k & 3) | 2 ((k >> 2) & 1): the four k rows that a transposing read of 16 lanes takes lie in different banks.
     // Operands are buffers: rows and k rows past the matrix, and stages past the last, read as zeros and fetch nothing.
-    constexpr int QROW = S::M * 2;                        // bytes of a k row of the transposed stage
+    constexpr int QROW = S::M * 2;                        // bytes of a k row of a stage
     const int kleft = g.kq - (nk - 1) * GD_K;             // k of the last stage that Q has
-    const int prows = g.N - n0 < S::N ? g.N - n0 : S::N, qrows = g.M - m0 < S::M ? g.M - m0 : S::M;
+    const int prows = g.N - n0 < S::N ? g.N - n0 : S::N;
     const uint32_t ppitch = 2u * (uint32_t)g.ldp;
     const uint32_t qpitch = 2u * (uint32_t)g.ldq, pbytes = (uint32_t)prows * ppitch;
-    const uint32_t qbytes = QT ? GD_K * qpitch - 2u * (uint32_t)m0 : (uint32_t)qrows * qpitch;        // of a transposed stage: up to the end of its rows
-    const uint32_t qbytes_last = QT ? (uint32_t)kleft * qpitch - 2u * (uint32_t)m0 : qbytes;
-    v4i pbuffer = buffer_of(g.P + (int64_t)n0 * g.ldp, pbytes);
-    v4i qbuffer = buffer_of(QT ? g.Q + m0 : g.Q + (int64_t)m0 * g.ldq, nk > 1 ? qbytes : qbytes_last);
-    uint32_t pat = 0, qat = 0;                            // k contiguous: bytes into a row
+    const uint32_t qbytes = GD_K * qpitch - 2u * (uint32_t)m0, qbytes_last = (uint32_t)kleft * qpitch - 2u * (uint32_t)m0;   // of a stage: up to the end of its rows
+    v4i pbuffer = buffer_of(static_cast<const uint16_t *>(g.P) + (int64_t)n0 * g.ldp, pbytes);
+    v4i qbuffer = buffer_of(g.Q + m0, nk > 1 ? qbytes : qbytes_last);
+    uint32_t pat = 0;                                     // bytes into a row of P
+    uint64_t qstep = (uint64_t)g.ldq * (GD_K * 2);
+    asm volatile("" : "+s"(qstep));                       // in a register: loaded again in every step it would be waited for with all LDS reads
     uint32_t poff[4], qoff[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int row = 32 * wave + 8 * i + (lane >> 3);
         const int col = (lane & 7) ^ ((row >> 1) & 7);
         poff[i] = (uint32_t)row * ppitch + 16u * col;
-        if constexpr (QT) {
-            constexpr int GPR = S::M / 8, RPI = 64 / GPR;      // granules of a k row, k rows per instruction
-            const int k = RPI * (4 * wave + i) + lane / GPR;
-            const int gran = (lane % GPR) ^ (4 * (k & 3) | 2 * ((k >> 2) & 1));
-            qoff[i] = (uint32_t)k * qpitch + 16u * gran;
-        } else {
-            qoff[i] = (uint32_t)row * qpitch + 16u * col;
-        }
+        constexpr int GPR = S::M / 8, RPI = 64 / GPR;          // granules of a k row, k rows per instruction
+        const int k = RPI * (4 * wave + i) + lane / GPR;
+        const int gran = (lane % GPR) ^ (4 * (k & 3) | 2 * ((k >> 2) & 1));
+        qoff[i] = (uint32_t)k * qpitch + 16u * gran;
     }
     // the four instructions of a wavefront and slot one by one, so that they can stand between matrix instructions; the fourth moves
     // the operand on to its next stage, kt + 1
@@ -530,51 +538,32 @@ __device__ __forceinline__ void bf16_tile_body(const GemmBf16Args &g, uint8_t *d
         pbuffer[2] = kt + 1 < nk ? (int)pbytes : 0;
     };
     auto dma_q = [&](const int kt, const uint32_t slot, const int i) {
-        lds_dma16_buffer(qbuffer, qoff[i], QT ? 0 : qat, lds0 + slot + wave * 4096 + i * 1024);
+        lds_dma16_buffer(qbuffer, qoff[i], 0, lds0 + slot + wave * 4096 + i * 1024);
         if (i < 3) return;
-        if constexpr (QT) {
-            const uint64_t base = ((uint64_t)(uint32_t)qbuffer[1] << 32 | (uint32_t)qbuffer[0]) + (uint64_t)g.ldq * (GD_K * 2);
-            qbuffer[0] = (int)(uint32_t)base;
-            qbuffer[1] = (int)(uint32_t)(base >> 32);
-        } else {
-            qat += GD_K * 2;
-        }
+        const uint64_t base = ((uint64_t)(uint32_t)qbuffer[1] << 32 | (uint32_t)qbuffer[0]) + qstep;
+        qbuffer[0] = (int)(uint32_t)base;
+        qbuffer[1] = (int)(uint32_t)(base >> 32);
         qbuffer[2] = kt + 2 < nk ? (int)qbytes : kt + 2 == nk ? (int)qbytes_last : 0;
     };
-    // k of the last stage past the end of a row of Q: what was fetched in their place is the next row, which may be infinite, and zeros
-    // of P do not cancel that (k rows past the end of a transposed Q are zeros already).
-    // A lane overwrites what it asked for itself, behind its own wait and in front of the barrier that publishes the stage.
-    auto zero_tail = [&](const uint32_t slot) {
-        typedef __attribute__((address_space(3))) v4i *lds_v4i;
-        asm volatile("" ::: "memory");   // not in front of the wait
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int k = 8 * ((lane & 7) ^ (((32 * wave + 8 * i + (lane >> 3)) >> 1) & 7));
-            if (k >= kleft) *(lds_v4i)(uintptr_t)(lds0 + slot + wave * 4096 + i * 1024 + 16 * lane) = v4i{0, 0, 0, 0};
-        }
-    };
-    // LDS read addresses: k contiguous: row * 128 + 16 * ((2u + c) ^ ((row >> 1) & 7)); (row >> 1) & 7 = (r >> 1) & 7 for every
-    // tile of the wavefront, so one lane address per u, tiles are immediate offsets; the addresses move on with the slot.  Transposed: lane l of a
+    // LDS read addresses: P: row * 128 + 16 * ((2u + c) ^ ((row >> 1) & 7)); (row >> 1) & 7 = (r >> 1) & 7 for every
+    // tile of the wavefront, so one lane address per u, tiles are immediate offsets; the addresses move on with the slot.  Q: lane l of a
     // group of 16 supplies the address of row k0 + (l >> 2), columns 4 (l & 3) .. + 3 and gets four k of column l; two
     // reads (h = 0, 1) make the eight k of a fragment.
-    uint32_t pa[4], qa[4];
+    uint32_t pa[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
         const int slot = (2 * u + c) ^ ((r >> 1) & 7);
         pa[u] = lds0 + (wn * 32 * WP + r) * 128 + 16 * slot;
-        if constexpr (!QT) qa[u] = lds0 + S::SLOT + (wm * 32 * WQ + r) * 128 + 16 * slot;
     }
     uint32_t qt[WQ][2];
-    if constexpr (QT) {
-        const int rr = (lane & 15) >> 2;
+    const int rr = (lane & 15) >> 2;
 #pragma unroll
-        for (int b = 0; b < WQ; ++b)
+    for (int b = 0; b < WQ; ++b)
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int gran = (wm * 32 * WQ + 32 * b) / 8 + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);
-                qt[b][h] = lds0 + S::SLOT + (8 * c + 4 * h + rr) * QROW + 16 * (gran ^ (4 * rr | 2 * h)) + 8 * (lane & 1);
-            }
-    }
+        for (int h = 0; h < 2; ++h) {
+            const int gran = (wm * 32 * WQ + 32 * b) / 8 + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);
+            qt[b][h] = lds0 + S::SLOT + (8 * c + 4 * h + rr) * QROW + 16 * (gran ^ (4 * rr | 2 * h)) + 8 * (lane & 1);
+        }
     typedef __attribute__((address_space(3))) const v8bf *lds_v8bf;
     typedef __bf16 v4bf __attribute__((ext_vector_type(4)));
     typedef __attribute__((address_space(3))) v4bf *lds_v4bf;
@@ -588,17 +577,15 @@ __device__ __forceinline__ void bf16_tile_body(const GemmBf16Args &g, uint8_t *d
             for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.0f;
 
     v8bf fp[2][WP], fq[2][WQ];
-    constexpr int READS = WP + (QT ? 2 : 1) * WQ;         // LDS reads of a quarter step
+    constexpr int READS = WP + 2 * WQ;         // LDS reads of a quarter step
     auto read_one = [&](const int u, const int i) {
         const int set = u & 1;
         if (i < WP) {
             fp[set][i] = *(lds_v8bf)(uintptr_t)(pa[u] + i * 32 * 128);
-        } else if constexpr (QT) {
+        } else {
             const int b = (i - WP) >> 1, h = (i - WP) & 1;
             const v4bf v = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_v4bf)(uintptr_t)(qt[b][h] + 16 * u * QROW));
             if (h == 0) fq[set][b].lo = v; else fq[set][b].hi = v;
-        } else {
-            fq[set][i - WP] = *(lds_v8bf)(uintptr_t)(qa[u] + (i - WP) * 32 * 128);
         }
     };
     // byte offset of the slot two further on in the ring
@@ -623,8 +610,9 @@ __device__ __forceinline__ void bf16_tile_body(const GemmBf16Args &g, uint8_t *d
     };
     // The slots are a ring in the order P(0), Q(0), P(1), Q(1), ...  Step kt: quarters 0 to 2 read the fragments of the next
     // quarter under their matrix instructions; then stage kt + 1 must have landed and every wavefront holds the last fragments of
-    // stage kt, so behind the barrier the last quarter reads the first fragments of stage kt + 1 and asks for Q(kt + 2) and
-    // P(kt + 3) in the two slots just left.
+    // stage kt, so behind the barrier the last quarter reads the first fragments of stage kt + 1 and asks for Q(kt + 2) in the slot of
+    // P(kt), and the first two quarters of the next step for P(kt + 3) in that of Q(kt): all of them in one quarter are more
+    // than a multiprocessor's input path takes in.
 #pragma unroll
     for (int j = 0; j < 4; ++j)
 #pragma unroll
@@ -633,7 +621,6 @@ __device__ __forceinline__ void bf16_tile_body(const GemmBf16Args &g, uint8_t *d
             else dma_p(j >> 1, j * S::SLOT, i);
         }
     SBN_WAIT_VMCNT(8);
-    if (!QT && nk == 1 && kleft < GD_K) zero_tail(S::SLOT);
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < READS; ++i) read_one(0, i);
@@ -641,26 +628,18 @@ __device__ __forceinline__ void bf16_tile_body(const GemmBf16Args &g, uint8_t *d
     for (int kt = 0; kt < nk; ++kt) {
         const uint32_t sp_next = advance(sp), sq_next = advance(sq);
         const uint32_t free = advance(sp_next);   // of Q(kt - 1)
-        constexpr int PQ[3] = {2, 2, 0};   // requests for P(kt + 2) in the quarters
 #pragma unroll
         for (int u = 0; u < 3; ++u)
             quarter(u, [&](const int s) {
                 spread(s, READS, [&](const int k) { read_one(u + 1, k); });
-                const int first = u == 0 ? 0 : u == 1 ? PQ[0] : PQ[0] + PQ[1];
-                if (PQ[u] > 0) spread(s, PQ[u], [&](const int k) { dma_p(kt + 2, free, first + k); });
+                if (u < 2) spread(s, 2, [&](const int k) { dma_p(kt + 2, free, 2 * u + k); });
             });
         SBN_WAIT_VMCNT(4);   // P(kt + 2) may fly
-        if (!QT && kt == nk - 2 && kleft < GD_K) zero_tail(sq_next);
         __syncthreads();
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            pa[u] += sp_next - sp;
-            if constexpr (!QT) qa[u] += sq_next - sq;
-        }
-        if constexpr (QT) {
+        for (int u = 0; u < 4; ++u) pa[u] += sp_next - sp;
 #pragma unroll
-            for (int b = 0; b < WQ; ++b) { qt[b][0] += sq_next - sq; qt[b][1] += sq_next - sq; }
-        }
+        for (int b = 0; b < WQ; ++b) { qt[b][0] += sq_next - sq; qt[b][1] += sq_next - sq; }
         quarter(3, [&](const int s) {
             spread(s, READS, [&](const int k) { read_one(0, k); });
             spread(s, 4, [&](const int k) { dma_q(kt + 2, sp, k); });
@@ -669,6 +648,185 @@ __device__ __forceinline__ void bf16_tile_body(const GemmBf16Args &g, uint8_t *d
         sq = sq_next;
     }
     SBN_WAIT_VMCNT(0);   // the surplus stages have landed
+    __syncthreads();
+    bf16_wave_epilogue<WP, WQ>(g, acc, alpha, dlds + wave * S::STAGING, n0 + wn * 32 * WP, m0 + wm * 32 * WQ, lane);
+}
+
+// dX: P holds a byte per value, the high half of a bf16 (see write_code_tile): half the bytes of a stage to bring and to read, and a
+// register of two values is one byte permutation, four for the eight of a fragment.  What bounds the product is the power the board
+// holds (the matrix instructions take 85 % of the cycles, at 1.6 GHz), and of that the operands' way through the L2 and LDS is
+// the part that can be saved.
+// A slot of P lasts for two stages (rows of 128 bytes), of Q for one: two slots of P and three of Q.  P(j) serves the stages 2j and
+// 2j + 1.  Half c of the lanes multiplies in quarter u the eight k at 32 (u / 2) + 16 c + 8 (u & 1), so that the bytes of two quarters
+// are one read of 16.
+template <bool BIG>
+__device__ __forceinline__ void bf16_dx_body(const GemmBf16Args &g, uint8_t *dlds, int n0, int m0)
+{
+    using S = Bf16Tile<BIG>;
+    constexpr int WP = S::WP, WQ = S::WQ;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wn = wave & 1, wm = wave >> 1;
+    const int r = lane & 31, c = lane >> 5;
+    const uint32_t lds0 = lds_address(dlds);
+    const int nk = g.K / GD_K;
+    const float alpha = 2.0f * (g.alpha ? *g.alpha : 1.0f);   // a scalar load: in front of everything that writes memory
+
+    // DMA roles, four instructions per slot and wavefront: one fills 8 rows x 128 bytes (lane l: row l / 8, slot l % 8 holding global column
+    // slot ^ ((row >> 1) & 7)).  Rows past the matrix and stages past the last read as zeros and fetch nothing.
+    const int kleft = g.kq - (nk - 1) * GD_K;             // k of the last stage that Q has
+    const int prows = g.N - n0 < S::N ? g.N - n0 : S::N, qrows = g.M - m0 < S::M ? g.M - m0 : S::M;
+    const uint32_t ppitch = (uint32_t)g.ldp, qpitch = 2u * (uint32_t)g.ldq;
+    const uint32_t pbytes = (uint32_t)prows * ppitch, qbytes = (uint32_t)qrows * qpitch;
+    v4i pbuffer = buffer_of(static_cast<const uint8_t *>(g.P) + (int64_t)n0 * g.ldp, pbytes);
+    v4i qbuffer = buffer_of(g.Q + (int64_t)m0 * g.ldq, qbytes);
+    uint32_t at = 0, qat = 0;                             // bytes into a row of P and Q
+    uint32_t poff[4], qoff[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int row = 32 * wave + 8 * i + (lane >> 3), col = (lane & 7) ^ ((row >> 1) & 7);
+        poff[i] = (uint32_t)row * ppitch + 16u * col;
+        qoff[i] = (uint32_t)row * qpitch + 16u * col;
+    }
+    constexpr uint32_t QRING = 2 * S::SLOT;               // slots 0, 1: P; 2, 3, 4: Q
+    // the instructions of a wavefront and slot one by one; the fourth moves the operand on
+    auto dma_p = [&](const int slot, const int i) {
+        lds_dma16_buffer(pbuffer, poff[i], at, lds0 + slot * S::SLOT + wave * 4096 + i * 1024);
+        if (i < 3) return;
+        at += 128;
+        pbuffer[2] = at < ppitch ? (int)pbytes : 0;
+    };
+    auto dma_q = [&](const uint32_t ring, const int i) {
+        lds_dma16_buffer(qbuffer, qoff[i], qat, lds0 + QRING + ring + wave * 4096 + i * 1024);
+        if (i < 3) return;
+        qat += 128;
+        qbuffer[2] = qat < 128u * nk ? (int)qbytes : 0;
+    };
+    // k of the last stage past the end of a row of Q: what was fetched in their place is the next row, which may be infinite, and zeros
+    // of P do not cancel that.
+    // A lane overwrites what it asked for itself, behind its own wait and in front of the barrier that publishes the stage.
+    auto zero_tail = [&](const uint32_t slot) {
+        typedef __attribute__((address_space(3))) v4i *lds_v4i;
+        asm volatile("" ::: "memory");   // not in front of the wait
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int k = 8 * ((lane & 7) ^ (((32 * wave + 8 * i + (lane >> 3)) >> 1) & 7));
+            if (k >= kleft) *(lds_v4i)(uintptr_t)(lds0 + slot + wave * 4096 + i * 1024 + 16 * lane) = v4i{0, 0, 0, 0};
+        }
+    };
+    // LDS read addresses: row * 128 + 16 * (granule ^ ((row >> 1) & 7)); (row >> 1) & 7 = (r >> 1) & 7 for every tile of the wavefront, so
+    // tiles are immediate offsets.  P: [stage parity][quarter / 2], Q: [quarter], moving on with the slots
+    uint32_t pa[2][2], qa[4];
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+#pragma unroll
+        for (int v = 0; v < 2; ++v) pa[e][v] = lds0 + (wn * 32 * WP + r) * 128 + 16 * ((4 * e + 2 * v + c) ^ ((r >> 1) & 7));
+#pragma unroll
+    for (int u = 0; u < 4; ++u) qa[u] = lds0 + QRING + (wm * 32 * WQ + r) * 128 + 16 * ((4 * (u >> 1) + 2 * c + (u & 1)) ^ ((r >> 1) & 7));
+    typedef unsigned v4u __attribute__((ext_vector_type(4)));
+    typedef __attribute__((address_space(3))) const v4u *lds_v4u;
+    typedef __attribute__((address_space(3))) const v8bf *lds_v8bf;
+
+    v16f acc[WP][WQ];
+#pragma unroll
+    for (int a = 0; a < WP; ++a)
+#pragma unroll
+        for (int b = 0; b < WQ; ++b)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.0f;
+
+    v4u raw[2][WP];                 // [quarter / 2][tile]: bytes of two quarters
+    v8bf fp[2], fq[2][WQ];          // fragments of the tile at hand and of the next
+    auto widen = [&](const int u, const int a) {   // eight bytes to bf16
+        const uint32_t w0 = raw[u >> 1][a][2 * (u & 1)], w1 = raw[u >> 1][a][2 * (u & 1) + 1];
+        return __builtin_bit_cast(v8bf, v4u{__builtin_amdgcn_perm(w0, w0, 0x010c000cu), __builtin_amdgcn_perm(w0, w0, 0x030c020cu),
+                                            __builtin_amdgcn_perm(w1, w1, 0x010c000cu), __builtin_amdgcn_perm(w1, w1, 0x030c020cu)});
+    };
+    uint32_t pslot = 0, qring = 0;  // bytes to the slots of the stage at hand
+    auto read_p = [&](const int e, const int v, const int a) { raw[v][a] = ((lds_v4u)(uintptr_t)pa[e][v])[a * 32 * 128 / 16]; };
+    auto read_q = [&](const int u, const int b) { fq[u & 1][b] = ((lds_v8bf)(uintptr_t)qa[u])[b * 32 * 128 / 16]; };
+    constexpr int SLOTS = WP * WQ;
+    // A quarter step: WP x WQ matrix instructions; side(s) is issued after instruction s, and the next tile's bytes are widened there.
+    auto quarter = [&](const int u, auto &&side) {
+#pragma unroll
+        for (int s = 0; s < SLOTS; ++s) {
+            const int a = s / WQ, b = s % WQ;
+            acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fp[a & 1], fq[u & 1][b], acc[a][b], 0, 0, 0);
+            side(s);
+            // (of the next quarter's first tile behind this quarter's last instruction but one: its bytes have long been there, or
+            // were read a quarter ago)
+            if (b == 0 && a + 1 < WP) fp[(a + 1) & 1] = widen(u, a + 1);
+            if (b == 0 && a + 1 == WP) fp[(a + 1) & 1] = widen((u + 1) & 3, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    auto spread = [&](const int s, const int n, auto &&op) {
+#pragma unroll
+        for (int k = 0; k < n; ++k)
+            if (k * SLOTS / n == s) op(k);
+    };
+    static_assert(WP % 2 == 0, "a quarter ends on the set of fragments that the next begins with");
+    // Step kt of parity e: quarters 0 to 2 read the fragments of the next quarter (P: of two quarters) under their matrix instructions;
+    // then stage kt + 1 must have landed and every wavefront holds the last fragments of stage kt, so behind the barrier the last
+    // quarter reads the first fragments of stage kt + 1.  The slot of Q(kt) takes Q(kt + 3), asked for in the last quarter and the
+    // first of the next step; the slot of P(kt / 2), after an odd kt, P(kt / 2 + 2) in the next step's second and third.
+    // Requests in flight at the wait behind Q(kt + 1): Q(kt + 2) and one P; behind the P that an even stage begins: Q(kt + 2).
+    auto step = [&](const int kt, const int e) {
+        quarter(0, [&](const int s) {
+            spread(s, WQ, [&](const int k) { read_q(1, k); });
+            spread(s, WP, [&](const int k) { read_p(e, 1, k); });
+            spread(s, 2, [&](const int k) { dma_q(qring >= S::SLOT ? qring - S::SLOT : 2u * S::SLOT, 2 + k); });
+        });
+        quarter(1, [&](const int s) {
+            spread(s, WQ, [&](const int k) { read_q(2, k); });
+            if (e == 0) spread(s, 2, [&](const int k) { dma_p(pslot ? 0 : 1, k); });
+        });
+        quarter(2, [&](const int s) {
+            spread(s, WQ, [&](const int k) { read_q(3, k); });
+            if (e == 0) spread(s, 2, [&](const int k) { dma_p(pslot ? 0 : 1, 2 + k); });
+        });
+        if (e == 0) SBN_WAIT_VMCNT(8); else SBN_WAIT_VMCNT(4);
+        const uint32_t left = qring;
+        qring = qring < 2u * S::SLOT ? qring + S::SLOT : 0;
+        if (kt == nk - 2 && kleft < GD_K) zero_tail(QRING + qring);
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < 4; ++u) qa[u] += qring - left;
+        if (e == 1) {
+            const uint32_t other = pslot ? 0u : (uint32_t)S::SLOT;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) pa[i >> 1][i & 1] += other - pslot;
+            pslot = other;
+        }
+        quarter(3, [&](const int s) {
+            spread(s, WQ, [&](const int k) { read_q(0, k); });
+            spread(s, WP, [&](const int k) { read_p(e ^ 1, 0, k); });
+            spread(s, 2, [&](const int k) { dma_q(left, k); });
+        });
+    };
+#pragma unroll
+    for (int i = 0; i < 4; ++i) dma_p(0, i);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) dma_q(0, i);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) dma_q(S::SLOT, i);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) dma_q(2 * S::SLOT, i);
+    SBN_WAIT_VMCNT(6);
+    if (nk == 1 && kleft < GD_K) zero_tail(QRING);
+    __syncthreads();
+#pragma unroll
+    for (int a = 0; a < WP; ++a) read_p(0, 0, a);
+#pragma unroll
+    for (int b = 0; b < WQ; ++b) read_q(0, b);
+    fp[0] = widen(0, 0);
+    int kt = 0;
+    for (; kt + 2 <= nk; kt += 2) {
+        step(kt, 0);
+        step(kt + 1, 1);
+    }
+    if (kt < nk) step(kt, 0);
+    SBN_WAIT_VMCNT(0);   // requests past the last stage deposit zeros
     __syncthreads();
     bf16_wave_epilogue<WP, WQ>(g, acc, alpha, dlds + wave * S::STAGING, n0 + wn * 32 * WP, m0 + wm * 32 * WQ, lane);
 }
@@ -682,8 +840,8 @@ __global__ void __launch_bounds__(64 * Bf16Tile<BIG>::WAVES) gemm_bf16_kernel(Ge
     int tn, tm;
     if (!bf16_tile_of_block(g, (int)blockIdx.x - grp.block0[prob], tn, tm)) return;
     const int n0 = tn * Bf16Tile<BIG>::N, m0 = tm * Bf16Tile<BIG>::M;
-    if (g.transposed) bf16_tile_body<BIG, true>(g, dlds, n0, m0);
-    else bf16_tile_body<BIG, false>(g, dlds, n0, m0);
+    if (g.transposed) bf16_dw_body<BIG>(g, dlds, n0, m0);
+    else bf16_dx_body<BIG>(g, dlds, n0, m0);
 }
 
 template <bool BIG>
@@ -773,7 +931,7 @@ sbn_status launch_backward_grouped(int count, const BackwardItem *items, const P
         const BackwardItem &it = items[i];
         const int64_t tokens = it.tokens, d_in = it.d_in, d_out = it.d_out;
         uint8_t *ws = static_cast<uint8_t *>(it.workspace);
-        uint16_t *wt = reinterpret_cast<uint16_t *>(ws);
+        uint8_t *wt = ws;   // a byte per weight in rows of whole 128, which the region for 2 bytes in rows of whole 64 holds
         ws += align_up((size_t)d_in * pad64(d_out) * 2, 256);
         int8_t *w8 = reinterpret_cast<int8_t *>(ws);
         ws += align_up((size_t)d_out * d_in, 256);
@@ -785,19 +943,19 @@ sbn_status launch_backward_grouped(int count, const BackwardItem *items, const P
         const uint16_t *dy = static_cast<const uint16_t *>(it.dY);
 
         if (it.dX) {
-            const int64_t ldw = pad64(d_out);
+            const int64_t ldw = ceil_div(d_out, 128) * 128;
             if (has_unpack(pat)) {
                 jobs.push_back({it.packed, nullptr, wt, ldw, (int)d_out, (int)d_in, (int)ceil_div(d_in, CHUNK), OPERAND_UNPACK});
             } else {
                 st = launch_expand_groups(it.packed, d_out, d_in, pat, w8, stream);
                 if (st != SBN_OK) return st;
-                jobs.push_back({w8, nullptr, wt, ldw, (int)d_out, (int)d_in, (int)ceil_div(d_in, 128), OPERAND_TRANSPOSE});
+                jobs.push_back({w8, nullptr, wt, ldw, (int)d_out, (int)d_in, (int)ceil_div(d_in, 128), OPERAND_CODES});
             }
             // dX[t, k] = gamma * sum_o dY[t, o] * W_eff^T[k, o]
             GemmBf16Args a{};
             a.P = wt; a.ldp = ldw; a.N = (int)d_in;
             a.Q = dy; a.ldq = d_out; a.M = (int)tokens; a.kq = (int)d_out;
-            a.K = (int)ldw;
+            a.K = (int)pad64(d_out);
             a.C = static_cast<uint16_t *>(it.dX); a.ldc = d_in; a.alpha = it.gamma;
             products.push_back(a);
         }

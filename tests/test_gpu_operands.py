@@ -84,3 +84,17 @@ def test_transposed_weights(N, M, d_out, d_in):
     dX = torch.full((d_out, d_in), float("nan"), dtype=torch.bfloat16, device=DEV)
     backward(dY, packed, gamma, torch.zeros(d_out, d_in, dtype=torch.int8, device=DEV), torch.ones(d_out, device=DEV), N, M, dX=dX)
     assert torch.equal(dX.float().cpu(), (torch.from_numpy(Weff).float() * gamma.cpu()).to(torch.bfloat16).float())
+
+
+@pytest.mark.parametrize("N,M", [(2, 4), (3, 4)])
+@pytest.mark.parametrize("d_out", [56, 64, 120, 136, 192, 200, 256, 264, 320, 392, 520])
+def test_weights_of_every_stage(N, M, d_out):
+    # one to nine stages of 64: a slot of weights lasts for two of them, of gradients for one; the last is whole or ends within a vector
+    d_in = 144
+    W = sbn_synth.latent_weight(d_out, d_in, 1300 + d_out)
+    packed, gamma = hip_pack(W, N, M)
+    _, _, Weff, _ = oracle_pack(W, N, M)
+    dY = torch.eye(d_out, dtype=torch.bfloat16, device=DEV)
+    dX = torch.full((d_out, d_in), float("nan"), dtype=torch.bfloat16, device=DEV)
+    backward(dY, packed, gamma, torch.zeros(d_out, d_in, dtype=torch.int8, device=DEV), torch.ones(d_out, device=DEV), N, M, dX=dX)
+    assert torch.equal(dX.float().cpu(), (torch.from_numpy(Weff).float() * gamma.cpu()).to(torch.bfloat16).float())
