@@ -726,13 +726,23 @@ __global__ void __launch_bounds__(64 * sp::NW) gemm_smfmac_kernel(Group grp, Tab
     if constexpr (sizeof(Table) == sizeof(PieceTableNone)) {
         // Decode batches (every problem at most 16 token units): a piece = (problem, row tile, a share of the token
         // units of at most tab.piece[0] = 4, 2 or 1: the widest that still gives every multiprocessor a piece), in that
-        // order, -per_block pieces in all; block b runs a contiguous run of them, so the pieces of a row tile that has
-        // more than one follow each other on one multiprocessor while its weights are still in L2.  Dealing token
-        // units to XCDs, as below, would leave most XCDs without work here.
-        const int P = -tab.per_block, nbk = (int)gridDim.x, b = (int)blockIdx.x, wmax = (int)tab.piece[0];
-        const int q = P / nbk, rem = P % nbk;
-        int f = b * q + (b < rem ? b : rem);
-        const int end = f + q + (b < rem ? 1 : 0);
+        // order, -per_block pieces in all.  XCD x runs the x-th of eight contiguous runs of them, as long as its share
+        // of the blocks, and deals it to its blocks in contiguous runs, so the pieces of a row tile that has more than
+        // one run side by side or one behind the other on one XCD, and its L2 fetches the tile's weights once.  With
+        // run b for block b they sit on as many XCDs, each of which fetches them: 2560 -> 6912 took 13.95 us at 256
+        // tokens and 14.56 at 512, now 12.60 and 13.60; twice that in one launch at 512 tokens 31.0, now 23.1; eight
+        // layers of 2560 -> 2560 at 256 tokens 26.9, now 24.1 (dense codes, twice 6912 at 512: 33.3, now 28.8).  A tile
+        // of one piece gains nothing and loses nothing (100 tokens: 12.2).  Dealing token units to XCDs, as below,
+        // would leave most XCDs without work here.
+        const int P = -tab.per_block, nbk = (int)gridDim.x, wmax = (int)tab.piece[0];
+        const int x = (int)blockIdx.x & 7, j = (int)blockIdx.x >> 3, b8 = nbk >> 3, more8 = nbk & 7;
+        const int before = x * b8 + (x < more8 ? x : more8), mine = b8 + (x < more8 ? 1 : 0);   // blocks of lower XCDs, of this one
+        const int whole = P / nbk, part = P % nbk;
+        const int run = whole * before + part * before / nbk;
+        const int len = whole * (before + mine) + part * (before + mine) / nbk - run;
+        const int q = len / mine, rem = len % mine;
+        int f = run + j * q + (j < rem ? j : rem);
+        const int end = f + q + (j < rem ? 1 : 0);
         int prob = 0, base = 0, parity = 0;
         auto piece_at = [&](int &f) {
             if (f >= end) return none;
