@@ -279,7 +279,6 @@ struct Stream {
     v4i tokens, weights;
     uint32_t token_at, weight_at;   // bytes into a row
     int ts, ps;                     // ring slots of the next piece's first stage and pair
-    bool wide;                      // the piece has more than 64 tokens: two instructions per stage
     bool landed;                    // everything asked for so far
 };
 
@@ -327,7 +326,7 @@ __device__ __forceinline__ void start_stream(Stream &st, const GemmArgs &g, cons
     const uint32_t K = (uint32_t)g.d_in, pitch = K / KSTEP * 32;
     st.tokens = token_buffer(g, p);
     st.weights = weight_buffer(g, p);
-    st.wide = p.tb > 2;
+    const bool wide = token_dma(p.tb) > 1;
     const uint32_t xoff = token_offset(g.d_in, wave, lane), woff = weight_offset(g.d_in, wave, lane);
     auto pair = [&](const int s) {
         const uint32_t slot = (uint32_t)(st.ps + s) % NWP;
@@ -340,7 +339,7 @@ __device__ __forceinline__ void start_stream(Stream &st, const GemmArgs &g, cons
         const uint32_t slot = (uint32_t)(st.ts + s) % NST;
         const v4i buffer = (uint32_t)KSTEP * s < K ? st.tokens : no_buffer();
         lds_dma16_buffer(buffer, xoff, (uint32_t)KSTEP * s, lds0 + slot * TSTAGE + wave * 1024);
-        if (st.wide) lds_dma16_buffer(buffer, xoff, (uint32_t)KSTEP * s + 64u * K, lds0 + slot * TSTAGE + (NW + wave) * 1024);
+        if (wide) lds_dma16_buffer(buffer, xoff, (uint32_t)KSTEP * s + 64u * K, lds0 + slot * TSTAGE + (NW + wave) * 1024);
     };
     // the order in which the iterations in front of the first would have asked
 #pragma unroll
@@ -391,22 +390,22 @@ __device__ __forceinline__ void piece_body(const Group &grp, const Piece &p, con
     const int nchunks = g.d_in / KSTEP;
     const int o0 = to * ROWS;
 
-    // ---- requests: at the end of the piece the stream goes on with the next one, where that has rows of the same length; otherwise
-    // it is started anew behind the main loop, and until then asks for nothing
+    // ---- requests: at the end of the piece the stream goes on with the next one, where that has rows of the same length and needs
+    // no more instructions per stage (whether it does is not asked between the matrix instructions: that branch cost 90 cycles per
+    // chunk, 12.8 us against 11.7 at 777 tokens, 2560 -> 2560); otherwise it is started anew behind the main loop, and until
+    // then asks for nothing
     const uint32_t K = (uint32_t)g.d_in, pitch = K / KSTEP * 32;
     const uint32_t xoff = token_offset(g.d_in, wave, lane), woff = weight_offset(g.d_in, wave, lane);
-    const bool goes_on = next.tb > 0 && grp.g[next.prob].d_in == g.d_in && nchunks >= NST && nchunks > 2 * (NWP - 1);
+    const bool goes_on = next.tb > 0 && token_dma(next.tb) <= NDT && grp.g[next.prob].d_in == g.d_in && nchunks >= NST && nchunks > 2 * (NWP - 1);
     const v4i next_tokens = goes_on ? token_buffer(grp.g[next.prob], next) : no_buffer();
     const v4i next_weights = goes_on ? weight_buffer(grp.g[next.prob], next) : no_buffer();
     auto request_tokens = [&](const int slot, const int i) {   // instruction i of NDT
         if (i == 0) {   // selections: a branch would part the instructions around it
             const bool turn = st.token_at >= K;
             st.tokens = turn ? next_tokens : st.tokens;
-            st.wide = turn ? next.tb > 2 : st.wide;
             st.token_at = turn ? 0 : st.token_at;
         }
         lds_dma16_buffer(st.tokens, xoff, st.token_at + 64u * i * K, lds0 + slot * TSTAGE + (NW * i + wave) * 1024);
-        if (NDT == 1 && st.wide) lds_dma16_buffer(st.tokens, xoff, st.token_at + 64u * K, lds0 + slot * TSTAGE + (NW + wave) * 1024);
         if (i == NDT - 1) st.token_at += KSTEP;
     };
     auto request_weights = [&](const int slot, const int i) {   // instruction i of NDW
@@ -592,7 +591,7 @@ __device__ __forceinline__ void piece_body(const Group &grp, const Piece &p, con
     st.ps = ps;
     if (next.tb > 0 && !goes_on) start_stream(st, grp.g[next.prob], next, lds0, wave, lane);
 
-    // ---- epilogue: rescale, transpose through the wavefront's staging area (a tile of 32 tokens x 32 rows of fp32 at a time) and
+    // ---- epilogue: rescale, transpose through the wavefront's staging area (4 KB of fp32 at a time) and
     // write whole lines with streaming stores (Y is not read again here and must not push the operands out
     // of L2; per-lane stores of 32 contiguous bytes measured 1.5x the write traffic); ragged edges and the int32
     // accumulator output store per lane.
@@ -623,56 +622,101 @@ __device__ __forceinline__ void piece_body(const Group &grp, const Piece &p, con
         if (fast_store) {
             int8_t *const est = lds + RING_BYTES + wave * STG_WAVE;
             const bool has_bias = g.bias != nullptr;
-            v4f bias4[RA];
-#pragma unroll
-            for (int a = 0; a < RA; ++a)
-                bias4[a] = has_bias ? *reinterpret_cast<const v4f *>(g.bias + orow + 32 * a + 4 * (lane & 7)) : v4f{0.f, 0.f, 0.f, 0.f};
             // tokens past the matrix lie past the end of the buffer, where stores are dropped
             const int64_t first = (int64_t)t0 * g.d_out + orow;
             const uint32_t pitch = 4u * (uint32_t)g.d_out;
             const auto out = __builtin_amdgcn_make_buffer_rsrc(g.Y + first, (short)0, (int)((uint32_t)(g.tokens - t0 < 32 * TB ? g.tokens - t0 : 32 * TB) * pitch - 4u * (uint32_t)orow), 0x00027000);
-            const uint32_t voff = (uint32_t)(lane >> 3) * pitch + 16u * (lane & 7);
+            v4f yv[2][4];
+            auto rescaled = [&](const int a, const int b, const int q) {
+                return v4f{(float)acc[a][b][4 * q + 0] * scale[b], (float)acc[a][b][4 * q + 1] * scale[b],
+                           (float)acc[a][b][4 * q + 2] * scale[b], (float)acc[a][b][4 * q + 3] * scale[b]};
+            };
             // A wavefront's LDS operations complete in order, so a tile can be written behind the reads of the one before without a
             // wait, and what a tile's stores wait for is covered by the conversions of the next tile.
-            v4f yv[2][4];
-            auto stage = [&](const int n) {
-                const int a = n % RA, b = n / RA;
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const v4f y = {(float)acc[a][b][4 * q + 0] * scale[b], (float)acc[a][b][4 * q + 1] * scale[b],
-                                   (float)acc[a][b][4 * q + 2] * scale[b], (float)acc[a][b][4 * q + 3] * scale[b]};
-                    *reinterpret_cast<v4f *>(est + r * 128 + 16 * ((2 * q + c) ^ ((r >> 1) & 7))) = y;
-                }
-                asm volatile("" ::: "memory");   // the reads are of what other lanes have written
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int t = 8 * i + (lane >> 3);
-                    yv[n & 1][i] = *reinterpret_cast<const v4f *>(est + t * 128 + 16 * ((lane & 7) ^ ((t >> 1) & 7)));
-                }
-                asm volatile("" ::: "memory");   // the next tile's writes stay behind them
-            };
-            auto leave = [&](const int n) {
-                const int a = n % RA, b = n / RA;
-                if (has_bias) {
-                    asm volatile("");   // a branch, not additions and selections
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) yv[n & 1][i] += bias4[a];
-                }
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, yv[n & 1][i]), out, voff + (uint32_t)(32 * b + 8 * i) * pitch + 128u * a, 0, 2);   // 2: streaming
-            };
-            stage(0);
-            SBN_WAIT_VMCNT(0);   // what was asked for of the next piece (the youngest half a step ago), in front of the first store
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int n = 1; n < RA * TB; ++n) {
-                stage(n);
+            static_assert(RA == 2, "two tiles of 32 rows x 32 tokens, or of 64 x 16, for 32 tokens");
+            auto sweep = [&](auto stage, auto leave) {
+                stage(0);
+                SBN_WAIT_VMCNT(0);   // what was asked for of the next piece (the youngest half a step ago), in front of the first store
                 __builtin_amdgcn_sched_barrier(0);
-                leave(n - 1);
-                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int n = 1; n < RA * TB; ++n) {
+                    stage(n);
+                    __builtin_amdgcn_sched_barrier(0);
+                    leave(n - 1);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                leave(RA * TB - 1);
+            };
+            // Output rows of whole 64 bytes: tiles of 32 x 32, 128 bytes of a token at a time, written past the caches.  Rows of
+            // other lengths share their 64-byte sectors with the neighbouring run: in runs of 256 bytes (64 rows x 16 tokens) half as
+            // many are shared, and the L2 puts their halves together while the outputs fit the last cache.  4096 tokens, 2560 ->
+            // 6920: 80 us in tiles past the caches, 64 in tiles, 66 in runs past the caches, 59.5 in runs (6924: 92 / 66 / 69 / 61;
+            // 6912: 51 past the caches, 59 through them); 5866 tokens, 1152 -> 7720 (181 MB) 97 / 74 / 70 / 70; 32768
+            // tokens, 2560 -> 6920 (907 MB) 512 / 506 / 425 / 499.
+            if ((g.d_out & 15) == 0) {
+                v4f bias4[RA];
+#pragma unroll
+                for (int a = 0; a < RA; ++a)
+                    bias4[a] = has_bias ? *reinterpret_cast<const v4f *>(g.bias + orow + 32 * a + 4 * (lane & 7)) : v4f{0.f, 0.f, 0.f, 0.f};
+                const uint32_t voff = (uint32_t)(lane >> 3) * pitch + 16u * (lane & 7);
+                sweep([&](const int n) {
+                    const int a = n % RA, b = n / RA;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) *reinterpret_cast<v4f *>(est + r * 128 + 16 * ((2 * q + c) ^ ((r >> 1) & 7))) = rescaled(a, b, q);
+                    asm volatile("" ::: "memory");   // the reads are of what other lanes have written
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const int t = 8 * i + (lane >> 3);
+                        yv[n & 1][i] = *reinterpret_cast<const v4f *>(est + t * 128 + 16 * ((lane & 7) ^ ((t >> 1) & 7)));
+                    }
+                    asm volatile("" ::: "memory");   // the next tile's writes stay behind them
+                }, [&](const int n) {
+                    const int a = n % RA, b = n / RA;
+                    if (has_bias) {
+                        asm volatile("");   // a branch, not additions and selections
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) yv[n & 1][i] += bias4[a];
+                    }
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, yv[n & 1][i]), out, voff + (uint32_t)(32 * b + 8 * i) * pitch + 128u * a, 0, 2);   // 2: streaming
+                });
+            } else {
+                const v4f bias4 = has_bias ? *reinterpret_cast<const v4f *>(g.bias + orow + 4 * (lane & 15)) : v4f{0.f, 0.f, 0.f, 0.f};
+                const uint32_t voff = (uint32_t)(lane >> 4) * pitch + 16u * (lane & 15);
+                const bool streaming = (int64_t)g.tokens * g.d_out > (192 << 18);   // more than 192 MB of outputs
+                sweep([&](const int n) {
+                    if ((r >> 4) == (n & 1)) {
+#pragma unroll
+                        for (int a = 0; a < RA; ++a)
+#pragma unroll
+                            for (int q = 0; q < 4; ++q)
+                                *reinterpret_cast<v4f *>(est + (r & 15) * 256 + 16 * ((8 * a + 2 * q + c) ^ (r & 15))) = rescaled(a, n / 2, q);
+                    }
+                    asm volatile("" ::: "memory");
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const int t = 4 * i + (lane >> 4);
+                        yv[n & 1][i] = *reinterpret_cast<const v4f *>(est + t * 256 + 16 * ((lane & 15) ^ t));
+                    }
+                    asm volatile("" ::: "memory");
+                }, [&](const int n) {
+                    if (has_bias) {
+                        asm volatile("");
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) yv[n & 1][i] += bias4;
+                    }
+                    if (streaming) {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+                            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, yv[n & 1][i]), out, voff + (uint32_t)(16 * n + 4 * i) * pitch, 0, 2);
+                    } else {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+                            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, yv[n & 1][i]), out, voff + (uint32_t)(16 * n + 4 * i) * pitch, 0, 0);
+                    }
+                });
             }
-            leave(RA * TB - 1);
         } else {
             SBN_WAIT_VMCNT(0);
 #pragma unroll

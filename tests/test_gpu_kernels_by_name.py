@@ -141,6 +141,7 @@ def test_pieces_scales_below_the_normal_range(N, M):
     [(4000, 3000, 640), (4000, 2600, 640), (5000, 3001, 640)],                              # rows of one length, others' outputs
     [(3000, 4000, 384), (4100, 3000, 512), (2000, 2100, 128), (3333, 4444, 512)],           # the stream of requests is started anew in between
     [(700, 1100, 384), (650, 900, 384), (97 * 8, 600, 896)],                                # from a list: pieces of all widths behind each other
+    [(8200, 6148, 128)], [(4100, 2564, 256), (700, 1496, 128)],                              # rows of outputs of no whole 64 bytes, more and less than 192 MB
     [(512, 13000, 128), (65, 17, 256)], [(300, 4700, 384), (512, 6001, 128), (100, 9000, 256)], [(33, 2000, 128)],   # decode batches: runs of uneven length, few blocks
 ])
 def test_pieces_one_behind_the_other(N, M, problems):
