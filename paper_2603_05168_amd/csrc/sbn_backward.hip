@@ -216,7 +216,7 @@ __device__ __forceinline__ void scale_four_rows(const uint4 *__restrict__ dY, co
 // per block) and dY / s_x (256 x four rows of eight values per block).  Bound by the bytes that they move; the decoders, which wait for their LDS, run beside the streams.
 // One launch per layer for W_eff^T and one for the other two left the device in a tail seven to fourteen times per training
 // step, and a block with 256 vectors of one row quad alone left a third of its lanes idle at 2560 outputs.  us per step of a block at
-// 16384 tokens, before and now: 617 -> 462 (5.6 to 5.8 TB/s); 6912 x 2560 at 1024 tokens (6:8) 23.0 -> 17.8.
+// 16384 tokens, before and then: 617 -> 462 (5.6 to 5.8 TB/s; less by the half of W_eff^T since that is a byte per weight); 6912 x 2560 at 1024 tokens (6:8) 23.0 -> 17.8.
 enum OperandKind { OPERAND_UNPACK, OPERAND_CODES, OPERAND_TRANSPOSE, OPERAND_SCALE };   // W_eff^T from packed weights, from int8; x~^T; dY / s_x
 struct OperandJob {
     const void *src;
@@ -471,10 +471,10 @@ __device__ __forceinline__ int bf16_product_of_block(const GemmBf16Group &grp)
 // multiprocessor), stages of 64 k filled by LDS-DMA: a ring of five slots that the two operands take in turns, so that P lies in
 // LDS two stages ahead and Q one.  A stage is consumed in quarters of 16 k; the fragments of the next quarter are read under the
 // matrix instructions of the current one, also across the barrier between two stages, and the requests for later stages
-// stand there as well, so a wavefront always has matrix instructions to issue: 1.45 us per stage of the large tile where one
-// barrier, eight requests and a first read in front of every stage's matrix instructions took 1.9 us.  What bounds it now: the
-// matrix pipe at the clock the board holds (1.9 PFLOP/s on operands from registers), and 10 us per tile for its first stages and
-// its result, which nothing covers.
+// stand there as well, so a wavefront always has matrix instructions to issue: 1.42 us per stage of the large tile of dW, 1.38 of
+// dX, where one barrier, eight requests and a first read in front of every stage's matrix instructions took 1.9 us.  What bounds
+// it now: the matrix pipe at the clock the board's power holds (1.85 to 1.89 PFLOP/s on operands from registers for dW, 1.95 to 2.03
+// for the ternary operand of dX), and 2.5 us per tile for its first stages and 3.2 for its result, which nothing covers.
 // The fifth slot is what LDS has left beside two whole stages.  With two, all requests of a stage had three quarters of one to
 // arrive in: three layers of 2560 x 2560 at 16384 tokens 943 us then and 927 now (the products alone), two of 6912 x 2560 1844
 // and 1806, a training step of 6912 x 2560 in two parts of 1024 tokens (small tiles) 324 and 306.
@@ -878,8 +878,10 @@ sbn_status launch_gemm_bf16_as(int count, const GemmBf16Args *args, hipStream_t 
 }
 
 // Estimated time in us of the products of a call with the tiles of one size: every multiprocessor's share of all tiles, or the
-// longest tile.  Measured: 256 x 256 takes 1.45 us per stage of 64 k (1.2 while most multiprocessors idle) and 10 us for its
-// first stages and its result; of 128 x 128 a multiprocessor holds two, 1.05 us per stage (0.6) and 7 us.
+// longest tile.  256 x 256 counts 1.45 us per stage of 64 k (1.2 while most multiprocessors idle) and 10 us for its first stages
+// and its result; of 128 x 128 a multiprocessor holds two, 1.05 us per stage (0.6) and 7 us.  Both take less by now, the large
+// tile 1.4 and 6, but in proportion: over 70 calls of 128 to 8192 tokens with both sizes measured the choice costs 0.38 % against
+// the faster one of each (at worst 1.10, 2048 tokens 2560 -> 6912: 163 us against 148).
 template <bool BIG>
 float gemm_bf16_estimate_us(int count, const GemmBf16Args *args)
 {
@@ -908,7 +910,7 @@ inline int64_t pad64(int64_t x) { return (x + 63) / 64 * 64; }
 
 size_t backward_workspace_bytes(int64_t tokens, int64_t d_out, int64_t d_in)
 {
-    // W_eff^T bf16 [d_in, pad64(d_out)] + int8 W_eff (generic patterns) + x~^T bf16 [d_in, pad64(tokens)]
+    // W_eff^T [d_in, 2 pad64(d_out)] bytes (a byte per weight in rows of whole 128 lies in it) + int8 W_eff (generic patterns) + x~^T bf16 [d_in, pad64(tokens)]
     // + dY / s_x bf16 [tokens, d_out] + the mask bit plane of the gradient-masked variant
     return align_up((size_t)d_in * pad64(d_out) * 2, 256) + align_up((size_t)d_out * d_in, 256) +
            align_up((size_t)d_in * pad64(tokens) * 2, 256) + align_up((size_t)tokens * d_out * 2, 256) +

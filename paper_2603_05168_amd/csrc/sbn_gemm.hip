@@ -197,8 +197,8 @@ __device__ __forceinline__ void load_scales(const GemmArgs &g, int tok0, int lan
 // ---- sparse path --------------------------------------------------------------------------------
 // One persistent block of eight wavefronts per multiprocessor; block tile 512 rows x 128 tokens.  Wavefront w owns the
 // rows 64 w .. 64 w + 63 (two row tiles of 32) and all tokens of the piece (TB = 1 .. 4 token tiles of 32), so one code
-// expansion (nine vector instructions) feeds TB matrix instructions: measured on this part, up to four vector
-// instructions per matrix instruction hide under it, more cost their full time.  The two wavefronts of a SIMD cover
+// expansion (a shift and a mask for each of four registers) feeds TB matrix instructions: measured on this part, up to
+// four vector instructions per matrix instruction hide under it, more cost their full time.  The two wavefronts of a SIMD cover
 // each other's waits.  Per 128-k step the wavefronts read 144 KB of operand fragments from LDS and the DMA deposits
 // 32 KB; measured with a microbenchmark, reads (475 bytes/ns) and deposits (105 bytes/ns from L2) overlap, so it is
 // the deposit path that is scarce: a step's 32 KB are 0.3 us of it against 0.5 us of matrix work.  Against two
@@ -214,9 +214,12 @@ __device__ __forceinline__ void load_scales(const GemmArgs &g, int tok0, int lan
 // A lane (row r = lane % 32, half c = lane / 32) reads index words 2c, 2c+1 and code words 2c, 2c+1 of its row's chunk
 // (two 8-byte LDS reads per row tile); sub-step u = 0, 1 uses word 2c + u, i.e. the lane supplies weights
 // [64c + 32u, +32) of the chunk.
-// Pieces follow one another without draining the pipeline: when the main loop of a piece ends, the first stages of the
-// block's next piece are requested BEFORE the epilogue of the finished one runs, and the epilogue transposes through a
-// staging area of its own, so the ring is never idle.
+// Pieces follow one another without draining the pipeline: the requests run on from a piece into the block's next one
+// under the last products, and the epilogue transposes through a staging area of its own, so the ring is never idle.
+// What bounds it now is the power of the board, which holds the clock at 1.6 GHz: 2:4 products of random operands from
+// registers run at 6.5 POP/s dense-equivalent with codes +-1 and 6.9 with +-64.  32768 tokens, 2560 -> 6912: 416 us before codes
+// of +-64, the tiles of the epilogue and the running requests, 357 now (3.25 POP/s); 4096 tokens 56.6 and 51.7, 2560 -> 2560
+// 22.5 and 21.7.
 namespace sp {
 
 constexpr int ROWS = 512;                      // rows of W per block tile
@@ -1061,7 +1064,7 @@ GemmArgs make_args(const LinearItem &it, int block_tokens = BT)
 
 // Deals the work of a launch to the blocks (host side).  Per XCD: the strips (problem, token group of 16 units, row
 // tile of 512) are cut into exactly m * nb pieces of at most four units, as even as the strip lengths allow (no block
-// is left with single-unit crumbs: a piece of one unit pays nine vector instructions per matrix instruction).  The
+// is left with single-unit crumbs: a piece of one unit pays a whole expansion per matrix instruction).  The
 // pieces stay in strip order and are dealt in m rounds of nb: the pieces that run at about the same time belong to a
 // few neighbouring strips, whose weights and tokens fit the XCD's L2 together (dealt by width alone, across all strips,
 // the same launch fetched 88 MB instead of 50 at 6912 x 2560 x 4096).  Inside a round the widest pieces go to the
