@@ -1228,6 +1228,8 @@ sbn_status launch_gemm_pieces(int count, const LinearItem *items, bool dense_cod
 //       (2560 -> 2560 at 17 .. 1500 tokens 13.2 .. 15.0 us, 6912 -> 2560 39 .. 43, 2560 -> 6912 at 512 / 777 / 1500 / 3000
 //       tokens, up to 1 / 2 / 3 / 6 units, 18 / 20 / 25 / 47).  Output rows of no whole 16 bytes are stored in single words,
 //       another 3.2 us and 0.55 us per MB of them (512 -> 476 / 478 at 1000 tokens 6.5 / 10.2 us, 512 -> 6911 at 8000 179)
+// The fit is of pieces before their requests ran on and decode batches were dealt by XCD; by name and without the quantizer 2560 ->
+// 6912 takes 13.6 us at 512 tokens and 18.5 at 1024 by now, so that the choice leans to the small tiles a little.
 static float gemm_large_estimate_us(int count, const LinearItem *items, bool dense)
 {
     bool stream = true;
