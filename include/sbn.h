@@ -227,6 +227,8 @@ sbn_status sbn_sparse_ternary_linear_grouped(int count, const void *const *X, co
  *            SBN_BWD_MASK_DW: the ablation study's "gradient masking" variant, dW = M (.) dense dW (only the
  *            weights of the current mask receive the term; needs `packed`); the paper's method leaves it off
  *   workspace >= sbn_workspace_bytes(SBN_OP_BACKWARD, tokens, d_out, d_in, N, M)
+ * Errors: SBN_EINVAL, SBN_EALIGN, SBN_ESIZE, SBN_EUNSUPPORTED (d_in or d_out % 8 != 0; operands that the products cannot
+ * address: 306 million tokens or 34 million outputs for dW, 536 million outputs for dX), SBN_EHIP.
  */
 enum { SBN_BWD_ACCUMULATE = 1, SBN_BWD_MASK_DW = 2 };
 sbn_status sbn_sparse_ternary_linear_backward(const void *dY, int64_t tokens, int64_t d_in,

@@ -561,7 +561,7 @@ sbn_status sbn_sparse_ternary_linear_backward(const void *dY, int64_t tokens, in
     if (st != SBN_OK) return st;
     if (!aligned(dY, 16) || !aligned(workspace, 256)) return SBN_EALIGN;
     if ((dX && !aligned(dX, 16)) || (dW && !aligned(dW, 16)) || (xq && !aligned(xq, 16))) return SBN_EALIGN;
-    if (d_in % 8 != 0 || d_out % 8 != 0) return SBN_EUNSUPPORTED;
+    if (d_in % 8 != 0 || d_out % 8 != 0 || !backward_takes(tokens, d_out, dX != nullptr, dW != nullptr)) return SBN_EUNSUPPORTED;
     if (ws_bytes < backward_workspace_bytes(tokens, d_out, d_in)) return SBN_ESIZE;
     return launch_backward(dY, tokens, d_in, d_out, pat, packed, gamma, xq, sx, dX, dW, flags, workspace,
                            ws_bytes, static_cast<hipStream_t>(stream));
@@ -590,7 +590,7 @@ sbn_status sbn_sparse_ternary_linear_backward_grouped(int count, const void *con
         if (st != SBN_OK) return st;
         if (!aligned(dY[i], 16) || (dX[i] && !aligned(dX[i], 16)) || (dW[i] && !aligned(dW[i], 16)) || (xq[i] && !aligned(xq[i], 16)))
             return SBN_EALIGN;
-        if (d_in[i] % 8 != 0 || d_out[i] % 8 != 0) return SBN_EUNSUPPORTED;
+        if (d_in[i] % 8 != 0 || d_out[i] % 8 != 0 || !backward_takes(tokens[i], d_out[i], dX[i] != nullptr, dW[i] != nullptr)) return SBN_EUNSUPPORTED;
         items[i] = BackwardItem{dY[i], tokens[i], d_in[i], d_out[i], packed[i], gamma[i], xq[i], sx[i], dX[i], dW[i],
                                 static_cast<uint8_t *>(workspace) + used};
         used += backward_workspace_bytes(tokens[i], d_out[i], d_in[i]);

@@ -324,8 +324,8 @@ struct GemmBf16Args {
     int transposed;       // Q is [k, ldq]
     int accumulate;
     int tiles_n, tiles_m;
-    const uint32_t *mask;   // null, or one bit per element of C (rows of mask_wpr words): zero bits block the new term
-    int mask_wpr;
+    const uint8_t *mask;    // null, or one bit per element of C (rows of mask_pitch bytes): zero bits block the new term
+    int mask_pitch;
 };
 
 // Tile order.  Blocks go to the eight XCDs round-robin and every XCD has its own L2, so XCD x takes
@@ -432,7 +432,7 @@ __device__ __forceinline__ void bf16_wave_epilogue(const GemmBf16Args &g, const 
             for (int i = 0; i < 4; ++i) { v[i] = lo[j][i] * alpha; v[4 + i] = hi[j][i] * alpha; }
             if (g.mask) {   // n is a multiple of 8: its mask bits sit in one byte
                 const int m = m0 + 32 * b + (64 / LPR) * j;
-                const uint32_t mb = g.mask[(int64_t)m * g.mask_wpr + (n >> 5)] >> (n & 31);
+                const uint32_t mb = g.mask[(int64_t)m * g.mask_pitch + (n >> 3)];
 #pragma unroll
                 for (int i = 0; i < 8; ++i) v[i] = (mb >> i) & 1u ? v[i] : 0.0f;
             }
@@ -506,16 +506,18 @@ __device__ __forceinline__ void bf16_dw_body(const GemmBf16Args &g, uint8_t *dld
     // row l / 8, slot l % 8 holding global column slot ^ ((row >> 1) & 7)).  Q: a stage is 64 k rows of M values,
     // one instruction fills 1024 bytes of them, slot s of row k holds the eight values of granule s ^ f(k),
     // f = 4 (k & 3) | 2 ((k >> 2) & 1): the four k rows that a transposing read of 16 lanes takes lie in different banks.
-    // Operands are buffers: rows and k rows past the matrix, and stages past the last, read as zeros and fetch nothing.
+    // Operands are buffers that move on with the stages: rows and k rows past the matrix, and stages past the last, read as zeros and fetch
+    // nothing.  Their size has 32 bits: of P it ends with the last row's part of the stage, of Q with the stage's rows unless those are longer
+    // than anything that is asked for (launch_backward_grouped sees to the rest).
     constexpr int QROW = S::M * 2;                        // bytes of a k row of a stage
     const int kleft = g.kq - (nk - 1) * GD_K;             // k of the last stage that Q has
     const int prows = g.N - n0 < S::N ? g.N - n0 : S::N;
     const uint32_t ppitch = 2u * (uint32_t)g.ldp;
-    const uint32_t qpitch = 2u * (uint32_t)g.ldq, pbytes = (uint32_t)prows * ppitch;
-    const uint32_t qbytes = GD_K * qpitch - 2u * (uint32_t)m0, qbytes_last = (uint32_t)kleft * qpitch - 2u * (uint32_t)m0;   // of a stage: up to the end of its rows
+    const uint32_t qpitch = 2u * (uint32_t)g.ldq, pbytes = (uint32_t)(prows - 1) * ppitch + GD_K * 2;
+    auto up_to_end = [&](const int k) { return (uint32_t)std::min((uint64_t)k * qpitch - 2u * (uint32_t)m0, (uint64_t)0xfffffff0u); };   // of k rows
+    const uint32_t qbytes = up_to_end(GD_K), qbytes_last = up_to_end(kleft);
     v4i pbuffer = buffer_of(static_cast<const uint16_t *>(g.P) + (int64_t)n0 * g.ldp, pbytes);
     v4i qbuffer = buffer_of(g.Q + m0, nk > 1 ? qbytes : qbytes_last);
-    uint32_t pat = 0;                                     // bytes into a row of P
     uint64_t qstep = (uint64_t)g.ldq * (GD_K * 2);
     asm volatile("" : "+s"(qstep));                       // in a register: loaded again in every step it would be waited for with all LDS reads
     uint32_t poff[4], qoff[4];
@@ -531,18 +533,21 @@ __device__ __forceinline__ void bf16_dw_body(const GemmBf16Args &g, uint8_t *dld
     }
     // the four instructions of a wavefront and slot one by one, so that they can stand between matrix instructions; the fourth moves
     // the operand on to its next stage, kt + 1
+    auto move_on = [](v4i &buffer, const uint64_t step) {
+        const uint64_t base = ((uint64_t)(uint32_t)buffer[1] << 32 | (uint32_t)buffer[0]) + step;
+        buffer[0] = (int)(uint32_t)base;
+        buffer[1] = (int)(uint32_t)(base >> 32);
+    };
     auto dma_p = [&](const int kt, const uint32_t slot, const int i) {
-        lds_dma16_buffer(pbuffer, poff[i], pat, lds0 + slot + wave * 4096 + i * 1024);
+        lds_dma16_buffer(pbuffer, poff[i], 0, lds0 + slot + wave * 4096 + i * 1024);
         if (i < 3) return;
-        pat += GD_K * 2;
+        move_on(pbuffer, GD_K * 2);
         pbuffer[2] = kt + 1 < nk ? (int)pbytes : 0;
     };
     auto dma_q = [&](const int kt, const uint32_t slot, const int i) {
         lds_dma16_buffer(qbuffer, qoff[i], 0, lds0 + slot + wave * 4096 + i * 1024);
         if (i < 3) return;
-        const uint64_t base = ((uint64_t)(uint32_t)qbuffer[1] << 32 | (uint32_t)qbuffer[0]) + qstep;
-        qbuffer[0] = (int)(uint32_t)base;
-        qbuffer[1] = (int)(uint32_t)(base >> 32);
+        move_on(qbuffer, qstep);
         qbuffer[2] = kt + 2 < nk ? (int)qbytes : kt + 2 == nk ? (int)qbytes_last : 0;
     };
     // LDS read addresses: P: row * 128 + 16 * ((2u + c) ^ ((row >> 1) & 7)); (row >> 1) & 7 = (r >> 1) & 7 for every
@@ -906,7 +911,28 @@ sbn_status launch_gemm_bf16(int count, const GemmBf16Args *args, hipStream_t str
 
 inline int64_t pad64(int64_t x) { return (x + 63) / 64 * 64; }
 
+// The products read their operands through buffers whose size has 32 bits: a whole tile's rows of both operands of dX, the last row's stage
+// behind the other rows of P of dW, and 63 rows of a stage of its Q.  Where the rows are so long that those of a large tile do not fit, the
+// product is cut into products of `fit` rows (a multiple of `unit`), of which it does the first and more in turn.
+constexpr int64_t OPERAND_END = (int64_t)1 << 32;
+constexpr int64_t rows_fit(int64_t pitch) { return (OPERAND_END - 1) / pitch; }
+constexpr int64_t rows_fit_moving(int64_t pitch) { return (OPERAND_END - 1 - GD_K * 2) / pitch + 1; }
+template <class Each>
+void cut_rows(int64_t rows, int64_t fit, int64_t unit, Each &&each)   // each(first, count)
+{
+    const int64_t most = fit >= Bf16Tile<true>::N ? rows : fit / unit * unit;
+    for (int64_t first = 0; first < rows; first += most) each(first, std::min(most, rows - first));
+}
+
 }  // namespace
+
+// Eight rows (the least that a product has columns) of x~^T and of W_eff^T, one of dY for dX, 63 for dW: some 306 million tokens and 34
+// million outputs for dW, 536 million outputs for dX.
+bool backward_takes(int64_t tokens, int64_t d_out, bool dx, bool dw)
+{
+    return (!dx || (rows_fit(ceil_div(d_out, 128) * 128) >= 8 && rows_fit(2 * d_out) >= 1)) &&
+           (!dw || (rows_fit_moving(2 * pad64(tokens)) >= 8 && (GD_K - 1) * 2 * d_out + 2 * Bf16Tile<true>::M < OPERAND_END));
+}
 
 size_t backward_workspace_bytes(int64_t tokens, int64_t d_out, int64_t d_in)
 {
@@ -959,7 +985,15 @@ sbn_status launch_backward_grouped(int count, const BackwardItem *items, const P
             a.Q = dy; a.ldq = d_out; a.M = (int)tokens; a.kq = (int)d_out;
             a.K = (int)pad64(d_out);
             a.C = static_cast<uint16_t *>(it.dX); a.ldc = d_in; a.alpha = it.gamma;
-            products.push_back(a);
+            cut_rows(tokens, rows_fit(2 * d_out), 1, [&](int64_t m0, int64_t m) {
+                cut_rows(d_in, rows_fit(ldw), 8, [&](int64_t n0, int64_t n) {
+                    GemmBf16Args part = a;
+                    part.P = wt + n0 * ldw; part.N = (int)n;
+                    part.Q = a.Q + m0 * d_out; part.M = (int)m;
+                    part.C = a.C + m0 * d_in + n0;
+                    products.push_back(part);
+                });
+            });
         }
         if (it.dW) {
             const int64_t ldt = pad64(tokens);
@@ -982,10 +1016,16 @@ sbn_status launch_backward_grouped(int count, const BackwardItem *items, const P
                 // ablation variant: only the weights of the current mask receive the new gradient term
                 st = launch_mask_bitplane(it.packed, d_out, d_in, pat, mask_bits, stream);
                 if (st != SBN_OK) return st;
-                a.mask = mask_bits;
-                a.mask_wpr = (int)((d_in + 31) / 32);
+                a.mask = reinterpret_cast<const uint8_t *>(mask_bits);
+                a.mask_pitch = (int)((d_in + 31) / 32 * 4);
             }
-            products.push_back(a);
+            cut_rows(d_in, rows_fit_moving(2 * ldt), 8, [&](int64_t n0, int64_t n) {
+                GemmBf16Args part = a;
+                part.P = xts + n0 * ldt; part.N = (int)n;
+                part.C = a.C + n0;
+                if (a.mask) part.mask = a.mask + n0 / 8;
+                products.push_back(part);
+            });
         }
     }
     st = launch_operands(jobs, pat, stream);

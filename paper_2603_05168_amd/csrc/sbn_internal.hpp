@@ -145,6 +145,7 @@ int pack_spin_limit();
 
 // ---- backward (sbn_backward.hip) ---------------------------------------------------------------
 size_t backward_workspace_bytes(int64_t tokens, int64_t d_out, int64_t d_in);
+bool backward_takes(int64_t tokens, int64_t d_out, bool dx, bool dw);   // whether the products can address the operands
 struct BackwardItem {
     const void *dY;
     int64_t tokens, d_in, d_out;

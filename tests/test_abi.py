@@ -222,6 +222,40 @@ def test_argument_errors_come_before_any_launch(sbn):
     assert sbn.sbn_last_error() == ""
 
 
+def test_backward_refuses_rows_it_cannot_address(sbn):
+    """On either side of each limit; a workspace of no bytes tells what was taken from what was refused before any launch."""
+    lib = ctypes.CDLL(sbn.lib_path())
+    lib.sbn_sparse_ternary_linear_backward.restype = lib.sbn_sparse_ternary_linear_backward_grouped.restype = ctypes.c_int
+    vp, i64, ci, sz = ctypes.c_void_p, ctypes.c_int64, ctypes.c_int, ctypes.c_size_t
+    A = 0x10000
+
+    def both(tokens, d_in, d_out, dX, dW):
+        one = lib.sbn_sparse_ternary_linear_backward(vp(A), i64(tokens), i64(d_in), i64(d_out), ci(2), ci(4), vp(A), vp(A), vp(A), vp(A),
+                                                     vp(dX), vp(dW), ci(0), vp(A), sz(0), vp(0))
+        P, I = (lambda v: (vp * 1)(v or None)), (lambda v: (i64 * 1)(v))   # noqa: E731
+        many = lib.sbn_sparse_ternary_linear_backward_grouped(ci(1), P(A), I(tokens), I(d_in), I(d_out), ci(2), ci(4), P(A), P(A), P(A), P(A),
+                                                              P(dX), P(dW), ci(0), vp(A), sz(0), vp(0))
+        assert one == many
+        return one
+
+    end = 1 << 32
+    # dW: seven rows of transposed activations, 2 bytes per token padded to 64, and a stage; 63 rows of gradients and a tile's columns
+    most = (end - 129) // 7 // 128 * 64
+    for d_in in (8, 2560):
+        assert both(most, d_in, 8, 0, A) == sbn.SBN_ESIZE and both(most + 1, d_in, 8, 0, A) == sbn.SBN_EUNSUPPORTED
+        assert both(most + 1, d_in, 8, A, 0) == sbn.SBN_ESIZE
+    most = (end - 513) // 63 // 2 // 8 * 8
+    assert both(64, 8, most, 0, A) == sbn.SBN_ESIZE and both(64, 8, most + 8, 0, A) == sbn.SBN_EUNSUPPORTED
+    # dX: eight rows of transposed weights, a byte per output padded to 128
+    most = (end - 1) // 8 // 128 * 128
+    for tokens in (1, 4096):
+        assert both(tokens, 8, most, A, 0) == sbn.SBN_ESIZE and both(tokens, 8, most + 8, A, 0) == sbn.SBN_EUNSUPPORTED
+    # what 256 rows, or as many as there are, behind one offset of 32 bits could be computed with
+    for tokens, d_in, d_out, dX, dW in ((1 << 23, 2560, 3840, A, A), (8421000, 2560, 8, A, A), (256, 8, 8421000, A, A), (64, 8, 34087000, 0, A),
+                                        (306783000, 8, 8, 0, A), (8, 8, 306783000, A, 0)):
+        assert both(tokens, d_in, d_out, dX, dW) == sbn.SBN_ESIZE
+
+
 def test_self_kernel_hook_refuses_on_the_host(sbn):
     lib = ctypes.CDLL(sbn.lib_path())
     lib.sbn_test_self_kernel.restype = ctypes.c_int

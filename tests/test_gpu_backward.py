@@ -366,3 +366,57 @@ def test_backward_dw_rounds_the_scaled_gradient_alone(rows):
     bound = 2.0 ** -8 * ref.abs() + tokens * 2.0 ** -24 * terms
     err = (dW.cpu().double() - ref).abs()
     assert (err <= bound).all(), f"{(err > bound).sum()} of {err.numel()} beyond the rounding of the result, worst {(err / bound).max():.2f}"
+
+
+def test_backward_operands_of_four_gigabytes():
+    # 128 rows of an operand (a tile of the smaller size), or the 64 of a stage, are 2^32 bytes: one gradient of 1 in a few rows makes
+    # rows of dW and dX that are rows of the other operand
+    s = sbn()
+
+    def call(tokens, d_out, d_in, dW=None, dX=None, mask_dw=False, **operands):
+        ws = s.new_workspace(s.sbn_workspace_bytes(s.SBN_OP_BACKWARD, tokens, d_out, d_in, 2, 4))
+        a = {"dY": None, "packed": None, "gamma": None, "xq": None, "sx": None, **operands}
+        s.sbn_sparse_ternary_linear_backward(a["dY"], a["packed"], a["gamma"], a["xq"], a["sx"], 2, 4, ws, d_in, dX=dX, dW=dW, mask_dw=mask_dw)
+        torch.cuda.synchronize()
+
+    nan = float("nan")
+    gen = torch.Generator(device=DEV).manual_seed(5)
+    # dW, long columns of activations, of which 128 and eight more are two products; eight of them behind a mask
+    tokens, d_out, d_in = 1 << 24, 8, 136
+    at = torch.tensor([0, 1 << 22, (1 << 23) - 1, 1 << 23, (1 << 24) - 64, (1 << 24) - 9, (1 << 24) - 2, (1 << 24) - 1], device=DEV)
+    xq = torch.randint(-128, 128, (tokens, d_in), generator=gen, device=DEV, dtype=torch.int8)
+    dY = torch.zeros(tokens, d_out, dtype=torch.bfloat16, device=DEV)
+    dY[at, torch.arange(8, device=DEV)] = 1.0
+    dW = torch.full((d_out, d_in), nan, dtype=torch.bfloat16, device=DEV)
+    sx = torch.ones(tokens, device=DEV)
+    call(tokens, d_out, d_in, dW, dY=dY, xq=xq, sx=sx)
+    assert torch.equal(dW, xq[at].to(torch.bfloat16))
+    W = sbn_synth.latent_weight(d_out, d_in, 1071)
+    call(tokens, d_out, d_in, dW, mask_dw=True, dY=dY, xq=xq, sx=sx, packed=hip_pack(W, 2, 4)[0])
+    assert torch.equal(dW, xq[at].to(torch.bfloat16) * torch.from_numpy(np.asarray(oracle_pack(W, 2, 4)[3])).to(DEV))
+    del xq, dY
+    # dW, long rows of gradients
+    tokens, d_out, d_in = 64, 1 << 25, 8
+    at = (torch.arange(64, device=DEV) * 532676609) % d_out
+    at[-1] = d_out - 1
+    xq = torch.randint(1, 128, (tokens, d_in), generator=gen, device=DEV, dtype=torch.int8)
+    dY = torch.zeros(tokens, d_out, dtype=torch.bfloat16, device=DEV)
+    dY[torch.arange(64, device=DEV), at] = 1.0
+    dW = torch.full((d_out, d_in), nan, dtype=torch.bfloat16, device=DEV)
+    call(tokens, d_out, d_in, dW, dY=dY, xq=xq, sx=torch.ones(tokens, device=DEV))
+    assert torch.unique(at).numel() == 64 and torch.equal(dW[at], xq.to(torch.bfloat16)) and dW.count_nonzero() == 64 * d_in
+    del dY, dW
+    # dX, long rows of gradients
+    tokens, d_out, d_in = 128, 1 << 24, 8
+    packed, gamma = hip_pack(sbn_synth.latent_weight(d_out, d_in, 1070), 2, 4)
+    Weff = torch.empty(d_out, d_in, dtype=torch.int8, device=DEV)
+    s.sbn_unpack(packed, d_out, d_in, 2, 4, W_eff=Weff)
+    at = (torch.arange(128, device=DEV) * 532676609) % d_out
+    at[-1] = d_out - 1
+    dY = torch.zeros(tokens, d_out, dtype=torch.bfloat16, device=DEV)
+    dY[torch.arange(128, device=DEV), at] = 1.0
+    dX = torch.full((tokens, d_in), nan, dtype=torch.bfloat16, device=DEV)
+    call(tokens, d_out, d_in, dX=dX, dY=dY, packed=packed, gamma=gamma)
+    assert torch.equal(dX, (Weff[at].float() * gamma).to(torch.bfloat16))
+    del dY
+    torch.cuda.empty_cache()
