@@ -342,7 +342,8 @@ void sbn_test_set_spin_limits(int gemv_polls, int pack_polls);
  * chooses by their sizes, so that a test reaches the edges of each whatever that choice is.  HOST arrays, one entry per
  * problem; xq, sx as written by sbn_act_quant; bias and acc_out may be NULL, and so may their entries.
  *   kernel     SBN_KERNEL_TILES: small block tiles; SBN_KERNEL_STREAM: streaming kernel for decode batches (at most 64
- *              tokens, d_out % 4 == 0, no bias and no acc_out); SBN_KERNEL_PIECES: persistent kernel on pieces of 512 rows;
+ *              tokens, d_out % 4 == 0, no bias and no acc_out); SBN_KERNEL_PIECES: persistent kernel on pieces of 512 rows
+ *              (d_in < 2^25);
  *              SBN_KERNEL_BLOCKS + 0, 1, 2: block tiles of 64 x 32, 128 x 32 and 128 x 64 rows x tokens
  *   supported  2:4 and N = M, d_in % 128 == 0; anything else SBN_EUNSUPPORTED.  Other errors as sbn_sparse_ternary_linear.
  */

@@ -285,6 +285,8 @@ struct Stream {
     bool landed;                    // everything asked for so far
 };
 
+// The sizes of both buffers, at most 128 tokens or 512 rows of weights, have 32 bits.
+constexpr int64_t ROW_END = (int64_t)1 << 25;   // of d_in: 128 times as many bytes do not fit them
 __device__ __forceinline__ v4i token_buffer(const GemmArgs &g, const Piece &p)
 {
     const int left = g.tokens - p.t0, rows = left < 32 * p.tb ? left : 32 * p.tb;
@@ -762,7 +764,7 @@ __device__ __forceinline__ void piece_run(const Group &grp, const Piece &p, cons
 // the XCD's units in the order strip, unit (the same number of units each, +-1), cut into pieces of at most four units
 // that do not cross a strip.
 // DENSE = the weights are dense 2-bit codes (the stored form of N = M, or any pattern converted to it) instead of 2:4.
-// UNIT = the rows are longer than CODE_SHIFT_MAX_K: codes +-1, whose sums fit an int32 whatever the length.
+// UNIT = the rows are longer than CODE_SHIFT_MAX_K: codes +-1, whose sums fit an int32 up to 2^24 values (2:4: 2^25).
 template <bool DENSE, bool UNIT, class Group, class Table>
 __global__ void __launch_bounds__(64 * sp::NW) gemm_smfmac_kernel(Group grp, Table tab)
 {
@@ -1167,6 +1169,8 @@ static int make_piece_table(const GemmGroup &grp, PieceTable &tab)
 
 sbn_status launch_gemm_pieces(int count, const LinearItem *items, bool dense_codes, hipStream_t stream)
 {
+    for (int i = 0; i < count; ++i)
+        if (items[i].d_in >= sp::ROW_END) return SBN_EUNSUPPORTED;
     // problems of at most 16 token units (512 tokens: decode batches) are dealt by row tile, up to GEMM_GROUP_WIDE per launch
     auto few_tokens = [&](int i) { return items[i].tokens <= 16 * 32 && items[i].d_in <= CODE_SHIFT_MAX_K; };
     auto long_rows = [&](int i) { return items[i].d_in > CODE_SHIFT_MAX_K; };   // a kernel of their own
@@ -1257,6 +1261,14 @@ static float gemm_large_estimate_us(int count, const LinearItem *items, bool den
            (word_mb > 0.0 ? 3.2f + 0.55f * (float)word_mb : 0.0f);
 }
 
+// Rows longer than the pieces can address; a block tile addresses 64 of them, a small tile 32.
+static bool beyond_pieces(int count, const LinearItem *items)
+{
+    for (int i = 0; i < count; ++i)
+        if (items[i].d_in >= sp::ROW_END && !gemv_batch_takes(items[i])) return true;
+    return false;
+}
+
 // Small block tiles where they are faster: their time grows with rows x tokens from 4.5 us on, that of the large kernels
 // starts two to five times higher and grows slower.  Over 279 calls of 17 to 16384 tokens, input dimensions 256 to 8192 and
 // one to sixteen problems, all kernels measured, the choice costs 0.6 % against the faster kernel of each (at worst 1.40, 384 tokens
@@ -1266,7 +1278,7 @@ static float gemm_large_estimate_us(int count, const LinearItem *items, bool den
 // 11.4 in pieces, 512 -> 512 6.9 either way.
 bool gemm_takes_tiles(int count, const LinearItem *items, bool dense_codes)
 {
-    return gemm_tile_estimate_us(count, items, dense_codes) < gemm_large_estimate_us(count, items, dense_codes);
+    return beyond_pieces(count, items) || gemm_tile_estimate_us(count, items, dense_codes) < gemm_large_estimate_us(count, items, dense_codes);
 }
 
 float gemm_estimate_us(int count, const LinearItem *items, bool dense_codes)
@@ -1282,7 +1294,7 @@ float gemm_estimate_us(int count, const LinearItem *items, bool dense_codes)
 // 13.6 us against 12.3).
 bool gemm_takes_blocks(int count, const LinearItem *items, bool dense_codes)
 {
-    return gemm_block_estimate_us(count, items, dense_codes) <
+    return !beyond_pieces(count, items) && gemm_block_estimate_us(count, items, dense_codes) <
            0.95f * std::min(gemm_tile_estimate_us(count, items, dense_codes), gemm_large_estimate_us(count, items, dense_codes));
 }
 

@@ -76,6 +76,11 @@ def test_choice_between_the_forward_kernels(sbn, N, M):
     # 158 this way)
     assert sbn.sbn_test_chosen_kernels([(16384, 768, 6912), (17, 8192, 768)], N, M) == [pieces, stream]
     assert sbn.sbn_test_chosen_kernels([(200, 2560, 2560)] * 3, N, M) == [tiles] * 3
+    # 128 tokens of 2^25 values are more bytes than the pieces can address; a call's problems are of one kernel
+    for tokens in (97, 600, 4096):
+        for d_out in (8, 1000, 8000):
+            assert sbn.sbn_test_chosen_kernels([(tokens, 1 << 25, d_out)], N, M) == [tiles] and not sbn.sbn_test_takes_blocks([(tokens, 1 << 25, d_out)], N, M)
+    assert sbn.sbn_test_chosen_kernels([(3000, 2560, 2560), (128, 1 << 25, 8)], N, M) == [tiles] * 2
 
 
 def test_packed_bytes(sbn):
@@ -207,6 +212,7 @@ def test_argument_errors_come_before_any_launch(sbn):
     assert kernel(Y=A + 4) == sbn.SBN_EALIGN
     assert kernel(d_in=200) == sbn.SBN_EUNSUPPORTED
     assert kernel(N=6, M=8) == sbn.SBN_EUNSUPPORTED
+    assert kernel(which=2, d_in=1 << 25) == sbn.SBN_EUNSUPPORTED
     for refused in ({"tokens": 65}, {"d_out": 66}, {"bias": A}):
         assert kernel(which=1, **refused) == sbn.SBN_EUNSUPPORTED
     # ceiling probes (their own library): unknown kind, missing host output, buffer too small to stream

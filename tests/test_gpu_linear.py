@@ -788,3 +788,27 @@ def test_small_block_tiles(N, M, tokens, shape, bias):
         bv = 0.0 if b is None else b.numpy().astype(np.float64)[None, :]
         assert (np.abs(Y.astype(np.float64) - (y + bv)) <= 4 * 2.0 ** -24 * (np.abs(y) + np.abs(bv))).all()
     check_forward(W, X, N, M, s.SBN_PATH_SMFMAC)
+
+
+def test_rows_of_two_to_the_25():
+    # 128 of them are 2^32 bytes, which is more than the pieces can address
+    s = sbn()
+    tokens, d_in, d_out, N, M = 128, 1 << 25, 8, 2, 4
+    gen = torch.Generator(device=DEV).manual_seed(25)
+    W = torch.empty(d_out, d_in, dtype=torch.bfloat16, device=DEV).normal_(0.0, 0.02, generator=gen)
+    packed = torch.empty(s.sbn_packed_bytes(d_out, d_in, N, M), dtype=torch.uint8, device=DEV)
+    gamma = torch.zeros(1, device=DEV)
+    s.sbn_quantize_mask_pack(W, N, M, packed, gamma, s.new_workspace(s.sbn_workspace_bytes(s.SBN_OP_QUANTIZE_MASK_PACK, 1, d_out, d_in, N, M)))
+    Weff = torch.empty(d_out, d_in, dtype=torch.int8, device=DEV)
+    s.sbn_unpack(packed, d_out, d_in, N, M, W_eff=Weff)
+    xq = torch.randint(-128, 128, (tokens, d_in), generator=gen, device=DEV, dtype=torch.int8)
+    sx = torch.full((tokens,), 30.0, device=DEV)
+    Y = torch.full((tokens, d_out), float("nan"), device=DEV)
+    acc = torch.full((tokens, d_out), -7, dtype=torch.int32, device=DEV)
+    ws = s.new_workspace(s.sbn_workspace_bytes(s.SBN_OP_LINEAR, tokens, d_out, d_in, N, M))
+    s.sbn_sparse_ternary_linear(None, packed, gamma, Y, N, M, ws, xq_out=xq, sx_out=sx, acc_out=acc)
+    want = sum(xq[:, k:k + (1 << 21)].double() @ Weff[:, k:k + (1 << 21)].double().t().contiguous() for k in range(0, d_in, 1 << 21))
+    assert torch.equal(acc.double(), want)
+    assert torch.equal(Y, want.float() * (gamma / 30.0))
+    del xq, ws
+    torch.cuda.empty_cache()
