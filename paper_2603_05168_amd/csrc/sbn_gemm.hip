@@ -652,13 +652,13 @@ __device__ __forceinline__ void piece_body(const Group &grp, const Piece &p, con
                 }
                 leave(RA * TB - 1);
             };
-            // Output rows of whole 64 bytes: tiles of 32 x 32, 128 bytes of a token at a time, written past the caches.  Rows of
-            // other lengths share their 64-byte sectors with the neighbouring run: in runs of 256 bytes (64 rows x 16 tokens) half as
-            // many are shared, and the L2 puts their halves together while the outputs fit the last cache.  4096 tokens, 2560 ->
-            // 6920: 80 us in tiles past the caches, 64 in tiles, 66 in runs past the caches, 59.5 in runs (6924: 92 / 66 / 69 / 61;
-            // 6912: 51 past the caches, 59 through them); 5866 tokens, 1152 -> 7720 (181 MB) 97 / 74 / 70 / 70; 32768
-            // tokens, 2560 -> 6920 (907 MB) 512 / 506 / 425 / 499.
-            if ((g.d_out & 15) == 0) {
+            // Output rows of whole 64 bytes: tiles of 32 x 32, 128 bytes of a token at a time, written past the caches.  Where a run of
+            // 128 bytes shares its 64-byte sectors with its neighbours, because rows have another length or the first does not begin
+            // on 64 bytes, runs of 256 bytes (64 rows x 16 tokens) share half as many, and the L2 puts their halves together.  4096
+            // tokens, 2560 -> 6920: 80 us in tiles past the caches, 64 in tiles, 66 in runs past the caches, 59.5 in runs (6924: 92 /
+            // 66 / 69 / 61; 6912: 51 past the caches, 59 through them; 6912 behind 16 bytes, quantizer included: 108 in tiles past the
+            // caches, 66 in runs).
+            if ((g.d_out & 15) == 0 && (reinterpret_cast<uintptr_t>(g.Y) & 63) == 0) {
                 v4f bias4[RA];
 #pragma unroll
                 for (int a = 0; a < RA; ++a)

@@ -163,3 +163,21 @@ def test_pieces_one_behind_the_other(N, M, problems):
     s.sbn_test_linear_kernel(s.SBN_KERNEL_PIECES, xqs, sxs, [p[0] for p in packs], [p[1] for p in packs], Ys, N, M)
     for Y, ref in zip(Ys, refs):
         assert torch.equal(Y, ref)
+
+
+@pytest.mark.parametrize("N,M", [(2, 4), (8, 8)])
+@pytest.mark.parametrize("offset", [0, 16, 32, 48, 64])
+@pytest.mark.parametrize("tokens,d_out,bias", [(600, 1024, False), (1100, 528, True), (97, 80, True)])
+def test_pieces_outputs_that_begin_anywhere(N, M, offset, tokens, d_out, bias):
+    # whole sectors of 64 bytes leave on one path, runs that share theirs on another: the same values, and nothing beside the outputs
+    s, d_in = sbn(), 384
+    packed, gamma, _, _ = _weights(d_out, d_in, N, M)
+    xq, sx, _, acc = _reference(tokens, d_out, d_in, N, M)
+    b = torch.randn(d_out, generator=torch.Generator().manual_seed(d_out)).to(DEV) if bias else None
+    buf = torch.full((32 + tokens * d_out + 32,), float("nan"), device=DEV)
+    assert buf.data_ptr() % 64 == 0
+    Y = buf[offset // 4:offset // 4 + tokens * d_out].view(tokens, d_out)
+    s.sbn_test_linear_kernel(s.SBN_KERNEL_PIECES, [xq], [sx], [packed], [gamma], [Y], N, M, [b] if bias else None)
+    want = acc.astype(np.float32) * (gamma.cpu().numpy() / sx.cpu().numpy())[:, None]
+    assert np.array_equal(Y.cpu().numpy(), want if b is None else want + b.cpu().numpy())
+    assert buf.isnan().sum() == 64
