@@ -689,7 +689,12 @@ __device__ __forceinline__ void piece_body(const Group &grp, const Piece &p, con
             } else {
                 const v4f bias4 = has_bias ? *reinterpret_cast<const v4f *>(g.bias + orow + 4 * (lane & 15)) : v4f{0.f, 0.f, 0.f, 0.f};
                 const uint32_t voff = (uint32_t)(lane >> 4) * pitch + 16u * (lane & 15);
-                const bool streaming = (int64_t)g.tokens * g.d_out > (192 << 18);   // more than 192 MB of outputs
+                // Past the caches only where the outputs would push out operands that are worth more: beyond 512 MB of them, of long
+                // rows.  Times in the caches / past them, rows of eight values past whole sectors: 32768 tokens 2560 -> 6920 (907 MB) 460 / 421 us,
+                // 6912 -> 6920 919 / 803, 65536 tokens 2560 -> 2568 (673 MB) 360 / 338; but 32768 tokens 2560 -> 2568 (337 MB) 174 /
+                // 176, 16384 tokens 2560 -> 6920 (454 MB) 221 / 227, 32768 tokens 1024 -> 6920 315 / 333, 512 -> 6920 287 / 327, 512 ->
+                // 2568 86 / 124.
+                const bool streaming = g.d_in >= 2048 && (int64_t)g.tokens * g.d_out > (512 << 18);
                 sweep([&](const int n) {
                     if ((r >> 4) == (n & 1)) {
 #pragma unroll

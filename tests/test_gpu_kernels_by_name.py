@@ -141,7 +141,7 @@ def test_pieces_scales_below_the_normal_range(N, M):
     [(4000, 3000, 640), (4000, 2600, 640), (5000, 3001, 640)],                              # rows of one length, others' outputs
     [(3000, 4000, 384), (4100, 3000, 512), (2000, 2100, 128), (3333, 4444, 512)],           # the stream of requests is started anew in between
     [(700, 1100, 384), (650, 900, 384), (97 * 8, 600, 896)],                                # from a list: pieces of all widths behind each other
-    [(8200, 6148, 128)], [(4100, 2564, 256), (700, 1496, 128)],                              # rows of outputs of no whole 64 bytes, more and less than 192 MB
+    [(8200, 6148, 128)], [(4100, 2564, 256), (700, 1496, 128)],                              # rows of outputs of no whole 64 bytes, in the caches
     [(512, 13000, 128), (65, 17, 256)], [(300, 4700, 384), (512, 6001, 128), (100, 9000, 256)], [(33, 2000, 128)],   # decode batches: runs of uneven length, few blocks
 ])
 def test_pieces_one_behind_the_other(N, M, problems):
@@ -181,3 +181,19 @@ def test_pieces_outputs_that_begin_anywhere(N, M, offset, tokens, d_out, bias):
     want = acc.astype(np.float32) * (gamma.cpu().numpy() / sx.cpu().numpy())[:, None]
     assert np.array_equal(Y.cpu().numpy(), want if b is None else want + b.cpu().numpy())
     assert buf.isnan().sum() == 64
+
+
+@pytest.mark.parametrize("tokens,d_out,d_in", [(33000, 4100, 2048), (33000, 4100, 256), (33000, 4096, 256)])
+def test_pieces_many_outputs_with_a_bias(tokens, d_out, d_in):
+    # more than 512 MB: past the caches in runs (long rows of no whole sectors), through them, past them in tiles
+    s = sbn()
+    packed, gamma = hip_pack(sbn_synth.latent_weight(d_out, d_in, 8300), 2, 4)
+    Weff = torch.zeros((d_out, d_in), dtype=torch.int8, device=DEV)
+    s.sbn_unpack(packed, d_out, d_in, 2, 4, Weff)
+    gen = torch.Generator(device=DEV).manual_seed(d_in)
+    xq = torch.randint(-128, 128, (tokens, d_in), generator=gen, device=DEV, dtype=torch.int8)
+    sx, bias = torch.rand(tokens, generator=gen, device=DEV) * 50 + 10, torch.randn(d_out, generator=gen, device=DEV)
+    Y = torch.full((tokens, d_out), float("nan"), device=DEV)
+    s.sbn_test_linear_kernel(s.SBN_KERNEL_PIECES, [xq], [sx], [packed], [gamma], [Y], 2, 4, [bias])
+    want = (xq.float() @ Weff.float().T) * (gamma / sx)[:, None]   # sums below 2^24, exact in fp32
+    assert torch.equal(Y, want + bias)
