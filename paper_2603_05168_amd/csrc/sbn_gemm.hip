@@ -525,9 +525,13 @@ __device__ __forceinline__ void piece_body(const Group &grp, const Piece &p, con
         }
     };
 
+    // gamma, from constant memory: behind the requests, which may write any memory as far as the compiler knows, it would be a vector load in
+    // front of the epilogue, waited for there together with everything that has been asked for of the next piece
+    float gamma = *reinterpret_cast<const __attribute__((address_space(4))) float *>(reinterpret_cast<uintptr_t>(g.gamma));
     int ts = st.ts, ps = st.ps;
     if (!st.landed) SBN_WAIT_VMCNT(WAIT_TOP);   // pair 0 and stage 0; what was asked for after them may fly
     __syncthreads();
+    asm volatile("" : "+s"(gamma));   // here it is
     if (next.tb > 0) request_scales(grp.g[next.prob], next, lds0, wave, lane);   // its area was read by the epilogue before this piece
     if constexpr (LIVE) {
 #pragma unroll
@@ -600,11 +604,10 @@ __device__ __forceinline__ void piece_body(const Group &grp, const Piece &p, con
     // write whole lines with streaming stores (Y is not read again here and must not push the operands out
     // of L2; per-lane stores of 32 contiguous bytes measured 1.5x the write traffic); ragged edges and the int32
     // accumulator output store per lane.
-    // The epilogue issues no vector loads: one would make the compiler wait for everything outstanding, the requests
-    // for the next piece included.  gamma is a scalar load, the s_x of the piece came into LDS with its first stages.
+    // A vector load of the epilogue makes the compiler wait for everything outstanding, the requests for the next piece included,
+    // so there is none but the bias where there is one: gamma has been fetched with the piece, its s_x came into LDS.
     if constexpr (LIVE) {
-        float sxv[TB + 1];
-        sxv[TB] = *g.gamma;
+        float sxv[TB];
 #pragma unroll
         for (int b = 0; b < TB; ++b) sxv[b] = *reinterpret_cast<const float *>(lds + SCALES_OFF + 512 * p.parity + 4 * (32 * b + r));
         auto shift_sums = [&](const int b) {
@@ -618,7 +621,7 @@ __device__ __forceinline__ void piece_body(const Group &grp, const Piece &p, con
         bool exact = true;   // whether a 64th of the scales is
 #pragma unroll
         for (int b = 0; b < TB; ++b) {
-            const float v = __fdiv_rn(sxv[TB], sxv[b]);
+            const float v = __fdiv_rn(gamma, sxv[b]);
             exact = exact && fabsf(v) >= 0x1p-100f;
             scale[b] = UNIT ? v : v * (1.0f / (1 << CODE_SHIFT));
         }
@@ -734,7 +737,7 @@ __device__ __forceinline__ void piece_body(const Group &grp, const Piece &p, con
                 const int t = t0 + 32 * b + r;
                 if constexpr (!UNIT) shift_sums(b);
 #pragma unroll
-                for (int a = 0; a < RA; ++a) store_tile(g, acc[a][b], orow + 32 * a + 4 * c, t, __fdiv_rn(sxv[TB], sxv[b]));
+                for (int a = 0; a < RA; ++a) store_tile(g, acc[a][b], orow + 32 * a + 4 * c, t, __fdiv_rn(gamma, sxv[b]));
             }
         }
     } else {
