@@ -634,26 +634,23 @@ __device__ __forceinline__ void piece_body(const Group &grp, const Piece &p, con
             const int64_t first = (int64_t)t0 * g.d_out + orow;
             const uint32_t pitch = 4u * (uint32_t)g.d_out;
             const auto out = __builtin_amdgcn_make_buffer_rsrc(g.Y + first, (short)0, (int)((uint32_t)(g.tokens - t0 < 32 * TB ? g.tokens - t0 : 32 * TB) * pitch - 4u * (uint32_t)orow), 0x00027000);
-            v4f yv[2][4];
+            v4f yv[4];
             auto rescaled = [&](const int a, const int b, const int q) {
                 return v4f{(float)acc[a][b][4 * q + 0] * scale[b], (float)acc[a][b][4 * q + 1] * scale[b],
                            (float)acc[a][b][4 * q + 2] * scale[b], (float)acc[a][b][4 * q + 3] * scale[b]};
             };
-            // A wavefront's LDS operations complete in order, so a tile can be written behind the reads of the one before without a
-            // wait, and what a tile's stores wait for is covered by the conversions of the next tile.
+            // A wavefront's LDS operations complete in order, so a tile is written behind the reads of the one before without a wait.
+            // Tile by tile: with a tile's stores behind the conversions of the next one (and their order kept by scheduling barriers)
+            // the results took 0.1 to 0.3 us longer per launch (2048 tokens 512 -> 2048 7.8 us / 7.6, 1714 tokens 384 -> 1800 8.2 /
+            // 7.9), 32768 tokens 2560 -> 6912 362 / 357.
             static_assert(RA == 2, "two tiles of 32 rows x 32 tokens, or of 64 x 16, for 32 tokens");
             auto sweep = [&](auto stage, auto leave) {
-                stage(0);
                 SBN_WAIT_VMCNT(0);   // what was asked for of the next piece (the youngest half a step ago), in front of the first store
-                __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int n = 1; n < RA * TB; ++n) {
+                for (int n = 0; n < RA * TB; ++n) {
                     stage(n);
-                    __builtin_amdgcn_sched_barrier(0);
-                    leave(n - 1);
-                    __builtin_amdgcn_sched_barrier(0);
+                    leave(n);
                 }
-                leave(RA * TB - 1);
             };
             // Output rows of whole 64 bytes: tiles of 32 x 32, 128 bytes of a token at a time, written past the caches.  Where a run of
             // 128 bytes shares its 64-byte sectors with its neighbours, because rows have another length or the first does not begin
@@ -675,7 +672,7 @@ __device__ __forceinline__ void piece_body(const Group &grp, const Piece &p, con
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
                         const int t = 8 * i + (lane >> 3);
-                        yv[n & 1][i] = *reinterpret_cast<const v4f *>(est + t * 128 + 16 * ((lane & 7) ^ ((t >> 1) & 7)));
+                        yv[i] = *reinterpret_cast<const v4f *>(est + t * 128 + 16 * ((lane & 7) ^ ((t >> 1) & 7)));
                     }
                     asm volatile("" ::: "memory");   // the next tile's writes stay behind them
                 }, [&](const int n) {
@@ -683,11 +680,11 @@ __device__ __forceinline__ void piece_body(const Group &grp, const Piece &p, con
                     if (has_bias) {
                         asm volatile("");   // a branch, not additions and selections
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) yv[n & 1][i] += bias4[a];
+                        for (int i = 0; i < 4; ++i) yv[i] += bias4[a];
                     }
 #pragma unroll
                     for (int i = 0; i < 4; ++i)
-                        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, yv[n & 1][i]), out, voff + (uint32_t)(32 * b + 8 * i) * pitch + 128u * a, 0, 2);   // 2: streaming
+                        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, yv[i]), out, voff + (uint32_t)(32 * b + 8 * i) * pitch + 128u * a, 0, 2);   // 2: streaming
                 });
             } else {
                 const v4f bias4 = has_bias ? *reinterpret_cast<const v4f *>(g.bias + orow + 4 * (lane & 15)) : v4f{0.f, 0.f, 0.f, 0.f};
@@ -710,23 +707,23 @@ __device__ __forceinline__ void piece_body(const Group &grp, const Piece &p, con
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
                         const int t = 4 * i + (lane >> 4);
-                        yv[n & 1][i] = *reinterpret_cast<const v4f *>(est + t * 256 + 16 * ((lane & 15) ^ t));
+                        yv[i] = *reinterpret_cast<const v4f *>(est + t * 256 + 16 * ((lane & 15) ^ t));
                     }
                     asm volatile("" ::: "memory");
                 }, [&](const int n) {
                     if (has_bias) {
                         asm volatile("");
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) yv[n & 1][i] += bias4;
+                        for (int i = 0; i < 4; ++i) yv[i] += bias4;
                     }
                     if (streaming) {
 #pragma unroll
                         for (int i = 0; i < 4; ++i)
-                            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, yv[n & 1][i]), out, voff + (uint32_t)(16 * n + 4 * i) * pitch, 0, 2);
+                            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, yv[i]), out, voff + (uint32_t)(16 * n + 4 * i) * pitch, 0, 2);
                     } else {
 #pragma unroll
                         for (int i = 0; i < 4; ++i)
-                            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, yv[n & 1][i]), out, voff + (uint32_t)(16 * n + 4 * i) * pitch, 0, 0);
+                            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, yv[i]), out, voff + (uint32_t)(16 * n + 4 * i) * pitch, 0, 0);
                     }
                 });
             }
