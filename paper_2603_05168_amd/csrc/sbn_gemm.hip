@@ -626,14 +626,17 @@ __device__ __forceinline__ void piece_body(const Group &grp, const Piece &p, con
             scale[b] = UNIT ? v : v * (1.0f / (1 << CODE_SHIFT));
         }
         // (a piece's outputs are addressed with 31 bits behind its first)
-        const bool fast_store = (g.d_out & 3) == 0 && orow + 32 * RA <= g.d_out && !g.acc_out && g.d_out <= (1 << 22) && (UNIT || __all(exact));
+        const bool fast_store = (g.d_out & 3) == 0 && !g.acc_out && g.d_out <= (1 << 22) && (UNIT || __all(exact));
         if (fast_store) {
             int8_t *const est = lds + RING_BYTES + wave * STG_WAVE;
             const bool has_bias = g.bias != nullptr;
-            // tokens past the matrix lie past the end of the buffer, where stores are dropped
+            // tokens past the matrix lie past the end of the buffer, where stores are dropped, and so do, by an offset of their own,
+            // rows of W past it (a ragged last wavefront; 2181 tokens 512 -> 480 stored lane by lane 6.6 us, this way 6.25)
             const int64_t first = (int64_t)t0 * g.d_out + orow;
             const uint32_t pitch = 4u * (uint32_t)g.d_out;
             const auto out = __builtin_amdgcn_make_buffer_rsrc(g.Y + first, (short)0, (int)((uint32_t)(g.tokens - t0 < 32 * TB ? g.tokens - t0 : 32 * TB) * pitch - 4u * (uint32_t)orow), 0x00027000);
+            auto offset = [&](const uint32_t at, const int row) { return orow + row < g.d_out ? at + 4u * (uint32_t)row : 0x80000000u; };
+            auto bias_of = [&](const int row) { return has_bias && orow + row < g.d_out ? *reinterpret_cast<const v4f *>(g.bias + orow + row) : v4f{0.f, 0.f, 0.f, 0.f}; };
             v4f yv[4];
             auto rescaled = [&](const int a, const int b, const int q) {
                 return v4f{(float)acc[a][b][4 * q + 0] * scale[b], (float)acc[a][b][4 * q + 1] * scale[b],
@@ -660,10 +663,12 @@ __device__ __forceinline__ void piece_body(const Group &grp, const Piece &p, con
             // caches, 66 in runs).
             if ((g.d_out & 15) == 0 && (reinterpret_cast<uintptr_t>(g.Y) & 63) == 0) {
                 v4f bias4[RA];
+                uint32_t voff[RA];
 #pragma unroll
-                for (int a = 0; a < RA; ++a)
-                    bias4[a] = has_bias ? *reinterpret_cast<const v4f *>(g.bias + orow + 32 * a + 4 * (lane & 7)) : v4f{0.f, 0.f, 0.f, 0.f};
-                const uint32_t voff = (uint32_t)(lane >> 3) * pitch + 16u * (lane & 7);
+                for (int a = 0; a < RA; ++a) {
+                    bias4[a] = bias_of(32 * a + 4 * (lane & 7));
+                    voff[a] = offset((uint32_t)(lane >> 3) * pitch, 32 * a + 4 * (lane & 7));
+                }
                 sweep([&](const int n) {
                     const int a = n % RA, b = n / RA;
 #pragma unroll
@@ -684,11 +689,11 @@ __device__ __forceinline__ void piece_body(const Group &grp, const Piece &p, con
                     }
 #pragma unroll
                     for (int i = 0; i < 4; ++i)
-                        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, yv[i]), out, voff + (uint32_t)(32 * b + 8 * i) * pitch + 128u * a, 0, 2);   // 2: streaming
+                        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, yv[i]), out, voff[a] + (uint32_t)(32 * b + 8 * i) * pitch, 0, 2);   // 2: streaming
                 });
             } else {
-                const v4f bias4 = has_bias ? *reinterpret_cast<const v4f *>(g.bias + orow + 4 * (lane & 15)) : v4f{0.f, 0.f, 0.f, 0.f};
-                const uint32_t voff = (uint32_t)(lane >> 4) * pitch + 16u * (lane & 15);
+                const v4f bias4 = bias_of(4 * (lane & 15));
+                const uint32_t voff = offset((uint32_t)(lane >> 4) * pitch, 4 * (lane & 15));
                 // Past the caches only where the outputs would push out operands that are worth more: beyond 512 MB of them, of long
                 // rows.  Times in the caches / past them, rows of eight values past whole sectors: 32768 tokens 2560 -> 6920 (907 MB) 460 / 421 us,
                 // 6912 -> 6920 919 / 803, 65536 tokens 2560 -> 2568 (673 MB) 360 / 338; but 32768 tokens 2560 -> 2568 (337 MB) 174 /
