@@ -602,20 +602,13 @@ __device__ __forceinline__ void piece_body(const Group &grp, const Piece &p, con
 
     // ---- epilogue: rescale, transpose through the wavefront's staging area (4 KB of fp32 at a time) and
     // write whole lines with streaming stores (Y is not read again here and must not push the operands out
-    // of L2; per-lane stores of 32 contiguous bytes measured 1.5x the write traffic); ragged edges and the int32
-    // accumulator output store per lane.
+    // of L2; per-lane stores of 32 contiguous bytes measured 1.5x the write traffic).
     // A vector load of the epilogue makes the compiler wait for everything outstanding, the requests for the next piece included,
     // so there is none but the bias where there is one: gamma has been fetched with the piece, its s_x came into LDS.
     if constexpr (LIVE) {
         float sxv[TB];
 #pragma unroll
         for (int b = 0; b < TB; ++b) sxv[b] = *reinterpret_cast<const float *>(lds + SCALES_OFF + 512 * p.parity + 4 * (32 * b + r));
-        auto shift_sums = [&](const int b) {
-#pragma unroll
-            for (int a = 0; a < RA; ++a)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) acc[a][b][i] >>= CODE_SHIFT;
-        };
         const int orow = o0 + wave * (32 * RA);
         float scale[TB];
         bool exact = true;   // whether a 64th of the scales is
@@ -733,13 +726,46 @@ __device__ __forceinline__ void piece_body(const Group &grp, const Piece &p, con
                 });
             }
         } else {
+            // Anything else: 32 tokens x 32 rows at a time into the staging area and out again a word per lane, two tokens side by side
+            // (each lane its own values, a row of Y apart: 4096 tokens 2560 -> 6913 110 us, 57 this way, 8000 tokens 512 -> 6911 176 /
+            // 58, 600 tokens 512 -> 1030 with accumulators 17.3 / 9.0).
             SBN_WAIT_VMCNT(0);
+            int8_t *const est = lds + RING_BYTES + wave * STG_WAVE;
+            const int8_t *const back = est + c * 128 + 4 * (r & 3);   // of token c; 2 i + c lies 256 i on, its granules swizzled with i & 7
 #pragma unroll
             for (int b = 0; b < TB; ++b) {
-                const int t = t0 + 32 * b + r;
-                if constexpr (!UNIT) shift_sums(b);
+                const float v = __fdiv_rn(gamma, sxv[b]);
+                const int t = t0 + 32 * b + c, left = (g.tokens - t + 1) >> 1;
 #pragma unroll
-                for (int a = 0; a < RA; ++a) store_tile(g, acc[a][b], orow + 32 * a + 4 * c, t, __fdiv_rn(gamma, sxv[b]));
+                for (int a = 0; a < RA; ++a) {
+                    const int o = orow + 32 * a + r, steps = o < g.d_out ? (left < 16 ? left : 16) : 0;
+                    const float bias = g.bias && o < g.d_out ? g.bias[o] : 0.0f;
+                    const int64_t at = (int64_t)t * g.d_out + o;
+                    auto sum = [&](const int i) { return UNIT ? acc[a][b][i] : acc[a][b][i] >> CODE_SHIFT; };
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        *reinterpret_cast<v4f *>(est + r * 128 + 16 * ((2 * q + c) ^ ((r >> 1) & 7))) =
+                            v4f{(float)sum(4 * q) * v, (float)sum(4 * q + 1) * v, (float)sum(4 * q + 2) * v, (float)sum(4 * q + 3) * v};
+                    asm volatile("" ::: "memory");   // the reads are of what other lanes have written
+                    float *y = g.Y + at;
+#pragma unroll 2
+                    for (int i = 0; i < steps; ++i, y += 2 * (int64_t)g.d_out) {
+                        const float value = *reinterpret_cast<const float *>(back + 256 * i + 16 * ((r >> 2) ^ (i & 7)));
+                        *y = g.bias ? value + bias : value;
+                    }
+                    asm volatile("" ::: "memory");   // the next writes stay behind them
+                    if (g.acc_out) {
+#pragma unroll
+                        for (int q = 0; q < 4; ++q)
+                            *reinterpret_cast<v4i *>(est + r * 128 + 16 * ((2 * q + c) ^ ((r >> 1) & 7))) = v4i{sum(4 * q), sum(4 * q + 1), sum(4 * q + 2), sum(4 * q + 3)};
+                        asm volatile("" ::: "memory");
+                        int32_t *out = g.acc_out + at;
+#pragma unroll 2
+                        for (int i = 0; i < steps; ++i, out += 2 * (int64_t)g.d_out)
+                            *out = *reinterpret_cast<const int32_t *>(back + 256 * i + 16 * ((r >> 2) ^ (i & 7)));
+                        asm volatile("" ::: "memory");
+                    }
+                }
             }
         }
     } else {

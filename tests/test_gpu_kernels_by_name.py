@@ -197,3 +197,25 @@ def test_pieces_many_outputs_with_a_bias(tokens, d_out, d_in):
     s.sbn_test_linear_kernel(s.SBN_KERNEL_PIECES, [xq], [sx], [packed], [gamma], [Y], 2, 4, [bias])
     want = (xq.float() @ Weff.float().T) * (gamma / sx)[:, None]   # sums below 2^24, exact in fp32
     assert torch.equal(Y, want + bias)
+
+
+@pytest.mark.parametrize("N,M", [(2, 4), (8, 8)])
+@pytest.mark.parametrize("tokens", [1, 2, 31, 66, 545])
+@pytest.mark.parametrize("d_out", [1, 31, 33, 63, 65, 127, 515, 68, 124, 572])
+def test_pieces_widths_past_whole_tiles(N, M, tokens, d_out):
+    # odd widths and accumulators leave a word at a time, a ragged last wavefront of whole vectors with the others; nothing beside them
+    s, d_in = sbn(), 256
+    packed, gamma, _, _ = _weights(d_out, d_in, N, M)
+    xq, sx, _, acc = _reference(tokens, d_out, d_in, N, M)
+    b = torch.randn(d_out, generator=torch.Generator().manual_seed(d_out)).to(DEV)
+    want = acc.astype(np.float32) * (gamma.cpu().numpy() / sx.cpu().numpy())[:, None]
+    for bias in (None, b):
+        for with_acc in (False, True):
+            buf = torch.full((tokens * d_out + 256,), float("nan"), device=DEV)
+            sums = torch.full((tokens * d_out + 256,), -7, dtype=torch.int32, device=DEV)
+            s.sbn_test_linear_kernel(s.SBN_KERNEL_PIECES, [xq], [sx], [packed], [gamma], [buf[:tokens * d_out].view(tokens, d_out)], N, M,
+                                     None if bias is None else [bias], [sums[:tokens * d_out].view(tokens, d_out)] if with_acc else None)
+            got = buf.cpu().numpy()
+            assert np.array_equal(got[:-256].reshape(tokens, d_out), want if bias is None else want + b.cpu().numpy()) and np.isnan(got[-256:]).all()
+            if with_acc:
+                assert np.array_equal(sums[:-256].view(tokens, d_out).cpu().numpy(), acc) and (sums[-256:] == -7).all()
