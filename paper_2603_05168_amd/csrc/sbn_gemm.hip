@@ -653,8 +653,12 @@ __device__ __forceinline__ void piece_body(const Group &grp, const Piece &p, con
             // on 64 bytes, runs of 256 bytes (64 rows x 16 tokens) share half as many, and the L2 puts their halves together.  4096
             // tokens, 2560 -> 6920: 80 us in tiles past the caches, 64 in tiles, 66 in runs past the caches, 59.5 in runs (6924: 92 /
             // 66 / 69 / 61; 6912: 51 past the caches, 59 through them; 6912 behind 16 bytes, quantizer included: 108 in tiles past the
-            // caches, 66 in runs).
-            if ((g.d_out & 15) == 0 && (reinterpret_cast<uintptr_t>(g.Y) & 63) == 0) {
+            // caches, 66 in runs).  Runs through the caches also where the rows of inputs are so short that the stores are all there is
+            // to wait for and the caches hold them: tiles / runs at 8192 tokens 128 -> 6912 (226 MB) 49.8 / 39.7, 4096 tokens 256 ->
+            // 4096 (67 MB) 16.9 / 16.1, 2851 tokens 256 -> 7632 24.8 / 20.6; but 16384 tokens 256 -> 4096 (268 MB) 54.1 / 55.2.
+            const int64_t outputs = (int64_t)g.tokens * g.d_out;
+            const bool short_rows = g.d_in <= 256 && outputs > (48 << 18) && outputs < (256 << 18);
+            if ((g.d_out & 15) == 0 && (reinterpret_cast<uintptr_t>(g.Y) & 63) == 0 && !short_rows) {
                 v4f bias4[RA];
                 uint32_t voff[RA];
 #pragma unroll
@@ -687,12 +691,15 @@ __device__ __forceinline__ void piece_body(const Group &grp, const Piece &p, con
             } else {
                 const v4f bias4 = bias_of(4 * (lane & 15));
                 const uint32_t voff = offset((uint32_t)(lane >> 4) * pitch, 4 * (lane & 15));
-                // Past the caches only where the outputs would push out operands that are worth more: beyond 512 MB of them, of long
-                // rows.  Times in the caches / past them, rows of eight values past whole sectors: 32768 tokens 2560 -> 6920 (907 MB) 460 / 421 us,
-                // 6912 -> 6920 919 / 803, 65536 tokens 2560 -> 2568 (673 MB) 360 / 338; but 32768 tokens 2560 -> 2568 (337 MB) 174 /
-                // 176, 16384 tokens 2560 -> 6920 (454 MB) 221 / 227, 32768 tokens 1024 -> 6920 315 / 333, 512 -> 6920 287 / 327, 512 ->
-                // 2568 86 / 124.
-                const bool streaming = g.d_in >= 2048 && (int64_t)g.tokens * g.d_out > (512 << 18);
+                // Past the caches where the outputs would push out operands that are worth more, beyond 512 MB of them, of long rows
+                // (through the caches / past them at 32768 tokens 2560 -> 6920 (907 MB) 460 / 421 us, 6912 -> 6920 919 / 803, 65536 tokens
+                // 2560 -> 2568 (673 MB) 360 / 338; but 32768 tokens 2560 -> 2568 (337 MB) 174 / 176, 16384 tokens 2560 -> 6920 (454 MB)
+                // 221 / 227, 32768 tokens 1024 -> 6920 315 / 333, 512 -> 6920 287 / 327, 512 -> 2568 86 / 124), and where there are so
+                // few that the end of the launch waits for the caches to give them back, if no run ends within 32 bytes (2048 tokens 512
+                // -> 2056 (17 MB) 9.9 / 9.0, 2000 tokens 2560 -> 2568 17.5 / 16.2, 3898 tokens 256 -> 888 7.75 / 7.5; but 4096 tokens
+                // 512 -> 1496 (25 MB) 10.2 / 11.3, 4096 tokens 1024 -> 1000 (16 MB) 10.2 / 10.3).
+                const bool halves = (g.d_out & 7) == 0 && (reinterpret_cast<uintptr_t>(g.Y) & 63) == 0;
+                const bool streaming = (halves && outputs < (20 << 18)) || (g.d_in >= 2048 && outputs > (512 << 18));
                 sweep([&](const int n) {
                     if ((r >> 4) == (n & 1)) {
 #pragma unroll

@@ -183,9 +183,10 @@ def test_pieces_outputs_that_begin_anywhere(N, M, offset, tokens, d_out, bias):
     assert buf.isnan().sum() == 64
 
 
-@pytest.mark.parametrize("tokens,d_out,d_in", [(33000, 4100, 2048), (33000, 4100, 256), (33000, 4096, 256)])
+@pytest.mark.parametrize("tokens,d_out,d_in", [(33000, 4100, 2048), (33000, 4100, 256), (33000, 4096, 256), (8200, 2064, 256)])
 def test_pieces_many_outputs_with_a_bias(tokens, d_out, d_in):
-    # more than 512 MB: past the caches in runs (long rows of no whole sectors), through them, past them in tiles
+    # more than 512 MB: past the caches in runs (long rows of no whole sectors), through them, past them in tiles; 68 MB of whole sectors
+    # and short rows of inputs: through them in runs
     s = sbn()
     packed, gamma = hip_pack(sbn_synth.latent_weight(d_out, d_in, 8300), 2, 4)
     Weff = torch.zeros((d_out, d_in), dtype=torch.int8, device=DEV)
