@@ -91,16 +91,47 @@ __device__ __forceinline__ void unpack_transpose_tile(const uint8_t *__restrict_
     write_code_tile(tile, wt, ld, (int64_t)chunk * CHUNK, o0, d_in);
 }
 
-// from int8 W_eff [rows, cols] (patterns without a decoder here)
+// from int8 W_eff [rows, cols] (patterns without a decoder here), cols a multiple of 8.  Bound by the bytes in and out: rows go into LDS as
+// they are read, their granules of 16 bytes XOR-swizzled with row / 16; a thread takes four weights of 16 rows back, 16 words, and
+// transposes them with byte permutations, so that whole 128 bytes leave.  Byte by byte the launch took 24.5 us at 2560 x 2560 and
+// 3:4, a byte per weight and half the bytes of the bf16 form that took 9.7; this way 6.7.
 __device__ __forceinline__ void transpose_codes_tile(const int8_t *__restrict__ src, int64_t rows, int64_t cols, uint8_t *__restrict__ wt, int64_t ld,
                                                      int64_t k0, int64_t o0, uint8_t *tile)
 {
-    for (int v = threadIdx.x; v < 128 * 128; v += 256) {
-        const int64_t o = o0 + (v >> 7), k = k0 + (v & 127);
-        const int8_t w = o < rows && k < cols ? src[o * cols + k] : (int8_t)0;
-        tile[(v & 127) * TB + (v >> 7)] = (uint8_t)code_byte((uint32_t)w & 3u);
+    const int g = threadIdx.x & 7;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int o = 32 * i + (int)(threadIdx.x >> 3);
+        uint2 v[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int64_t k = k0 + 16 * g + 8 * h;
+            v[h] = o0 + o < rows && k < cols ? *reinterpret_cast<const uint2 *>(src + (o0 + o) * cols + k) : make_uint2(0, 0);
+        }
+        // 0, 1, -1 -> 0x00, 0x3f, 0xbf: 63 times the lowest bit, and the sign
+        auto coded = [](uint32_t w) { const uint32_t n = w & 0x01010101u; return ((n << 6) - n) | (w & 0x80808080u); };
+        *reinterpret_cast<uint4 *>(tile + o * 128 + 16 * (g ^ ((o >> 4) & 7))) = make_uint4(coded(v[0].x), coded(v[0].y), coded(v[1].x), coded(v[1].y));
     }
-    write_code_tile(tile, wt, ld, k0, o0, cols);
+    static_assert(code_byte(1) == 0x3f && code_byte(3) == 0xbf, "as above");
+    __syncthreads();
+    const int kg = threadIdx.x >> 3;   // rows 16 g .. + 15, weights 4 kg .. + 3
+    if (k0 + 4 * kg >= cols) return;
+    uint32_t out[4][4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        uint32_t w[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) w[i] = *reinterpret_cast<const uint32_t *>(tile + (16 * g + 4 * q + i) * 128 + 16 * ((kg >> 2) ^ g) + 4 * (kg & 3));
+        const uint32_t a = __builtin_amdgcn_perm(w[1], w[0], 0x05010400u), b = __builtin_amdgcn_perm(w[1], w[0], 0x07030602u);
+        const uint32_t c = __builtin_amdgcn_perm(w[3], w[2], 0x05010400u), d = __builtin_amdgcn_perm(w[3], w[2], 0x07030602u);
+        out[0][q] = __builtin_amdgcn_perm(c, a, 0x05040100u);
+        out[1][q] = __builtin_amdgcn_perm(c, a, 0x07060302u);
+        out[2][q] = __builtin_amdgcn_perm(d, b, 0x05040100u);
+        out[3][q] = __builtin_amdgcn_perm(d, b, 0x07060302u);
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        *reinterpret_cast<uint4 *>(wt + (k0 + 4 * kg + j) * ld + o0 + 16 * g) = make_uint4(out[j][0], out[j][1], out[j][2], out[j][3]);
 }
 
 // int8 [rows, cols] -> bf16 transposed: dst [cols, ld] with dst[c, r] = src[r, c], zeros for r in [rows, ld), ld a multiple of 64;
