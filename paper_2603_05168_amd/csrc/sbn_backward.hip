@@ -706,7 +706,10 @@ __device__ __forceinline__ void bf16_dx_body(const GemmBf16Args &g, uint8_t *dld
     const int r = lane & 31, c = lane >> 5;
     const uint32_t lds0 = lds_address(dlds);
     const int nk = g.K / GD_K;
-    const float alpha = 2.0f * (g.alpha ? *g.alpha : 1.0f);   // a scalar load: in front of everything that writes memory
+    // a scalar load: in front of everything that writes memory.  Twice that, for weights of +-0.5, unless it has no double
+    const float gamma = g.alpha ? *g.alpha : 1.0f;
+    const bool no_double = fabsf(gamma) >= 0x1p127f;
+    const float alpha = no_double ? gamma : 2.0f * gamma;
 
     // DMA roles, four instructions per slot and wavefront: one fills 8 rows x 128 bytes (lane l: row l / 8, slot l % 8 holding global column
     // slot ^ ((row >> 1) & 7)).  Rows past the matrix and stages past the last read as zeros and fetch nothing.
@@ -864,6 +867,12 @@ __device__ __forceinline__ void bf16_dx_body(const GemmBf16Args &g, uint8_t *dld
     if (kt < nk) step(kt, 0);
     SBN_WAIT_VMCNT(0);   // requests past the last stage deposit zeros
     __syncthreads();
+    if (no_double) {
+#pragma unroll
+        for (int a = 0; a < WP; ++a)
+#pragma unroll
+            for (int b = 0; b < WQ; ++b) acc[a][b] *= 2.0f;
+    }
     bf16_wave_epilogue<WP, WQ>(g, acc, alpha, dlds + wave * S::STAGING, n0 + wn * 32 * WP, m0 + wm * 32 * WQ, lane);
 }
 

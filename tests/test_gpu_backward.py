@@ -420,3 +420,24 @@ def test_backward_operands_of_four_gigabytes():
     assert torch.equal(dX, (Weff[at].float() * gamma).to(torch.bfloat16))
     del dY
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("tokens,d_in", [(64, 128), (4096, 4096)])   # small tiles, large ones
+@pytest.mark.parametrize("size", [1e38, 2e38, 3e38])
+def test_backward_scale_that_has_no_double(tokens, d_in, size):
+    # the transposed weights are +-0.5 and the scale twice gamma, as long as there is a float for it
+    s = sbn()
+    d_out, N, M = 64, 2, 4
+    W = torch.full((d_out, d_in), size, dtype=torch.bfloat16)
+    W[1::2] *= -1
+    packed, gamma = hip_pack(W, N, M)
+    _, g, Weff, _ = oracle_pack(W, N, M)
+    assert gamma.item() == g and np.isfinite(g) and np.abs(Weff).sum() == d_out * d_in // 2
+    dY = torch.zeros(tokens, d_out, dtype=torch.bfloat16, device=DEV)
+    at = torch.arange(tokens, device=DEV)
+    dY[at, at % d_out] = 2.0 ** -100
+    dX = torch.full((tokens, d_in), float("nan"), dtype=torch.bfloat16, device=DEV)
+    ws = s.new_workspace(s.sbn_workspace_bytes(s.SBN_OP_BACKWARD, tokens, d_out, d_in, N, M))
+    s.sbn_sparse_ternary_linear_backward(dY, packed, gamma, None, None, N, M, ws, d_in, dX=dX)
+    want = (torch.from_numpy(np.asarray(Weff, dtype=np.float32)).to(DEV) * (gamma * 2.0 ** -100)).to(torch.bfloat16)
+    assert torch.equal(dX, want[at % d_out])
