@@ -300,6 +300,32 @@ def test_backward_tile_edges(N, M, tokens, d_out, d_in, accumulate):
         assert err.max().item() <= 2e-2 and err.square().mean().sqrt().item() <= 2.0 ** -8, what
 
 
+@pytest.mark.parametrize("accumulate", [False, True])
+@pytest.mark.parametrize("tokens,d_out,d_in", [(4100, 2056, 2568), (4100, 2504, 2568)])   # tiles of 256; 33 stages of dX, and 40 of which the last holds 8
+def test_backward_masked_large_tiles(tokens, d_out, d_in, accumulate):
+    s, N, M = sbn(), 2, 4
+    packed, gamma = hip_pack(sbn_synth.latent_weight(d_out, d_in, 7100 + d_out), N, M)
+    Weff = torch.empty(d_out, d_in, dtype=torch.int8, device=DEV)
+    mask = torch.empty(d_out, d_in, dtype=torch.uint8, device=DEV)
+    s.sbn_unpack(packed, d_out, d_in, N, M, W_eff=Weff, mask=mask)
+    X, dY = sbn_synth.activations(tokens, d_in, 7101, device=DEV), sbn_synth.grad_output(tokens, d_out, 7102, device=DEV)
+    xq, sx = torch.empty(tokens, d_in, dtype=torch.int8, device=DEV), torch.empty(tokens, device=DEV)
+    s.sbn_act_quant(X, xq, sx)
+    old = sbn_synth.grad_output(d_out, d_in, 7103, device=DEV)
+    dX = torch.full((tokens, d_in), float("nan"), dtype=torch.bfloat16, device=DEV)
+    dW = old.clone() if accumulate else torch.full((d_out, d_in), float("nan"), dtype=torch.bfloat16, device=DEV)
+    ws = s.new_workspace(s.sbn_workspace_bytes(s.SBN_OP_BACKWARD, tokens, d_out, d_in, N, M))
+    ws.fill_(0xff)
+    s.sbn_sparse_ternary_linear_backward(dY, packed, gamma, xq, sx, N, M, ws, d_in, dX=dX, dW=dW, accumulate=accumulate, mask_dw=True)
+    outside = mask == 0
+    assert torch.equal(dW[outside], old[outside] if accumulate else torch.zeros_like(old[outside]))
+    ref_x = gamma.double() * (dY.double() @ Weff.double())
+    ref_w = ((dY.double() / sx.double()[:, None]).t().contiguous() @ xq.double()) * mask + (old.double() if accumulate else 0.0)
+    for got, ref, what in ((dX, ref_x, "dX"), (dW, ref_w, "dW")):
+        err = (got.double() - ref).abs() / torch.maximum(ref.abs(), ref.square().mean().sqrt())
+        assert err.max().item() <= 2e-2 and err.square().mean().sqrt().item() <= 2.0 ** -8, what
+
+
 def test_backward_grouped_shared_rows_with_scales_of_their_own():
     # two layers on the same int8 rows with different per-token scales: the operand that carries the scale is not shared
     s = sbn()

@@ -98,3 +98,19 @@ def test_weights_of_every_stage(N, M, d_out):
     dX = torch.full((d_out, d_in), float("nan"), dtype=torch.bfloat16, device=DEV)
     backward(dY, packed, gamma, torch.zeros(d_out, d_in, dtype=torch.int8, device=DEV), torch.ones(d_out, device=DEV), N, M, dX=dX)
     assert torch.equal(dX.float().cpu(), (torch.from_numpy(Weff).float() * gamma.cpu()).to(torch.bfloat16).float())
+
+
+@pytest.mark.parametrize("N,M", [(2, 4), (3, 4)])
+@pytest.mark.parametrize("d_out", [56, 64, 120, 136, 192, 200, 256, 264, 320, 392, 520])
+def test_weights_of_every_stage_in_large_tiles(N, M, d_out):
+    # as above where the device takes tiles of 256 x 256 (one round of them; of 128 x 128 it would be two, 1.4 times as long)
+    tokens = d_in = 4096
+    packed, gamma = hip_pack(sbn_synth.latent_weight(d_out, d_in, 1400 + d_out), N, M)
+    Weff = torch.empty(d_out, d_in, dtype=torch.int8, device=DEV)
+    sbn().sbn_unpack(packed, d_out, d_in, N, M, W_eff=Weff)
+    t = torch.arange(tokens, device=DEV)
+    dY = torch.zeros(tokens, d_out, dtype=torch.bfloat16, device=DEV)
+    dY[t, (t * 7) % d_out] = 1.0                                        # dX[t, k] = gamma W_eff[7 t mod d_out, k]
+    dX = torch.full((tokens, d_in), float("nan"), dtype=torch.bfloat16, device=DEV)
+    backward(dY, packed, gamma, torch.zeros(tokens, d_in, dtype=torch.int8, device=DEV), torch.ones(tokens, device=DEV), N, M, dX=dX)
+    assert torch.equal(dX, (Weff.float() * gamma).to(torch.bfloat16)[(t * 7) % d_out])
