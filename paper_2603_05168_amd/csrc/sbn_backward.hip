@@ -505,7 +505,8 @@ __device__ __forceinline__ int bf16_product_of_block(const GemmBf16Group &grp)
 // stand there as well, so a wavefront always has matrix instructions to issue: 1.42 us per stage of the large tile of dW, 1.38 of
 // dX, where one barrier, eight requests and a first read in front of every stage's matrix instructions took 1.9 us.  What bounds
 // it now: the matrix pipe at the clock the board's power holds (1.85 to 1.89 PFLOP/s on operands from registers for dW, 1.95 to 2.03
-// for the ternary operand of dX), and 2.5 us per tile for its first stages and 3.2 for its result, which nothing covers.
+// for the ternary operand of dX) inside a tile, 2.5 us per tile for its first stages and 3.2 for its result, which nothing covers, and
+// rounds of tiles that end unevenly: 1.2 to 1.4 PFLOP/s over a launch of a training step.
 // The fifth slot is what LDS has left beside two whole stages.  With two, all requests of a stage had three quarters of one to
 // arrive in: three layers of 2560 x 2560 at 16384 tokens 943 us then and 927 now (the products alone), two of 6912 x 2560 1844
 // and 1806, a training step of 6912 x 2560 in two parts of 1024 tokens (small tiles) 324 and 306.
@@ -689,9 +690,9 @@ __device__ __forceinline__ void bf16_dw_body(const GemmBf16Args &g, uint8_t *dld
 }
 
 // dX: P holds a byte per value, the high half of a bf16 (see write_code_tile): half the bytes of a stage to bring and to read, and a
-// register of two values is one byte permutation, four for the eight of a fragment.  What bounds the product is the power the board
-// holds (the matrix instructions take 85 % of the cycles, at 1.6 GHz), and of that the operands' way through the L2 and LDS is
-// the part that can be saved.
+// register of two values is one byte permutation, four for the eight of a fragment.  A matrix instruction executes in 61 to 75 % of
+// the SIMD cycles of a training step's products, first stages, results and last rounds included, at the 1.6 GHz that the board's power
+// holds; of that power the operands' way through the L2 and LDS is the part that can be saved.
 // A slot of P lasts for two stages (rows of 128 bytes), of Q for one: two slots of P and three of Q.  P(j) serves the stages 2j and
 // 2j + 1.  Half c of the lanes multiplies in quarter u the eight k at 32 (u / 2) + 16 c + 8 (u & 1), so that the bytes of two quarters
 // are one read of 16.

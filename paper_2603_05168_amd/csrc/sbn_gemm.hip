@@ -117,7 +117,7 @@ __device__ __forceinline__ void store_tile(const GemmArgs &g, const v16i &acc, i
     }
 }
 
-// Epilogue of both GEMM kernels.  A wavefront owns RA row tiles x TB token tiles of 32x32; a lane
+// Epilogue of the dense comparison kernel.  A wavefront owns RA row tiles x TB token tiles of 32x32; a lane
 // holds one token and rows 8q + 4c + i of each row tile, so a direct store would put only 32
 // contiguous bytes per token into each instruction (measured: 1.5x the algorithmic write traffic).
 // The accumulators are rescaled, transposed through the now idle LDS ring (32 tokens x 32*RA rows of
@@ -216,10 +216,12 @@ __device__ __forceinline__ void load_scales(const GemmArgs &g, int tok0, int lan
 // [64c + 32u, +32) of the chunk.
 // Pieces follow one another without draining the pipeline: the requests run on from a piece into the block's next one
 // under the last products, and the epilogue transposes through a staging area of its own, so the ring is never idle.
-// What bounds it now is the power of the board, which holds the clock at 1.6 GHz: 2:4 products of random operands from
-// registers run at 6.5 POP/s dense-equivalent with codes +-1 and 6.9 with +-64.  32768 tokens, 2560 -> 6912: 416 us before codes
-// of +-64, the tiles of the epilogue and the running requests, 357 now (3.25 POP/s); 4096 tokens 56.6 and 51.7, 2560 -> 2560
-// 22.5 and 21.7.
+// What bounds it: no one thing.  The board's power holds the clock at 1.6 GHz, where 2:4 products of random operands from
+// registers run at 6.5 POP/s dense-equivalent with codes +-1 and 6.9 with +-64, but a matrix instruction executes in 46 % of the SIMD
+// cycles of 32768 tokens, 2560 -> 6912 (14 pieces per multiprocessor), and in 29 % at 4096 tokens (one or two): a step takes 1500
+// cycles for 1024 of matrix work, and the results stand beside it, all multiprocessors storing at about the same time: 365 us, 306
+// without an output store; 4096 tokens 54 and 43, 2560 -> 2560 22.2 and 19.4 (a build for timing alone).  Before codes of +-64, the
+// tiles of the epilogue and the running requests 416, 56.6 and 22.5.
 namespace sp {
 
 constexpr int ROWS = 512;                      // rows of W per block tile
@@ -601,8 +603,7 @@ __device__ __forceinline__ void piece_body(const Group &grp, const Piece &p, con
     if (next.tb > 0 && !goes_on) start_stream(st, grp.g[next.prob], next, lds0, wave, lane);
 
     // ---- epilogue: rescale, transpose through the wavefront's staging area (4 KB of fp32 at a time) and
-    // write whole lines with streaming stores (Y is not read again here and must not push the operands out
-    // of L2; per-lane stores of 32 contiguous bytes measured 1.5x the write traffic).
+    // write runs of 128 or 256 bytes (per-lane stores of 32 contiguous bytes measured 1.5x the write traffic).
     // A vector load of the epilogue makes the compiler wait for everything outstanding, the requests for the next piece included,
     // so there is none but the bias where there is one: gamma has been fetched with the piece, its s_x came into LDS.
     if constexpr (LIVE) {
@@ -821,10 +822,11 @@ __global__ void __launch_bounds__(64 * sp::NW) gemm_smfmac_kernel(Group grp, Tab
         // order, -per_block pieces in all.  XCD x runs the x-th of eight contiguous runs of them, as long as its share
         // of the blocks, and deals it to its blocks in contiguous runs, so the pieces of a row tile that has more than
         // one run side by side or one behind the other on one XCD, and its L2 fetches the tile's weights once.  With
-        // run b for block b they sit on as many XCDs, each of which fetches them: 2560 -> 6912 took 13.95 us at 256
-        // tokens and 14.56 at 512, now 12.60 and 13.60; twice that in one launch at 512 tokens 31.0, now 23.1; eight
-        // layers of 2560 -> 2560 at 256 tokens 26.9, now 24.1 (dense codes, twice 6912 at 512: 33.3, now 28.8).  A tile
-        // of one piece gains nothing and loses nothing (100 tokens: 12.2).  Dealing token units to XCDs, as below,
+        // run b for block b they sit on as many XCDs, each of which fetches them.  Both orders in turn: 2560 -> 6912 13.95 us
+        // against 12.60 at 256 tokens and 14.56 against 13.60 at 512; twice that in one launch at 512 tokens 31.0 against
+        // 23.1; eight layers of 2560 -> 2560 at 256 tokens 26.9 against 24.1 (dense codes, twice 6912 at 512: 33.3 against
+        // 28.8).  A tile of one piece gains nothing and loses nothing (100 tokens: 12.2).  (From a graph, with the results
+        // tile by tile, these take 11.5, 12.8, 22.2, 21.6, 29.1 and 11.1 by now.)  Dealing token units to XCDs, as below,
         // would leave most XCDs without work here.
         const int P = -tab.per_block, nbk = (int)gridDim.x, wmax = (int)tab.piece[0];
         const int x = (int)blockIdx.x & 7, j = (int)blockIdx.x >> 3, b8 = nbk >> 3, more8 = nbk & 7;
@@ -1275,8 +1277,9 @@ sbn_status launch_gemm_pieces(int count, const LinearItem *items, bool dense_cod
 //       (2560 -> 2560 at 17 .. 1500 tokens 13.2 .. 15.0 us, 6912 -> 2560 39 .. 43, 2560 -> 6912 at 512 / 777 / 1500 / 3000
 //       tokens, up to 1 / 2 / 3 / 6 units, 18 / 20 / 25 / 47).  Output rows of no whole 16 bytes are stored in single words,
 //       another 3.2 us and 0.55 us per MB of them (512 -> 476 / 478 at 1000 tokens 6.5 / 10.2 us, 512 -> 6911 at 8000 179)
-// The fit is of pieces before their requests ran on and decode batches were dealt by XCD; by name and without the quantizer 2560 ->
-// 6912 takes 13.6 us at 512 tokens and 18.5 at 1024 by now, so that the choice leans to the small tiles a little.
+// The fit is of pieces before their requests ran on, decode batches were dealt by XCD and odd widths left through LDS.  By name, without
+// the quantizer, 2560 -> 6912 takes 18.9 us at 1024 tokens and 365 at 32768 by now, where this says 23 and 547, and 512 -> 6911 at
+// 8000 tokens 60, so that the choice leans to the small tiles: a little where d_out % 4 is 0, much where it is not.
 static float gemm_large_estimate_us(int count, const LinearItem *items, bool dense)
 {
     bool stream = true;
@@ -1315,10 +1318,10 @@ static bool beyond_pieces(int count, const LinearItem *items)
 // Small block tiles where they are faster: their time grows with rows x tokens from 4.5 us on, that of the large kernels
 // starts two to five times higher and grows slower.  Over 279 calls of 17 to 16384 tokens, input dimensions 256 to 8192 and
 // one to sixteen problems, all kernels measured, the choice costs 0.6 % against the faster kernel of each (at worst 1.40, 384 tokens
-// 4096 -> 14336 with dense codes: 56 us against 40); 256 tokens, 2560 -> 6912: 13.5 us in tiles, 17.8 in pieces; 512 tokens,
-// 2560 -> 2560: 11.1 / 14.0; 777 tokens: 14.9 / 13.8.  Over 365 calls more of 200 to 8000 tokens with 475 to 6912 outputs, most
+// 4096 -> 14336 with dense codes: 56 us against 40); 256 tokens, 2560 -> 6912: 13.5 us in tiles, 17.8 in pieces as they were
+// then (11.5 by name by now); 512 tokens, 2560 -> 2560: 11.1 / 14.0 (11.3); 777 tokens: 14.9 / 13.8 (11.7).  Over 365 calls more of 200 to 8000 tokens with 475 to 6912 outputs, most
 // of them no multiple of four: 0.2 %, at worst 1.09 (8000 tokens, 512 -> 1500: 23 / 25 us); 2181 tokens, 512 -> 475 7.6 in tiles,
-// 11.4 in pieces, 512 -> 512 6.9 either way.
+// 11.4 in pieces (7.2), 512 -> 512 6.9 either way (6.3).
 bool gemm_takes_tiles(int count, const LinearItem *items, bool dense_codes)
 {
     return beyond_pieces(count, items) || gemm_tile_estimate_us(count, items, dense_codes) < gemm_large_estimate_us(count, items, dense_codes);
